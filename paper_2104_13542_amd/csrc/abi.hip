@@ -188,6 +188,47 @@ std::vector<storm::SelfGroup> storm::self_groups(const storm_robot *robot)
     return g;
 }
 
+int storm::anchor_sphere(const float *sp, int lo, int hi, double &radius)
+{
+    int best = lo;
+    radius = INFINITY;
+    for (int k = lo; k < hi; ++k) {
+        double r = 0.0;
+        for (int m = lo; m < hi; ++m) {
+            const double dx = (double)sp[5 * m + 1] - sp[5 * k + 1], dy = (double)sp[5 * m + 2] - sp[5 * k + 2],
+                         dz = (double)sp[5 * m + 3] - sp[5 * k + 3];
+            r = fmax(r, sqrt(dx * dx + dy * dy + dz * dz) + (double)sp[5 * m + 4]);
+        }
+        if (r < radius) {
+            radius = r;
+            best = k;
+        }
+    }
+    return best;
+}
+
+// A frame without spheres gets a radius that no test passes.
+std::vector<float> storm::body_bounds(const storm_robot *robot)
+{
+    std::vector<float> out(2 * STORM_NFRAMES, 0.0f);
+    const float *sp = robot->spheres;
+    for (int b = 0; b < STORM_NFRAMES; ++b) {
+        int lo = 0;
+        while (lo < robot->n_spheres && (int)sp[5 * lo] < b + 1) ++lo;
+        int hi = lo;
+        while (hi < robot->n_spheres && (int)sp[5 * hi] == b + 1) ++hi;
+        int a = 0;
+        out[2 * b + 1] = -1.0e30f;
+        if (hi > lo) {
+            double radius = 0.0;
+            a = storm::anchor_sphere(sp, lo, hi, radius);
+            out[2 * b + 1] = (float)(radius - (double)sp[5 * a + 4]);
+        }
+        memcpy(&out[2 * b], &a, sizeof(float));
+    }
+    return out;
+}
+
 // Self-collision work items: one per (group, partner body), partners
 // [s_begin, s_end) the spheres of that body, written as eight integers
 // (t_first | count << 8, group, s_begin, s_end, a_t, a_s, bits of reach2, 0).
@@ -204,23 +245,6 @@ int storm::self_segments(const storm_robot *robot, std::vector<int> &items)
 {
     const std::vector<SelfGroup> groups = self_groups(robot);
     const float *sp = robot->spheres;
-    auto anchor = [&](int lo, int hi, double &radius) {
-        int best = lo;
-        radius = INFINITY;
-        for (int k = lo; k < hi; ++k) {
-            double r = 0.0;
-            for (int m = lo; m < hi; ++m) {
-                const double dx = (double)sp[5 * m + 1] - sp[5 * k + 1], dy = (double)sp[5 * m + 2] - sp[5 * k + 2],
-                             dz = (double)sp[5 * m + 3] - sp[5 * k + 3];
-                r = fmax(r, sqrt(dx * dx + dy * dy + dz * dz) + (double)sp[5 * m + 4]);
-            }
-            if (r < radius) {
-                radius = r;
-                best = k;
-            }
-        }
-        return best;
-    };
     struct Item {
         int v[8];
         int rounds, order;
@@ -231,12 +255,12 @@ int storm::self_segments(const storm_robot *robot, std::vector<int> &items)
         const SelfGroup &g = groups[gi];
         pairs += (long long)g.count * g.s_end;
         double rt = 0.0;
-        const int at = anchor(g.t_first, g.t_first + g.count, rt);
+        const int at = anchor_sphere(sp, g.t_first, g.t_first + g.count, rt);
         for (int lo = 0; lo < g.s_end;) {
             int hi = lo + 1;
             while (hi < g.s_end && (int)sp[5 * hi] == (int)sp[5 * lo]) ++hi;
             double rs = 0.0;
-            const int as = anchor(lo, hi, rs);
+            const int as = anchor_sphere(sp, lo, hi, rs);
             const double reach = rt + rs + 1.0e-3;
             const float reach2 = nextafterf((float)(reach * reach), INFINITY);
             Item it{};
@@ -387,6 +411,7 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
     std::vector<float> net_bias;
     if (params->self_model == 1) storm::pack_selfnet(robot->self_mlp, net_frag, net_bias);
     const std::vector<float> thr = storm::self_thresholds(robot, reach_bound(robot));
+    const std::vector<float> bounds = storm::body_bounds(robot);
     const int n_seg = (int)seg.size() / 8;
 
     ProblemDev &P = c->P;
@@ -432,7 +457,7 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
     c->R.n_pairs = n_pairs;
 
     float *tables, *halton, *box_obs, *mean, *sigma2, *u, *C, *dt_raw, *lim_raw, *sig_raw, *obs_raw, *sph_raw_d;
-    float *self_thr, *grad_part, *cost_part, *grad, *adam, *ball, *qbuf = nullptr;
+    float *self_thr, *body_bound, *grad_part, *cost_part, *grad, *adam, *ball, *qbuf = nullptr;
     float4 *sph_obs, *obs_bound, *sph_local;
     int32_t *sph_body, *self_seg;
     uint32_t *counters;
@@ -474,6 +499,7 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
     STORM_TRY(dalloc(c, &sph_local, (size_t)robot->n_spheres));
     STORM_TRY(dalloc(c, &sph_body, (size_t)robot->n_spheres));
     STORM_TRY(dalloc(c, &self_thr, thr.size()));
+    STORM_TRY(dalloc(c, &body_bound, bounds.size()));
     STORM_TRY(dalloc(c, &self_seg, (size_t)8 * n_seg));
     // staging copies of the host inputs (freed at destroy with the rest)
     STORM_TRY(dalloc(c, &dt_raw, (size_t)H));
@@ -501,6 +527,7 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
             STORM_TRY(hipMemcpyAsync(self_seg, seg.data(), sizeof(int) * seg.size(), hipMemcpyHostToDevice, s));
         if (!thr.empty())
             STORM_TRY(hipMemcpyAsync(self_thr, thr.data(), sizeof(float) * thr.size(), hipMemcpyHostToDevice, s));
+        STORM_TRY(hipMemcpyAsync(body_bound, bounds.data(), sizeof(float) * bounds.size(), hipMemcpyHostToDevice, s));
         P.tables = tables;
         P.halton = halton;
         P.sph_obs = sph_obs;
@@ -525,6 +552,7 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
         c->R.sph_local = sph_local;
         c->R.sph_body = sph_body;
         c->R.self_thr = self_thr;
+        c->R.body_bound = reinterpret_cast<const float2 *>(body_bound);
         c->R.self_items = self_seg;
         c->R.n_self_items = n_seg;
         STORM_TRY(storm::launch_init_tables(P, dt_raw, lim_raw, params->acc_stop, params->gamma, params->w_term,

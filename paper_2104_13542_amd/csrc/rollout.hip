@@ -16,10 +16,12 @@
 //   B   waves 0-2  forward kinematics (Eq. 8), one row of the eight frames
 //                  per wave, to LDS
 //       wave W-1   the hinge norms over the joints (Eq. 10-11)
-//   C   waves 0..W-3  world centres of the body spheres to LDS
+//   C   waves 0..W-3  world centres of the body spheres and the capsules
+//                  that hold them, to LDS
 //       wave W-2   manipulability (Eq. 12)
 //       wave W-1   pose (Eq. 9)
-//   D   all waves  environment (spheres x obstacles) split over waves, then
+//   D1  all waves  obstacles near each body, by capsules
+//   D2  all waves  environment (spheres x obstacles) split over waves, then
 //                  self-collision (sphere pairs) as items taken from a queue,
 //                  each behind a broad-phase test
 //   E   wave 0     weighted running cost (Eq. 15), horizon sum (Eq. 2) as a
@@ -43,42 +45,40 @@ namespace {
 __host__ __device__ constexpr int rollout_cen_rows(int S) { return 3 * S > 43 ? 3 * S : 43; }
 static_assert(2 * 16 <= 96, "the collision partials of 16 waves fit over the frame rows");
 
-// Wavefront-wide maximum of a non-negative float: IEEE bit patterns of
-// non-negative floats order like unsigned integers, so the maximum runs on
-// the bits through DPP lane moves (quad permutes, half-row and row mirrors,
-// then the row broadcasts that carry each row's result into the next) and is
-// read back from lane 63, the lane every step feeds, into an SGPR.
-__device__ __forceinline__ float wave_max_nonneg(float x)
+// Value of lane kLane of the caller's 16-lane row.
+template <int kLane>
+__device__ __forceinline__ float row_lane(float x)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x150 + kLane, 0xf, 0xf, false));  // row_newbcast
+}
+
+// Maximum of a non-negative float over the caller's 16-lane row, in every
+// lane: IEEE bit patterns of non-negative floats order like unsigned
+// integers, so it runs on the bits through DPP lane moves.
+__device__ __forceinline__ float row_max_nonneg(float x)
 {
     uint32_t b = __float_as_uint(x);
     b = max(b, (uint32_t)__builtin_amdgcn_mov_dpp((int)b, 0xb1, 0xf, 0xf, false));   // quad_perm [1, 0, 3, 2]
     b = max(b, (uint32_t)__builtin_amdgcn_mov_dpp((int)b, 0x4e, 0xf, 0xf, false));   // quad_perm [2, 3, 0, 1]
     b = max(b, (uint32_t)__builtin_amdgcn_mov_dpp((int)b, 0x141, 0xf, 0xf, false));  // row_half_mirror
     b = max(b, (uint32_t)__builtin_amdgcn_mov_dpp((int)b, 0x140, 0xf, 0xf, false));  // row_mirror
-    b = max(b, (uint32_t)__builtin_amdgcn_mov_dpp((int)b, 0x142, 0xa, 0xf, false));  // row_bcast:15, rows 1 and 3
-    b = max(b, (uint32_t)__builtin_amdgcn_mov_dpp((int)b, 0x143, 0xc, 0xf, false));  // row_bcast:31, rows 2 and 3
-    return __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)b, 63));
+    return __uint_as_float(b);
 }
 
-// Candidates of one 64-obstacle chunk above which the environment broad phase
-// refines the wave's ball into eight balls of eight lanes (measured: the
-// refinement pays for itself from about this many candidates on).
-constexpr int kFineCandidates = 8;
+// Whether the capsule (segment a.xyz + t b.xyz, t in [0, 1], radius `reach`
+// already holding the obstacle's; b.w = 1 / |b.xyz|^2) meets the point o.
+// The margin of the culling radii covers the rounding of t, which moves the
+// nearest point by far less.
+__device__ __forceinline__ bool capsule_hits(const float4 a, const float4 b, float reach, float ox, float oy, float oz)
+{
+    const float dx = ox - a.x, dy = oy - a.y, dz = oz - a.z;
+    const float t = fminf(fmaxf(fmaf(dx, b.x, fmaf(dy, b.y, dz * b.z)) * b.w, 0.0f), 1.0f);
+    const float ex = fmaf(-t, b.x, dx), ey = fmaf(-t, b.y, dy), ez = fmaf(-t, b.z, dz);
+    return fmaf(ex, ex, fmaf(ey, ey, ez * ez)) < reach * fabsf(reach);
+}
 
 // LDS copy of the goal (R row-major, p) and the cost weights, by index.
 constexpr int kParArot = 12, kParApos = 15, kParW = 18, kParKm = 25, kParCount = 26;
-
-// Lane 0's value, as a wave-uniform (SGPR) float.
-__device__ __forceinline__ float uniform_lane0(float x)
-{
-    return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
-}
-
-// Culling record o, or one that no test can pass for o beyond the scene.
-__device__ __forceinline__ float4 load_bound(const float4 *__restrict__ b, int o, int n)
-{
-    return o < n ? b[o] : make_float4(3.0e38f, 3.0e38f, 3.0e38f, 0.0f);
-}
 
 // The ball-on-tray term (appendix on dynamic object balancing), by the pose
 // wave: every lane forms the flange frame of the current state q0 and moves
@@ -87,7 +87,7 @@ __device__ __forceinline__ float4 load_bound(const float4 *__restrict__ b, int o
 // and the two segmented scans of Eq. 7's scheme give the ball's velocity
 // and position; the term is the distance from the tray centre.
 __device__ __forceinline__ void ball_term(const ProblemDev &P, const RobotDev &R, const float *__restrict__ x0,
-                                          const float *s_fr, float *s_terms, const int lane, const int h,
+                                          const float *s_fr, float *s_terms, const int pos, const int h,
                                           const int H, const float *__restrict__ tab)
 {
     float r0[9] = {1.0f, 0.0f, 0.0f, 0.0f, 1.0f, 0.0f, 0.0f, 0.0f, 1.0f}, p0[3] = {0.0f, 0.0f, 0.0f};
@@ -99,7 +99,7 @@ __device__ __forceinline__ void ball_term(const ProblemDev &P, const RobotDev &R
     }
     const float bw[3] = {P.ball[0] - p0[0], P.ball[1] - p0[1], P.ball[2] - p0[2]};
     float xb[2], vb[2], ab[2];
-    const float *E = s_fr + 7 * 12 * kLanes + lane;
+    const float *E = s_fr + 7 * 12 * kLanes + pos;
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
         xb[c] = fmaf(r0[c], bw[0], fmaf(r0[3 + c], bw[1], r0[6 + c] * bw[2]));
@@ -116,7 +116,7 @@ __device__ __forceinline__ void ball_term(const ProblemDev &P, const RobotDev &R
         const float e = x - P.ball_c[c];
         d2 = fmaf(e, e, d2);
     }
-    s_terms[8 * kLanes + lane] = fast_sqrt(d2);
+    s_terms[8 * kLanes + pos] = fast_sqrt(d2);
 }
 
 // One 64-lane tile of one problem, executed by the W waves of the calling
@@ -132,31 +132,43 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
     // LDS rows of 64 floats, overlaid where their lifetimes do not meet
     // (rollout_lds_bytes), so that two workgroups of the batched form fit on
     // one CU:
-    //   frames [96]              B - C,  then the collision partials [2W]  D - E
+    //   frames [96]              B - C,  then the collision partials [2W]  D2 - E
     //   terms [kTerms]           B - E
-    //   |c|^2 [S], centres [3S]  C - D;  before them noise [8] A0 - A1,
+    //   centres [3S]             C - D2;  before them noise [8] A0 - A1,
     //                            sin/cos [14] and hinges [21] A1 - B
     //   velocities, accelerations [14]  A1 - C (task-space form only)
+    // then the capsules of the spheres [S][4 rows][8] (C - D2) and the
+    // culling records of the obstacles (A0 - D2).
     const int S = R.n_spheres;
     float *s_fr = smem;                        // [8 frames][12][64]: R row-major, p
     float *s_penv = s_fr;                      // [W][64] (over the frames, after phase C)
     float *s_pself = s_penv + W * kLanes;      // [W][64]
     float *s_terms = s_fr + 96 * kLanes;       // [kTerms][64]
-    float *s_cn = s_terms + kTerms * kLanes;   // [S][64]: |c|^2 of the sphere centres
-    float *s_cen = s_cn + S * kLanes;          // [S][3][64]
+    float *s_cen = s_terms + kTerms * kLanes;  // [S][3][64]
     float *s_eps = s_cen;                      // [8][64] (before the centres)
     float *s_sc = s_eps + 8 * kLanes;          // [7][2][64]: sin q_j, cos q_j
     float *s_lim = s_sc + 14 * kLanes;         // [3][7][64]: squared joint, velocity, stop hinges per joint
     float *s_v = s_cen + rollout_cen_rows(S) * kLanes;  // [7][64] (task-space form only)
     float *s_acc = s_v + kDof * kLanes;                  // [7][64]
+    float4 *s_cap = reinterpret_cast<float4 *>(s_v + (kTask ? 2 * kDof * kLanes : 0));  // [S][4][2]
+    float4 *s_bound = s_cap + 8 * S;                     // [obstacles]
 
     const int lane = threadIdx.x & (kLanes - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int N = P.N, H = P.H;
-    const int pl = lane / H;
+    // the particle and step of this lane (lane / H by a reciprocal: exact, as
+    // the quotients of lane + 1/2 stay 1/128 away from the integers)
+    const int pl = (int)(((float)lane + 0.5f) * __builtin_amdgcn_rcpf((float)H));
     const int h = lane - pl * H;
     const int i = tile * P.ppt + pl;
     const bool valid = pl < P.ppt && i < N;
+    // From the joint angles on, the points of the tile lie in LDS by step,
+    // then particle, so that the 16 lanes of a row are neighbours in time:
+    // `pos` is where this lane's point goes; positions past the last point
+    // repeat it (`src`, from phase B on).
+    const int n_pts = P.ppt * H;
+    const int pos = pl < P.ppt ? h * P.ppt + pl : lane;
+    const int src = min(lane, n_pts - 1);
     const bool live = valid && i < N - P.n_null;  // sampled (non-null) particle
     const uint32_t mask = P.cost_mask;
     const float *__restrict__ tab = P.tables;
@@ -171,16 +183,22 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
     const float dt_h = tab[kTabDt + h];
     const float vs_h = tab[kTabVstop + h];
     const float q0_j = vector_load_f32(x0 + jw), v0_j = vector_load_f32(x0 + kDof + jw);
-    // culling record of obstacle `lane` (first 64 obstacles) for phase D
-    const float4 bound0 = (mask & STORM_COST_ENV) ? load_bound(P.obs_bound, lane, P.n_sph_obs + P.n_box_obs)
-                                                  : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    // the obstacles' culling records for phase D, one per thread of the waves
+    // that draw no noise
+    const int nobs = (mask & STORM_COST_ENV) && S > 0 ? P.n_sph_obs + P.n_box_obs : 0;
+    const int ob_t = (int)threadIdx.x - 4 * kLanes;
+    static_assert((W - 4) * kLanes >= STORM_MAX_OBSTACLES, "one culling record per thread");
+    if (ob_t >= 0 && ob_t < nobs) s_bound[ob_t] = P.obs_bound[ob_t];
     // the goal and the cost weights that phases C and E read, staged in
     // LDS by the last wave while the noise is drawn (read where they are
     // used, as scalar loads, they would add a memory round trip to those
     // serial phases)
     __shared__ float s_par[kParCount];
-    __shared__ int s_self_next;  // head of the self-collision item queue (phase D)
+    __shared__ int s_self_next;  // head of the self-collision item queue (phase D2)
+    __shared__ int s_near_n[kFrames];  // obstacles near each body (phase D1)
+    __shared__ uint8_t s_near[kFrames * STORM_MAX_OBSTACLES];
     if (wave == W - 1 && lane == kParCount) s_self_next = 0;
+    if (wave == W - 2 && lane < kFrames) s_near_n[lane] = 0;
     if (wave == W - 1 && lane < kParCount) {
         const float wts[kParCount - 12] = {P.alpha_rot[0], P.alpha_rot[1], P.alpha_rot[2], P.alpha_pos[0],
                                            P.alpha_pos[1], P.alpha_pos[2], P.w_pos,        P.w_rot,
@@ -224,20 +242,20 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
         if (live) u = fmaf(sig_j, e, mu_j);
         const float v = v0_j + segmented_scan(dt_h * u, h, H);
         const float q = q0_j + segmented_scan(dt_h * v, h, H);
-        if (kTask) s_v[j * kLanes + lane] = v;
+        if (kTask) s_v[j * kLanes + pos] = v;
         // this joint's squared joint, velocity and stop hinges (Eq. 10-11),
         // summed over the joints in phase C
         const float hj = hinge_box(q, tab[kTabJlo + j], tab[kTabJhi + j]);
         const float hv = hinge_box(v, tab[kTabVlo + j], tab[kTabVhi + j]);
         const float hs = fmaxf(fabsf(v) - vs_h, 0.0f);
-        s_lim[(0 * kDof + j) * kLanes + lane] = hj * hj;
-        s_lim[(1 * kDof + j) * kLanes + lane] = hv * hv;
-        s_lim[(2 * kDof + j) * kLanes + lane] = hs * hs;
+        s_lim[(0 * kDof + j) * kLanes + pos] = hj * hj;
+        s_lim[(1 * kDof + j) * kLanes + pos] = hv * hv;
+        s_lim[(2 * kDof + j) * kLanes + pos] = hs * hs;
         float sq, cq;
         sincosf(q, &sq, &cq);
-        s_sc[(2 * j) * kLanes + lane] = sq;
-        s_sc[(2 * j + 1) * kLanes + lane] = cq;
-        if (kTask) s_acc[j * kLanes + lane] = u;
+        s_sc[(2 * j) * kLanes + pos] = sq;
+        s_sc[(2 * j + 1) * kLanes + pos] = cq;
+        if (kTask) s_acc[j * kLanes + pos] = u;
         if (valid) {
             const size_t o = ((size_t)j * N + i) * H + h;
             P.u[o] = u;
@@ -259,8 +277,8 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
         for (int f = 0; f < kFrames; ++f) {
             float st = 0.0f, ct = 1.0f;
             if (f < kDof) {
-                st = s_sc[(2 * f) * kLanes + lane];
-                ct = s_sc[(2 * f + 1) * kLanes + lane];
+                st = s_sc[(2 * f) * kLanes + src];
+                ct = s_sc[(2 * f + 1) * kLanes + src];
             }
             dh_step_row(r, p, R.ca[f], R.sa[f], R.a[f], R.d[f], ct, st);
 #pragma unroll
@@ -293,6 +311,11 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
             const STORM_CONST_AS int32_t *body = uniform_ptr(R.sph_body);
             int fb = -1;
             float F[12];
+            // where in its row's span of steps this lane lies, in [0, 1]
+            const float step = floorf(((float)src + 0.5f) * __builtin_amdgcn_rcpf((float)P.ppt));
+            const float step0 = row_lane<0>(step);
+            const float tau =
+                fminf((step - step0) * __builtin_amdgcn_rcpf(fmaxf(row_lane<15>(step) - step0, 1.0f)), 1.0f);
             for (int s = s0; s < s1; ++s) {
                 const STORM_CONST_AS float *sl = uniform_ptr(reinterpret_cast<const float *>(R.sph_local)) + 4 * s;
                 const int b = body[s];
@@ -307,7 +330,28 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
                     cc[c] = fmaf(F[c * 3 + 0], sl[0], fmaf(F[c * 3 + 1], sl[1], fmaf(F[c * 3 + 2], sl[2], F[9 + c])));
                     s_cen[(s * 3 + c) * kLanes + lane] = cc[c];
                 }
-                s_cn[s * kLanes + lane] = fmaf(cc[0], cc[0], fmaf(cc[1], cc[1], cc[2] * cc[2]));
+                if (nobs == 0) continue;
+                // The capsule of each row of 16 points, which phase D tests
+                // against the obstacles: the chord from the row's first
+                // centre a to its last, and as radius the largest distance
+                // of a centre to the chord's point at its own time (any
+                // point of the chord serves), plus r_s.  A row with a
+                // centre that is not finite gets a ball that meets
+                // everything.
+                const float ax = row_lane<0>(cc[0]), ay = row_lane<0>(cc[1]), az = row_lane<0>(cc[2]);
+                const float dx = cc[0] - ax, dy = cc[1] - ay, dz = cc[2] - az;
+                const float bx = row_lane<15>(dx), by = row_lane<15>(dy), bz = row_lane<15>(dz);
+                const float ex = fmaf(-tau, bx, dx), ey = fmaf(-tau, by, dy), ez = fmaf(-tau, bz, dz);
+                const float rad =
+                    fast_sqrt(row_max_nonneg(fminf(fmaf(ex, ex, fmaf(ey, ey, ez * ez)), 1.0e30f)));
+                const float len2 = fmaf(bx, bx, fmaf(by, by, bz * bz));
+                if ((lane & 15) == 0) {
+                    const bool cull = rad < 1.0e6f;
+                    const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                    float4 *cap = s_cap + (s * 4 + (lane >> 4)) * 2;
+                    cap[0] = cull ? make_float4(ax, ay, az, rad + sl[3]) : make_float4(0.0f, 0.0f, 0.0f, 1.0e15f);
+                    cap[1] = cull ? make_float4(bx, by, bz, __builtin_amdgcn_rcpf(fmaxf(len2, 1.0e-20f))) : zero;
+                }
             }
         }
     } else if (wave == W - 1) {
@@ -338,7 +382,7 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
             s_terms[0 * kLanes + lane] = fast_sqrt(pos2);
             s_terms[1 * kLanes + lane] = fast_sqrt(rot2);
         }
-        if (kTask && (mask & STORM_COST_BALL)) ball_term(P, R, x0, s_fr, s_terms, lane, h, H, tab);
+        if (kTask && (mask & STORM_COST_BALL)) ball_term(P, R, x0, s_fr, s_terms, pos, h, H, tab);
     } else {
         const bool task_out = kTask && (out.xd != nullptr || out.xdd != nullptr);
         if ((mask & STORM_COST_MANIP) || task_out) {
@@ -364,10 +408,12 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
                     qdd[k] = s_acc[k * kLanes + lane];
                 }
                 task_space(s_fr + lane, kLanes, qd, qdd, xd, xdd);
-                if (valid)
+                // the point at position `lane`
+                const int hp = lane / P.ppt, ip = tile * P.ppt + (lane - hp * P.ppt);
+                if (lane < n_pts && ip < N)
 #pragma unroll
                     for (int c = 0; c < 6; ++c) {
-                        const size_t at = ((size_t)c * N + i) * H + h;
+                        const size_t at = ((size_t)c * N + ip) * H + hp;
                         if (out.xd) out.xd[at] = xd[c];
                         if (out.xdd) out.xdd[at] = xdd[c];
                     }
@@ -376,82 +422,80 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
     }
     __syncthreads();
 
-    // ---- D: collision terms ---------------------------------------------------
+    // ---- D1: obstacles near each body ------------------------------------------
+    // The environment term is bound by VALU issue, so what counts is how many
+    // exact tests (20 instructions each) survive the cull.  Rows of 16 points
+    // ordered by step sweep short, nearly straight pieces, which a capsule
+    // holds tightly: on 4096 x 64 with 100 obstacles (one particle per wave)
+    // 171 of 5200 sphere-obstacle pairs stay, against 131 that truly come
+    // within a lane's reach; one ball per wave refined into eight kept 267-374
+    // and tested every sphere against every obstacle first.  Issued VALU per
+    // tile 24.6k -> 15.5k there, 12.9k -> 10.1k in the 256-problem batch;
+    // the control step of 64 x 4096 x 64 20.7 -> 16.0 ms.
+    // Both collision terms cull at the level of the whole wave and take exact
+    // distances (and their square roots) only where some lane of the wave may
+    // touch; a culled record touches at no lane, so the terms equal the
+    // brute-force ones.  First, bodies against obstacles: a lane holds one
+    // row's capsule of one body (that of the body's anchor sphere, widened to
+    // hold all of the body's spheres) and each half of the wave takes another
+    // obstacle; the waves share the obstacles.
+    if (nobs > 0) {
+        const int body = lane & 7, row = (lane >> 3) & 3, half = lane >> 5;
+        const float2 rec = R.body_bound[body];
+        const float4 *cap = s_cap + (__float_as_int(rec.x) * 4 + row) * 2;
+        const float4 a = cap[0], b = cap[1];
+        const float reach = a.w + rec.y;
+        for (int o0 = 2 * wave; o0 < nobs; o0 += 2 * W) {
+            const int o = o0 + half;
+            const float4 ob = o < nobs ? s_bound[o] : make_float4(3.0e38f, 3.0e38f, 3.0e38f, 0.0f);
+            uint64_t near = __builtin_amdgcn_ballot_w64(capsule_hits(a, b, reach + ob.w, ob.x, ob.y, ob.z));
+            if (near == 0) continue;
+            near |= near >> 16;  // the four rows of a body
+            near |= near >> 8;
+            if (row == 0 && ((near >> lane) & 1ull)) {
+                const int k = atomicAdd(&s_near_n[body], 1);
+                s_near[body * STORM_MAX_OBSTACLES + k] = (uint8_t)o;
+            }
+        }
+    }
+    __syncthreads();
+
+    // ---- D2: collision terms --------------------------------------------------
     // Environment (spheres round robin over the waves), then self-collision
-    // (items from a queue).  Both cull first at the level of the whole wave
-    // and take exact distances (and their square roots) only where some lane
-    // of the wave may touch; a culled record touches at no lane, so the
-    // terms equal the brute-force ones.
+    // (items from a queue).
     float env = 0.0f, selfpen = 0.0f;
-    if (mask & STORM_COST_ENV) {
+    if (nobs > 0) {
         const STORM_CONST_AS float *sob = uniform_ptr(reinterpret_cast<const float *>(P.sph_obs));
         const STORM_CONST_AS float *box = uniform_ptr(P.box_obs);
         const STORM_CONST_AS float *sloc = uniform_ptr(reinterpret_cast<const float *>(R.sph_local));
-        const int nso = P.n_sph_obs, nobs = P.n_sph_obs + P.n_box_obs;
+        const STORM_CONST_AS int32_t *sbody = uniform_ptr(R.sph_body);
+        const int nso = P.n_sph_obs;
         for (int s = wave; s < S; s += W) {
+            const int b = sbody[s];
+            const int n_near = __builtin_amdgcn_readfirstlane(s_near_n[b]);
+            if (n_near == 0) continue;
             const float x = s_cen[(s * 3 + 0) * kLanes + lane];
             const float y = s_cen[(s * 3 + 1) * kLanes + lane];
             const float z = s_cen[(s * 3 + 2) * kLanes + lane];
             const float rs = sloc[4 * s + 3];
             const float rs2 = rs * rs;
-            // Broad phase: the wave's 64 centres of this sphere lie in the
-            // ball of radius rad about lane 0's centre; by the triangle
-            // inequality an obstacle whose bounding ball is farther than
-            // rad + r_s from that point touches the sphere at no lane.  One
-            // lane tests one obstacle, and a ballot gives the candidates.  A
-            // non-finite centre anywhere in the wave turns the culling off.
-            const float rx = uniform_lane0(x), ry = uniform_lane0(y), rz = uniform_lane0(z);
-            const float ax = x - rx, ay = y - ry, az = z - rz;
-            const float rad = fast_sqrt(wave_max_nonneg(fminf(fmaf(ax, ax, fmaf(ay, ay, az * az)), 1.0e30f)));
-            const bool cull = rad < 1.0e6f;
-            const float rad_rs = rad + rs;
+            const float4 *cap = s_cap + (s * 4 + (lane >> 4)) * 2;
+            const float4 ca = cap[0], cb = cap[1];
             float best = 0.0f;
-            for (int o0 = 0; o0 < nobs; o0 += kLanes) {
-                const float4 bd = o0 == 0 ? bound0 : load_bound(P.obs_bound, o0 + lane, nobs);
-                const float dx = bd.x - rx, dy = bd.y - ry, dz = bd.z - rz;
-                const float reach = bd.w + rad_rs;
-                uint64_t cand = cull ? __builtin_amdgcn_ballot_w64(fmaf(dx, dx, fmaf(dy, dy, dz * dz)) < reach * reach)
-                                     : __builtin_amdgcn_ballot_w64(o0 + lane < nobs);
-                if (cull && __builtin_popcountll(cand) > kFineCandidates) {
-                    // Many candidates: trajectories that sweep far over the
-                    // horizon make the wave's ball large.  Eight balls of
-                    // eight lanes instead (centre: the group's first lane;
-                    // radius: the group's largest distance to it); an
-                    // obstacle stays a candidate where it reaches one of them.
-                    // The centres come through swizzles within each 32-lane
-                    // half, the radii through DPP maxima within each group.
-                    float gx[8], gy[8], gz[8], gr[8];
-                    {
-                        const float cx = __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(x), 0x18));
-                        const float cy = __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(y), 0x18));
-                        const float cz = __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(z), 0x18));
-                        const float bx = x - cx, by = y - cy, bz = z - cz;
-                        uint32_t u = __float_as_uint(fmaf(bx, bx, fmaf(by, by, bz * bz)));
-                        u = max(u, (uint32_t)__builtin_amdgcn_mov_dpp((int)u, 0xb1, 0xf, 0xf, false));
-                        u = max(u, (uint32_t)__builtin_amdgcn_mov_dpp((int)u, 0x4e, 0xf, 0xf, false));
-                        u = max(u, (uint32_t)__builtin_amdgcn_mov_dpp((int)u, 0x141, 0xf, 0xf, false));
-                        const float r8 = fast_sqrt(__uint_as_float(u)) + rs;
-#pragma unroll
-                        for (int g = 0; g < 8; ++g) {
-                            gx[g] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), 8 * g));
-                            gy[g] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(y), 8 * g));
-                            gz[g] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(z), 8 * g));
-                            gr[g] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r8), 8 * g));
-                        }
-                    }
-                    bool hit = false;
-#pragma unroll
-                    for (int g = 0; g < 8; ++g) {
-                        const float ex = bd.x - gx[g], ey = bd.y - gy[g], ez = bd.z - gz[g];
-                        const float rg = bd.w + gr[g];
-                        hit |= fmaf(ex, ex, fmaf(ey, ey, ez * ez)) < rg * rg;
-                    }
-                    cand &= __builtin_amdgcn_ballot_w64(hit);
-                }
-                // Narrow phase over the candidates, in increasing obstacle
-                // order (the maximum does not depend on the order).
+            for (int k0 = 0; k0 < n_near; k0 += 16) {
+                // the sphere's four capsules against 16 of its body's
+                // obstacles at a time
+                const int k = k0 + (lane & 15);
+                const int ob_l = s_near[b * STORM_MAX_OBSTACLES + min(k, n_near - 1)];
+                const float4 ob = s_bound[ob_l];
+                uint64_t hits =
+                    __builtin_amdgcn_ballot_w64(k < n_near && capsule_hits(ca, cb, ca.w + ob.w, ob.x, ob.y, ob.z));
+                hits |= hits >> 32;  // the four rows
+                uint32_t cand = (uint32_t)(hits | hits >> 16) & 0xffffu;
+                // Narrow phase over the candidates (the maximum does not
+                // depend on their order).
                 while (cand != 0) {
-                    const int o = o0 + (int)__builtin_ctzll(cand);
+                    const int o = __builtin_amdgcn_readlane(ob_l, __builtin_ctz(cand));
                     cand &= cand - 1;
                     if (o < nso) {
                         // the direct squared distance (no cancellation) against
@@ -537,7 +581,7 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
                 mx[k] = -2.0f * s_cen[(t * 3 + 0) * kLanes + lane];
                 my[k] = -2.0f * s_cen[(t * 3 + 1) * kLanes + lane];
                 mz[k] = -2.0f * s_cen[(t * 3 + 2) * kLanes + lane];
-                nt[k] = s_cn[t * kLanes + lane];
+                nt[k] = 0.25f * fmaf(mx[k], mx[k], fmaf(my[k], my[k], mz[k] * mz[k]));
             }
             const STORM_CONST_AS float *tg = thr + (size_t)grp * S * 8;
             // one round: partners s0 and s1 (s1 == s0 for the last of an odd
@@ -552,7 +596,7 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
                     cx[u] = s_cen[(s * 3 + 0) * kLanes + lane];
                     cy[u] = s_cen[(s * 3 + 1) * kLanes + lane];
                     cz[u] = s_cen[(s * 3 + 2) * kLanes + lane];
-                    ns[u] = s_cn[s * kLanes + lane];
+                    ns[u] = fmaf(cx[u], cx[u], fmaf(cy[u], cy[u], cz[u] * cz[u]));
                     const STORM_CONST_AS float *th = tp + u * dt;
 #pragma unroll
                     for (int k = 0; k < 4; ++k)
@@ -601,20 +645,20 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
 #pragma unroll
         for (int k = 0; k < kTerms; ++k) t[k] = 0.0f;
         if (mask & STORM_COST_POSE) {
-            t[0] = s_terms[0 * kLanes + lane];
-            t[1] = s_terms[1 * kLanes + lane];
+            t[0] = s_terms[0 * kLanes + pos];
+            t[1] = s_terms[1 * kLanes + pos];
         }
-        if (mask & STORM_COST_JOINT) t[2] = s_terms[2 * kLanes + lane];
-        if (mask & STORM_COST_VEL) t[3] = s_terms[3 * kLanes + lane];
-        if (mask & STORM_COST_STOP) t[4] = s_terms[4 * kLanes + lane];
+        if (mask & STORM_COST_JOINT) t[2] = s_terms[2 * kLanes + pos];
+        if (mask & STORM_COST_VEL) t[3] = s_terms[3 * kLanes + pos];
+        if (mask & STORM_COST_STOP) t[4] = s_terms[4 * kLanes + pos];
         if (mask & STORM_COST_MANIP) {
-            const float m = s_terms[5 * kLanes + lane];
+            const float m = s_terms[5 * kLanes + pos];
             t[5] = m < s_par[kParKm] ? 1.0f - m : 0.0f;
         }
         if (mask & STORM_COST_SELF)
-            for (int w = 0; w < W; ++w) t[6] = fmaxf(t[6], s_pself[w * kLanes + lane]);
+            for (int w = 0; w < W; ++w) t[6] = fmaxf(t[6], s_pself[w * kLanes + pos]);
         if (mask & STORM_COST_ENV)
-            for (int w = 0; w < W; ++w) t[7] += s_penv[w * kLanes + lane];
+            for (int w = 0; w < W; ++w) t[7] += s_penv[w * kLanes + pos];
         const float *wc = s_par + kParW;  // w_pos, w_rot, a_joint, a_vel, a_stop, a_manip, a_coll
         float c = wc[0] * t[0];
         c = fmaf(wc[1], t[1], c);
@@ -624,7 +668,7 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
         c = fmaf(wc[5], t[5], c);
         c = fmaf(wc[6], t[6] + t[7], c);
         if (kTask && (mask & STORM_COST_BALL)) {
-            t[8] = s_terms[8 * kLanes + lane];
+            t[8] = s_terms[8 * kLanes + pos];
             c = fmaf(P.w_ball, t[8], c);
         }
         if (valid) {
@@ -702,27 +746,27 @@ __global__ __launch_bounds__(W * kLanes) void rollout_batch_kernel(const Problem
     }
 }
 
-size_t rollout_lds_bytes(int S, int W, bool task = false)
+// The rows, the capsules of S spheres and the culling records of n_obs
+// obstacles (the 2 W collision partials sit over the 96 frame rows).
+size_t rollout_lds_bytes(int S, int n_obs, bool task = false)
 {
-    (void)W;  // the 2 W collision partials sit over the 96 frame rows
-    return (size_t)(96 + kTerms + S + rollout_cen_rows(S) + (task ? 2 * kDof : 0)) * kLanes * sizeof(float);
+    return (size_t)(96 + kTerms + rollout_cen_rows(S) + (task ? 2 * kDof : 0)) * kLanes * sizeof(float) +
+           (size_t)(8 * S + n_obs) * sizeof(float4);
 }
 
 }  // namespace
 
 hipError_t set_rollout_lds_limit()
 {
-    const int bytes16 = (int)rollout_lds_bytes(STORM_MAX_SPHERES, 16);
-    const int bytes8 = (int)rollout_lds_bytes(STORM_MAX_SPHERES, 8);
-    const int task16 = (int)rollout_lds_bytes(STORM_MAX_SPHERES, 16, true);
-    const int task8 = (int)rollout_lds_bytes(STORM_MAX_SPHERES, 8, true);
+    const int plain = (int)rollout_lds_bytes(STORM_MAX_SPHERES, STORM_MAX_OBSTACLES);
+    const int task = (int)rollout_lds_bytes(STORM_MAX_SPHERES, STORM_MAX_OBSTACLES, true);
     const void *fns[6] = {reinterpret_cast<const void *>(&rollout_kernel<16, false>),
                           reinterpret_cast<const void *>(&rollout_kernel<8, false>),
                           reinterpret_cast<const void *>(&rollout_batch_kernel<16>),
                           reinterpret_cast<const void *>(&rollout_batch_kernel<8>),
                           reinterpret_cast<const void *>(&rollout_kernel<16, true>),
                           reinterpret_cast<const void *>(&rollout_kernel<8, true>)};
-    const int bytes[6] = {bytes16, bytes8, bytes16, bytes8, task16, task8};
+    const int bytes[6] = {plain, plain, plain, plain, task, task};
     for (int k = 0; k < 6; ++k) {
         const hipError_t e = hipFuncSetAttribute(fns[k], hipFuncAttributeMaxDynamicSharedMemorySize, bytes[k]);
         if (e != hipSuccess) return e;
@@ -731,10 +775,10 @@ hipError_t set_rollout_lds_limit()
 }
 
 hipError_t launch_rollout_batch(const ProblemDev *probs, const int2 *items, int n_items, uint32_t *next,
-                                const RobotDev &R, const float *x0s, const float *goals, int waves, int grid,
-                                hipStream_t stream)
+                                const RobotDev &R, const float *x0s, const float *goals, int max_obs, int waves,
+                                int grid, hipStream_t stream)
 {
-    const size_t lds = rollout_lds_bytes(R.n_spheres, waves);
+    const size_t lds = rollout_lds_bytes(R.n_spheres, max_obs);
     if (waves == 16) {
         hipLaunchKernelGGL(rollout_batch_kernel<16>, dim3((unsigned)grid), dim3(16 * kLanes), lds, stream, probs,
                            items, n_items, next, R, x0s, goals);
@@ -753,7 +797,7 @@ hipError_t launch_rollout(const ProblemDev &P, const RobotDev &R, const float *x
     // the task-space form only where it is asked for: the ball term, or the
     // flange velocity and acceleration outputs
     const bool task = (P.cost_mask & STORM_COST_BALL) || P.selfnet || out.xd != nullptr || out.xdd != nullptr;
-    const size_t lds = rollout_lds_bytes(R.n_spheres, waves, task);
+    const size_t lds = rollout_lds_bytes(R.n_spheres, P.n_sph_obs + P.n_box_obs, task);
     const dim3 grid((unsigned)P.n_tiles);
     if (waves != 16 && waves != 8) return hipErrorInvalidValue;
     auto kernel = waves == 16 ? (task ? rollout_kernel<16, true> : rollout_kernel<16, false>)

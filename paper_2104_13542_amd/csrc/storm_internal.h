@@ -91,6 +91,7 @@ struct RobotDev {
     const float4 *sph_local;  // [S] body-frame centre (x, y, z), radius
     const int32_t *sph_body;  // [S] frame index 0..7 the sphere is attached to
     const float *self_thr;    // [groups][S][8] expanded pair test thresholds (4), contact distances (4)
+    const float2 *body_bound;  // [8] per frame: anchor sphere (int bits), what its radius lacks to hold the body's spheres
     const int32_t *self_items;  // [n_self_items][8] self-collision work items (self_segments)
 };
 
@@ -162,8 +163,8 @@ void pack_selfnet(const float *prm, std::vector<_Float16> &frag, std::vector<flo
 // Many problems: persistent rollout over a (problem, tile) work queue, and one
 // update workgroup per problem (descriptors in device memory).
 hipError_t launch_rollout_batch(const ProblemDev *probs, const int2 *items, int n_items, uint32_t *next,
-                                const RobotDev &R, const float *x0s, const float *goals, int waves, int grid,
-                                hipStream_t stream);
+                                const RobotDev &R, const float *x0s, const float *goals, int max_obs, int waves,
+                                int grid, hipStream_t stream);
 hipError_t launch_update_batch(const ProblemDev *probs, int n_problems, float *cmd, int shift, hipStream_t stream);
 // Differentiable form: adjoint + fixed-order reduction (grad, J) per joint;
 // with it > 0 the same launch takes Adam step `it` on the stored mean, and
@@ -193,6 +194,11 @@ struct SelfGroup {
 };
 std::vector<SelfGroup> self_groups(const storm_robot *robot);
 int self_segments(const storm_robot *robot, std::vector<int> &items);
+// The sphere of [lo, hi) about whose centre (in the body's frame) the ball
+// that holds all of them is smallest, and that ball's radius.
+int anchor_sphere(const float *spheres, int lo, int hi, double &radius);
+// Two floats per frame, the bodies' bounds of RobotDev::body_bound.
+std::vector<float> body_bounds(const storm_robot *robot);
 std::vector<float> self_thresholds(const storm_robot *robot, double reach);
 
 }  // namespace storm
