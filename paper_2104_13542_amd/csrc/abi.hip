@@ -12,8 +12,9 @@
 
 using namespace storm;
 
-// Scratch of storm_rollout_grad_noalloc: the adjoint's partial gradients
-// [kAdjChunks][7][kMaxH] and partial horizon-cost sums [kAdjChunks] of any
+// Scratch of storm_rollout_grad_noalloc (layout of ProblemDev::grad_part): the
+// adjoint's partial horizon-cost sums [kAdjChunks] and partial gradients
+// [kAdjChunks][7][kMaxH] of any
 // context (its chunk count is at most kAdjChunks), 0.9 MB per device, held
 // until the process ends.  Host code never uses this name as an address: the
 // device address of each device's copy comes from hipGetSymbolAddress, once
@@ -457,10 +458,11 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
     c->R.n_pairs = n_pairs;
 
     float *tables, *halton, *box_obs, *mean, *sigma2, *u, *C, *dt_raw, *lim_raw, *sig_raw, *obs_raw, *sph_raw_d;
-    float *self_thr, *body_bound, *grad_part, *cost_part, *grad, *adam, *ball, *qbuf = nullptr;
+    float *self_thr, *body_bound, *grad_part, *grad, *adam, *ball, *qbuf = nullptr;
     float4 *sph_obs, *obs_bound, *sph_local;
     int32_t *sph_body, *self_seg;
     uint32_t *counters;
+    PlainDev dev;
     hipError_t e = hipSuccess;
 #define STORM_TRY(expr)        \
     do {                       \
@@ -481,12 +483,12 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
     STORM_TRY(dalloc(c, &counters, (size_t)4));
     {
         const int chunks = P.n_tiles < storm::kAdjChunks ? P.n_tiles : storm::kAdjChunks;
-        STORM_TRY(dalloc(c, &grad_part, (size_t)chunks * STORM_DOF * storm::kMaxH));
-        STORM_TRY(dalloc(c, &cost_part, (size_t)chunks));
+        STORM_TRY(dalloc(c, &grad_part, storm::kAdjChunks + (size_t)chunks * STORM_DOF * storm::kMaxH));
     }
     STORM_TRY(dalloc(c, &grad, (size_t)H * STORM_DOF));
     STORM_TRY(dalloc(c, &adam, (size_t)2 * H * STORM_DOF));
     STORM_TRY(dalloc(c, &ball, (size_t)8));
+    STORM_TRY(dalloc(c, &c->dev, (size_t)1));
     if (P.selfnet) {
         STORM_TRY(dalloc(c, &qbuf, (size_t)STORM_DOF * N * H));
         STORM_TRY(dalloc(c, &c->net_frag, net_frag.size()));
@@ -541,7 +543,6 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
         P.status = counters + 1;
         P.last_step = counters + 2;
         P.grad_part = grad_part;
-        P.cost_part = cost_part;
         P.grad = grad;
         P.ball = ball;
         P.qbuf = qbuf;
@@ -552,9 +553,12 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
         c->R.sph_local = sph_local;
         c->R.sph_body = sph_body;
         c->R.self_thr = self_thr;
-        c->R.body_bound = reinterpret_cast<const float2 *>(body_bound);
+        c->R.body_bound = body_bound;
         c->R.self_items = self_seg;
         c->R.n_self_items = n_seg;
+        dev.P = P;
+        dev.R = c->R;
+        STORM_TRY(hipMemcpyAsync(c->dev, &dev, sizeof(dev), hipMemcpyHostToDevice, s));
         STORM_TRY(storm::launch_init_tables(P, dt_raw, lim_raw, params->acc_stop, params->gamma, params->w_term,
                                             params->k_jl, params->k_vl, sig_raw, comb, params->n_knots, obs_raw,
                                             n_obs,
@@ -577,9 +581,9 @@ fail:
 static hipError_t enqueue_rollout(storm_ctx ctx, const float *d_x0, const float *d_goal, const float *d_noise,
                                   const StepOut &out, hipStream_t s)
 {
-    hipError_t e = storm::launch_rollout(ctx->P, ctx->R, d_x0, d_goal, d_noise, out, ctx->waves, s);
+    hipError_t e = storm::launch_rollout(ctx->P, ctx->R.n_spheres, ctx->dev, d_x0, d_goal, d_noise, out, ctx->waves, s);
     if (e == hipSuccess && ctx->P.selfnet)
-        e = storm::launch_selfnet(ctx->P, ctx->net_frag, ctx->net_bias, out, s);
+        e = storm::launch_selfnet(ctx->P, ctx->dev, out, s);
     return e;
 }
 
@@ -615,7 +619,7 @@ int32_t storm_rollout_update(storm_ctx ctx, float *d_mean, float *d_sigma2, floa
     if (!ctx || !d_cmd) return STORM_E_NULL;
     if (ctx->error != STORM_OK) return ctx->error;
     if (!ctx->pending) return STORM_E_STATE;
-    const hipError_t e = storm::launch_update(ctx->P, d_mean, d_sigma2, d_cmd, shift != 0,
+    const hipError_t e = storm::launch_update(ctx->P, ctx->dev, d_mean, d_sigma2, d_cmd, shift != 0,
                                               static_cast<hipStream_t>(stream));
     if (e != hipSuccess) {
         ctx->error = STORM_E_DEVICE;
@@ -726,9 +730,9 @@ hipError_t enqueue_refine(storm_ctx ctx, const float *d_x0, const float *d_goal,
     // each launch: adjoint, then the reduction with Adam step `it` fused; the
     // last also writes the command and the shift
     for (int it = 1; e == hipSuccess && it <= iterations; ++it)
-        e = storm::launch_grad(ctx->P, ctx->R, d_x0, d_goal, ctx->P.mean, nullptr, nullptr, nullptr, it, lr,
+        e = storm::launch_grad(ctx->P, ctx->dev, ctx->P.grad_part, d_x0, d_goal, ctx->P.mean, nullptr, nullptr, nullptr, it, lr,
                                it == iterations ? d_cmd : nullptr, shift, s);
-    if (e == hipSuccess && iterations == 0) e = storm::launch_command(ctx->P, d_cmd, shift, s);
+    if (e == hipSuccess && iterations == 0) e = storm::launch_command(ctx->dev, d_cmd, shift, s);
     return e;
 }
 
@@ -760,7 +764,7 @@ int32_t create_graph(storm_ctx ctx, const float *d_x0, const float *d_goal, floa
         const bool last = k == iterations - 1;
         e = enqueue_rollout(ctx, d_x0, d_goal, nullptr, none, s);
         if (e == hipSuccess)
-            e = storm::launch_update(ctx->P, nullptr, nullptr, d_cmd, last && shift != 0 && refine_iters == 0, s);
+            e = storm::launch_update(ctx->P, ctx->dev, nullptr, nullptr, d_cmd, last && shift != 0 && refine_iters == 0, s);
     }
     if (e == hipSuccess && refine_iters > 0) e = enqueue_refine(ctx, d_x0, d_goal, refine_iters, lr, d_cmd, shift, s);
     hipGraph_t graph = nullptr;
@@ -792,7 +796,7 @@ int32_t storm_rollout_control(storm_ctx ctx, const float *d_x0, const float *d_g
     for (int k = 0; e == hipSuccess && k < iterations; ++k) {
         e = enqueue_rollout(ctx, d_x0, d_goal, nullptr, none, s);
         if (e == hipSuccess)
-            e = storm::launch_update(ctx->P, nullptr, nullptr, d_cmd, k == iterations - 1 && shift != 0, s);
+            e = storm::launch_update(ctx->P, ctx->dev, nullptr, nullptr, d_cmd, k == iterations - 1 && shift != 0, s);
     }
     if (e != hipSuccess) {
         ctx->error = STORM_E_DEVICE;
@@ -821,7 +825,7 @@ int32_t storm_rollout_grad(storm_ctx ctx, const float *d_x0, const float *d_goal
     if (!ctx || !d_x0 || !d_goal || !d_mean) return STORM_E_NULL;
     if (ctx->error != STORM_OK) return ctx->error;
     if (ctx->P.grad_mask & ~kDiffMask) return STORM_E_UNSUPPORTED;
-    if (storm::launch_grad(ctx->P, ctx->R, d_x0, d_goal, d_mean, d_noise, d_grad, d_J, 0, 0.0f, nullptr, 0,
+    if (storm::launch_grad(ctx->P, ctx->dev, ctx->P.grad_part, d_x0, d_goal, d_mean, d_noise, d_grad, d_J, 0, 0.0f, nullptr, 0,
                            static_cast<hipStream_t>(stream)) != hipSuccess) {
         ctx->error = STORM_E_DEVICE;
         return STORM_E_DEVICE;
@@ -835,14 +839,12 @@ int32_t storm_rollout_grad_noalloc(storm_ctx ctx, const float *d_x0, const float
     if (!ctx || !d_x0 || !d_goal || !d_mean) return STORM_E_NULL;
     if (ctx->error != STORM_OK) return ctx->error;
     if (ctx->P.grad_mask & ~kDiffMask) return STORM_E_UNSUPPORTED;
-    ProblemDev P = ctx->P;
+    const ProblemDev &P = ctx->P;
     const size_t chunks = (size_t)(P.n_tiles < kAdjChunks ? P.n_tiles : kAdjChunks);
     if (chunks * STORM_DOF * kMaxH > kNoallocGradFloats || P.H > kMaxH) return STORM_E_RANGE;
     // the partials go to this device's static scratch instead of the
     // context's own buffers; everything else is the context's
-    P.grad_part = ctx->scratch;
-    P.cost_part = ctx->scratch + kNoallocGradFloats;
-    if (storm::launch_grad(P, ctx->R, d_x0, d_goal, d_mean, d_noise, d_grad, d_J, 0, 0.0f, nullptr, 0,
+    if (storm::launch_grad(P, ctx->dev, ctx->scratch, d_x0, d_goal, d_mean, d_noise, d_grad, d_J, 0, 0.0f, nullptr, 0,
                            static_cast<hipStream_t>(stream)) != hipSuccess) {
         ctx->error = STORM_E_DEVICE;
         return STORM_E_DEVICE;

@@ -28,7 +28,7 @@ constexpr int kRedThreads = 1024;
 // Phases A-D for one tile, then the tile's share of the chunk partials:
 // acc (thread t < 7H: joint t / H, step t % H) gains the sum over the tile's
 // particles of dC/du, cacc (thread 0) the tile's horizon-cost sum.
-__device__ __forceinline__ void adjoint_tile(const ProblemDev &P, const RobotDev &R, const int tile,
+__device__ __forceinline__ void adjoint_tile(ProblemRef P, RobotRef R, const int N, const int H, const int tile,
                                              const float *__restrict__ x0, const float *__restrict__ goal,
                                              const float *__restrict__ mean, const float *__restrict__ noise,
                                              float &acc, float &cacc)
@@ -47,21 +47,20 @@ __device__ __forceinline__ void adjoint_tile(const ProblemDev &P, const RobotDev
 
     const int lane = threadIdx.x & (kLanes - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int N = P.N, H = P.H;
     const int pl = lane / H;
     const int h = lane - pl * H;
     const int i = tile * P.ppt + pl;
     const bool valid = pl < P.ppt && i < N;
     const bool live = valid && i < N - P.n_null;
     const uint32_t mask = P.grad_mask;
-    const float *__restrict__ tab = P.tables;
+    const global_ptr<const float> tab = as_global(P.tables);
     const float dt_h = tab[kTabDt + h];
     const float hw_h = tab[kTabHw + h];
 
     // ---- A: noise, controls, integrator ---------------------------------------
     if (wave < 2) {
         float e[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (live) standard_noise4(P, noise, wave, i, h, *P.last_step, e);
+        if (live) standard_noise4(P, noise, wave, i, h, *as_global(P.last_step), e);
 #pragma unroll
         for (int m = 0; m < 4; ++m) s_eps[4 * wave + m][lane] = e[m];
     }
@@ -76,7 +75,7 @@ __device__ __forceinline__ void adjoint_tile(const ProblemDev &P, const RobotDev
             if (comb) e = f;
         }
         float u = 0.0f;
-        if (live) u = fmaf(sqrtf(P.cov_step ? P.sigma2[h * kDof + j] : P.sigma2[j]), e, mean[h * kDof + j]);
+        if (live) u = fmaf(sqrtf(as_global(P.sigma2)[P.cov_step ? h * kDof + j : j]), e, mean[h * kDof + j]);
         const float v = x0[kDof + j] + segmented_scan(dt_h * u, h, H);
         const float q = x0[j] + segmented_scan(dt_h * v, h, H);
         s_q[j][lane] = q;
@@ -236,43 +235,33 @@ __device__ __forceinline__ void adjoint_tile(const ProblemDev &P, const RobotDev
 
 // Chunks of tiles of one problem: min(n_tiles, kAdjChunks), chunk c covering
 // tiles [c T / n, (c + 1) T / n); one workgroup per chunk, tiles in order.
-__device__ __forceinline__ int adj_chunks(const ProblemDev &P) { return min(P.n_tiles, kAdjChunks); }
-
-__device__ __forceinline__ void adjoint_chunk(const ProblemDev &P, const RobotDev &R, const int c,
+__device__ __forceinline__ void adjoint_chunk(ProblemRef P, RobotRef R, const int N, const int H, const int c,
                                               const float *__restrict__ x0, const float *__restrict__ goal,
-                                              const float *__restrict__ mean, const float *__restrict__ noise)
+                                              const float *__restrict__ mean, const float *__restrict__ noise,
+                                              float *__restrict__ part)
 {
-    const int n = adj_chunks(P), T = P.n_tiles;
+    const int T = P.n_tiles, n = min(T, kAdjChunks);
     const int t0 = (int)((long long)c * T / n), t1 = (int)((long long)(c + 1) * T / n);
     float acc = 0.0f, cacc = 0.0f;
-    for (int tile = t0; tile < t1; ++tile) adjoint_tile(P, R, tile, x0, goal, mean, noise, acc, cacc);
-    if ((int)threadIdx.x < kDof * P.H) {
-        const int j = threadIdx.x / P.H, hh = threadIdx.x - j * P.H;
-        P.grad_part[((size_t)c * kDof + j) * kMaxH + hh] = acc;
+    for (int tile = t0; tile < t1; ++tile) adjoint_tile(P, R, N, H, tile, x0, goal, mean, noise, acc, cacc);
+    if ((int)threadIdx.x < kDof * H) {
+        const int j = threadIdx.x / H, hh = threadIdx.x - j * H;
+        as_global(part)[kAdjChunks + ((size_t)c * kDof + j) * kMaxH + hh] = acc;
     }
-    if (threadIdx.x == 0) P.cost_part[c] = cacc;
+    if (threadIdx.x == 0) as_global(part)[c] = cacc;
 }
 
-// The fields the first loads of a tile depend on come first, as scalar
-// arguments, so that they are preloaded into SGPRs; the rest of the problem
-// follows in P.
-__global__ __launch_bounds__(kAdjWaves *kLanes) void adjoint_kernel(const float *__restrict__ mean, uint32_t *last_step,
-                                                                    float *sigma2, const float *halton,
-                                                                    const float *tables, int32_t N, int32_t H,
-                                                                    int32_t ppt, ProblemDev P, RobotDev R,
+// All arguments fit the 14 dwords that are preloaded into SGPRs; the rest of
+// the problem comes from its descriptor in device memory.
+__global__ __launch_bounds__(kAdjWaves *kLanes) void adjoint_kernel(const PlainDev *dev,
+                                                                    const float *__restrict__ mean,
                                                                     const float *__restrict__ x0,
                                                                     const float *__restrict__ goal,
-                                                                    const float *__restrict__ noise)
+                                                                    const float *__restrict__ noise,
+                                                                    float *__restrict__ part, int32_t N, int32_t H)
 {
-    ProblemDev Q = P;
-    Q.last_step = last_step;
-    Q.sigma2 = sigma2;
-    Q.halton = halton;
-    Q.tables = tables;
-    Q.N = N;
-    Q.H = H;
-    Q.ppt = ppt;
-    adjoint_chunk(Q, R, blockIdx.x, x0, goal, mean, noise);
+    const STORM_CONST_AS PlainDev &D = *uniform_ptr(dev);
+    adjoint_chunk(D.P, D.R, N, H, blockIdx.x, x0, goal, mean, noise, part);
 }
 
 // Batched form: workgroup k takes chunk items[k] = (problem, chunk).  At
@@ -281,13 +270,15 @@ __global__ __launch_bounds__(kAdjWaves *kLanes) void adjoint_kernel(const float 
 // stalls (large workload: 2.2 -> 1.65 ms per launch; 88 VGPRs unbounded).
 __global__ __launch_bounds__(kAdjWaves *kLanes) __attribute__((amdgpu_waves_per_eu(6))) void adjoint_batch_kernel(const ProblemDev *__restrict__ probs,
                                                                           const int2 *__restrict__ items,
-                                                                          RobotDev R, const float *__restrict__ x0s,
+                                                                          const RobotDev *robot,
+                                                                          const float *__restrict__ x0s,
                                                                           const float *__restrict__ goals)
 {
     const STORM_CONST_AS int32_t *it = uniform_ptr(reinterpret_cast<const int32_t *>(items));
     const int p = it[2 * blockIdx.x], c = it[2 * blockIdx.x + 1];
-    const ProblemDev P = load_uniform(probs + p);
-    adjoint_chunk(P, R, c, x0s + (size_t)p * 3 * kDof, goals + (size_t)p * 12, P.mean, nullptr);
+    ProblemRef P = uniform_ptr(probs)[p];
+    adjoint_chunk(P, *uniform_ptr(robot), P.N, P.H, c, x0s + (size_t)p * 3 * kDof, goals + (size_t)p * 12, P.mean,
+                  nullptr, P.grad_part);
 }
 
 __device__ __forceinline__ float wave_sum(float x)
@@ -302,38 +293,38 @@ __device__ __forceinline__ float wave_sum(float x)
 // are added in order.
 // One Adam step with gradient g on the stored mean, element t (moments
 // restart at it == 1).
-__device__ __forceinline__ void adam_step(const ProblemDev &P, int t, float g, int it, float lr, float b1, float b2,
+__device__ __forceinline__ void adam_step(ProblemRef P, int t, float g, int it, float lr, float b1, float b2,
                                           float eps)
 {
-    const float m0 = it == 1 ? 0.0f : P.adam_m[t];
-    const float v0 = it == 1 ? 0.0f : P.adam_v[t];
+    const float m0 = it == 1 ? 0.0f : as_global(P.adam_m)[t];
+    const float v0 = it == 1 ? 0.0f : as_global(P.adam_v)[t];
     const float m = fmaf(b1, m0, (1.0f - b1) * g);
     const float v = fmaf(b2, v0, (1.0f - b2) * g * g);
-    P.adam_m[t] = m;
-    P.adam_v[t] = v;
+    as_global(P.adam_m)[t] = m;
+    as_global(P.adam_v)[t] = v;
     const float mh = m / (1.0f - powf(b1, (float)it));
     const float vh = v / (1.0f - powf(b2, (float)it));
-    P.mean[t] -= lr * mh / (sqrtf(vh) + eps);
+    as_global(P.mean)[t] -= lr * mh / (sqrtf(vh) + eps);
 }
 
 // cmd = mu_0, then the warm-start shift of the stored mean (and of a
 // per-step variance, sigma_init^2 appended) if requested.
-__device__ __forceinline__ void command(const ProblemDev &P, float *__restrict__ cmd, int shift)
+__device__ __forceinline__ void command(ProblemRef P, float *__restrict__ cmd, int shift)
 {
     __shared__ float s_mu[kDof * kMaxH];
     __shared__ float s_s2[kDof * kMaxH];
     const int t = threadIdx.x;
     const int n = P.H * kDof;
     for (int k = t; k < n; k += blockDim.x) {
-        s_mu[k] = P.mean[k];
-        if (P.cov_step) s_s2[k] = P.sigma2[k];
+        s_mu[k] = as_global(P.mean)[k];
+        if (P.cov_step) s_s2[k] = as_global(P.sigma2)[k];
     }
     __syncthreads();
     if (t < kDof) cmd[t] = s_mu[t];
     if (shift)
         for (int k = t; k < n; k += blockDim.x) {
-            P.mean[k] = k + kDof < n ? s_mu[k + kDof] : 0.0f;
-            if (P.cov_step) P.sigma2[k] = k + kDof < n ? s_s2[k + kDof] : P.tables[kTabSig0 + k % kDof];
+            as_global(P.mean)[k] = k + kDof < n ? s_mu[k + kDof] : 0.0f;
+            if (P.cov_step) as_global(P.sigma2)[k] = k + kDof < n ? s_s2[k + kDof] : as_global(P.tables)[kTabSig0 + k % kDof];
         }
 }
 
@@ -344,7 +335,8 @@ __device__ __forceinline__ void command(const ProblemDev &P, float *__restrict__
 // mu[h][j]; with cmd, it writes the command mu[0][j] and the warm-start
 // shift of the joint (the next step's value through a DPP wave shift), with
 // a per-step variance shifted alike.
-__device__ __forceinline__ void grad_step(const ProblemDev &P, int j, float *__restrict__ grad_out,
+__device__ __forceinline__ void grad_step(ProblemRef P, int j, const float *__restrict__ part,
+                                          float *__restrict__ grad_out,
                                           float *__restrict__ J_out, int it, float lr, float *__restrict__ cmd,
                                           int shift)
 {
@@ -358,7 +350,7 @@ __device__ __forceinline__ void grad_step(const ProblemDev &P, int j, float *__r
     const int r = t / H, h = t - r * H;
     float acc = 0.0f;
     if (r < rows) {
-        const float *__restrict__ src = P.grad_part + (size_t)j * kMaxH + h;
+        const global_ptr<const float> src = as_global(part) + kAdjChunks + (size_t)j * kMaxH + h;
         float v[kMaxPerThread];
 #pragma unroll
         for (int i = 0; i < kMaxPerThread; ++i) {
@@ -371,7 +363,7 @@ __device__ __forceinline__ void grad_step(const ProblemDev &P, int j, float *__r
     s_red[t] = acc;
     if (j == 0) {
         float cs = 0.0f;
-        for (int k = t; k < T; k += kRedThreads) cs += P.cost_part[k];
+        for (int k = t; k < T; k += kRedThreads) cs += as_global(part)[k];
         cs = wave_sum(cs);
         if (lane == 0) s_wave[wave] = cs;
     }
@@ -395,80 +387,86 @@ __device__ __forceinline__ void grad_step(const ProblemDev &P, int j, float *__r
             if (k + m < rows) p4[m] += s_red[(k + m) * H + lane];
         const float g = ((p4[0] + p4[1]) + (p4[2] + p4[3])) * invN;
         const int e = lane * kDof + j;
-        P.grad[e] = g;
+        as_global(P.grad)[e] = g;
         if (grad_out) grad_out[e] = g;
         if (it > 0) adam_step(P, e, g, it, lr, 0.9f, 0.999f, 1e-8f);
-        if (cmd) mu = P.mean[e];
+        if (cmd) mu = as_global(P.mean)[e];
     }
     if (cmd) {
         const float mu_next = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(mu), 0x130, 0xf, 0xf,
                                                                          true));  // wave_shl:1
         if (lane == 0) cmd[j] = mu;
-        if (shift && lane < H) P.mean[lane * kDof + j] = lane + 1 < H ? mu_next : 0.0f;
+        if (shift && lane < H) as_global(P.mean)[lane * kDof + j] = lane + 1 < H ? mu_next : 0.0f;
         if (shift && P.cov_step) {
             // a per-step variance moves forward too, sigma_init^2 appended
-            const float s2 = lane < H ? P.sigma2[lane * kDof + j] : 0.0f;
+            const float s2 = lane < H ? as_global(P.sigma2)[lane * kDof + j] : 0.0f;
             const float s2_next = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s2), 0x130, 0xf, 0xf,
                                                                              true));  // wave_shl:1
-            if (lane < H) P.sigma2[lane * kDof + j] = lane + 1 < H ? s2_next : P.tables[kTabSig0 + j];
+            if (lane < H) as_global(P.sigma2)[lane * kDof + j] = lane + 1 < H ? s2_next : as_global(P.tables)[kTabSig0 + j];
         }
     }
 }
 
-__global__ __launch_bounds__(kRedThreads) void grad_step_kernel(ProblemDev P, float *__restrict__ grad_out,
-                                                                float *__restrict__ J_out, int it, float lr,
-                                                                float *__restrict__ cmd, int shift)
+// All arguments fit the 14 dwords that are preloaded into SGPRs.
+__global__ __launch_bounds__(kRedThreads) void grad_step_kernel(const PlainDev *dev,
+                                                                const float *__restrict__ part,
+                                                                float *__restrict__ grad_out,
+                                                                float *__restrict__ J_out, float *__restrict__ cmd,
+                                                                int it, float lr, int shift)
 {
-    grad_step(P, blockIdx.x, grad_out, J_out, it, lr, cmd, shift);
+    grad_step(uniform_ptr(dev)->P, blockIdx.x, part, grad_out, J_out, it, lr, cmd, shift);
 }
 
-__global__ void command_kernel(ProblemDev P, float *__restrict__ cmd, int shift) { command(P, cmd, shift); }
+__global__ void command_kernel(const PlainDev *dev, float *__restrict__ cmd, int shift)
+{
+    command(uniform_ptr(dev)->P, cmd, shift);
+}
 
 // Batched forms: workgroup p * 7 + j serves joint j of problem p.
 __global__ __launch_bounds__(kRedThreads) void grad_step_batch_kernel(const ProblemDev *__restrict__ probs, int it,
                                                                       float lr, float *__restrict__ cmd, int shift)
 {
     const int p = blockIdx.x / kDof, j = blockIdx.x - p * kDof;
-    const ProblemDev P = load_uniform(probs + p);
-    grad_step(P, j, nullptr, nullptr, it, lr, cmd ? cmd + (size_t)p * kDof : nullptr, shift);
+    ProblemRef P = uniform_ptr(probs)[p];
+    grad_step(P, j, P.grad_part, nullptr, nullptr, it, lr, cmd ? cmd + (size_t)p * kDof : nullptr, shift);
 }
 
 __global__ void command_batch_kernel(const ProblemDev *__restrict__ probs, float *__restrict__ cmd, int shift)
 {
-    const ProblemDev P = load_uniform(probs + blockIdx.x);
+    ProblemRef P = uniform_ptr(probs)[blockIdx.x];
     command(P, cmd + (size_t)blockIdx.x * kDof, shift);
 }
 
 }  // namespace
 
-hipError_t launch_grad(const ProblemDev &P, const RobotDev &R, const float *x0, const float *goal, const float *mean,
-                       const float *noise, float *grad_out, float *J_out, int it, float lr, float *cmd, int shift,
-                       hipStream_t stream)
+hipError_t launch_grad(const ProblemDev &P, const PlainDev *dev, float *part, const float *x0, const float *goal,
+                       const float *mean, const float *noise, float *grad_out, float *J_out, int it, float lr,
+                       float *cmd, int shift, hipStream_t stream)
 {
     const int chunks = P.n_tiles < kAdjChunks ? P.n_tiles : kAdjChunks;
-    hipLaunchKernelGGL(adjoint_kernel, dim3((unsigned)chunks), dim3(kAdjWaves * kLanes), 0, stream, mean, P.last_step,
-                       P.sigma2, P.halton, P.tables, P.N, P.H, P.ppt, P, R, x0, goal, noise);
+    hipLaunchKernelGGL(adjoint_kernel, dim3((unsigned)chunks), dim3(kAdjWaves * kLanes), 0, stream, dev, mean, x0, goal,
+                       noise, part, P.N, P.H);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(grad_step_kernel, dim3(kDof), dim3(kRedThreads), 0, stream, P, grad_out, J_out, it, lr, cmd,
-                       shift);
+    hipLaunchKernelGGL(grad_step_kernel, dim3(kDof), dim3(kRedThreads), 0, stream, dev, part, grad_out, J_out, cmd,
+                       it, lr, shift);
     return hipGetLastError();
 }
 
-hipError_t launch_command(const ProblemDev &P, float *cmd, int shift, hipStream_t stream)
+hipError_t launch_command(const PlainDev *dev, float *cmd, int shift, hipStream_t stream)
 {
-    hipLaunchKernelGGL(command_kernel, dim3(1), dim3(256), 0, stream, P, cmd, shift);
+    hipLaunchKernelGGL(command_kernel, dim3(1), dim3(256), 0, stream, dev, cmd, shift);
     return hipGetLastError();
 }
 
 hipError_t launch_refine_batch(const ProblemDev *probs, int n_problems, const int2 *items, int n_items,
-                               const RobotDev &R, const float *x0s, const float *goals, int iterations, float lr,
-                               float *cmd, int shift, hipStream_t stream)
+                               const RobotDev *robot, const float *x0s, const float *goals, int iterations,
+                               float lr, float *cmd, int shift, hipStream_t stream)
 {
     hipError_t e = hipSuccess;
     for (int it = 1; e == hipSuccess && it <= iterations; ++it) {
         hipLaunchKernelGGL(adjoint_batch_kernel, dim3((unsigned)n_items), dim3(kAdjWaves * kLanes), 0, stream,
-                           probs, items, R, x0s, goals);
+                           probs, items, robot, x0s, goals);
         e = hipGetLastError();
         if (e != hipSuccess) break;
         hipLaunchKernelGGL(grad_step_batch_kernel, dim3((unsigned)(n_problems * kDof)), dim3(kRedThreads), 0, stream,

@@ -21,6 +21,7 @@ struct storm_batch_s {
     std::vector<storm_ctx> ctxs;  // per-problem workspace, tables and policy state
     RobotDev R{};                  // robot constants (problem 0's: every problem shares the robot)
     ProblemDev *d_probs = nullptr; // [P] descriptors
+    RobotDev *d_robot = nullptr;   // the robot constants in device memory
     int2 *d_items_cost = nullptr;  // work queue, most expensive tiles first
     int2 *d_items_plain = nullptr; // work queue in problem order
     int n_items = 0;
@@ -71,11 +72,10 @@ double tile_cost(const ProblemDev &P, int n_spheres, int n_pairs)
 
 int32_t launch_batch_step(storm_batch b, const float *d_x0, const float *d_goal, hipStream_t s)
 {
-    const RobotDev &R = b->R;
     const int2 *items = b->cfg.cost_order ? b->d_items_cost : b->d_items_plain;
     const hipError_t e =
-        launch_rollout_batch(b->d_probs, items, b->n_items, b->d_next, R, d_x0, d_goal, b->max_obs, b->cfg.waves,
-                             b->cfg.grid, s);
+        launch_rollout_batch(b->d_probs, items, b->n_items, b->d_next, b->d_robot, b->R.n_spheres, b->max_obs, d_x0,
+                             d_goal, b->cfg.waves, b->cfg.grid, s);
     return e == hipSuccess ? STORM_OK : STORM_E_DEVICE;
 }
 
@@ -111,7 +111,7 @@ int32_t batch_graph(storm_batch b, const float *d_x0, const float *d_goal, float
         if (e == hipSuccess) e = launch_update_batch(b->d_probs, b->n_problems, d_cmd, last_shift, s);
     }
     if (e == hipSuccess && refine_iters > 0)
-        e = launch_refine_batch(b->d_probs, b->n_problems, b->d_adj_items, b->n_adj_items, b->R, d_x0, d_goal,
+        e = launch_refine_batch(b->d_probs, b->n_problems, b->d_adj_items, b->n_adj_items, b->d_robot, d_x0, d_goal,
                                 refine_iters, lr, d_cmd, shift != 0, s);
     hipGraph_t graph = nullptr;
     const hipError_t e2 = hipStreamEndCapture(s, &graph);
@@ -209,6 +209,8 @@ int32_t storm_batch_init(storm_batch *out, int32_t n_problems, const storm_param
     std::vector<int2> sorted(plain.size());
     for (size_t k = 0; k < order.size(); ++k) sorted[k] = plain[order[k]];
     if (e == hipSuccess) e = balloc(b, &b->d_probs, (size_t)n_problems);
+    if (e == hipSuccess) e = balloc(b, &b->d_robot, (size_t)1);
+    if (e == hipSuccess) e = hipMemcpy(b->d_robot, &b->R, sizeof(RobotDev), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = balloc(b, &b->d_items_cost, plain.size());
     if (e == hipSuccess) e = balloc(b, &b->d_items_plain, plain.size());
     if (e == hipSuccess) e = balloc(b, &b->d_next, (size_t)1);
@@ -280,7 +282,7 @@ int32_t storm_batch_refine(storm_batch b, const float *d_x0, const float *d_goal
     if (!(lr >= 0.0f) || !isfinite(lr)) return STORM_E_PARAM;
     if (b->error != STORM_OK) return b->error;
     if (!b->differentiable) return STORM_E_UNSUPPORTED;
-    if (launch_refine_batch(b->d_probs, b->n_problems, b->d_adj_items, b->n_adj_items, b->R, d_x0, d_goal,
+    if (launch_refine_batch(b->d_probs, b->n_problems, b->d_adj_items, b->n_adj_items, b->d_robot, d_x0, d_goal,
                             iterations, lr, d_cmd, shift != 0, static_cast<hipStream_t>(stream)) != hipSuccess) {
         b->error = STORM_E_DEVICE;
         return STORM_E_DEVICE;

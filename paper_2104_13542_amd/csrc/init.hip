@@ -39,6 +39,12 @@ __global__ void tables_kernel(ProblemDev P, float *tables, const float *dt_raw, 
         tables[kTabSig0 + t] = (float)(s * s);
         if (!P.cov_step) P.sigma2[t] = (float)(s * s);
     }
+    if (t == 0) {
+        const float par[14] = {P.alpha_rot[0], P.alpha_rot[1], P.alpha_rot[2], P.alpha_pos[0], P.alpha_pos[1],
+                               P.alpha_pos[2], P.w_pos,        P.w_rot,        P.a_joint,      P.a_vel,
+                               P.a_stop,       P.a_manip,      P.a_coll,       P.k_m};
+        for (int k = 0; k < 14; ++k) tables[kTabPar + k] = par[k];
+    }
     if (t < 8) P.ball[t] = 0.0f;  // no ball state until storm_rollout_set_ball
     if (t == 0) {
         *P.step = 0u;

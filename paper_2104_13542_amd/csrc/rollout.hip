@@ -77,6 +77,13 @@ __device__ __forceinline__ bool capsule_hits(const float4 a, const float4 b, flo
     return fmaf(ex, ex, fmaf(ey, ey, ez * ez)) < reach * fabsf(reach);
 }
 
+// The fields of a problem that the first loads of a tile depend on.
+struct TileFirst {
+    uint32_t *step;
+    const float *mean, *halton;
+    int32_t N, H, n_halton, n_null;
+};
+
 // LDS copy of the goal (R row-major, p) and the cost weights, by index.
 constexpr int kParArot = 12, kParApos = 15, kParW = 18, kParKm = 25, kParCount = 26;
 
@@ -86,9 +93,9 @@ constexpr int kParArot = 12, kParApos = 15, kParW = 18, kParKm = 25, kParCount =
 // h) takes the in-plane gravity in the flange frame of its rolled-out state
 // and the two segmented scans of Eq. 7's scheme give the ball's velocity
 // and position; the term is the distance from the tray centre.
-__device__ __forceinline__ void ball_term(const ProblemDev &P, const RobotDev &R, const float *__restrict__ x0,
+__device__ __forceinline__ void ball_term(ProblemRef P, RobotRef R, const float *__restrict__ x0,
                                           const float *s_fr, float *s_terms, const int pos, const int h,
-                                          const int H, const float *__restrict__ tab)
+                                          const int H, global_ptr<const float> tab)
 {
     float r0[9] = {1.0f, 0.0f, 0.0f, 0.0f, 1.0f, 0.0f, 0.0f, 0.0f, 1.0f}, p0[3] = {0.0f, 0.0f, 0.0f};
 #pragma unroll
@@ -97,13 +104,13 @@ __device__ __forceinline__ void ball_term(const ProblemDev &P, const RobotDev &R
         if (f < kDof) sincosf(x0[f], &st, &ct);
         dh_step(r0, p0, R.ca[f], R.sa[f], R.a[f], R.d[f], ct, st);
     }
-    const float bw[3] = {P.ball[0] - p0[0], P.ball[1] - p0[1], P.ball[2] - p0[2]};
+    const float bw[3] = {as_global(P.ball)[0] - p0[0], as_global(P.ball)[1] - p0[1], as_global(P.ball)[2] - p0[2]};
     float xb[2], vb[2], ab[2];
     const float *E = s_fr + 7 * 12 * kLanes + pos;
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
         xb[c] = fmaf(r0[c], bw[0], fmaf(r0[3 + c], bw[1], r0[6 + c] * bw[2]));
-        vb[c] = fmaf(r0[c], P.ball[3], fmaf(r0[3 + c], P.ball[4], r0[6 + c] * P.ball[5]));
+        vb[c] = fmaf(r0[c], as_global(P.ball)[3], fmaf(r0[3 + c], as_global(P.ball)[4], r0[6 + c] * as_global(P.ball)[5]));
         ab[c] = fmaf(E[c * kLanes], P.ball_g[0], fmaf(E[(3 + c) * kLanes], P.ball_g[1],
                                                       E[(6 + c) * kLanes] * P.ball_g[2]));
     }
@@ -124,8 +131,11 @@ __device__ __forceinline__ void ball_term(const ProblemDev &P, const RobotDev &R
 // kTask: the task-space form, which adds the flange velocity and
 // acceleration outputs (Eq. 8), the ball-on-tray term and the joint
 // positions the learned self-collision network reads.
-template <int W, bool kTask = false>
-__device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev &R, const int tile,
+// The fields of the descriptors are scalar loads where they are used (held as
+// copies they overflowed the SGPRs into lanes of VGPRs, 180 lane moves per
+// wave and tile).
+template <int W, bool kTask>
+__device__ __forceinline__ void rollout_tile(ProblemRef P, RobotRef R, const TileFirst &first, const int tile,
                                              const float *__restrict__ x0, const float *__restrict__ goal,
                                              const float *__restrict__ noise, const StepOut &out, float *smem)
 {
@@ -155,31 +165,31 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
 
     const int lane = threadIdx.x & (kLanes - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int N = P.N, H = P.H;
+    const int N = first.N, H = first.H, ppt = P.ppt;
     // the particle and step of this lane (lane / H by a reciprocal: exact, as
     // the quotients of lane + 1/2 stay 1/128 away from the integers)
     const int pl = (int)(((float)lane + 0.5f) * __builtin_amdgcn_rcpf((float)H));
     const int h = lane - pl * H;
-    const int i = tile * P.ppt + pl;
-    const bool valid = pl < P.ppt && i < N;
+    const int i = tile * ppt + pl;
+    const bool valid = pl < ppt && i < N;
     // From the joint angles on, the points of the tile lie in LDS by step,
     // then particle, so that the 16 lanes of a row are neighbours in time:
     // `pos` is where this lane's point goes; positions past the last point
     // repeat it (`src`, from phase B on).
-    const int n_pts = P.ppt * H;
-    const int pos = pl < P.ppt ? h * P.ppt + pl : lane;
+    const int n_pts = ppt * H;
+    const int pos = pl < ppt ? h * ppt + pl : lane;
     const int src = min(lane, n_pts - 1);
-    const bool live = valid && i < N - P.n_null;  // sampled (non-null) particle
+    const bool live = valid && i < N - first.n_null;  // sampled (non-null) particle
     const uint32_t mask = P.cost_mask;
-    const float *__restrict__ tab = P.tables;
+    const global_ptr<const float> tab = as_global(P.tables);
 
     // Per-joint inputs of phase A1, loaded up front so that their latency
     // overlaps the noise generation.
     const int jw = wave < kDof ? wave : 0;
     // (vector loads throughout, so that the first barrier waits for none of
     // them: the state and the policy come fresh from the previous kernels)
-    const float mu_j = live ? P.mean[h * kDof + jw] : 0.0f;
-    const float sig_j = sqrtf(P.cov_step ? P.sigma2[h * kDof + jw] : vector_load_f32(P.sigma2 + jw));
+    const float mu_j = live ? as_global(first.mean)[h * kDof + jw] : 0.0f;
+    const float sig_j = sqrtf(P.cov_step ? as_global(P.sigma2)[h * kDof + jw] : vector_load_f32(P.sigma2 + jw));
     const float dt_h = tab[kTabDt + h];
     const float vs_h = tab[kTabVstop + h];
     const float q0_j = vector_load_f32(x0 + jw), v0_j = vector_load_f32(x0 + kDof + jw);
@@ -188,7 +198,7 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
     const int nobs = (mask & STORM_COST_ENV) && S > 0 ? P.n_sph_obs + P.n_box_obs : 0;
     const int ob_t = (int)threadIdx.x - 4 * kLanes;
     static_assert((W - 4) * kLanes >= STORM_MAX_OBSTACLES, "one culling record per thread");
-    if (ob_t >= 0 && ob_t < nobs) s_bound[ob_t] = P.obs_bound[ob_t];
+    if (ob_t >= 0 && ob_t < nobs) s_bound[ob_t] = load_float4(as_global(P.obs_bound) + ob_t);
     // the goal and the cost weights that phases C and E read, staged in
     // LDS by the last wave while the noise is drawn (read where they are
     // used, as scalar loads, they would add a memory round trip to those
@@ -199,18 +209,6 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
     __shared__ uint8_t s_near[kFrames * STORM_MAX_OBSTACLES];
     if (wave == W - 1 && lane == kParCount) s_self_next = 0;
     if (wave == W - 2 && lane < kFrames) s_near_n[lane] = 0;
-    if (wave == W - 1 && lane < kParCount) {
-        const float wts[kParCount - 12] = {P.alpha_rot[0], P.alpha_rot[1], P.alpha_rot[2], P.alpha_pos[0],
-                                           P.alpha_pos[1], P.alpha_pos[2], P.w_pos,        P.w_rot,
-                                           P.a_joint,      P.a_vel,        P.a_stop,       P.a_manip,
-                                           P.a_coll,       P.k_m};
-        float v = 0.0f;
-#pragma unroll
-        for (int k = 0; k < kParCount - 12; ++k) v = lane == 12 + k ? wts[k] : v;
-        const float g = goal[lane < 12 ? lane : 0];
-        s_par[lane] = lane < 12 ? g : v;
-    }
-
     // ---- A0: standard noise ------------------------------------------------
     // waves 0-3, one per SIMD: wave w makes the normal pair w / 2 of Philox
     // call w % 2, i.e. joints 4 (w % 2) + 2 (w / 2) and the next (the
@@ -220,11 +218,14 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
         const int k = wave & 1, half = wave >> 1;
         const int j0 = 4 * k + 2 * half;
         float e[2] = {0.0f, 0.0f};
-        const uint32_t counter = *P.step;
-        if (live) standard_noise2(P, noise, k, half, i, h, counter, e);
+        const uint32_t counter = *as_global(first.step);
+        if (live) standard_noise2(first, P.seed_lo, P.seed_hi, noise, k, half, i, h, counter, e);
         s_eps[j0 * kLanes + lane] = e[0];
         s_eps[(j0 + 1) * kLanes + lane] = e[1];
-        if (tile == 0 && threadIdx.x == 0) *P.last_step = counter;
+        if (tile == 0 && threadIdx.x == 0) *as_global(P.last_step) = counter;
+    } else if (wave == W - 1 && lane < kParCount) {
+        const float g = goal[lane < 12 ? lane : 0], w = tab[kTabPar + (lane < 12 ? 0 : lane - 12)];
+        s_par[lane] = lane < 12 ? g : w;
     }
     __syncthreads();
 
@@ -233,7 +234,7 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
         const int j = wave;
         float e = s_eps[j * kLanes + lane];
         // the comb filter on the sampled Gaussian particles' noise (Sec. 3.3)
-        const bool comb = P.comb && noise == nullptr && live && i >= P.n_halton;
+        const bool comb = P.comb && noise == nullptr && live && i >= first.n_halton;
         if (__builtin_amdgcn_ballot_w64(comb) != 0) {
             const float f = comb_noise(s_eps + j * kLanes, lane, h, H, tab);
             if (comb) e = f;
@@ -258,8 +259,8 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
         if (kTask) s_acc[j * kLanes + pos] = u;
         if (valid) {
             const size_t o = ((size_t)j * N + i) * H + h;
-            P.u[o] = u;
-            if (kTask && P.qbuf != nullptr) P.qbuf[o] = q;
+            as_global(P.u)[o] = u;
+            if (kTask && P.qbuf != nullptr) as_global(P.qbuf)[o] = q;
             if (out.u) out.u[o] = u;
             if (out.q) out.q[o] = q;
             if (out.v) out.v[o] = v;
@@ -312,7 +313,7 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
             int fb = -1;
             float F[12];
             // where in its row's span of steps this lane lies, in [0, 1]
-            const float step = floorf(((float)src + 0.5f) * __builtin_amdgcn_rcpf((float)P.ppt));
+            const float step = floorf(((float)src + 0.5f) * __builtin_amdgcn_rcpf((float)ppt));
             const float step0 = row_lane<0>(step);
             const float tau =
                 fminf((step - step0) * __builtin_amdgcn_rcpf(fmaxf(row_lane<15>(step) - step0, 1.0f)), 1.0f);
@@ -409,7 +410,7 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
                 }
                 task_space(s_fr + lane, kLanes, qd, qdd, xd, xdd);
                 // the point at position `lane`
-                const int hp = lane / P.ppt, ip = tile * P.ppt + (lane - hp * P.ppt);
+                const int hp = lane / ppt, ip = tile * ppt + (lane - hp * ppt);
                 if (lane < n_pts && ip < N)
 #pragma unroll
                     for (int c = 0; c < 6; ++c) {
@@ -441,10 +442,10 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
     // obstacle; the waves share the obstacles.
     if (nobs > 0) {
         const int body = lane & 7, row = (lane >> 3) & 3, half = lane >> 5;
-        const float2 rec = R.body_bound[body];
-        const float4 *cap = s_cap + (__float_as_int(rec.x) * 4 + row) * 2;
+        const float anchor = as_global(R.body_bound)[2 * body], widen = as_global(R.body_bound)[2 * body + 1];
+        const float4 *cap = s_cap + (__float_as_int(anchor) * 4 + row) * 2;
         const float4 a = cap[0], b = cap[1];
-        const float reach = a.w + rec.y;
+        const float reach = a.w + widen;
         for (int o0 = 2 * wave; o0 < nobs; o0 += 2 * W) {
             const int o = o0 + half;
             const float4 ob = o < nobs ? s_bound[o] : make_float4(3.0e38f, 3.0e38f, 3.0e38f, 0.0f);
@@ -681,38 +682,32 @@ __device__ __forceinline__ void rollout_tile(const ProblemDev &P, const RobotDev
         // running costs; the particle's last lane holds its total
         const float C_i = segmented_scan(tab[kTabHw + h] * c, h, H);
         if (valid && h == H - 1) {
-            P.C[i] = C_i;
+            as_global(P.C)[i] = C_i;
             if (out.C) out.C[i] = C_i;
         }
     }
 }
 
-// The fields the first loads of a tile depend on come first, as scalar
-// arguments, so that they are preloaded into SGPRs; the rest of the problem
-// follows in P.
-template <int W, bool kTask>
-__global__ __launch_bounds__(W * kLanes) void rollout_kernel(uint32_t *step, float *mean, float *sigma2,
-                                                             const float *halton, const float *tables, int32_t N,
-                                                             int32_t H, int32_t ppt, int32_t n_halton,
-                                                             int32_t n_null, uint32_t cost_mask, ProblemDev P,
-                                                             RobotDev R, const float *__restrict__ x0,
-                                                             const float *__restrict__ goal,
+// Every argument of the usual call fits the 14 dwords that are preloaded into
+// SGPRs at wave launch, so that no load of the kernel arguments (host memory)
+// stands before the work; what else a tile needs it reads from the descriptor
+// in device memory.  The fields that most first loads depend on come along.
+// kDebug: with the noise override and the optional outputs, which are read
+// from the argument segment.
+template <int W, bool kTask, bool kDebug>
+__global__ __launch_bounds__(W * kLanes) void rollout_kernel(const PlainDev *dev, int32_t N, int32_t H,
+                                                             const float *__restrict__ x0,
+                                                             const float *__restrict__ goal, const float *mean,
+                                                             uint32_t *step, float *C_out,
                                                              const float *__restrict__ noise, StepOut out)
 {
     extern __shared__ float smem[];
-    ProblemDev Q = P;
-    Q.step = step;
-    Q.mean = mean;
-    Q.sigma2 = sigma2;
-    Q.halton = halton;
-    Q.tables = tables;
-    Q.N = N;
-    Q.H = H;
-    Q.ppt = ppt;
-    Q.n_halton = n_halton;
-    Q.n_null = n_null;
-    Q.cost_mask = cost_mask;
-    rollout_tile<W, kTask>(Q, R, blockIdx.x, x0, goal, noise, out, smem);
+    StepOut o{};
+    if (kDebug) o = out;
+    o.C = C_out;
+    const STORM_CONST_AS PlainDev &D = *uniform_ptr(dev);
+    const TileFirst first{step, mean, D.P.halton, N, H, D.P.n_halton, D.P.n_null};
+    rollout_tile<W, kTask>(D.P, D.R, first, blockIdx.x, x0, goal, kDebug ? noise : nullptr, o, smem);
 }
 
 // Persistent form for many problems: each workgroup takes (problem, tile)
@@ -723,7 +718,7 @@ __global__ __launch_bounds__(W * kLanes) void rollout_kernel(uint32_t *step, flo
 template <int W>
 __global__ __launch_bounds__(W * kLanes) void rollout_batch_kernel(const ProblemDev *__restrict__ probs,
                                                                    const int2 *__restrict__ items, int n_items,
-                                                                   uint32_t *next, RobotDev R,
+                                                                   uint32_t *next, const RobotDev *robot,
                                                                    const float *__restrict__ x0s,
                                                                    const float *__restrict__ goals)
 {
@@ -740,8 +735,11 @@ __global__ __launch_bounds__(W * kLanes) void rollout_batch_kernel(const Problem
             return;
         }
         const int p = it[2 * item], tile = it[2 * item + 1];
-        const ProblemDev P = load_uniform(probs + p);
-        rollout_tile<W>(P, R, tile, x0s + (size_t)p * 3 * kDof, goals + (size_t)p * 12, nullptr, StepOut{}, smem);
+        const STORM_CONST_AS RobotDev *R = uniform_ptr(robot);
+        asm volatile("" : "+s"(R));  // fields read in each tile, not kept over the loop
+        ProblemRef P = uniform_ptr(probs)[p];
+        const TileFirst first{P.step, P.mean, P.halton, P.N, P.H, P.n_halton, P.n_null};
+        rollout_tile<W, false>(P, *R, first, tile, x0s + (size_t)p * 3 * kDof, goals + (size_t)p * 12, nullptr, StepOut{}, smem);
         __syncthreads();
     }
 }
@@ -760,50 +758,59 @@ hipError_t set_rollout_lds_limit()
 {
     const int plain = (int)rollout_lds_bytes(STORM_MAX_SPHERES, STORM_MAX_OBSTACLES);
     const int task = (int)rollout_lds_bytes(STORM_MAX_SPHERES, STORM_MAX_OBSTACLES, true);
-    const void *fns[6] = {reinterpret_cast<const void *>(&rollout_kernel<16, false>),
-                          reinterpret_cast<const void *>(&rollout_kernel<8, false>),
-                          reinterpret_cast<const void *>(&rollout_batch_kernel<16>),
-                          reinterpret_cast<const void *>(&rollout_batch_kernel<8>),
-                          reinterpret_cast<const void *>(&rollout_kernel<16, true>),
-                          reinterpret_cast<const void *>(&rollout_kernel<8, true>)};
-    const int bytes[6] = {plain, plain, plain, plain, task, task};
-    for (int k = 0; k < 6; ++k) {
-        const hipError_t e = hipFuncSetAttribute(fns[k], hipFuncAttributeMaxDynamicSharedMemorySize, bytes[k]);
+    const void *fns[10] = {reinterpret_cast<const void *>(&rollout_kernel<16, false, false>),
+                           reinterpret_cast<const void *>(&rollout_kernel<8, false, false>),
+                           reinterpret_cast<const void *>(&rollout_kernel<16, false, true>),
+                           reinterpret_cast<const void *>(&rollout_kernel<8, false, true>),
+                           reinterpret_cast<const void *>(&rollout_batch_kernel<16>),
+                           reinterpret_cast<const void *>(&rollout_batch_kernel<8>),
+                           reinterpret_cast<const void *>(&rollout_kernel<16, true, false>),
+                           reinterpret_cast<const void *>(&rollout_kernel<8, true, false>),
+                           reinterpret_cast<const void *>(&rollout_kernel<16, true, true>),
+                           reinterpret_cast<const void *>(&rollout_kernel<8, true, true>)};
+    for (int k = 0; k < 10; ++k) {
+        const hipError_t e =
+            hipFuncSetAttribute(fns[k], hipFuncAttributeMaxDynamicSharedMemorySize, k < 6 ? plain : task);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
 hipError_t launch_rollout_batch(const ProblemDev *probs, const int2 *items, int n_items, uint32_t *next,
-                                const RobotDev &R, const float *x0s, const float *goals, int max_obs, int waves,
-                                int grid, hipStream_t stream)
+                                const RobotDev *robot, int n_spheres, int max_obs, const float *x0s,
+                                const float *goals, int waves, int grid, hipStream_t stream)
 {
-    const size_t lds = rollout_lds_bytes(R.n_spheres, max_obs);
+    const size_t lds = rollout_lds_bytes(n_spheres, max_obs);
     if (waves == 16) {
         hipLaunchKernelGGL(rollout_batch_kernel<16>, dim3((unsigned)grid), dim3(16 * kLanes), lds, stream, probs,
-                           items, n_items, next, R, x0s, goals);
+                           items, n_items, next, robot, x0s, goals);
     } else if (waves == 8) {
         hipLaunchKernelGGL(rollout_batch_kernel<8>, dim3((unsigned)grid), dim3(8 * kLanes), lds, stream, probs,
-                           items, n_items, next, R, x0s, goals);
+                           items, n_items, next, robot, x0s, goals);
     } else {
         return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_rollout(const ProblemDev &P, const RobotDev &R, const float *x0, const float *goal,
+hipError_t launch_rollout(const ProblemDev &P, int n_spheres, const PlainDev *dev, const float *x0, const float *goal,
                           const float *noise, const StepOut &out, int waves, hipStream_t stream)
 {
-    // the task-space form only where it is asked for: the ball term, or the
-    // flange velocity and acceleration outputs
+    // the task-space form only where it is asked for: the ball term, the
+    // network's joint positions, or the flange velocity and acceleration
     const bool task = (P.cost_mask & STORM_COST_BALL) || P.selfnet || out.xd != nullptr || out.xdd != nullptr;
-    const size_t lds = rollout_lds_bytes(R.n_spheres, P.n_sph_obs + P.n_box_obs, task);
+    const bool debug = noise != nullptr || out.u != nullptr || out.q != nullptr || out.v != nullptr ||
+                       out.a != nullptr || out.c != nullptr || out.terms != nullptr || out.xd != nullptr ||
+                       out.xdd != nullptr;
+    const size_t lds = rollout_lds_bytes(n_spheres, P.n_sph_obs + P.n_box_obs, task);
     const dim3 grid((unsigned)P.n_tiles);
     if (waves != 16 && waves != 8) return hipErrorInvalidValue;
-    auto kernel = waves == 16 ? (task ? rollout_kernel<16, true> : rollout_kernel<16, false>)
-                              : (task ? rollout_kernel<8, true> : rollout_kernel<8, false>);
-    hipLaunchKernelGGL(kernel, grid, dim3(waves * kLanes), lds, stream, P.step, P.mean, P.sigma2, P.halton, P.tables,
-                       P.N, P.H, P.ppt, P.n_halton, P.n_null, P.cost_mask, P, R, x0, goal, noise, out);
+    auto kernel = waves == 16 ? (task ? (debug ? rollout_kernel<16, true, true> : rollout_kernel<16, true, false>)
+                                      : (debug ? rollout_kernel<16, false, true> : rollout_kernel<16, false, false>))
+                              : (task ? (debug ? rollout_kernel<8, true, true> : rollout_kernel<8, true, false>)
+                                      : (debug ? rollout_kernel<8, false, true> : rollout_kernel<8, false, false>));
+    hipLaunchKernelGGL(kernel, grid, dim3(waves * kLanes), lds, stream, dev, P.N, P.H, x0, goal, P.mean, P.step,
+                       out.C, noise, out);
     return hipGetLastError();
 }
 

@@ -100,8 +100,7 @@ __device__ __forceinline__ float segmented_suffix_scan(float x, int h, int H)
 // step order written as its convolution, sum over k <= h of g_k e_{h-k},
 // with the response g in the tables; e_{h-k} is the lane k below, in the
 // same particle.
-__device__ __forceinline__ float comb_noise(const float *row, int lane, int h, int H,
-                                            const float *__restrict__ tab)
+__device__ __forceinline__ float comb_noise(const float *row, int lane, int h, int H, global_ptr<const float> tab)
 {
     // eight terms per batch, every read of a batch in flight at once (the
     // response is zero past H, and within the table's kMaxH entries)
@@ -119,32 +118,14 @@ __device__ __forceinline__ float comb_noise(const float *row, int lane, int h, i
     return acc;
 }
 
-// Standard noise of joints 4k..4k+3 for one (particle, step) point from the
-// override, the Halton table or Philox (k = 0 or 1).
-__device__ __forceinline__ void standard_noise4(const ProblemDev &P, const float *__restrict__ noise, int k, int i,
-                                                int h, uint32_t counter, float e[4])
-{
-    const int j0 = 4 * k;
-    if (noise != nullptr) {
-#pragma unroll
-        for (int m = 0; m < 4; ++m) e[m] = j0 + m < kDof ? noise[((size_t)(j0 + m) * P.N + i) * P.H + h] : 0.0f;
-    } else if (i < P.n_halton) {
-#pragma unroll
-        for (int m = 0; m < 4; ++m)
-            e[m] = j0 + m < kDof ? P.halton[((size_t)(j0 + m) * P.n_halton + i) * P.H + h] : 0.0f;
-    } else {
-        uint32_t c0 = (uint32_t)i, c1 = (uint32_t)h, c2 = (uint32_t)k, c3 = counter;
-        philox4x32_10(c0, c1, c2, c3, P.seed_lo, P.seed_hi);
-        box_muller(c0, c1, e[0], e[1]);
-        box_muller(c2, c3, e[2], e[3]);
-    }
-}
-
 // Standard noise of joints 4k + 2 half and 4k + 2 half + 1 for one (particle,
-// step) point: the same values as standard_noise4's e[2 half], e[2 half + 1]
-// (the Philox call of k, then the Box-Muller transform of its half).
-__device__ __forceinline__ void standard_noise2(const ProblemDev &P, const float *__restrict__ noise, int k, int half,
-                                                int i, int h, uint32_t counter, float e[2])
+// step) point: from the override, the Halton table, or the Box-Muller
+// transform of one half of Philox call k.  Prob: anything with N, H,
+// n_halton and halton.
+template <class Prob>
+__device__ __forceinline__ void standard_noise2(Prob &P, uint32_t seed_lo, uint32_t seed_hi,
+                                                const float *__restrict__ noise, int k, int half, int i, int h,
+                                                uint32_t counter, float e[2])
 {
     const int j0 = 4 * k + 2 * half;
     if (noise != nullptr) {
@@ -153,14 +134,36 @@ __device__ __forceinline__ void standard_noise2(const ProblemDev &P, const float
     } else if (i < P.n_halton) {
 #pragma unroll
         for (int m = 0; m < 2; ++m)
-            e[m] = j0 + m < kDof ? P.halton[((size_t)(j0 + m) * P.n_halton + i) * P.H + h] : 0.0f;
+            e[m] = j0 + m < kDof ? as_global(P.halton)[((size_t)(j0 + m) * P.n_halton + i) * P.H + h] : 0.0f;
     } else {
         uint32_t c0 = (uint32_t)i, c1 = (uint32_t)h, c2 = (uint32_t)k, c3 = counter;
-        philox4x32_10(c0, c1, c2, c3, P.seed_lo, P.seed_hi);
+        philox4x32_10(c0, c1, c2, c3, seed_lo, seed_hi);
         if (half == 0)
             box_muller(c0, c1, e[0], e[1]);
         else
             box_muller(c2, c3, e[0], e[1]);
+    }
+}
+
+// Standard noise of joints 4k..4k+3 (k = 0 or 1): the same values as
+// standard_noise2's of both halves.
+template <class Prob>
+__device__ __forceinline__ void standard_noise4(Prob &P, const float *__restrict__ noise, int k, int i, int h,
+                                                uint32_t counter, float e[4])
+{
+    const int j0 = 4 * k;
+    if (noise != nullptr) {
+#pragma unroll
+        for (int m = 0; m < 4; ++m) e[m] = j0 + m < kDof ? noise[((size_t)(j0 + m) * P.N + i) * P.H + h] : 0.0f;
+    } else if (i < P.n_halton) {
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+            e[m] = j0 + m < kDof ? as_global(P.halton)[((size_t)(j0 + m) * P.n_halton + i) * P.H + h] : 0.0f;
+    } else {
+        uint32_t c0 = (uint32_t)i, c1 = (uint32_t)h, c2 = (uint32_t)k, c3 = counter;
+        philox4x32_10(c0, c1, c2, c3, P.seed_lo, P.seed_hi);
+        box_muller(c0, c1, e[0], e[1]);
+        box_muller(c2, c3, e[2], e[3]);
     }
 }
 

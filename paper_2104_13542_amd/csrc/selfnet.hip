@@ -33,9 +33,16 @@ constexpr int kOffA2 = kOffA1 + 64 * kNetA1 * 2;
 constexpr int kNetLds = kOffA2 + 64 * kNetA2 * 2;
 static_assert(64 * kNetA3 * 4 <= 64 * kNetA1 * 2, "last hidden layer fits in the first layer's space");
 
-__global__ __launch_bounds__(kNetThreads) void selfnet_kernel(ProblemDev P, const _Float16 *__restrict__ frag,
-                                                              const float *__restrict__ bias, StepOut out)
+// kDebug: with the per-step outputs, which are read from the argument segment
+// (the other arguments are preloaded into SGPRs).
+template <bool kDebug>
+__global__ __launch_bounds__(kNetThreads) void selfnet_kernel(const PlainDev *dev, int32_t N, int32_t H,
+                                                              const float *__restrict__ qbuf,
+                                                              const _Float16 *__restrict__ frag,
+                                                              const float *__restrict__ bias, float *C_out,
+                                                              float *c_out, float *terms_out)
 {
+    ProblemRef P = uniform_ptr(dev)->P;
     __shared__ __attribute__((aligned(16))) unsigned char s_lds[kNetLds];
     _Float16 *s_x = reinterpret_cast<_Float16 *>(s_lds);
     _Float16 *s_a1 = reinterpret_cast<_Float16 *>(s_lds + kOffA1);
@@ -45,17 +52,17 @@ __global__ __launch_bounds__(kNetThreads) void selfnet_kernel(ProblemDev P, cons
     const int lane = threadIdx.x & (kLanes - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tile = blockIdx.x;
-    const int N = P.N, H = P.H;
+    const int ppt = kLanes / H;
 
     // row `lane` of the tile; wave j < 7 encodes joint j of every row.  Its
     // position is loaded first, so that waiting for it does not wait for the
     // weight loads behind it (an invalid row reads particle 0 and is ignored).
     const int pl = lane / H;
     const int h = lane - pl * H;
-    const int i = tile * P.ppt + pl;
-    const bool valid = pl < P.ppt && i < N;
+    const int i = tile * ppt + pl;
+    const bool valid = pl < ppt && i < N;
     const int jq = wave < kDof ? wave : 0;
-    const float qv = P.qbuf[((size_t)jq * N + (valid ? i : 0)) * H + h];
+    const float qv = qbuf[((size_t)jq * N + (valid ? i : 0)) * H + h];
     __builtin_amdgcn_sched_barrier(0);  // keep that load ahead of the weight loads
 
     // every weight fragment this wave uses, loaded up front (52 VGPRs)
@@ -123,14 +130,15 @@ __global__ __launch_bounds__(kNetThreads) void selfnet_kernel(ProblemDev P, cons
         const float dist = net_output(s_a3, bias, lane);
         const float term = fmaxf(dist, 0.0f);  // Eq. 13
         const float dc = P.a_coll * term;
-        const float added = segmented_scan(P.tables[kTabHw + h] * dc, h, H);
+        const float added = segmented_scan(as_global(P.tables)[kTabHw + h] * dc, h, H);
         if (valid) {
-            if (out.terms) out.terms[((size_t)6 * N + i) * H + h] = term;
-            if (out.c) out.c[(size_t)i * H + h] += dc;
+            if (kDebug && terms_out) terms_out[((size_t)6 * N + i) * H + h] = term;
+            if (kDebug && c_out) c_out[(size_t)i * H + h] += dc;
             if (h == H - 1) {
-                const float C = P.C[i] + added;
-                P.C[i] = C;
-                if (out.C) out.C[i] = C;
+                const global_ptr<float> C = as_global(P.C) + i;
+                const float sum = *C + added;
+                *C = sum;
+                if (C_out) C_out[i] = sum;
             }
         }
     }
@@ -138,10 +146,11 @@ __global__ __launch_bounds__(kNetThreads) void selfnet_kernel(ProblemDev P, cons
 
 }  // namespace
 
-hipError_t launch_selfnet(const ProblemDev &P, const _Float16 *frag, const float *bias, const StepOut &out,
-                          hipStream_t stream)
+hipError_t launch_selfnet(const ProblemDev &P, const PlainDev *dev, const StepOut &out, hipStream_t stream)
 {
-    hipLaunchKernelGGL(selfnet_kernel, dim3((unsigned)P.n_tiles), dim3(kNetThreads), 0, stream, P, frag, bias, out);
+    auto kernel = out.c != nullptr || out.terms != nullptr ? selfnet_kernel<true> : selfnet_kernel<false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)P.n_tiles), dim3(kNetThreads), 0, stream, dev, P.N, P.H, P.qbuf,
+                       P.net_frag, P.net_bias, out.C, out.c, out.terms);
     return hipGetLastError();
 }
 

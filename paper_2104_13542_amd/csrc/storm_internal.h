@@ -31,7 +31,8 @@ constexpr int kTabVlo = 208;        // band-shrunk joint velocity limits [7]
 constexpr int kTabVhi = 216;
 constexpr int kTabComb = 224;        // comb filter response g_k (e'_h = sum_k g_k e_{h-k}) [H]
 constexpr int kTabSig0 = 288;        // sigma_init^2 [7], appended by a per-step covariance shift
-constexpr int kTabSize = 296;
+constexpr int kTabPar = 295;         // cost weights in the order of the rollout's LDS copy [14]
+constexpr int kTabSize = 309;
 
 // Learned self-collision network (Eq. 13): layer widths, the packed FP16
 // weight fragments (offsets in halves: per column block, k-step and lane, 4
@@ -73,8 +74,7 @@ struct ProblemDev {
     uint32_t *step;         // sampling step counter (Philox counter word 3)
     uint32_t *status;       // asynchronous status flags
     uint32_t *last_step;    // counter value the last rollout sampled with (reused by the adjoint)
-    float *grad_part;       // [chunks][7][kMaxH] adjoint partial gradients per tile chunk
-    float *cost_part;       // [chunks] adjoint partial horizon-cost sums per tile chunk
+    float *grad_part;       // adjoint partials per tile chunk: horizon-cost sums [kAdjChunks], gradients [chunks][7][kMaxH]
     float *grad;            // [H][7] gradient of the expected horizon cost
     float *adam_m, *adam_v; // [H][7] Adam moments of the refinement
     float *ball;            // [8]: ball position, velocity (world frame) at the current state, pad
@@ -91,30 +91,48 @@ struct RobotDev {
     const float4 *sph_local;  // [S] body-frame centre (x, y, z), radius
     const int32_t *sph_body;  // [S] frame index 0..7 the sphere is attached to
     const float *self_thr;    // [groups][S][8] expanded pair test thresholds (4), contact distances (4)
-    const float2 *body_bound;  // [8] per frame: anchor sphere (int bits), what its radius lacks to hold the body's spheres
+    const float *body_bound;  // [8][2] per frame: anchor sphere (int bits), what its radius lacks to hold the body's spheres
     const int32_t *self_items;  // [n_self_items][8] self-collision work items (self_segments)
+};
+
+// What the plain kernels read of one problem, in device memory.  Kernel
+// arguments lie in host memory, which a wave reads over PCIe; a descriptor in
+// device memory behind one preloaded pointer is nearer (traced rollout at
+// N=64, H=16: 5.5 -> 4.7 us; at N=1024, H=30 without collisions 9.0 -> 8.5 us,
+// its adjoint 8.5 -> 8.0 us).
+struct PlainDev {
+    ProblemDev P;
+    RobotDev R;
 };
 
 // Wave-uniform reads through the constant address space: the backend turns
 // them into scalar loads whose results feed VALU instructions as SGPR operands.
 #define STORM_CONST_AS __attribute__((address_space(4)))
+using ProblemRef = const STORM_CONST_AS ProblemDev &;
+using RobotRef = const STORM_CONST_AS RobotDev &;
 template <typename T>
 __device__ __forceinline__ const STORM_CONST_AS T *uniform_ptr(const T *p)
 {
     return (const STORM_CONST_AS T *)(p);
 }
 
-// Copy a struct from device memory through wave-uniform scalar loads.
+// Pointers known to point to global memory: one that a kernel reads from a
+// descriptor in memory is otherwise accessed with flat instructions, which
+// count as LDS traffic too, so that LDS waits wait for them.
 template <typename T>
-__device__ __forceinline__ T load_uniform(const T *p)
+using global_ptr = __attribute__((address_space(1))) T *;
+template <typename T>
+__device__ __forceinline__ global_ptr<T> as_global(T *p)
 {
-    static_assert(sizeof(T) % 4 == 0, "struct of 32-bit words");
-    T v;
-    const STORM_CONST_AS uint32_t *src = uniform_ptr(reinterpret_cast<const uint32_t *>(p));
-    uint32_t *dst = reinterpret_cast<uint32_t *>(&v);
-#pragma unroll
-    for (int k = 0; k < (int)(sizeof(T) / 4); ++k) dst[k] = src[k];
-    return v;
+    return (global_ptr<T>)p;
+}
+
+// A 16-byte record of global memory.
+__device__ __forceinline__ float4 load_float4(global_ptr<const float4> p)
+{
+    typedef float vec4 __attribute__((ext_vector_type(4)));
+    const vec4 v = *(global_ptr<const vec4>)p;
+    return make_float4(v.x, v.y, v.z, v.w);
 }
 
 // A 32-bit word read by a vector (buffer) load even where its address is
@@ -144,7 +162,9 @@ hipError_t launch_init_tables(const ProblemDev &P, const float *d_dt_raw, const 
                               float4 *d_sph_obs, float *d_box_obs,
                               float4 *d_obs_bound, const float *d_sph_raw, int n_spheres, float4 *d_sph_local,
                               int32_t *d_sph_body, hipStream_t stream);
-hipError_t launch_rollout(const ProblemDev &P, const RobotDev &R, const float *x0, const float *goal,
+// Plain launches take the host's copy of the problem for the launch shape and
+// the device's (PlainDev) for the kernel.
+hipError_t launch_rollout(const ProblemDev &P, int n_spheres, const PlainDev *dev, const float *x0, const float *goal,
                           const float *noise, const StepOut &out, int waves, hipStream_t stream);
 // Raise the dynamic-LDS limit of the rollout kernels to what the largest
 // sphere model needs (idempotent).
@@ -152,35 +172,35 @@ hipError_t set_rollout_lds_limit();
 // Whether the learned self-collision network's weight matrices (W1, W2, W3
 // of storm_robot.self_mlp) hold FP16 values only, as its kernel requires.
 bool selfnet_weights_fp16(const float *prm);
-hipError_t launch_update(const ProblemDev &P, float *mean_out, float *sigma2_out, float *cmd, int shift,
+hipError_t launch_update(const ProblemDev &P, const PlainDev *dev, float *mean_out, float *sigma2_out, float *cmd, int shift,
                          hipStream_t stream);
 // Learned self-collision term: after the rollout, adds a_coll max(0, d) to
-// every running cost and its horizon sum to C (frag and bias packed by
-// pack_selfnet from the parameter layout of storm_robot.self_mlp).
-hipError_t launch_selfnet(const ProblemDev &P, const _Float16 *frag, const float *bias, const StepOut &out,
-                          hipStream_t stream);
+// every running cost and its horizon sum to C (weights packed by pack_selfnet
+// from the parameter layout of storm_robot.self_mlp).
+hipError_t launch_selfnet(const ProblemDev &P, const PlainDev *dev, const StepOut &out, hipStream_t stream);
 void pack_selfnet(const float *prm, std::vector<_Float16> &frag, std::vector<float> &bias);
 // Many problems: persistent rollout over a (problem, tile) work queue, and one
 // update workgroup per problem (descriptors in device memory).
 hipError_t launch_rollout_batch(const ProblemDev *probs, const int2 *items, int n_items, uint32_t *next,
-                                const RobotDev &R, const float *x0s, const float *goals, int max_obs, int waves,
-                                int grid, hipStream_t stream);
+                                const RobotDev *robot, int n_spheres, int max_obs, const float *x0s,
+                                const float *goals, int waves, int grid, hipStream_t stream);
 hipError_t launch_update_batch(const ProblemDev *probs, int n_problems, float *cmd, int shift, hipStream_t stream);
 // Differentiable form: adjoint + fixed-order reduction (grad, J) per joint;
 // with it > 0 the same launch takes Adam step `it` on the stored mean, and
 // with cmd it also writes the command and the shift of the refined mean.
 // launch_command writes them for a refinement of zero steps.
-hipError_t launch_grad(const ProblemDev &P, const RobotDev &R, const float *x0, const float *goal, const float *mean,
-                       const float *noise, float *grad_out, float *J_out, int it, float lr, float *cmd, int shift,
-                       hipStream_t stream);
-hipError_t launch_command(const ProblemDev &P, float *cmd, int shift, hipStream_t stream);
+// The partials go to `part` (layout of ProblemDev::grad_part).
+hipError_t launch_grad(const ProblemDev &P, const PlainDev *dev, float *part, const float *x0, const float *goal,
+                       const float *mean, const float *noise, float *grad_out, float *J_out, int it, float lr,
+                       float *cmd, int shift, hipStream_t stream);
+hipError_t launch_command(const PlainDev *dev, float *cmd, int shift, hipStream_t stream);
 // Batched refinement: `iterations` Adam steps on the gradient of every
 // problem (adjoint over the (problem, chunk) items, then reduce + Adam per
 // (problem, joint)), the last also writing the commands cmd [P][7] and the
 // shift.
 hipError_t launch_refine_batch(const ProblemDev *probs, int n_problems, const int2 *items, int n_items,
-                               const RobotDev &R, const float *x0s, const float *goals, int iterations, float lr,
-                               float *cmd, int shift, hipStream_t stream);
+                               const RobotDev *robot, const float *x0s, const float *goals, int iterations,
+                               float lr, float *cmd, int shift, hipStream_t stream);
 hipError_t launch_fk(const RobotDev &R, const float *q, int n, float *pose, float *manip, hipStream_t stream);
 
 // Self-collision work items of the robot's sphere pairs, eight integers
@@ -212,6 +232,7 @@ struct storm_ctx_s {
     storm_params params{};
     storm::ProblemDev P{};
     storm::RobotDev R{};
+    storm::PlainDev *dev = nullptr;  // P and R in device memory
     _Float16 *net_frag = nullptr;  // learned self-collision weights (packed), when self_model = 1
     float *net_bias = nullptr;
     float *scratch = nullptr;    // this device's static scratch (storm_rollout_grad_noalloc)

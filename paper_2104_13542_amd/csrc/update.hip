@@ -86,8 +86,6 @@ __device__ __forceinline__ T in_vgpr(T x)
 // The same for a pointer, kept a global-memory pointer so that accesses
 // through it stay global (not flat) instructions.
 template <typename T>
-using global_ptr = __attribute__((address_space(1))) T *;
-template <typename T>
 __device__ __forceinline__ global_ptr<T> global_in_vgpr(T *p)
 {
     global_ptr<T> g = (global_ptr<T>)p;
@@ -128,14 +126,20 @@ __host__ __device__ inline int update_slots(int N, int H)
     return 0;
 }
 
+// The fields of a problem that the first loads depend on.
+struct UpdateFirst {
+    const float *C, *u;
+    float *mean;
+    int32_t N, H;
+};
+
 // `cov` is P.cov_step, passed apart so that the plain kernel can fix it at
 // compile time; kSlots the register path's controls per thread
 // (update_slots), 32 when that path is not taken.
 template <int kSlots>
-__device__ __forceinline__ void update_joint(const ProblemDev &P, const int j, float *__restrict__ mean_out,
-                                             float *__restrict__ sigma2_out, float *__restrict__ cmd, int shift,
-                                             const bool cov, const float alpha_mu, const float alpha_sigma,
-                                             const float sigma2_min, UpdateLds &L)
+__device__ __forceinline__ void update_joint(ProblemRef P, const UpdateFirst &first, const int j,
+                                             float *__restrict__ mean_out, float *__restrict__ sigma2_out,
+                                             float *__restrict__ cmd, int shift, const bool cov, UpdateLds &L)
 {
     float *s_buf = L.buf;
     float *s_red = L.red;
@@ -146,9 +150,9 @@ __device__ __forceinline__ void update_joint(const ProblemDev &P, const int j, f
 
     const int t = threadIdx.x;
     const int lane = t & (kLanes - 1), wave = __builtin_amdgcn_readfirstlane(t / kLanes);
-    const int N = P.N, H = P.H;
+    const int N = first.N, H = first.H;
     const float beta = P.beta;
-    const float *__restrict__ C = P.C;
+    const global_ptr<const float> C = as_global(first.C);
     int *s_idx = reinterpret_cast<int *>(s_buf);
     float *s_wl = s_buf + kList;
 
@@ -156,7 +160,7 @@ __device__ __forceinline__ void update_joint(const ProblemDev &P, const int j, f
     const int rows = kThreads / H;
     const int r = t / H, h = t - r * H;
     const bool in_rows = r < rows;
-    const float *__restrict__ U = P.u + (size_t)j * N * H + h;
+    const global_ptr<const float> U = as_global(first.u) + (size_t)j * N * H + h;
     const bool regs = N <= kSlots * rows && N <= 2 * kThreads && kSlots * rows <= kChunk;
     const float nib = -1.0f / beta;
 
@@ -170,13 +174,13 @@ __device__ __forceinline__ void update_joint(const ProblemDev &P, const int j, f
         if (t < N) c0 = C[t];
         if (t + kThreads < N) c1 = C[t + kThreads];
         const __amdgpu_buffer_rsrc_t ub = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float *>(P.u + (size_t)j * N * H), (short)0, N * H * (int)sizeof(float), 0x00020000);
+            const_cast<float *>(first.u + (size_t)j * N * H), (short)0, N * H * (int)sizeof(float), 0x00020000);
         const int stride = rows * H * (int)sizeof(float);
 #pragma unroll
         for (int k = 0; k < kSlots; ++k)
             uu[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ub, t * 4 + k * stride, 0, 0));
     }
-    const float mu = in_rows ? P.mean[h * kDof + j] : 0.0f;
+    const float mu = in_rows ? as_global(first.mean)[h * kDof + j] : 0.0f;
     // What the tail reads is fetched now, with the first loads, since each
     // would add a memory round trip to the tail: the old variances and the
     // noise counter through vector loads (waited for only where they are
@@ -186,12 +190,12 @@ __device__ __forceinline__ void update_joint(const ProblemDev &P, const int j, f
     const float sig_old = cov ? (t < H ? vector_load_f32(P.sigma2 + t * kDof + j) : 0.0f) : vector_load_f32(P.sigma2 + j);
     const float sig_init = cov && shift ? vector_load_f32(P.tables + kTabSig0 + j) : 0.0f;
     const uint32_t step0 = vector_load_u32(P.step);
-    const global_ptr<float> mean_p = global_in_vgpr(P.mean), sigma2_p = global_in_vgpr(P.sigma2);
+    const global_ptr<float> mean_p = global_in_vgpr(first.mean), sigma2_p = global_in_vgpr(P.sigma2);
     const global_ptr<float> cmd_p = global_in_vgpr(cmd), mean_out_p = global_in_vgpr(mean_out),
                             sigma2_out_p = global_in_vgpr(sigma2_out);
     const global_ptr<uint32_t> step_p = global_in_vgpr(P.step);
     shift = in_vgpr(shift);
-    const float a_mu = in_vgpr(alpha_mu), a_sigma = in_vgpr(alpha_sigma), s2_min = in_vgpr(sigma2_min);
+    const float a_mu = in_vgpr(P.alpha_mu), a_sigma = in_vgpr(P.alpha_sigma), s2_min = in_vgpr(P.sigma2_min);
 
     float S0 = 0.0f, x1 = 0.0f, x2 = 0.0f;
     int any_nonfinite = 0;
@@ -405,27 +409,19 @@ __device__ __forceinline__ void update_joint(const ProblemDev &P, const int j, f
     }
 }
 
-// The fields the first loads depend on, and the scalars of the tail, come
-// first, as scalar arguments, so that they are preloaded into SGPRs (16
-// dwords); the rest of the problem follows in P.  kCov: one variance per
-// (step, joint) instead of one per joint.
+// All arguments fit the 14 dwords that are preloaded into SGPRs; the rest of
+// the problem comes from its descriptor in device memory.  kCov: one variance
+// per (step, joint) instead of one per joint.
 template <bool kCov, int kSlots>
-__global__ __launch_bounds__(kThreads) void update_kernel(float *C, float *u, float *mean, float *sigma2, int32_t N,
-                                                          int32_t H, float beta, float alpha_mu, float alpha_sigma,
-                                                          float sigma2_min, int shift, ProblemDev P,
-                                                          float *__restrict__ mean_out, float *__restrict__ sigma2_out,
-                                                          float *__restrict__ cmd)
+__global__ __launch_bounds__(kThreads) void update_kernel(const PlainDev *dev, const float *C, const float *u,
+                                                          float *__restrict__ mean_out,
+                                                          float *__restrict__ sigma2_out, float *__restrict__ cmd,
+                                                          int32_t N, int16_t H, int16_t shift)
 {
     __shared__ UpdateLds L;
-    ProblemDev Q = P;
-    Q.C = C;
-    Q.u = u;
-    Q.mean = mean;
-    Q.sigma2 = sigma2;
-    Q.N = N;
-    Q.H = H;
-    Q.beta = beta;
-    update_joint<kSlots>(Q, blockIdx.x, mean_out, sigma2_out, cmd, shift, kCov, alpha_mu, alpha_sigma, sigma2_min, L);
+    ProblemRef P = uniform_ptr(dev)->P;
+    const UpdateFirst first{C, u, P.mean, N, H};
+    update_joint<kSlots>(P, first, blockIdx.x, mean_out, sigma2_out, cmd, shift, kCov, L);
 }
 
 // Workgroup (p, j) of a batch; commands go to cmd[p][7].
@@ -434,18 +430,16 @@ __global__ __launch_bounds__(kThreads) void update_batch_kernel(const ProblemDev
 {
     __shared__ UpdateLds L;
     const int p = blockIdx.x / kDof, j = blockIdx.x - p * kDof;
-    const ProblemDev P = load_uniform(probs + p);
+    ProblemRef P = uniform_ptr(probs)[p];
+    const UpdateFirst first{P.C, P.u, P.mean, P.N, P.H};
     const int slots = update_slots(P.N, P.H);
     float *c = cmd + (size_t)p * kDof;
     if (slots == 8)
-        update_joint<8>(P, j, nullptr, nullptr, c, shift, P.cov_step != 0u, P.alpha_mu, P.alpha_sigma, P.sigma2_min,
-                          L);
+        update_joint<8>(P, first, j, nullptr, nullptr, c, shift, P.cov_step != 0u, L);
     else if (slots == 16)
-        update_joint<16>(P, j, nullptr, nullptr, c, shift, P.cov_step != 0u, P.alpha_mu, P.alpha_sigma, P.sigma2_min,
-                          L);
+        update_joint<16>(P, first, j, nullptr, nullptr, c, shift, P.cov_step != 0u, L);
     else
-        update_joint<32>(P, j, nullptr, nullptr, c, shift, P.cov_step != 0u, P.alpha_mu, P.alpha_sigma, P.sigma2_min,
-                          L);
+        update_joint<32>(P, first, j, nullptr, nullptr, c, shift, P.cov_step != 0u, L);
 }
 
 }  // namespace
@@ -457,7 +451,7 @@ hipError_t launch_update_batch(const ProblemDev *probs, int n_problems, float *c
     return hipGetLastError();
 }
 
-hipError_t launch_update(const ProblemDev &P, float *mean_out, float *sigma2_out, float *cmd, int shift,
+hipError_t launch_update(const ProblemDev &P, const PlainDev *dev, float *mean_out, float *sigma2_out, float *cmd, int shift,
                          hipStream_t stream)
 {
     const int slots = update_slots(P.N, P.H);
@@ -467,8 +461,8 @@ hipError_t launch_update(const ProblemDev &P, float *mean_out, float *sigma2_out
                              : (slots == 8    ? update_kernel<false, 8>
                                 : slots == 16 ? update_kernel<false, 16>
                                               : update_kernel<false, 32>);
-    hipLaunchKernelGGL(kernel, dim3(kDof), dim3(kThreads), 0, stream, P.C, P.u, P.mean, P.sigma2, P.N, P.H, P.beta,
-                       P.alpha_mu, P.alpha_sigma, P.sigma2_min, shift, P, mean_out, sigma2_out, cmd);
+    hipLaunchKernelGGL(kernel, dim3(kDof), dim3(kThreads), 0, stream, dev, P.C, P.u, mean_out, sigma2_out, cmd,
+                       P.N, (int16_t)P.H, (int16_t)shift);
     return hipGetLastError();
 }
 
