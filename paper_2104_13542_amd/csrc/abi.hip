@@ -157,37 +157,7 @@ void fill_robot_consts(const storm_robot *robot, RobotDev &R)
     R.n_spheres = robot->n_spheres;
 }
 
-// Upper bound of the distance from the base of any body-sphere centre: the
-// frame origins move along a chain whose links have lengths at most
-// |a_k| + |d_k|, and a sphere sits |local centre| from its frame origin.
-double reach_bound(const storm_robot *robot)
-{
-    double r = 0.0, loc = 0.0;
-    for (int k = 0; k < STORM_NFRAMES; ++k) r += fabs((double)robot->dh[k][0]) + fabs((double)robot->dh[k][1]);
-    for (int s = 0; s < robot->n_spheres; ++s) {
-        const float *q = robot->spheres + 5 * s;
-        loc = fmax(loc, sqrt((double)q[1] * q[1] + (double)q[2] * q[2] + (double)q[3] * q[3]));
-    }
-    return r + loc;
-}
-
 }  // namespace
-
-std::vector<storm::SelfGroup> storm::self_groups(const storm_robot *robot)
-{
-    const int S = robot->n_spheres;
-    std::vector<SelfGroup> g;
-    for (int t = 0; t < S;) {
-        const int body = (int)robot->spheres[5 * t];
-        int n = 1;
-        while (t + n < S && n < 4 && (int)robot->spheres[5 * (t + n)] == body) ++n;
-        int s_end = 0;  // spheres are sorted by body
-        while (s_end < S && (int)robot->spheres[5 * s_end] <= body - 2) ++s_end;
-        g.push_back(SelfGroup{t, n, s_end});
-        t += n;
-    }
-    return g;
-}
 
 int storm::anchor_sphere(const float *sp, int lo, int hi, double &radius)
 {
@@ -230,86 +200,54 @@ std::vector<float> storm::body_bounds(const storm_robot *robot)
     return out;
 }
 
-// Self-collision work items: one per (group, partner body), partners
-// [s_begin, s_end) the spheres of that body, written as eight integers
-// (t_first | count << 8, group, s_begin, s_end, a_t, a_s, bits of reach2, 0).
-// Broad phase: a_t is the sphere of the group, a_s the sphere of the partner
-// body, about whose centres the balls of radius R_t = max |c_t - c_a_t| + r_t
-// and R_s (likewise) hold every sphere of each side (each anchor chosen to
-// make its radius smallest); reach2 = (R_t + R_s + 1 mm)^2 rounded up.  Where
-// the anchors' centres are farther apart than R_t + R_s, no pair of the item
-// touches, and the millimetre covers the FP32 rounding of the centres
-// (micrometres within the robot's reach).  The rollout workgroup's waves take
-// the items from a queue in this order: most rounds (pairs of partners)
-// first.  Returns the pair count.
-int storm::self_segments(const storm_robot *robot, std::vector<int> &items)
+// The spheres of each body in runs of up to four, as even as they come (at
+// most 64 / 4 + 8 runs), and one item per pair of runs whose bodies are at
+// least two apart: first sphere and count - 1 of the later and of the earlier
+// run (6, 2, 6 and 2 bits), the runs' anchor spheres (6 bits each), the sum of
+// the radii about the anchors that hold the runs, and what the anchors' own
+// radii lack of it (each with 0.1 mm for the rounding of the centres, which is
+// micrometres within the robot's reach).
+int storm::self_pairs(const storm_robot *robot, std::vector<int> &items)
 {
-    const std::vector<SelfGroup> groups = self_groups(robot);
-    const float *sp = robot->spheres;
-    struct Item {
-        int v[8];
-        int rounds, order;
+    struct Run {
+        int first, count, body, anchor;
+        double lack;  // what the anchor's radius lacks to hold the run
     };
-    std::vector<Item> list;
-    long long pairs = 0;
-    for (int gi = 0; gi < (int)groups.size(); ++gi) {
-        const SelfGroup &g = groups[gi];
-        pairs += (long long)g.count * g.s_end;
-        double rt = 0.0;
-        const int at = anchor_sphere(sp, g.t_first, g.t_first + g.count, rt);
-        for (int lo = 0; lo < g.s_end;) {
-            int hi = lo + 1;
-            while (hi < g.s_end && (int)sp[5 * hi] == (int)sp[5 * lo]) ++hi;
-            double rs = 0.0;
-            const int as = anchor_sphere(sp, lo, hi, rs);
-            const double reach = rt + rs + 1.0e-3;
-            const float reach2 = nextafterf((float)(reach * reach), INFINITY);
-            Item it{};
-            it.v[0] = g.t_first | (g.count << 8);
-            it.v[1] = gi;
-            it.v[2] = lo;
-            it.v[3] = hi;
-            it.v[4] = at;
-            it.v[5] = as;
-            memcpy(&it.v[6], &reach2, sizeof(float));
-            it.rounds = (hi - lo + 1) / 2;
-            it.order = (int)list.size();
-            list.push_back(it);
-            lo = hi;
-        }
-    }
-    std::stable_sort(list.begin(), list.end(), [](const Item &x, const Item &y) { return x.rounds > y.rounds; });
-    items.clear();
-    for (const Item &it : list) items.insert(items.end(), it.v, it.v + 8);
-    return (int)pairs;
-}
-
-// Records of the expanded pair test, [group][s][8] for partner s of the
-// group spheres t = t_first + k: entries k = 0..3 the threshold of
-// |c_s|^2 - 2 c_s.c_t + |c_t|^2 < (r_s + r_t)^2 + slack, entries 4 + k the
-// contact distance r_s + r_t.  The FP32 evaluation of the test errs by less
-// than 2^-24 * 12 (|c_s| + |c_t|)^2, and the slack, 2^-18 (2 reach + r_s +
-// r_t)^2, is over five times that with both centres within the robot's
-// reach.  Slots past a group's count, and partners s outside its range, hold
-// the threshold -1e30 (never a hit) and contact distance 0.
-std::vector<float> storm::self_thresholds(const storm_robot *robot, double reach)
-{
     const int S = robot->n_spheres;
-    const std::vector<SelfGroup> groups = self_groups(robot);
-    std::vector<float> thr(groups.size() * (size_t)S * 8, 0.0f);
-    for (size_t gi = 0; gi < groups.size(); ++gi)
-        for (int s = 0; s < S; ++s)
-            for (int k = 0; k < 4; ++k) {
-                float *rec = &thr[(gi * S + s) * 8];
-                rec[k] = -1.0e30f;
-                if (s >= groups[gi].s_end || k >= groups[gi].count) continue;
-                const int t = groups[gi].t_first + k;
-                const double rs = (double)robot->spheres[5 * s + 4] + (double)robot->spheres[5 * t + 4];
-                const double span = 2.0 * reach + rs;
-                rec[k] = (float)(rs * rs + ldexp(span * span, -18));
-                rec[4 + k] = (float)rs;
-            }
-    return thr;
+    const float *sp = robot->spheres;
+    std::vector<Run> runs;
+    for (int lo = 0; lo < S;) {
+        int hi = lo;
+        while (hi < S && (int)sp[5 * hi] == (int)sp[5 * lo]) ++hi;
+        const int parts = (hi - lo + 3) / 4;
+        for (int k = 0; k < parts; ++k) {
+            Run r{};
+            r.first = lo + (hi - lo) * k / parts;
+            r.count = lo + (hi - lo) * (k + 1) / parts - r.first;
+            r.body = (int)sp[5 * lo];
+            double radius = 0.0;
+            r.anchor = anchor_sphere(sp, r.first, r.first + r.count, radius);
+            r.lack = radius - (double)sp[5 * r.anchor + 4];
+            runs.push_back(r);
+        }
+        lo = hi;
+    }
+    items.clear();
+    int pairs = 0;
+    for (const Run &t : runs)
+        for (const Run &s : runs) {
+            if (s.body > t.body - 2) continue;
+            const double lack = t.lack + s.lack + 1.0e-4;
+            const float reach[2] = {(float)(lack + sp[5 * t.anchor + 4] + sp[5 * s.anchor + 4]), (float)lack};
+            int bits[2];
+            memcpy(bits, reach, sizeof(reach));
+            items.push_back(t.first | (t.count - 1) << 6 | s.first << 8 | (s.count - 1) << 14);
+            items.push_back(t.anchor | s.anchor << 6);
+            items.push_back(bits[0]);
+            items.push_back(bits[1]);
+            pairs += t.count * s.count;
+        }
+    return pairs;
 }
 
 namespace {
@@ -407,13 +345,12 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
     const float comb[3] = {params->comb_filter ? params->comb[0] : 1.0f, params->comb_filter ? params->comb[1] : 0.0f,
                            params->comb_filter ? params->comb[2] : 0.0f};
     std::vector<int> seg;
-    const int n_pairs = storm::self_segments(robot, seg);
+    const int n_pairs = storm::self_pairs(robot, seg);
     std::vector<_Float16> net_frag;
     std::vector<float> net_bias;
     if (params->self_model == 1) storm::pack_selfnet(robot->self_mlp, net_frag, net_bias);
-    const std::vector<float> thr = storm::self_thresholds(robot, reach_bound(robot));
     const std::vector<float> bounds = storm::body_bounds(robot);
-    const int n_seg = (int)seg.size() / 8;
+    const int n_seg = (int)seg.size() / 4;
 
     ProblemDev &P = c->P;
     P.N = N;
@@ -458,8 +395,8 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
     c->R.n_pairs = n_pairs;
 
     float *tables, *halton, *box_obs, *mean, *sigma2, *u, *C, *dt_raw, *lim_raw, *sig_raw, *obs_raw, *sph_raw_d;
-    float *self_thr, *body_bound, *grad_part, *grad, *adam, *ball, *qbuf = nullptr;
-    float4 *sph_obs, *obs_bound, *sph_local;
+    float *body_bound, *grad_part, *grad, *adam, *ball, *qbuf = nullptr;
+    float4 *obs_bound, *sph_local;
     int32_t *sph_body, *self_seg;
     uint32_t *counters;
     PlainDev dev;
@@ -473,7 +410,6 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
     } while (0)
     STORM_TRY(dalloc(c, &tables, storm::kTabSize));
     STORM_TRY(dalloc(c, &halton, (size_t)STORM_DOF * params->n_halton * H));
-    STORM_TRY(dalloc(c, &sph_obs, (size_t)n_sph_obs));
     STORM_TRY(dalloc(c, &box_obs, (size_t)16 * n_box_obs));
     STORM_TRY(dalloc(c, &obs_bound, (size_t)n_obs));
     STORM_TRY(dalloc(c, &mean, (size_t)H * STORM_DOF));
@@ -500,9 +436,8 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
     }
     STORM_TRY(dalloc(c, &sph_local, (size_t)robot->n_spheres));
     STORM_TRY(dalloc(c, &sph_body, (size_t)robot->n_spheres));
-    STORM_TRY(dalloc(c, &self_thr, thr.size()));
     STORM_TRY(dalloc(c, &body_bound, bounds.size()));
-    STORM_TRY(dalloc(c, &self_seg, (size_t)8 * n_seg));
+    STORM_TRY(dalloc(c, &self_seg, seg.size()));
     // staging copies of the host inputs (freed at destroy with the rest)
     STORM_TRY(dalloc(c, &dt_raw, (size_t)H));
     STORM_TRY(dalloc(c, &lim_raw, (size_t)3 * STORM_DOF));
@@ -527,12 +462,9 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
                                      hipMemcpyHostToDevice, s));
         if (n_seg > 0)
             STORM_TRY(hipMemcpyAsync(self_seg, seg.data(), sizeof(int) * seg.size(), hipMemcpyHostToDevice, s));
-        if (!thr.empty())
-            STORM_TRY(hipMemcpyAsync(self_thr, thr.data(), sizeof(float) * thr.size(), hipMemcpyHostToDevice, s));
         STORM_TRY(hipMemcpyAsync(body_bound, bounds.data(), sizeof(float) * bounds.size(), hipMemcpyHostToDevice, s));
         P.tables = tables;
         P.halton = halton;
-        P.sph_obs = sph_obs;
         P.box_obs = box_obs;
         P.obs_bound = obs_bound;
         P.mean = mean;
@@ -552,7 +484,6 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
         P.adam_v = adam + (size_t)H * STORM_DOF;
         c->R.sph_local = sph_local;
         c->R.sph_body = sph_body;
-        c->R.self_thr = self_thr;
         c->R.body_bound = body_bound;
         c->R.self_items = self_seg;
         c->R.n_self_items = n_seg;
@@ -562,7 +493,7 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
         STORM_TRY(storm::launch_init_tables(P, dt_raw, lim_raw, params->acc_stop, params->gamma, params->w_term,
                                             params->k_jl, params->k_vl, sig_raw, comb, params->n_knots, obs_raw,
                                             n_obs,
-                                            sph_obs, box_obs, obs_bound, sph_raw_d, robot->n_spheres, sph_local,
+                                            box_obs, obs_bound, sph_raw_d, robot->n_spheres, sph_local,
                                             sph_body, s));
         STORM_TRY(hipStreamSynchronize(s));
     }
@@ -581,7 +512,7 @@ fail:
 static hipError_t enqueue_rollout(storm_ctx ctx, const float *d_x0, const float *d_goal, const float *d_noise,
                                   const StepOut &out, hipStream_t s)
 {
-    hipError_t e = storm::launch_rollout(ctx->P, ctx->R.n_spheres, ctx->dev, d_x0, d_goal, d_noise, out, ctx->waves, s);
+    hipError_t e = storm::launch_rollout(ctx->P, ctx->R, ctx->dev, d_x0, d_goal, d_noise, out, ctx->waves, s);
     if (e == hipSuccess && ctx->P.selfnet)
         e = storm::launch_selfnet(ctx->P, ctx->dev, out, s);
     return e;

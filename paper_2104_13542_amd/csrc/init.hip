@@ -64,32 +64,24 @@ __global__ void tables_kernel(ProblemDev P, float *tables, const float *dt_raw, 
 }
 
 // Geometry records in device form, one flat index space over all of them.
-//   sphere obstacles: (centre, radius)
-//   all obstacles:    the culling ball (centre, bounding radius + margin)
+//   all obstacles:    (centre, radius), of a cuboid to its corners
 //   cuboids:          the world-to-box map l = M x + t with M = R^T,
 //                     t = -R^T c, then the half extents
 //   body spheres:     (local centre, radius) and the frame index
 __global__ void geometry_kernel(const float *sph_obs_raw, int n_so, const float *box_raw, int n_bo,
-                                float4 *sph_obs, float *box_obs, float4 *obs_bound, const float *sph_raw, int S,
+                                float *box_obs, float4 *obs_bound, const float *sph_raw, int S,
                                 float4 *sph_local, int32_t *sph_body)
 {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t < n_so) {
-        const float *r = sph_obs_raw + t * STORM_OBSTACLE_STRIDE;
-        sph_obs[t] = make_float4(r[1], r[2], r[3], r[4]);
-    }
     if (t < n_so + n_bo) {
-        // culling record: the obstacle lies inside the ball (centre, radius);
-        // a cuboid's ball has the radius of its half-extent diagonal.  The
-        // 1e-4 m margin dwarfs the FP32 rounding of any distance the cull or
-        // the exact tests form, so no contact the exact tests would report is
-        // ever culled.
+        // the ball that holds the obstacle: a sphere itself, or the half-extent
+        // diagonal of a cuboid (rounding is the culls' margin's business)
         const bool sphere = t < n_so;
         const float *r = sphere ? sph_obs_raw + t * STORM_OBSTACLE_STRIDE
                                 : box_raw + (t - n_so) * STORM_OBSTACLE_STRIDE;
         const double rad = sphere ? (double)r[4]
                                   : sqrt((double)r[4] * r[4] + (double)r[5] * r[5] + (double)r[6] * r[6]);
-        obs_bound[t] = make_float4(r[1], r[2], r[3], (float)(rad + 1e-4));
+        obs_bound[t] = make_float4(r[1], r[2], r[3], (float)rad);
     }
     if (t < n_bo) {
         const float *r = box_raw + t * STORM_OBSTACLE_STRIDE;
@@ -203,7 +195,7 @@ __global__ void halton_smooth_kernel(int n_halton, int K, int H, const double *Z
 
 hipError_t launch_init_tables(const ProblemDev &P, const float *d_dt_raw, const float *d_lim_raw, float acc_stop,
                               float gamma, float w_term, float k_jl, float k_vl, const float *d_sigma_init,
-                              const float comb[3], int n_knots, const float *d_obs_raw, int n_obs, float4 *d_sph_obs, float *d_box_obs,
+                              const float comb[3], int n_knots, const float *d_obs_raw, int n_obs, float *d_box_obs,
                               float4 *d_obs_bound, const float *d_sph_raw, int n_spheres, float4 *d_sph_local,
                               int32_t *d_sph_body, hipStream_t stream)
 {
@@ -219,7 +211,7 @@ hipError_t launch_init_tables(const ProblemDev &P, const float *d_dt_raw, const 
     const int gthreads = 256;
     const int gblocks = ng > 0 ? (ng + gthreads - 1) / gthreads : 1;
     hipLaunchKernelGGL(geometry_kernel, dim3(gblocks), dim3(gthreads), 0, stream, d_obs_raw, n_so,
-                       d_obs_raw + (size_t)STORM_OBSTACLE_STRIDE * n_so, n_bo, d_sph_obs, d_box_obs, d_obs_bound,
+                       d_obs_raw + (size_t)STORM_OBSTACLE_STRIDE * n_so, n_bo, d_box_obs, d_obs_bound,
                        d_sph_raw, S, d_sph_local, d_sph_body);
     e = hipGetLastError();
     if (e != hipSuccess || P.n_halton == 0) return e;

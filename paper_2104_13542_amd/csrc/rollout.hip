@@ -20,14 +20,14 @@
 //                  that hold them, to LDS
 //       wave W-2   manipulability (Eq. 12)
 //       wave W-1   pose (Eq. 9)
-//   D1  all waves  obstacles near each body, by capsules
+//   D1  all waves  obstacles near each body and near pairs of sphere runs,
+//                  by capsules
 //   D2  all waves  environment (spheres x obstacles) split over waves, then
-//                  self-collision (sphere pairs) as items taken from a queue,
-//                  each behind a broad-phase test
+//                  self-collision (sphere pairs) as items taken from a queue
 //   E   wave 4     weighted running cost (Eq. 15), horizon sum (Eq. 2) as a
 //                  segmented DPP scan
-// Obstacle, sphere and pair records are indexed by wave-uniform loop
-// counters, so they are fetched with scalar loads into SGPRs; every per-point
+// Obstacle and sphere records are indexed by wave-uniform counters, so they
+// are fetched with scalar loads into SGPRs; every per-point
 // LDS array is [row][lane] (conflict-free), and rows whose lifetimes do not
 // overlap share space (about 80 KB per workgroup with 52 spheres, so that the
 // batched form holds two workgroups per CU).  Reductions run in a fixed
@@ -49,7 +49,7 @@ static_assert(2 * 16 <= 96, "the collision partials of 16 waves fit over the fra
 template <int kLane>
 __device__ __forceinline__ float row_lane(float x)
 {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x150 + kLane, 0xf, 0xf, false));  // row_newbcast
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x150 + kLane, 0xf, 0xf, true));  // row_newbcast
 }
 
 // Maximum of a non-negative float over the caller's 16-lane row, in every
@@ -58,17 +58,20 @@ __device__ __forceinline__ float row_lane(float x)
 __device__ __forceinline__ float row_max_nonneg(float x)
 {
     uint32_t b = __float_as_uint(x);
-    b = max(b, (uint32_t)__builtin_amdgcn_mov_dpp((int)b, 0xb1, 0xf, 0xf, false));   // quad_perm [1, 0, 3, 2]
-    b = max(b, (uint32_t)__builtin_amdgcn_mov_dpp((int)b, 0x4e, 0xf, 0xf, false));   // quad_perm [2, 3, 0, 1]
-    b = max(b, (uint32_t)__builtin_amdgcn_mov_dpp((int)b, 0x141, 0xf, 0xf, false));  // row_half_mirror
-    b = max(b, (uint32_t)__builtin_amdgcn_mov_dpp((int)b, 0x140, 0xf, 0xf, false));  // row_mirror
+    b = max(b, (uint32_t)__builtin_amdgcn_mov_dpp((int)b, 0xb1, 0xf, 0xf, true));   // quad_perm [1, 0, 3, 2]
+    b = max(b, (uint32_t)__builtin_amdgcn_mov_dpp((int)b, 0x4e, 0xf, 0xf, true));   // quad_perm [2, 3, 0, 1]
+    b = max(b, (uint32_t)__builtin_amdgcn_mov_dpp((int)b, 0x141, 0xf, 0xf, true));  // row_half_mirror
+    b = max(b, (uint32_t)__builtin_amdgcn_mov_dpp((int)b, 0x140, 0xf, 0xf, true));  // row_mirror
     return __uint_as_float(b);
 }
 
+// What every culling radius is widened by (m): it dwarfs the FP32 rounding of
+// any distance that a cull or an exact test forms, so that no contact which an
+// exact test would report is ever culled.
+constexpr float kCullMargin = 1.0e-4f;
+
 // Whether the capsule (segment a.xyz + t b.xyz, t in [0, 1], radius `reach`
 // already holding the obstacle's; b.w = 1 / |b.xyz|^2) meets the point o.
-// The margin of the culling radii covers the rounding of t, which moves the
-// nearest point by far less.
 __device__ __forceinline__ bool capsule_hits(const float4 a, const float4 b, float reach, float ox, float oy, float oz)
 {
     const float dx = ox - a.x, dy = oy - a.y, dz = oz - a.z;
@@ -164,6 +167,22 @@ struct TileQueue {
     }
 };
 
+// Whether two capsules of the same row of points may meet: the difference of
+// their axes runs from a1 - a2 along b1 - b2 (both at the same time at every
+// point of the row), and the spheres come within `reach` of each other at no
+// point where that segment stays farther from the origin.
+__device__ __forceinline__ bool capsules_meet(const float4 a1, const float4 b1, const float4 a2, const float4 b2,
+                                              float reach)
+{
+    const float dx = a1.x - a2.x, dy = a1.y - a2.y, dz = a1.z - a2.z;
+    const float bx = b1.x - b2.x, by = b1.y - b2.y, bz = b1.z - b2.z;
+    const float len2 = fmaf(bx, bx, fmaf(by, by, bz * bz));
+    const float dot = fmaf(dx, bx, fmaf(dy, by, dz * bz));
+    const float t = fminf(fmaxf(-dot * __builtin_amdgcn_rcpf(fmaxf(len2, 1.0e-20f)), 0.0f), 1.0f);
+    const float ex = fmaf(t, bx, dx), ey = fmaf(t, by, dy), ez = fmaf(t, bz, dz);
+    return fmaf(ex, ex, fmaf(ey, ey, ez * ez)) < reach * reach;
+}
+
 // One 64-lane tile of one problem, executed by the W waves of the calling
 // workgroup; smem is the workgroup's dynamic LDS (rollout_lds_bytes).
 // kTask: the task-space form, which adds the flange velocity and
@@ -185,8 +204,8 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
     //   centres [3S]             C - D2;  before them noise [8] A0 - A1,
     //                            sin/cos [14] and hinges [21] A1 - B
     //   velocities, accelerations [14]  A1 - C (task-space form only)
-    // then the capsules of the spheres [S][4 rows][8] (C - D2) and the
-    // culling records of the obstacles (A0 - D2).
+    // then the capsules of the spheres [S][4 rows][8] (C - D2), the records of
+    // the obstacles (A0 - D2) and the lists of phase D1 (D1 - D2).
     const int S = R.n_spheres;
     float *s_fr = smem;                        // [8 frames][12][64]: R row-major, p
     float *s_penv = s_fr;                      // [W][64] (over the frames, after phase C)
@@ -199,7 +218,14 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
     float *s_v = s_cen + rollout_cen_rows(S) * kLanes;  // [7][64] (task-space form only)
     float *s_acc = s_v + kDof * kLanes;                  // [7][64]
     float4 *s_cap = reinterpret_cast<float4 *>(s_v + (kTask ? 2 * kDof * kLanes : 0));  // [S][4][2]
-    float4 *s_bound = s_cap + 8 * S;                     // [obstacles]
+    const uint32_t mask = P.cost_mask;
+    const int nobs = (mask & STORM_COST_ENV) && S > 0 ? P.n_sph_obs + P.n_box_obs : 0;
+    const int n_items = (mask & STORM_COST_SELF) ? R.n_self_items : 0;
+    float4 *s_bound = s_cap + 8 * S;             // [obstacles] centre, radius (of a cuboid: to its corners)
+    float4 *s_box = s_bound + nobs;              // [cuboids][4] their records
+    int2 *s_self = reinterpret_cast<int2 *>(s_box + (nobs > 0 ? 4 * P.n_box_obs : 0));  // [items] those that stay: runs
+                                                                      // and anchors, and the runs' joint reach
+    uint8_t *s_near = reinterpret_cast<uint8_t *>(s_self + n_items);  // [8][obstacles] obstacles near each body
 
     const int lane = threadIdx.x & (kLanes - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -218,35 +244,56 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
     const int pos = pl < ppt ? h * ppt + pl : lane;
     const int src = min(lane, n_pts - 1);
     const bool live = valid && i < N - first.n_null;  // sampled (non-null) particle
-    const uint32_t mask = P.cost_mask;
     const global_ptr<const float> tab = as_global(P.tables);
 
     // Per-joint inputs of phase A1, loaded up front so that their latency
-    // overlaps the noise generation.
-    const int jw = wave < kDof ? wave : 0;
-    // (vector loads throughout, so that the first barrier waits for none of
-    // them: the state and the policy come fresh from the previous kernels)
-    const float mu_j = live ? as_global(first.mean)[h * kDof + jw] : 0.0f;
-    const float sig_j = sqrtf(P.cov_step ? as_global(P.sigma2)[h * kDof + jw] : vector_load_f32(P.sigma2 + jw));
-    const float dt_h = tab[kTabDt + h];
-    const float vs_h = tab[kTabVstop + h];
-    const float q0_j = vector_load_f32(x0 + jw), v0_j = vector_load_f32(x0 + kDof + jw);
-    // the obstacles' culling records for phase D, one per thread of the waves
-    // that draw no noise
-    const int nobs = (mask & STORM_COST_ENV) && S > 0 ? P.n_sph_obs + P.n_box_obs : 0;
-    const int ob_t = (int)threadIdx.x - 4 * kLanes;
-    static_assert((W - 4) * kLanes >= STORM_MAX_OBSTACLES, "one culling record per thread");
-    if (ob_t >= 0 && ob_t < nobs) s_bound[ob_t] = load_float4(as_global(P.obs_bound) + ob_t);
+    // overlaps the noise generation (vector loads throughout, so that the
+    // first barrier waits for none of them: the state and the policy come
+    // fresh from the previous kernels).
+    float mu_j = 0.0f, sig2_j = 0.0f, dt_h = 0.0f, vs_h = 0.0f, q0_j = 0.0f, v0_j = 0.0f;
+    if (wave < kDof) {
+        if (live) mu_j = as_global(first.mean)[h * kDof + wave];
+        sig2_j = P.cov_step ? as_global(P.sigma2)[h * kDof + wave] : vector_load_f32(P.sigma2 + wave);
+        dt_h = tab[kTabDt + h];
+        vs_h = tab[kTabVstop + h];
+        q0_j = vector_load_f32(x0 + wave);
+        v0_j = vector_load_f32(x0 + kDof + wave);
+    }
+    // the obstacles' records, by the waves that draw no noise
+    if (wave >= 4 && nobs > 0) {
+        const int n_rec = nobs + 4 * P.n_box_obs;
+        for (int k = (int)threadIdx.x - 4 * kLanes; k < n_rec; k += (W - 4) * kLanes)
+            s_bound[k] = load_float4(k < nobs ? as_global(P.obs_bound) + k
+                                              : as_global(reinterpret_cast<const float4 *>(P.box_obs)) + (k - nobs));
+    }
+    // phase D1's bound of the body that this lane tests (as well early)
+    const int body8 = lane & (kFrames - 1);
+    float anchor = 0.0f, widen = 0.0f;
+    if (2 * wave < nobs) {
+        anchor = as_global(R.body_bound)[2 * body8];
+        widen = as_global(R.body_bound)[2 * body8 + 1];
+    }
     // the goal and the cost weights that phases C and E read, staged in
     // LDS by the last wave while the noise is drawn (read where they are
     // used, as scalar loads, they would add a memory round trip to those
     // serial phases)
     __shared__ float s_par2[2][kParCount];  // (by parity: the costs of a tile are summed during the next one's noise)
     float *s_par = s_par2[queue.parity];
-    __shared__ int s_self_next;  // head of the self-collision item queue (phase D2)
+    __shared__ int s_self_n, s_self_next;  // self-collision items that stay (phase D1), and the queue's head (D2)
+    __shared__ float4 s_sph[STORM_MAX_SPHERES];  // body-frame centre, radius
+    __shared__ uint8_t s_body[STORM_MAX_SPHERES];  // frame
     __shared__ int s_near_n[kFrames];  // obstacles near each body (phase D1)
-    __shared__ uint8_t s_near[kFrames * STORM_MAX_OBSTACLES];
-    if (wave == W - 1 && lane == kParCount) s_self_next = 0;
+    if (wave == W - 1 && lane == kParCount) s_self_n = s_self_next = 0;
+    if (wave == W - 3 && lane < S && (mask & (STORM_COST_SELF | STORM_COST_ENV))) {
+        s_sph[lane] = load_float4(as_global(R.sph_local) + lane);
+        s_body[lane] = (uint8_t)as_global(R.sph_body)[lane];
+    }
+    // phase D1's first self-collision item of this lane (last wave first)
+    const int g_first = 16 * (W - 1 - wave) + (lane & 15);
+    int item[4] = {0, 0, 0, 0};
+    if (g_first < n_items)
+#pragma unroll
+        for (int k = 0; k < 4; ++k) item[k] = as_global(R.self_items)[4 * g_first + k];
     if (wave == W - 2 && lane < kFrames) s_near_n[lane] = 0;
     // ---- A0: standard noise ------------------------------------------------
     // waves 0-3, one per SIMD: wave w makes the normal pair w / 2 of Philox
@@ -279,7 +326,7 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
             if (comb) e = f;
         }
         float u = 0.0f;
-        if (live) u = fmaf(sig_j, e, mu_j);
+        if (live) u = fmaf(sqrtf(sig2_j), e, mu_j);
         const float v = v0_j + segmented_scan(dt_h * u, h, H);
         const float q = q0_j + segmented_scan(dt_h * v, h, H);
         if (kTask) s_v[j * kLanes + pos] = v;
@@ -347,53 +394,59 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
     // that the collision phase is spread evenly over all waves.
     constexpr int WC = W - kPoseWaves;
     if (wave < WC) {
-        if (mask & (STORM_COST_SELF | STORM_COST_ENV)) {
+        const int s0 = wave * S / WC, s1 = (wave + 1) * S / WC;
+        if ((mask & (STORM_COST_SELF | STORM_COST_ENV)) && s0 < s1) {
             // a contiguous run of spheres per wave (sorted by body): the
             // frame of a body is read from LDS once per run
-            const int s0 = wave * S / WC, s1 = (wave + 1) * S / WC;
-            const STORM_CONST_AS int32_t *body = uniform_ptr(R.sph_body);
-            int fb = -1;
-            float F[12];
             // where in its row's span of steps this lane lies, in [0, 1]
             const float step = floorf(((float)src + 0.5f) * __builtin_amdgcn_rcpf((float)ppt));
             const float step0 = row_lane<0>(step);
             const float tau =
                 fminf((step - step0) * __builtin_amdgcn_rcpf(fmaxf(row_lane<15>(step) - step0, 1.0f)), 1.0f);
+            // (the next sphere's record is read one ahead)
+            float F[12];
+            int fb = __builtin_amdgcn_readfirstlane((int)s_body[s0]);
+            float4 next = s_sph[s0];
+#pragma unroll
+            for (int c = 0; c < 12; ++c) F[c] = s_fr[(fb * 12 + c) * kLanes + lane];
             for (int s = s0; s < s1; ++s) {
-                const STORM_CONST_AS float *sl = uniform_ptr(reinterpret_cast<const float *>(R.sph_local)) + 4 * s;
-                const int b = body[s];
+                const float4 loc = next;
+                const int after = min(s + 1, s1 - 1), b_next = s_body[after];
+                next = s_sph[after];
+                float cc[3];
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    cc[c] = fmaf(F[c * 3 + 0], loc.x, fmaf(F[c * 3 + 1], loc.y, fmaf(F[c * 3 + 2], loc.z, F[9 + c])));
+                    s_cen[(s * 3 + c) * kLanes + lane] = cc[c];
+                }
+                // The capsule of each row of 16 points, which phase D tests
+                // against the obstacles and other spheres: the chord from the row's first
+                // centre a to its last, and as radius the largest distance
+                // of a centre to the chord's point at its own time (any
+                // point of the chord serves), plus r_s and a margin.  A row with a
+                // centre that is not finite gets a ball that meets
+                // everything.
+                const float dx = cc[0] - row_lane<0>(cc[0]), dy = cc[1] - row_lane<0>(cc[1]),
+                            dz = cc[2] - row_lane<0>(cc[2]);
+                const float bx = row_lane<15>(dx), by = row_lane<15>(dy), bz = row_lane<15>(dz);
+                const float ex = fmaf(-tau, bx, dx), ey = fmaf(-tau, by, dy), ez = fmaf(-tau, bz, dz);
+                const float rad = fast_sqrt(row_max_nonneg(fminf(fmaf(ex, ex, fmaf(ey, ey, ez * ez)), 1.0e30f)));
+                const float inv = __builtin_amdgcn_rcpf(fmaxf(fmaf(bx, bx, fmaf(by, by, bz * bz)), 1.0e-20f));
+                float4 *cap = s_cap + (s * 4 + (lane >> 4)) * 2;
+                if ((lane & 15) == 0) {
+                    cap[0] = make_float4(cc[0], cc[1], cc[2], rad + (loc.w + kCullMargin));
+                    cap[1] = make_float4(bx, by, bz, inv);
+                    if (!(rad < 1.0e6f)) {
+                        const float zero = fminf(rad, 0.0f);  // (formed here, rarely)
+                        cap[0] = make_float4(zero, zero, zero, 1.0e15f);
+                        cap[1] = make_float4(zero, zero, zero, zero);
+                    }
+                }
+                const int b = __builtin_amdgcn_readfirstlane(b_next);
                 if (b != fb) {
 #pragma unroll
                     for (int c = 0; c < 12; ++c) F[c] = s_fr[(b * 12 + c) * kLanes + lane];
                     fb = b;
-                }
-                float cc[3];
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    cc[c] = fmaf(F[c * 3 + 0], sl[0], fmaf(F[c * 3 + 1], sl[1], fmaf(F[c * 3 + 2], sl[2], F[9 + c])));
-                    s_cen[(s * 3 + c) * kLanes + lane] = cc[c];
-                }
-                if (nobs == 0) continue;
-                // The capsule of each row of 16 points, which phase D tests
-                // against the obstacles: the chord from the row's first
-                // centre a to its last, and as radius the largest distance
-                // of a centre to the chord's point at its own time (any
-                // point of the chord serves), plus r_s.  A row with a
-                // centre that is not finite gets a ball that meets
-                // everything.
-                const float ax = row_lane<0>(cc[0]), ay = row_lane<0>(cc[1]), az = row_lane<0>(cc[2]);
-                const float dx = cc[0] - ax, dy = cc[1] - ay, dz = cc[2] - az;
-                const float bx = row_lane<15>(dx), by = row_lane<15>(dy), bz = row_lane<15>(dz);
-                const float ex = fmaf(-tau, bx, dx), ey = fmaf(-tau, by, dy), ez = fmaf(-tau, bz, dz);
-                const float rad =
-                    fast_sqrt(row_max_nonneg(fminf(fmaf(ex, ex, fmaf(ey, ey, ez * ez)), 1.0e30f)));
-                const float len2 = fmaf(bx, bx, fmaf(by, by, bz * bz));
-                if ((lane & 15) == 0) {
-                    const bool cull = rad < 1.0e6f;
-                    const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                    float4 *cap = s_cap + (s * 4 + (lane >> 4)) * 2;
-                    cap[0] = cull ? make_float4(ax, ay, az, rad + sl[3]) : make_float4(0.0f, 0.0f, 0.0f, 1.0e15f);
-                    cap[1] = cull ? make_float4(bx, by, bz, __builtin_amdgcn_rcpf(fmaxf(len2, 1.0e-20f))) : zero;
                 }
             }
         }
@@ -484,9 +537,8 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
     // row's capsule of one body (that of the body's anchor sphere, widened to
     // hold all of the body's spheres) and each half of the wave takes another
     // obstacle; the waves share the obstacles.
-    if (nobs > 0) {
-        const int body = lane & 7, row = (lane >> 3) & 3, half = lane >> 5;
-        const float anchor = as_global(R.body_bound)[2 * body], widen = as_global(R.body_bound)[2 * body + 1];
+    if (2 * wave < nobs) {
+        const int body = body8, row = (lane >> 3) & 3, half = lane >> 5;
         const float4 *cap = s_cap + (__float_as_int(anchor) * 4 + row) * 2;
         const float4 a = cap[0], b = cap[1];
         const float reach = a.w + widen;
@@ -499,7 +551,34 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
             near |= near >> 8;
             if (row == 0 && ((near >> lane) & 1ull)) {
                 const int k = atomicAdd(&s_near_n[body], 1);
-                s_near[body * STORM_MAX_OBSTACLES + k] = (uint8_t)o;
+                s_near[body * nobs + k] = (uint8_t)o;
+            }
+        }
+    }
+    // Self-collision items (pairs of runs of up to four spheres of a body) by
+    // the capsules of the runs' anchor spheres, widened to hold the runs: a
+    // lane tests one row of one item.
+    if (mask & STORM_COST_SELF) {
+        const global_ptr<const int32_t> items = as_global(R.self_items);
+        const int row = lane >> 4;
+        // (16 items a wave, from the last wave down: the obstacles of the
+        // loop above start at the first)
+        for (int g0 = 16 * (W - 1 - wave); g0 < n_items; g0 += 16 * W) {
+            const int g = g0 + (lane & 15);
+            if (g != g_first && g < n_items)
+#pragma unroll
+                for (int k = 0; k < 4; ++k) item[k] = items[4 * g + k];
+            const int anchors = item[1];
+            const float4 *ct = s_cap + ((anchors & 63) * 4 + row) * 2, *cs = s_cap + ((anchors >> 6) * 4 + row) * 2;
+            uint64_t meet = __builtin_amdgcn_ballot_w64(
+                g < n_items &&
+                capsules_meet(ct[0], ct[1], cs[0], cs[1], (ct[0].w + cs[0].w) + __int_as_float(item[3])));
+            if (meet == 0) continue;
+            meet |= meet >> 32;  // the four rows
+            meet |= meet >> 16;
+            if (row == 0 && ((meet >> lane) & 1ull)) {
+                const int k = atomicAdd(&s_self_n, 1);
+                s_self[k] = make_int2(item[0] | anchors << 16, item[2]);
             }
         }
     }
@@ -510,20 +589,20 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
     // (items from a queue).
     float env = 0.0f, selfpen = 0.0f;
     if (nobs > 0) {
-        const STORM_CONST_AS float *sob = uniform_ptr(reinterpret_cast<const float *>(P.sph_obs));
-        const STORM_CONST_AS float *box = uniform_ptr(P.box_obs);
-        const STORM_CONST_AS float *sloc = uniform_ptr(reinterpret_cast<const float *>(R.sph_local));
-        const STORM_CONST_AS int32_t *sbody = uniform_ptr(R.sph_body);
         const int nso = P.n_sph_obs;
-        for (int s = wave; s < S; s += W) {
-            const int b = sbody[s];
-            const int n_near = __builtin_amdgcn_readfirstlane(s_near_n[b]);
-            if (n_near == 0) continue;
+        // lane k holds the body of this wave's k-th sphere and how many
+        // obstacles are near it
+        const int s_mine = wave + lane * W;
+        const int body_l = s_mine < S ? (int)s_body[s_mine] : 0;
+        const int near_l = s_mine < S ? s_near_n[body_l] : 0;
+        for (uint64_t left = __builtin_amdgcn_ballot_w64(near_l > 0); left != 0; left &= left - 1) {
+            const int k_s = (int)__builtin_ctzll(left), s = wave + k_s * W;
+            const int n_near = __builtin_amdgcn_readlane(near_l, k_s);
+            const uint8_t *near = s_near + __builtin_amdgcn_readlane(body_l, k_s) * nobs;
             const float x = s_cen[(s * 3 + 0) * kLanes + lane];
             const float y = s_cen[(s * 3 + 1) * kLanes + lane];
             const float z = s_cen[(s * 3 + 2) * kLanes + lane];
-            const float rs = sloc[4 * s + 3];
-            const float rs2 = rs * rs;
+            const float rs = s_sph[s].w;
             const float4 *cap = s_cap + (s * 4 + (lane >> 4)) * 2;
             const float4 ca = cap[0], cb = cap[1];
             float best = 0.0f;
@@ -531,7 +610,7 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
                 // the sphere's four capsules against 16 of its body's
                 // obstacles at a time
                 const int k = k0 + (lane & 15);
-                const int ob_l = s_near[b * STORM_MAX_OBSTACLES + min(k, n_near - 1)];
+                const int ob_l = near[min(k, n_near - 1)];
                 const float4 ob = s_bound[ob_l];
                 uint64_t hits =
                     __builtin_amdgcn_ballot_w64(k < n_near && capsule_hits(ca, cb, ca.w + ob.w, ob.x, ob.y, ob.z));
@@ -544,32 +623,32 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
                     cand &= cand - 1;
                     if (o < nso) {
                         // the direct squared distance (no cancellation) against
-                        // the squared contact distance, from the obstacle's own
-                        // 16-byte record; where a lane touches, the penetration
-                        // (r_s + r_o) - |x - c| at every lane (at or below zero
-                        // where a lane does not touch)
-                        const STORM_CONST_AS float *so = sob + 4 * o;
-                        const float dx = x - so[0], dy = y - so[1], dz = z - so[2];
+                        // the squared contact distance; where a lane touches,
+                        // the penetration (r_s + r_o) - |x - c| at every lane
+                        // (at or below zero where a lane does not touch)
+                        const float4 so = s_bound[o];
+                        const float dx = x - so.x, dy = y - so.y, dz = z - so.z;
                         const float d2 = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-                        const float rc = rs + so[3];
+                        const float rc = rs + so.w;
                         if (__builtin_amdgcn_ballot_w64(d2 < rc * rc) != 0) best = fmaxf(best, rc - fast_sqrt(d2));
                     } else {
-                        const STORM_CONST_AS float *bb = box + (size_t)(o - nso) * 16;
-                        const float lx = fmaf(bb[0], x, fmaf(bb[1], y, fmaf(bb[2], z, bb[9])));
-                        const float ly = fmaf(bb[3], x, fmaf(bb[4], y, fmaf(bb[5], z, bb[10])));
-                        const float lz = fmaf(bb[6], x, fmaf(bb[7], y, fmaf(bb[8], z, bb[11])));
+                        const float4 *bb = s_box + (o - nso) * 4;
+                        const float4 b0 = bb[0], b1 = bb[1], b2 = bb[2], b3 = bb[3];
+                        const float lx = fmaf(b0.x, x, fmaf(b0.y, y, fmaf(b0.z, z, b2.y)));
+                        const float ly = fmaf(b0.w, x, fmaf(b1.x, y, fmaf(b1.y, z, b2.z)));
+                        const float lz = fmaf(b1.z, x, fmaf(b1.w, y, fmaf(b2.x, z, b2.w)));
                         // excess per axis, clamped to [0, 1 m]: one instruction
                         // with the clamp modifier; body spheres are below 1 m, so
                         // clamping cannot turn a miss into a hit and leaves every
                         // axis of a hit exact
-                        const float ox = fminf(fmaxf(fabsf(lx) - bb[12], 0.0f), 1.0f);
-                        const float oy = fminf(fmaxf(fabsf(ly) - bb[13], 0.0f), 1.0f);
-                        const float oz = fminf(fmaxf(fabsf(lz) - bb[14], 0.0f), 1.0f);
+                        const float ox = fminf(fmaxf(fabsf(lx) - b3.x, 0.0f), 1.0f);
+                        const float oy = fminf(fmaxf(fabsf(ly) - b3.y, 0.0f), 1.0f);
+                        const float oz = fminf(fmaxf(fabsf(lz) - b3.z, 0.0f), 1.0f);
                         const float out2 = fmaf(ox, ox, fmaf(oy, oy, oz * oz));
-                        const bool hit = out2 < rs2;
+                        const bool hit = out2 < rs * rs;
                         if (__builtin_amdgcn_ballot_w64(hit) != 0) {
                             const float qin =
-                                fminf(fmaxf(fabsf(lx) - bb[12], fmaxf(fabsf(ly) - bb[13], fabsf(lz) - bb[14])), 0.0f);
+                                fminf(fmaxf(fabsf(lx) - b3.x, fmaxf(fabsf(ly) - b3.y, fabsf(lz) - b3.z)), 0.0f);
                             const float pen = rs - (fast_sqrt(out2) + qin);
                             if (hit) best = fmaxf(best, pen);
                         }
@@ -580,103 +659,66 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
         }
     }
     if (mask & STORM_COST_SELF) {
-        // Pairs by groups of up to four spheres t of one body, held in
-        // registers as (-2 c_t, |c_t|^2), against their partners s streamed
-        // from LDS, two partners per round.  Per pair, the expanded form
-        // a = |c_t|^2 - 2 c_s.c_t (three FMAs) less the pair's threshold;
-        // the group's minimum plus |c_s|^2 is negative at a lane where some
-        // pair may touch: one compare per partner and one branch per round,
-        // no per-pair lane masks.  Only a partner, and then a pair, that some
-        // lane passes gets the exact penetration (r_s + r_t) - |c_s - c_t|,
-        // at every lane: a lane whose pair fails the expanded test is apart
-        // by more than the contact distance plus the rounding, so its
-        // penetration is negative and leaves the maximum unchanged.  Unused
-        // slots of a short group repeat its last sphere against a threshold
-        // of -1e30, and the round after the last partner of an odd count
-        // repeats that partner.
-        //
-        // Work comes as items (one group against the spheres of one partner
-        // body) from a queue in LDS, so that waves done early with the
-        // environment term take more.  Broad phase per item: one sphere of
-        // each side (the anchors) with the radius about it that holds all of
-        // that side's spheres; where the anchors are farther apart than the
-        // two radii at every lane, no pair of the item touches and the item
-        // is skipped (its penetrations are all negative: the maximum is the
-        // same).
-        const STORM_CONST_AS int32_t *items = uniform_ptr(R.self_items);
-        const STORM_CONST_AS float *thr = uniform_ptr(R.self_thr);
-        const int n_items = R.n_self_items;
-        for (;;) {
+        // The items that stayed, from a queue in LDS (their order does not
+        // matter to a maximum), so that waves done early with the
+        // environment take more; the next one is drawn ahead.  An item whose
+        // runs' balls (about their anchors) meet at some point gets the
+        // squared distances of all its pairs; where the least of them is
+        // within the largest contact distance at some point, the
+        // penetrations (r_s + r_t) - |c_s - c_t| of all, at every point
+        // (negative where the spheres are apart).  Short runs repeat their
+        // last sphere.  Everything of an item is in flight at once: the
+        // plain form has about one item per wave here, and its time is the
+        // chain of LDS round trips.
+        const int n_near_items = __builtin_amdgcn_readfirstlane(s_self_n);
+        auto draw = [&]() __attribute__((always_inline)) {
             int g = 0;
             if (lane == 0) g = atomicAdd(&s_self_next, 1);
-            g = __builtin_amdgcn_readfirstlane(g);
-            if (g >= n_items) break;
-            const STORM_CONST_AS int32_t *it = items + 8 * g;
-            const int code = it[0], grp = it[1], s_begin = it[2], s_end = it[3], at = it[4], as = it[5];
-            const float reach2 = __int_as_float(it[6]);
-            const float ax = s_cen[(at * 3 + 0) * kLanes + lane] - s_cen[(as * 3 + 0) * kLanes + lane];
-            const float ay = s_cen[(at * 3 + 1) * kLanes + lane] - s_cen[(as * 3 + 1) * kLanes + lane];
-            const float az = s_cen[(at * 3 + 2) * kLanes + lane] - s_cen[(as * 3 + 2) * kLanes + lane];
-            if (__builtin_amdgcn_ballot_w64(fmaf(ax, ax, fmaf(ay, ay, az * az)) < reach2) == 0) continue;
-            const int t_first = code & 255, count = code >> 8;
-            float mx[4], my[4], mz[4], nt[4];
+            return g;
+        };
+        int drawn = draw();
+        for (;;) {
+            const int g = __builtin_amdgcn_readfirstlane(drawn);
+            if (g >= n_near_items) break;
+            drawn = draw();
+            const int2 rec = s_self[g];
+            const int code = __builtin_amdgcn_readfirstlane(rec.x);
+            const float *at = s_cen + (code >> 16 & 63) * 3 * kLanes + lane;
+            const float *as = s_cen + (code >> 22) * 3 * kLanes + lane;
+            const float ax = at[0] - as[0], ay = at[kLanes] - as[kLanes], az = at[2 * kLanes] - as[2 * kLanes];
+            const float reach = __int_as_float(rec.y);
+            if (__builtin_amdgcn_ballot_w64(fmaf(ax, ax, fmaf(ay, ay, az * az)) < reach * reach) == 0) continue;
+            const int t_first = code & 63, t_last = code >> 6 & 3, s_first = code >> 8 & 63, s_last = code >> 14 & 3;
+            float ct[4][3], cs[4][3], rt[4], rs[4], d2[4][4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const int t = t_first + (k < count ? k : count - 1);
-                mx[k] = -2.0f * s_cen[(t * 3 + 0) * kLanes + lane];
-                my[k] = -2.0f * s_cen[(t * 3 + 1) * kLanes + lane];
-                mz[k] = -2.0f * s_cen[(t * 3 + 2) * kLanes + lane];
-                nt[k] = 0.25f * fmaf(mx[k], mx[k], fmaf(my[k], my[k], mz[k] * mz[k]));
+                const int t = t_first + min(k, t_last), u = s_first + min(k, s_last);
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    ct[k][c] = s_cen[(t * 3 + c) * kLanes + lane];
+                    cs[k][c] = s_cen[(u * 3 + c) * kLanes + lane];
+                }
+                rt[k] = s_sph[t].w;
+                rs[k] = s_sph[u].w;
             }
-            const STORM_CONST_AS float *tg = thr + (size_t)grp * S * 8;
-            // one round: partners s0 and s1 (s1 == s0 for the last of an odd
-            // count), whose records start at tp and tp + dt
-            auto round = [&](const int s0, const int s1, const STORM_CONST_AS float *tp, const int dt)
-                              __attribute__((always_inline)) {
-                const int ps[2] = {s0, s1};
-                float cx[2], cy[2], cz[2], ns[2], m[2], d[2][4];
+            float least = 3.0e38f;
 #pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const int s = ps[u];
-                    cx[u] = s_cen[(s * 3 + 0) * kLanes + lane];
-                    cy[u] = s_cen[(s * 3 + 1) * kLanes + lane];
-                    cz[u] = s_cen[(s * 3 + 2) * kLanes + lane];
-                    ns[u] = fmaf(cx[u], cx[u], fmaf(cy[u], cy[u], cz[u] * cz[u]));
-                    const STORM_CONST_AS float *th = tp + u * dt;
+            for (int k = 0; k < 4; ++k)
 #pragma unroll
-                    for (int k = 0; k < 4; ++k)
-                        d[u][k] = fmaf(cx[u], mx[k], fmaf(cy[u], my[k], fmaf(cz[u], mz[k], nt[k]))) - th[k];
-                    m[u] = fminf(fminf(d[u][0], d[u][1]), fminf(d[u][2], d[u][3])) + ns[u];
+                for (int u = 0; u < 4; ++u) {
+                    const float dx = cs[u][0] - ct[k][0], dy = cs[u][1] - ct[k][1], dz = cs[u][2] - ct[k][2];
+                    d2[k][u] = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+                    least = fminf(least, d2[k][u]);
                 }
-                // the contact distances come with the thresholds (one scalar
-                // load per round), not in the rare branch
-                float rc[2][4];
+            const float r_max = fmaxf(fmaxf(rt[0], rt[1]), fmaxf(rt[2], rt[3])) +
+                                fmaxf(fmaxf(rs[0], rs[1]), fmaxf(rs[2], rs[3]));
+            // (an equal or smaller penetration than 0 changes nothing, so the
+            // rounding of either side's square does not matter)
+            if (__builtin_amdgcn_ballot_w64(least < r_max * r_max * 1.000001f) == 0) continue;
 #pragma unroll
-                for (int u = 0; u < 2; ++u)
+            for (int k = 0; k < 4; ++k)
 #pragma unroll
-                    for (int k = 0; k < 4; ++k) rc[u][k] = tp[u * dt + 4 + k];
-                asm volatile("" : : "s"(rc[0][0]), "s"(rc[0][1]), "s"(rc[0][2]), "s"(rc[0][3]), "s"(rc[1][0]),
-                             "s"(rc[1][1]), "s"(rc[1][2]), "s"(rc[1][3]));
-                if (__builtin_expect(__builtin_amdgcn_ballot_w64(fminf(m[0], m[1]) < 0.0f) != 0, 0)) {
-                    // the partners, then the pairs, that some lane passes
-#pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        if (__builtin_amdgcn_ballot_w64(m[u] < 0.0f) == 0) continue;
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            if (k >= count || __builtin_amdgcn_ballot_w64(d[u][k] + ns[u] < 0.0f) == 0) continue;
-                            const float dx = fmaf(0.5f, mx[k], cx[u]), dy = fmaf(0.5f, my[k], cy[u]),
-                                        dz = fmaf(0.5f, mz[k], cz[u]);
-                            const float pen = rc[u][k] - fast_sqrt(fmaf(dx, dx, fmaf(dy, dy, dz * dz)));
-                            selfpen = fmaxf(selfpen, pen);
-                        }
-                    }
-                }
-            };
-            int sp = s_begin;
-            const STORM_CONST_AS float *tp = tg + 8 * s_begin;
-            for (; sp + 1 < s_end; sp += 2, tp += 16) round(sp, sp + 1, tp, 8);
-            if (sp < s_end) round(sp, sp, tp, 0);
+                for (int u = 0; u < 4; ++u) selfpen = fmaxf(selfpen, (rs[u] + rt[k]) - fast_sqrt(d2[k][u]));
         }
     }
     s_penv[wave * kLanes + lane] = env;
@@ -766,8 +808,9 @@ __global__ __launch_bounds__(W * kLanes) void rollout_kernel(const PlainDev *dev
 // first, and the next item is drawn during the current one: no barrier and no
 // memory round trip of its own stands between two tiles.  256 problems 2.35
 // -> 2.19 ms, 64 x 4096 x 64 with refinement 16.36 -> 16.00 ms.
+// (Four waves per SIMD: two workgroups of 8 waves share a CU.)
 template <int W>
-__global__ __launch_bounds__(W * kLanes) void rollout_batch_kernel(const ProblemDev *__restrict__ probs,
+__global__ __launch_bounds__(W * kLanes) __attribute__((amdgpu_waves_per_eu(4))) void rollout_batch_kernel(const ProblemDev *__restrict__ probs,
                                                                    const int2 *__restrict__ items, int n_items,
                                                                    uint32_t *next, const RobotDev *robot,
                                                                    const float *__restrict__ x0s,
@@ -792,20 +835,22 @@ __global__ __launch_bounds__(W * kLanes) void rollout_batch_kernel(const Problem
     }
 }
 
-// The rows, the capsules of S spheres and the culling records of n_obs
-// obstacles (the 2 W collision partials sit over the 96 frame rows).
-size_t rollout_lds_bytes(int S, int n_obs, bool task = false)
+// The rows, the capsules of S spheres, the records of n_obs obstacles (n_box
+// cuboids among them) and the lists of phase D1 (the 2 W collision partials sit
+// over the 96 frame rows).
+size_t rollout_lds_bytes(int S, int n_obs, int n_box, int n_items, bool task = false)
 {
     return (size_t)(96 + kTerms + rollout_cen_rows(S) + (task ? 2 * kDof : 0)) * kLanes * sizeof(float) +
-           (size_t)(8 * S + n_obs) * sizeof(float4);
+           (size_t)(8 * S + n_obs + 4 * n_box) * sizeof(float4) + (size_t)n_items * sizeof(int2) +
+           (size_t)kFrames * n_obs;
 }
 
 }  // namespace
 
 hipError_t set_rollout_lds_limit()
 {
-    const int plain = (int)rollout_lds_bytes(STORM_MAX_SPHERES, STORM_MAX_OBSTACLES);
-    const int task = (int)rollout_lds_bytes(STORM_MAX_SPHERES, STORM_MAX_OBSTACLES, true);
+    const int plain = (int)rollout_lds_bytes(STORM_MAX_SPHERES, STORM_MAX_OBSTACLES, STORM_MAX_OBSTACLES, kMaxSelfItems);
+    const int task = (int)rollout_lds_bytes(STORM_MAX_SPHERES, STORM_MAX_OBSTACLES, STORM_MAX_OBSTACLES, kMaxSelfItems, true);
     const void *fns[10] = {reinterpret_cast<const void *>(&rollout_kernel<16, false, false>),
                            reinterpret_cast<const void *>(&rollout_kernel<8, false, false>),
                            reinterpret_cast<const void *>(&rollout_kernel<16, false, true>),
@@ -825,10 +870,10 @@ hipError_t set_rollout_lds_limit()
 }
 
 hipError_t launch_rollout_batch(const ProblemDev *probs, const int2 *items, int n_items, uint32_t *next,
-                                const RobotDev *robot, int n_spheres, int max_obs, const float *x0s,
-                                const float *goals, int waves, int grid, hipStream_t stream)
+                                const RobotDev &R, const RobotDev *robot, int max_obs, int max_box,
+                                const float *x0s, const float *goals, int waves, int grid, hipStream_t stream)
 {
-    const size_t lds = rollout_lds_bytes(n_spheres, max_obs);
+    const size_t lds = rollout_lds_bytes(R.n_spheres, max_obs, max_box, R.n_self_items);
     if (waves == 16) {
         hipLaunchKernelGGL(rollout_batch_kernel<16>, dim3((unsigned)grid), dim3(16 * kLanes), lds, stream, probs,
                            items, n_items, next, robot, x0s, goals);
@@ -841,7 +886,7 @@ hipError_t launch_rollout_batch(const ProblemDev *probs, const int2 *items, int 
     return hipGetLastError();
 }
 
-hipError_t launch_rollout(const ProblemDev &P, int n_spheres, const PlainDev *dev, const float *x0, const float *goal,
+hipError_t launch_rollout(const ProblemDev &P, const RobotDev &R, const PlainDev *dev, const float *x0, const float *goal,
                           const float *noise, const StepOut &out, int waves, hipStream_t stream)
 {
     // the task-space form only where it is asked for: the ball term, the
@@ -850,7 +895,7 @@ hipError_t launch_rollout(const ProblemDev &P, int n_spheres, const PlainDev *de
     const bool debug = noise != nullptr || out.u != nullptr || out.q != nullptr || out.v != nullptr ||
                        out.a != nullptr || out.c != nullptr || out.terms != nullptr || out.xd != nullptr ||
                        out.xdd != nullptr;
-    const size_t lds = rollout_lds_bytes(n_spheres, P.n_sph_obs + P.n_box_obs, task);
+    const size_t lds = rollout_lds_bytes(R.n_spheres, P.n_sph_obs + P.n_box_obs, P.n_box_obs, R.n_self_items, task);
     const dim3 grid((unsigned)P.n_tiles);
     if (waves != 16 && waves != 8) return hipErrorInvalidValue;
     auto kernel = waves == 16 ? (task ? (debug ? rollout_kernel<16, true, true> : rollout_kernel<16, true, false>)

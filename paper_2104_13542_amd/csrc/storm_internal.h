@@ -19,6 +19,7 @@ constexpr int kLanes = 64;  // CDNA wavefront width
 // manipulability terms while the others place the body spheres
 constexpr int kPoseWaves = 2;
 constexpr int kMaxH = STORM_MAX_HORIZON;
+constexpr int kMaxSelfItems = 276;  // pairs of at most 24 groups of one body's spheres each
 constexpr int kAdjChunks = 512;  // adjoint workgroups (tile chunks) per problem, at most
 
 // Offsets (in floats) inside the per-problem table block built at init.
@@ -64,9 +65,8 @@ struct ProblemDev {
     float w_ball, ball_g[3], ball_c[2];  // ball term: weight, gravity (world), tray centre (flange x, y)
     const float *tables;    // [kTabSize]
     const float *halton;    // [7][n_halton][H] smoothed Halton standard noise
-    const float4 *sph_obs;  // [n_sph_obs] centre, radius
     const float *box_obs;   // [n_box_obs][16]: M = R^T (9, row-major), t = -R^T c (3), half extents (3), pad
-    const float4 *obs_bound;  // [n_sph_obs + n_box_obs] centre, culling radius (bounding sphere + 1e-4 m)
+    const float4 *obs_bound;  // [n_sph_obs + n_box_obs] centre, radius (of a cuboid: to its corners)
     float *mean;            // [H][7]
     float *sigma2;          // [7], or [H][7] with cov_step
     float *u;               // [7][N][H] controls of the last step
@@ -90,9 +90,8 @@ struct RobotDev {
     int32_t n_spheres, n_pairs, n_self_items, pad0;
     const float4 *sph_local;  // [S] body-frame centre (x, y, z), radius
     const int32_t *sph_body;  // [S] frame index 0..7 the sphere is attached to
-    const float *self_thr;    // [groups][S][8] expanded pair test thresholds (4), contact distances (4)
     const float *body_bound;  // [8][2] per frame: anchor sphere (int bits), what its radius lacks to hold the body's spheres
-    const int32_t *self_items;  // [n_self_items][8] self-collision work items (self_segments)
+    const int32_t *self_items;  // [n_self_items][4] self-collision work items (self_pairs)
 };
 
 // What the plain kernels read of one problem, in device memory.  Kernel
@@ -159,12 +158,12 @@ struct StepOut {
 hipError_t launch_init_tables(const ProblemDev &P, const float *d_dt_raw, const float *d_lim_raw, float acc_stop,
                               float gamma, float w_term, float k_jl, float k_vl, const float *d_sigma_init,
                               const float comb[3], int n_knots, const float *d_obs_raw, int n_obs,
-                              float4 *d_sph_obs, float *d_box_obs,
+                              float *d_box_obs,
                               float4 *d_obs_bound, const float *d_sph_raw, int n_spheres, float4 *d_sph_local,
                               int32_t *d_sph_body, hipStream_t stream);
 // Plain launches take the host's copy of the problem for the launch shape and
 // the device's (PlainDev) for the kernel.
-hipError_t launch_rollout(const ProblemDev &P, int n_spheres, const PlainDev *dev, const float *x0, const float *goal,
+hipError_t launch_rollout(const ProblemDev &P, const RobotDev &R, const PlainDev *dev, const float *x0, const float *goal,
                           const float *noise, const StepOut &out, int waves, hipStream_t stream);
 // Raise the dynamic-LDS limit of the rollout kernels to what the largest
 // sphere model needs (idempotent).
@@ -182,8 +181,8 @@ void pack_selfnet(const float *prm, std::vector<_Float16> &frag, std::vector<flo
 // Many problems: persistent rollout over a (problem, tile) work queue, and one
 // update workgroup per problem (descriptors in device memory).
 hipError_t launch_rollout_batch(const ProblemDev *probs, const int2 *items, int n_items, uint32_t *next,
-                                const RobotDev *robot, int n_spheres, int max_obs, const float *x0s,
-                                const float *goals, int waves, int grid, hipStream_t stream);
+                                const RobotDev &R, const RobotDev *robot, int max_obs, int max_box,
+                                const float *x0s, const float *goals, int waves, int grid, hipStream_t stream);
 hipError_t launch_update_batch(const ProblemDev *probs, int n_problems, float *cmd, int shift, hipStream_t stream);
 // Differentiable form: adjoint + fixed-order reduction (grad, J) per joint;
 // with it > 0 the same launch takes Adam step `it` on the stored mean, and
@@ -203,23 +202,15 @@ hipError_t launch_refine_batch(const ProblemDev *probs, int n_problems, const in
                                float lr, float *cmd, int shift, hipStream_t stream);
 hipError_t launch_fk(const RobotDev &R, const float *q, int n, float *pose, float *manip, hipStream_t stream);
 
-// Self-collision work items of the robot's sphere pairs, eight integers
-// each (the rollout's queue; defined with its layout in the interface unit);
-// returns the pair count.
-// Self-collision groups: the spheres of one body in runs of up to four,
-// (t_first, count), whose partners are the spheres s < s_end on bodies at
-// least two earlier in the chain.
-struct SelfGroup {
-    int t_first, count, s_end;
-};
-std::vector<SelfGroup> self_groups(const storm_robot *robot);
-int self_segments(const storm_robot *robot, std::vector<int> &items);
+// Self-collision work items of the robot: pairs of groups (runs of up to four
+// spheres of one body) on bodies at least two apart, four integers each;
+// returns the number of sphere pairs.
+int self_pairs(const storm_robot *robot, std::vector<int> &items);
 // The sphere of [lo, hi) about whose centre (in the body's frame) the ball
 // that holds all of them is smallest, and that ball's radius.
 int anchor_sphere(const float *spheres, int lo, int hi, double &radius);
 // Two floats per frame, the bodies' bounds of RobotDev::body_bound.
 std::vector<float> body_bounds(const storm_robot *robot);
-std::vector<float> self_thresholds(const storm_robot *robot, double reach);
 
 }  // namespace storm
 
