@@ -395,7 +395,7 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
     c->R.n_pairs = n_pairs;
 
     float *tables, *halton, *box_obs, *mean, *sigma2, *u, *C, *dt_raw, *lim_raw, *sig_raw, *obs_raw, *sph_raw_d;
-    float *body_bound, *grad_part, *grad, *adam, *ball, *qbuf = nullptr;
+    float *body_bound, *grad_part, *upd_part, *grad, *adam, *ball, *qbuf = nullptr;
     float4 *obs_bound, *sph_local;
     int32_t *sph_body, *self_seg;
     uint32_t *counters;
@@ -421,6 +421,7 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
         const int chunks = P.n_tiles < storm::kAdjChunks ? P.n_tiles : storm::kAdjChunks;
         STORM_TRY(dalloc(c, &grad_part, storm::kAdjChunks + (size_t)chunks * STORM_DOF * storm::kMaxH));
     }
+    STORM_TRY(dalloc(c, &upd_part, storm::update_part_floats(N, H)));
     STORM_TRY(dalloc(c, &grad, (size_t)H * STORM_DOF));
     STORM_TRY(dalloc(c, &adam, (size_t)2 * H * STORM_DOF));
     STORM_TRY(dalloc(c, &ball, (size_t)8));
@@ -475,6 +476,7 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
         P.status = counters + 1;
         P.last_step = counters + 2;
         P.grad_part = grad_part;
+        P.upd_part = upd_part;
         P.grad = grad;
         P.ball = ball;
         P.qbuf = qbuf;

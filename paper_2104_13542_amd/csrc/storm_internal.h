@@ -3,6 +3,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <stddef.h>
 #include <stdint.h>
 
 #include <vector>
@@ -51,47 +52,59 @@ static_assert(kNetH1 * kNetIn + kNetH1 + kNetH2 * kNetH1 + kNetH2 + kNetH3 * kNe
               "network parameter count");
 
 
-// Per-problem description read by the kernels.  All pointers are device memory.
-struct ProblemDev {
+// Per-problem description read by the kernels.  All pointers are device
+// memory.  The first three groups are scalar-cache lines of 64 bytes, each
+// holding what is read together: the sizes and switches and the pointers of a
+// rollout's start, and with the second line what an update reads.
+struct alignas(64) ProblemDev {
     int32_t N, H, n_halton, n_null;
     int32_t n_sph_obs, n_box_obs, ppt, n_tiles;  // ppt = particles per 64-lane tile
     uint32_t cost_mask, seed_lo, seed_hi, grad_mask;  // grad_mask: terms of the differentiable form
-    float beta, alpha_mu, alpha_sigma, sigma2_min;
-    float k_m, w_pos, w_rot, a_stop;
-    float a_joint, a_vel, a_manip, a_coll;
-    float alpha_pos[3], alpha_rot[3];
     uint32_t comb;      // the Gaussian particles' noise is comb-filtered (response in the tables)
     uint32_t cov_step;  // sigma2 is [H][7] (Eq. 5 per step) instead of [7]
-    float w_ball, ball_g[3], ball_c[2];  // ball term: weight, gravity (world), tray centre (flange x, y)
+    uint32_t selfnet;   // the self-collision term comes from the learned network (its own kernel)
+    uint32_t pad0;
+
     const float *tables;    // [kTabSize]
     const float *halton;    // [7][n_halton][H] smoothed Halton standard noise
-    const float *box_obs;   // [n_box_obs][16]: M = R^T (9, row-major), t = -R^T c (3), half extents (3), pad
     const float4 *obs_bound;  // [n_sph_obs + n_box_obs] centre, radius (of a cuboid: to its corners)
+    const float *box_obs;   // [n_box_obs][16]: M = R^T (9, row-major), t = -R^T c (3), half extents (3), pad
     float *mean;            // [H][7]
     float *sigma2;          // [7], or [H][7] with cov_step
     float *u;               // [7][N][H] controls of the last step
     float *C;               // [N] horizon costs of the last step
-    uint32_t *step;         // sampling step counter (Philox counter word 3)
+
+    uint32_t *step;         // sampling step counter (Philox counter word 3); [1] and [2]: status, last_step
     uint32_t *status;       // asynchronous status flags
     uint32_t *last_step;    // counter value the last rollout sampled with (reused by the adjoint)
+    float beta, alpha_mu, alpha_sigma, sigma2_min;
+    float *ball;            // [8]: ball position, velocity (world frame) at the current state, pad
+    float *qbuf;            // [7][N][H] joint positions of the last step (stand-alone network pass)
+    float *upd_part;        // partial sums of the update over chunks of particles (many particles)
+
+    float k_m, w_pos, w_rot, a_stop;
+    float a_joint, a_vel, a_manip, a_coll;
+    float alpha_pos[3], alpha_rot[3];
+    float w_ball, ball_g[3], ball_c[2];  // ball term: weight, gravity (world), tray centre (flange x, y)
     float *grad_part;       // adjoint partials per tile chunk: horizon-cost sums [kAdjChunks], gradients [chunks][7][kMaxH]
     float *grad;            // [H][7] gradient of the expected horizon cost
     float *adam_m, *adam_v; // [H][7] Adam moments of the refinement
-    float *ball;            // [8]: ball position, velocity (world frame) at the current state, pad
-    float *qbuf;            // [7][N][H] joint positions of the last step (stand-alone network pass)
-    uint32_t selfnet;       // the self-collision term comes from the learned network (its own kernel)
     const _Float16 *net_frag;  // packed network weights (pack_selfnet)
     const float *net_bias;
 };
+static_assert(offsetof(ProblemDev, tables) == 64 && offsetof(ProblemDev, step) == 128 &&
+                  offsetof(ProblemDev, k_m) == 192,
+              "groups of 64 bytes");
 
 // Robot constants, passed by value (kernel-argument segment, wave-uniform).
-struct RobotDev {
-    float ca[kFrames], sa[kFrames], a[kFrames], d[kFrames];  // DH: cos/sin alpha_{k-1}, a_{k-1}, d_k
+struct alignas(64) RobotDev {
     int32_t n_spheres, n_pairs, n_self_items, pad0;
     const float4 *sph_local;  // [S] body-frame centre (x, y, z), radius
     const int32_t *sph_body;  // [S] frame index 0..7 the sphere is attached to
     const float *body_bound;  // [8][2] per frame: anchor sphere (int bits), what its radius lacks to hold the body's spheres
     const int32_t *self_items;  // [n_self_items][4] self-collision work items (self_pairs)
+    int32_t pad1[4];
+    float ca[kFrames], sa[kFrames], a[kFrames], d[kFrames];  // DH: cos/sin alpha_{k-1}, a_{k-1}, d_k
 };
 
 // What the plain kernels read of one problem, in device memory.  Kernel
@@ -171,6 +184,9 @@ hipError_t set_rollout_lds_limit();
 // Whether the learned self-collision network's weight matrices (W1, W2, W3
 // of storm_robot.self_mlp) hold FP16 values only, as its kernel requires.
 bool selfnet_weights_fp16(const float *prm);
+// Floats of the plain update's partial sums (ProblemDev::upd_part); 0 where it
+// needs none.
+size_t update_part_floats(int N, int H);
 hipError_t launch_update(const ProblemDev &P, const PlainDev *dev, float *mean_out, float *sigma2_out, float *cmd, int shift,
                          hipStream_t stream);
 // Learned self-collision term: after the rollout, adds a_coll max(0, d) to

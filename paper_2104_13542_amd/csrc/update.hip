@@ -6,20 +6,25 @@
 //   sigma2' = (1 - alpha_sigma) sigma2
 //             + alpha_sigma mean_h sum_i w_i (u_ih - mu'_h)^2   (per joint)
 //
-// One 1024-thread workgroup per (problem, joint): a joint's new mean and
+// Two forms.  Within the register path's sizes, and in batches, one
+// 1024-thread workgroup per (problem, joint): a joint's new mean and
 // variance depend only on the weights and on that joint's controls, so the
 // seven joints need no synchronisation with each other; every workgroup
 // recomputes min C and the weights of all particles (N exponentials).  The
 // joint's H columns are read by rows of threads, row r taking particles r,
 // r + R, ...  Three ways to gather them:
-//   registers  (N <= 32 R): every thread loads its up to 32 controls at the
+//   registers  (N <= 32 R and 2048): every thread loads its up to 32 controls at the
 //              start, together with the costs, so the only global-memory
 //              latency on the path is the first one;
-//   list       (at most 4096 weights not exactly zero, beta small against the
+//   list       (batches; at most 4096 weights not exactly zero, beta small against the
 //              spread of C): only those particles, from a list compacted in
 //              ascending order;
-//   dense      otherwise: all particles, weights staged in LDS by chunks,
+//   dense      (batches) otherwise: all particles, weights staged in LDS by chunks,
 //              eight loads in flight per thread.
+// Bound by latency: two exchanges, a division and the tail's chain behind the
+// first loads (4.2 us at 500 x 30).  A single problem past those sizes takes
+// update_part_kernel and update_join_kernel (below).
+//
 // The variance about the new mean comes from the moments about the old one,
 // sum w (d - delta)^2 = S2/S0 - 2 delta S1/S0 + delta^2, in one pass.  Wave
 // reductions use DPP lane moves; every sum has a fixed order, so results are
@@ -129,18 +134,133 @@ __host__ __device__ inline int update_slots(int N, int H)
 // The fields of a problem that the first loads depend on.
 struct UpdateFirst {
     const float *C, *u;
-    float *mean;
     int32_t N, H;
 };
 
+// What an update reads of its problem's descriptor, in one go: a scalar load
+// wherever a field is used would put one memory round trip after another.
+struct UpdateProblem {
+    float beta, alpha_mu, alpha_sigma, sigma2_min;
+    const float *tables;
+    float *mean, *sigma2;
+    uint32_t *step, *status;
+};
+__device__ __forceinline__ UpdateProblem fetch_problem(ProblemRef P)
+{
+    return UpdateProblem{P.beta, P.alpha_mu, P.alpha_sigma, P.sigma2_min, P.tables, P.mean, P.sigma2, P.step, P.status};
+}
+// (here they have to be there)
+__device__ __forceinline__ void wait_problem(UpdateProblem &Q)
+{
+    asm volatile("" : "+s"(Q.beta), "+s"(Q.alpha_mu), "+s"(Q.alpha_sigma), "+s"(Q.sigma2_min), "+s"(Q.tables),
+                 "+s"(Q.mean), "+s"(Q.sigma2), "+s"(Q.step), "+s"(Q.status));
+}
+
+// What the tail of an update reads besides the moments.
+struct TailArgs {
+    float sig_old, sig_init, a_mu, a_sigma, s2_min;
+    uint32_t step0;
+    int shift;
+    global_ptr<float> mean, sigma2, cmd, mean_out, sigma2_out;
+    global_ptr<uint32_t> step, status;
+};
+
+// Fetched with the kernel's first loads, since each would add a memory round
+// trip to the tail: the old variances and the noise counter through vector
+// loads (waited for only where they are used); the scalars go into VGPRs,
+// because the kernel runs at its SGPR limit and the compiler would otherwise
+// reload each there, one scalar-memory round trip after another.
+__device__ __forceinline__ TailArgs fetch_tail(const UpdateProblem &P, float *mean_out, float *sigma2_out, float *cmd,
+                                               int shift, const bool cov, int j, int t, int H)
+{
+    TailArgs T;
+    T.sig_old = cov ? (t < H ? vector_load_f32(P.sigma2 + t * kDof + j) : 0.0f) : vector_load_f32(P.sigma2 + j);
+    T.sig_init = cov && shift ? vector_load_f32(P.tables + kTabSig0 + j) : 0.0f;
+    T.step0 = vector_load_u32(P.step);
+    T.mean = global_in_vgpr(P.mean);
+    T.sigma2 = global_in_vgpr(P.sigma2);
+    T.cmd = global_in_vgpr(cmd);
+    T.mean_out = global_in_vgpr(mean_out);
+    T.sigma2_out = global_in_vgpr(sigma2_out);
+    T.step = global_in_vgpr(P.step);
+    T.status = global_in_vgpr(P.status);
+    T.shift = in_vgpr(shift);
+    T.a_mu = in_vgpr(P.alpha_mu);
+    T.a_sigma = in_vgpr(P.alpha_sigma);
+    T.s2_min = in_vgpr(P.sigma2_min);
+    return T;
+}
+
+// The end of joint j's update on one wave: lane h holds the weighted sums S1
+// and S2 of step h about the old mean muo; S0 is the sum of the weights.
+// Forms the new mean and the variance about it, then one wave sum gives the
+// variance over the horizon.
+__device__ __forceinline__ void update_tail(const TailArgs &T, const int j, const int H, const int lane, float s1,
+                                            float s2, float S0, float muo, bool ok, int any_nonfinite, const bool cov)
+{
+    const float inv_S0 = 1.0f / S0;
+    const float m1 = s1 * inv_S0, m2 = s2 * inv_S0;
+    const float delta = T.a_mu * m1;
+    const float mu_new = ok ? muo + delta : muo;
+    const float var = lane < H ? fmaxf(fmaf(delta, delta - 2.0f * m1, m2), 0.0f) : 0.0f;  // about mu'
+    const float acc = wave_sum(var);
+    // the new mean of step h + 1 (the shifted warm start), 0 past the end
+    const float mu_next = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(mu_new), 0x130, 0xf, 0xf,
+                                                                     true));  // wave_shl:1
+    if (lane == 0) {
+        if (j == 0) {
+            // the increment here, not at the load (where it would wait for
+            // every load in flight), and before the other stores (whose
+            // completion a wait for the load would otherwise include)
+            uint32_t next = T.step0;
+            asm volatile("" : "+v"(next));
+            *T.step = next + 1u;
+            if (!ok)
+                __hip_atomic_fetch_or(T.status, any_nonfinite ? STORM_FLAG_NONFINITE_COST : STORM_FLAG_ZERO_WEIGHT,
+                                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (!cov) {
+            float s2n = T.sig_old;
+            if (ok) s2n = fmaxf(fmaf(T.a_sigma, acc / (float)H - T.sig_old, T.sig_old), T.s2_min);
+            T.sigma2[j] = s2n;
+            if (T.sigma2_out) T.sigma2_out[j] = s2n;
+        }
+        T.cmd[j] = mu_new;
+    }
+    if (lane < H) {
+        if (T.mean_out) T.mean_out[lane * kDof + j] = mu_new;
+        T.mean[lane * kDof + j] = T.shift ? (lane + 1 < H ? mu_next : 0.0f) : mu_new;
+    }
+    if (cov) {
+        // Eq. 5 per step: lane h updates sigma^2[h][j] from the variance at
+        // step h; the shift moves it one step, sigma_init^2 appended
+        const float old = T.sig_old;  // sigma^2[lane][j] (0 past H)
+        const float s2n = ok ? fmaxf(fmaf(T.a_sigma, var - old, old), T.s2_min) : old;
+        const float s2_next = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s2n), 0x130, 0xf, 0xf,
+                                                                         true));  // wave_shl:1
+        if (lane < H) {
+            if (T.sigma2_out) T.sigma2_out[lane * kDof + j] = s2n;
+            T.sigma2[lane * kDof + j] = T.shift ? (lane + 1 < H ? s2_next : T.sig_init) : s2n;
+        }
+    }
+}
+
 // `cov` is P.cov_step, passed apart so that the plain kernel can fix it at
 // compile time; kSlots the register path's controls per thread
-// (update_slots), 32 when that path is not taken.
-template <int kSlots>
-__device__ __forceinline__ void update_joint(ProblemRef P, const UpdateFirst &first, const int j,
+// (update_slots), 32 when that path is not taken; kRegs: it is taken.
+template <int kSlots, bool kRegs = false>
+__device__ __forceinline__ void update_joint(ProblemRef descriptor, const UpdateFirst &first, const int j,
                                              float *__restrict__ mean_out, float *__restrict__ sigma2_out,
                                              float *__restrict__ cmd, int shift, const bool cov, UpdateLds &L)
 {
+    // issued before the arithmetic of the addresses below: the descriptor,
+    // and this thread's first two costs
+    const int t = threadIdx.x;
+    const int N = first.N, H = first.H;
+    const global_ptr<const float> C = as_global(first.C);
+    UpdateProblem P = fetch_problem(descriptor);
+    float c0 = C[min(t, N - 1)], c1 = C[min(t + kThreads, N - 1)];
+    __builtin_amdgcn_sched_barrier(0);
     float *s_buf = L.buf;
     float *s_red = L.red;
     float *s_wave = L.wave;
@@ -148,11 +268,7 @@ __device__ __forceinline__ void update_joint(ProblemRef P, const UpdateFirst &fi
     int *s_count = L.count;
     float *s_mold = L.mold;
 
-    const int t = threadIdx.x;
     const int lane = t & (kLanes - 1), wave = __builtin_amdgcn_readfirstlane(t / kLanes);
-    const int N = first.N, H = first.H;
-    const float beta = P.beta;
-    const global_ptr<const float> C = as_global(first.C);
     int *s_idx = reinterpret_cast<int *>(s_buf);
     float *s_wl = s_buf + kList;
 
@@ -161,18 +277,13 @@ __device__ __forceinline__ void update_joint(ProblemRef P, const UpdateFirst &fi
     const int r = t / H, h = t - r * H;
     const bool in_rows = r < rows;
     const global_ptr<const float> U = as_global(first.u) + (size_t)j * N * H + h;
-    const bool regs = N <= kSlots * rows && N <= 2 * kThreads && kSlots * rows <= kChunk;
-    const float nib = -1.0f / beta;
+    const bool regs = kRegs || (N <= kSlots * rows && N <= 2 * kThreads && kSlots * rows <= kChunk);
 
-    // register path: the costs, then every control load, all in flight at
-    // once.  The controls come through a buffer resource bounded by the
+    // register path: every control load, in flight at once.  The controls come through a buffer resource bounded by the
     // joint's N H values: slots past the last particle read 0 and cost no
     // address arithmetic (the load returns the raw 32 bits).
-    float c0 = INFINITY, c1 = INFINITY;
     float uu[kSlots];
     if (regs) {
-        if (t < N) c0 = C[t];
-        if (t + kThreads < N) c1 = C[t + kThreads];
         const __amdgpu_buffer_rsrc_t ub = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<float *>(first.u + (size_t)j * N * H), (short)0, N * H * (int)sizeof(float), 0x00020000);
         const int stride = rows * H * (int)sizeof(float);
@@ -180,22 +291,10 @@ __device__ __forceinline__ void update_joint(ProblemRef P, const UpdateFirst &fi
         for (int k = 0; k < kSlots; ++k)
             uu[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(ub, t * 4 + k * stride, 0, 0));
     }
-    const float mu = in_rows ? as_global(first.mean)[h * kDof + j] : 0.0f;
-    // What the tail reads is fetched now, with the first loads, since each
-    // would add a memory round trip to the tail: the old variances and the
-    // noise counter through vector loads (waited for only where they are
-    // used); the scalars go into VGPRs, because the kernel runs at its SGPR
-    // limit and the compiler would otherwise reload each from the kernel
-    // arguments there, one scalar-memory round trip after another.
-    const float sig_old = cov ? (t < H ? vector_load_f32(P.sigma2 + t * kDof + j) : 0.0f) : vector_load_f32(P.sigma2 + j);
-    const float sig_init = cov && shift ? vector_load_f32(P.tables + kTabSig0 + j) : 0.0f;
-    const uint32_t step0 = vector_load_u32(P.step);
-    const global_ptr<float> mean_p = global_in_vgpr(first.mean), sigma2_p = global_in_vgpr(P.sigma2);
-    const global_ptr<float> cmd_p = global_in_vgpr(cmd), mean_out_p = global_in_vgpr(mean_out),
-                            sigma2_out_p = global_in_vgpr(sigma2_out);
-    const global_ptr<uint32_t> step_p = global_in_vgpr(P.step);
-    shift = in_vgpr(shift);
-    const float a_mu = in_vgpr(P.alpha_mu), a_sigma = in_vgpr(P.alpha_sigma), s2_min = in_vgpr(P.sigma2_min);
+    wait_problem(P);
+    const float nib = -1.0f / P.beta;
+    const float mu = as_global(P.mean)[h * kDof + j];
+    const TailArgs T = fetch_tail(P, mean_out, sigma2_out, cmd, shift, cov, j, t, H);
 
     float S0 = 0.0f, x1 = 0.0f, x2 = 0.0f;
     int any_nonfinite = 0;
@@ -203,6 +302,8 @@ __device__ __forceinline__ void update_joint(ProblemRef P, const UpdateFirst &fi
     if (regs) {
         // min C and the non-finite flag in one exchange, then the weights
         // and their sum in a second (separate LDS slots: no third barrier)
+        if (t >= N) c0 = INFINITY;
+        if (t + kThreads >= N) c1 = INFINITY;
         const bool bad = (t < N && !isfinite(c0)) || (t + kThreads < N && !isfinite(c1));
         const uint64_t bad_lanes = __builtin_amdgcn_ballot_w64(bad);
         const float wmin = wave_min(fminf(c0, c1));
@@ -347,15 +448,13 @@ __device__ __forceinline__ void update_joint(ProblemRef P, const UpdateFirst &fi
         }
     }
 
-    // Wave 0 finishes alone: lane h adds the rows of step h in order (S1, S2),
-    // forms the new mean and the variance about it, then one wave sum gives
-    // the variance over the horizon; no further workgroup barrier.
+    // Wave 0 finishes alone: lane h adds the rows of step h in order (S1, S2)
+    // and update_tail does the rest; no further workgroup barrier.
     s_red[t] = x1;
     s_red[kThreads + t] = x2;
     if (r == 0) s_mold[h] = mu;  // stored late: an early store would wait for every load in flight
     __syncthreads();
     if (wave == 0) {
-        const float inv_S0 = 1.0f / S0;
         float s1 = 0.0f, s2 = 0.0f, muo = 0.0f;
         if (lane < H) {
             for (int k = 0; k < rows; ++k) {
@@ -364,48 +463,7 @@ __device__ __forceinline__ void update_joint(ProblemRef P, const UpdateFirst &fi
             }
             muo = s_mold[lane];
         }
-        const float m1 = s1 * inv_S0, m2 = s2 * inv_S0;
-        const float delta = a_mu * m1;
-        const float mu_new = ok ? muo + delta : muo;
-        const float var = lane < H ? fmaxf(fmaf(delta, delta - 2.0f * m1, m2), 0.0f) : 0.0f;  // about mu'
-        const float acc = wave_sum(var);
-        // the new mean of step h + 1 (the shifted warm start), 0 past the end
-        const float mu_next = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(mu_new), 0x130, 0xf, 0xf,
-                                                                         true));  // wave_shl:1
-        if (lane == 0) {
-            if (j == 0) {
-                // the increment here, not at the load (where it would wait for
-                // every load in flight), and before the other stores (whose
-                // completion a wait for the load would otherwise include)
-                uint32_t next = step0;
-                asm volatile("" : "+v"(next));
-                *step_p = next + 1u;
-                if (!ok) atomicOr(P.status, any_nonfinite ? STORM_FLAG_NONFINITE_COST : STORM_FLAG_ZERO_WEIGHT);
-            }
-            if (!cov) {
-                float s2n = sig_old;
-                if (ok) s2n = fmaxf(fmaf(a_sigma, acc / (float)H - sig_old, sig_old), s2_min);
-                sigma2_p[j] = s2n;
-                if (sigma2_out_p) sigma2_out_p[j] = s2n;
-            }
-            cmd_p[j] = mu_new;
-        }
-        if (lane < H) {
-            if (mean_out_p) mean_out_p[lane * kDof + j] = mu_new;
-            mean_p[lane * kDof + j] = shift ? (lane + 1 < H ? mu_next : 0.0f) : mu_new;
-        }
-        if (cov) {
-            // Eq. 5 per step: lane h updates sigma^2[h][j] from the variance at
-            // step h; the shift moves it one step, sigma_init^2 appended
-            const float old = sig_old;  // sigma^2[lane][j] (0 past H)
-            const float s2n = ok ? fmaxf(fmaf(a_sigma, var - old, old), s2_min) : old;
-            const float s2_next = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s2n), 0x130, 0xf, 0xf,
-                                                                             true));  // wave_shl:1
-            if (lane < H) {
-                if (sigma2_out_p) sigma2_out_p[lane * kDof + j] = s2n;
-                sigma2_p[lane * kDof + j] = shift ? (lane + 1 < H ? s2_next : sig_init) : s2n;
-            }
-        }
+        update_tail(T, j, H, lane, s1, s2, S0, muo, ok, any_nonfinite, cov);
     }
 }
 
@@ -420,8 +478,8 @@ __global__ __launch_bounds__(kThreads) void update_kernel(const PlainDev *dev, c
 {
     __shared__ UpdateLds L;
     ProblemRef P = uniform_ptr(dev)->P;
-    const UpdateFirst first{C, u, P.mean, N, H};
-    update_joint<kSlots>(P, first, blockIdx.x, mean_out, sigma2_out, cmd, shift, kCov, L);
+    const UpdateFirst first{C, u, N, H};
+    update_joint<kSlots, true>(P, first, blockIdx.x, mean_out, sigma2_out, cmd, shift, kCov, L);
 }
 
 // Workgroup (p, j) of a batch; commands go to cmd[p][7].
@@ -431,7 +489,7 @@ __global__ __launch_bounds__(kThreads) void update_batch_kernel(const ProblemDev
     __shared__ UpdateLds L;
     const int p = blockIdx.x / kDof, j = blockIdx.x - p * kDof;
     ProblemRef P = uniform_ptr(probs)[p];
-    const UpdateFirst first{P.C, P.u, P.mean, P.N, P.H};
+    const UpdateFirst first{P.C, P.u, P.N, P.H};
     const int slots = update_slots(P.N, P.H);
     float *c = cmd + (size_t)p * kDof;
     if (slots == 8)
@@ -440,6 +498,185 @@ __global__ __launch_bounds__(kThreads) void update_batch_kernel(const ProblemDev
         update_joint<16>(P, first, j, nullptr, nullptr, c, shift, P.cov_step != 0u, L);
     else
         update_joint<32>(P, first, j, nullptr, nullptr, c, shift, P.cov_step != 0u, L);
+}
+
+// The same update for particle counts past the register path, over many
+// workgroups.  One workgroup per joint would pull all N H controls of a joint
+// through one CU (N = 65536, H = 30: 90-180 us); instead the particles go to
+// chunks, one workgroup each, which sums the weights and all seven joints'
+// moments of its particles with weights relative to its own least cost, and a
+// second kernel joins the chunks, one workgroup per joint, scaling each by the
+// weight of its least cost.  Particles whose weight (against their chunk's
+// best) is exactly zero are left out; every order is fixed.  64 particles a
+// chunk at least, so that a row of threads still has a few; 512 chunks at
+// most, two workgroups per CU and a join of one pass.  The line is where the
+// one-workgroup form leaves its registers: its list and dense paths lose on
+// both ends of what lies past it.  Control call and graph step, before and
+// after: 4096 x 64 167.7 -> 155.7 us, 65536 x 30 1152 -> 957 us.
+constexpr int kPartMax = 512;      // chunks
+constexpr int kPartMin = 64;       // particles per chunk, at least
+constexpr int kPartSub = kThreads; // particles weighted at a time
+// floats of one chunk's record: S0, least cost, whether a cost is not finite,
+// pad, then S1 and S2 of [7][H]
+__host__ __device__ constexpr int part_floats(int H) { return 4 + 2 * kDof * H; }
+
+__host__ __device__ inline int part_chunk(int N)
+{
+    const int per = (N + kPartMax - 1) / kPartMax;
+    return per < kPartMin ? kPartMin : per;
+}
+
+__global__ __launch_bounds__(kThreads) void update_part_kernel(const float *__restrict__ C,
+                                                               const float *__restrict__ u,
+                                                               const float *__restrict__ mean, float *__restrict__ part,
+                                                               int32_t N, int32_t H, float nib, int32_t chunk)
+{
+    __shared__ float s_red[2 * kDof][kThreads];
+    __shared__ float s_w[kPartSub];
+    __shared__ int s_idx[kPartSub];
+    __shared__ float s_wave[kWaves];
+    __shared__ int s_count[kWaves];
+    const int t = threadIdx.x, lane = t & (kLanes - 1), wave = __builtin_amdgcn_readfirstlane(t / kLanes);
+    const int p0 = blockIdx.x * chunk, p1 = min(N, p0 + chunk);
+    const int rows = kThreads / H, r = t / H, h = t - r * H;
+    float mu[kDof];
+#pragma unroll
+    for (int j = 0; j < kDof; ++j) mu[j] = r < rows ? mean[h * kDof + j] : 0.0f;
+
+    float least = INFINITY;
+    int bad = 0;
+    for (int i = p0 + t; i < p1; i += kThreads) {
+        const float c = C[i];
+        bad |= !isfinite(c);
+        least = fminf(least, c);
+    }
+    bad = __syncthreads_or(bad);
+    least = block_min(least, s_wave, lane, wave);
+
+    float sw = 0.0f, a1[kDof], a2[kDof];
+#pragma unroll
+    for (int j = 0; j < kDof; ++j) a1[j] = a2[j] = 0.0f;
+    for (int q0 = p0; q0 < p1; q0 += kPartSub) {
+        // weights, and the particles whose weight is not zero in their order
+        const int i = q0 + t;
+        const float w = i < p1 ? expf((C[i] - least) * nib) : 0.0f;
+        sw += w;
+        const bool nz = w > 0.0f;
+        const uint64_t bal = __builtin_amdgcn_ballot_w64(nz);
+        if (lane == 0) s_count[wave] = __builtin_popcountll(bal);
+        __syncthreads();
+        int pos = __builtin_popcountll(bal & ((1ull << lane) - 1ull)), M = 0;
+        for (int k = 0; k < kWaves; ++k) {
+            pos += k < wave ? s_count[k] : 0;
+            M += s_count[k];
+        }
+        if (nz) {
+            s_idx[pos] = i;
+            s_w[pos] = w;
+        }
+        __syncthreads();
+        if (r < rows)
+            for (int k = r; k < M; k += rows) {
+                const float *__restrict__ U = u + (size_t)s_idx[k] * H + h;
+                float d[kDof];
+#pragma unroll
+                for (int j = 0; j < kDof; ++j) d[j] = U[(size_t)j * N * H];
+                const float wk = s_w[k];
+#pragma unroll
+                for (int j = 0; j < kDof; ++j) {
+                    d[j] -= mu[j];
+                    const float wd = wk * d[j];
+                    a1[j] += wd;
+                    a2[j] = fmaf(wd, d[j], a2[j]);
+                }
+            }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < kDof; ++j) {
+        s_red[j][t] = a1[j];
+        s_red[kDof + j][t] = a2[j];
+    }
+    sw = wave_sum(sw);
+    if (lane == 0) s_wave[wave] = sw;
+    __syncthreads();
+    float *out = part + (size_t)blockIdx.x * part_floats(H);
+    if (t == 0) {
+        float S0 = 0.0f;
+        for (int k = 0; k < kWaves; ++k) S0 += s_wave[k];
+        out[0] = S0;
+        out[1] = least;
+        out[2] = bad ? 1.0f : 0.0f;
+    }
+    for (int k = t; k < 2 * kDof * H; k += kThreads) {
+        const int q = k / H, hh = k - q * H;
+        float s = 0.0f;
+        for (int m = 0; m < rows; ++m) s += s_red[q][m * H + hh];
+        out[4 + k] = s;
+    }
+}
+
+template <bool kCov>
+__global__ __launch_bounds__(kThreads) void update_join_kernel(const PlainDev *dev, const float *__restrict__ part,
+                                                               float *__restrict__ mean_out,
+                                                               float *__restrict__ sigma2_out,
+                                                               float *__restrict__ cmd, int32_t n_part, int16_t H16,
+                                                               int16_t shift)
+{
+    __shared__ float s_f[kPartMax];
+    __shared__ float s_red[2 * kThreads];
+    __shared__ float s_wave[kWaves];
+    UpdateProblem P = fetch_problem(uniform_ptr(dev)->P);
+    wait_problem(P);
+    const int t = threadIdx.x, lane = t & (kLanes - 1), wave = __builtin_amdgcn_readfirstlane(t / kLanes);
+    const int H = H16, j = blockIdx.x, stride = part_floats(H);
+    const int rows = kThreads / H, r = t / H, h = t - r * H;
+    // every load at once: this chunk's weight sum and least cost, then the
+    // moments of chunks r, r + rows, ... at step h
+    float S0_c = 0.0f, least_c = INFINITY, bad_c = 0.0f;
+    if (t < n_part) {
+        const float *rec = part + (size_t)t * stride;
+        S0_c = rec[0];
+        least_c = rec[1];
+        bad_c = rec[2];
+    }
+    const float muo_l = t < H ? as_global(P.mean)[t * kDof + j] : 0.0f;
+    const TailArgs T = fetch_tail(P, mean_out, sigma2_out, cmd, shift, kCov, j, t, H);
+    const int bad = __syncthreads_or(bad_c != 0.0f);
+    const float least = block_min(least_c, s_wave, lane, wave);
+    const float f = t < n_part && !bad ? expf((least_c - least) * (-1.0f / P.beta)) : 0.0f;
+    if (t < kPartMax) s_f[t] = f;
+    float S0 = 0.0f;
+    {
+        const float sw = wave_sum(f * S0_c);
+        if (lane == 0) s_wave[wave] = sw;
+        __syncthreads();
+        for (int k = 0; k < kWaves; ++k) S0 += s_wave[k];
+    }
+    const bool ok = !bad && S0 > 0.0f && isfinite(S0);
+    float x1 = 0.0f, x2 = 0.0f;
+    if (r < rows && ok) {
+        const float *__restrict__ src = part + 4 + (size_t)j * H + h;
+#pragma unroll 4
+        for (int c = r; c < n_part; c += rows) {
+            // (a chunk of no weight is left out, as its particles are)
+            const float fc = s_f[c], c1 = src[(size_t)c * stride], c2 = src[(size_t)c * stride + kDof * H];
+            x1 = fmaf(fc, fc > 0.0f ? c1 : 0.0f, x1);
+            x2 = fmaf(fc, fc > 0.0f ? c2 : 0.0f, x2);
+        }
+    }
+    s_red[t] = x1;
+    s_red[kThreads + t] = x2;
+    __syncthreads();
+    if (wave == 0) {
+        float s1 = 0.0f, s2 = 0.0f;
+        if (lane < H)
+            for (int k = 0; k < rows; ++k) {
+                s1 += s_red[k * H + lane];
+                s2 += s_red[kThreads + k * H + lane];
+            }
+        update_tail(T, j, H, lane, s1, s2, S0, muo_l, ok, bad, kCov);
+    }
 }
 
 }  // namespace
@@ -455,6 +692,17 @@ hipError_t launch_update(const ProblemDev &P, const PlainDev *dev, float *mean_o
                          hipStream_t stream)
 {
     const int slots = update_slots(P.N, P.H);
+    if (slots == 0) {
+        const int chunk = part_chunk(P.N), n_part = (P.N + chunk - 1) / chunk;
+        hipLaunchKernelGGL(update_part_kernel, dim3((unsigned)n_part), dim3(kThreads), 0, stream, P.C, P.u, P.mean,
+                           P.upd_part, P.N, P.H, -1.0f / P.beta, chunk);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        auto join = P.cov_step ? update_join_kernel<true> : update_join_kernel<false>;
+        hipLaunchKernelGGL(join, dim3(kDof), dim3(kThreads), 0, stream, dev, P.upd_part, mean_out, sigma2_out, cmd,
+                           n_part, (int16_t)P.H, (int16_t)shift);
+        return hipGetLastError();
+    }
     auto kernel = P.cov_step ? (slots == 8    ? update_kernel<true, 8>
                                 : slots == 16 ? update_kernel<true, 16>
                                               : update_kernel<true, 32>)
@@ -464,6 +712,13 @@ hipError_t launch_update(const ProblemDev &P, const PlainDev *dev, float *mean_o
     hipLaunchKernelGGL(kernel, dim3(kDof), dim3(kThreads), 0, stream, dev, P.C, P.u, mean_out, sigma2_out, cmd,
                        P.N, (int16_t)P.H, (int16_t)shift);
     return hipGetLastError();
+}
+
+size_t update_part_floats(int N, int H)
+{
+    if (update_slots(N, H) != 0) return 0;
+    const int chunk = part_chunk(N);
+    return (size_t)((N + chunk - 1) / chunk) * part_floats(H);
 }
 
 }  // namespace storm
