@@ -80,12 +80,37 @@ __device__ __forceinline__ bool capsule_hits(const float4 a, const float4 b, flo
     return fmaf(ex, ex, fmaf(ey, ey, ez * ez)) < reach * fabsf(reach);
 }
 
-// The fields of a problem that the first loads of a tile depend on.
+// What the start of a tile reads of the problem and the robot, fetched in one
+// go: a scalar load wherever a field is used would put one memory round trip
+// after another before the first work.
 struct TileFirst {
     uint32_t *step;
-    const float *mean, *halton;
-    int32_t N, H, n_halton, n_null;
+    const float *mean;
+    int32_t N, H, n_halton, n_null, n_sph_obs, n_box_obs, ppt, n_spheres, n_self_items;
+    uint32_t cost_mask, seed_lo, seed_hi, comb, cov_step;
+    const float *tables, *halton;
+    const float4 *obs_bound;
+    const float *box_obs;
+    float *sigma2;
+    const float4 *sph_local;
+    const int32_t *sph_body;
+    const float *body_bound;
+    const int32_t *self_items;
 };
+// (step, mean, N and H: known to the plain kernel from its arguments)
+__device__ __forceinline__ TileFirst fetch_first(ProblemRef P, RobotRef R, uint32_t *step, const float *mean,
+                                                 int32_t N, int32_t H)
+{
+    TileFirst F{step,         mean,          N,           H,           P.n_halton,  P.n_null,     P.n_sph_obs,
+                P.n_box_obs,  P.ppt,         R.n_spheres, R.n_self_items, P.cost_mask, P.seed_lo, P.seed_hi,
+                P.comb,       P.cov_step,    P.tables,    P.halton,    P.obs_bound, P.box_obs,    P.sigma2,
+                R.sph_local,  R.sph_body,    R.body_bound, R.self_items};
+    asm volatile("" : "+s"(F.n_halton), "+s"(F.n_null), "+s"(F.n_sph_obs), "+s"(F.n_box_obs), "+s"(F.ppt),
+                 "+s"(F.n_spheres), "+s"(F.n_self_items), "+s"(F.cost_mask), "+s"(F.seed_lo), "+s"(F.seed_hi),
+                 "+s"(F.comb), "+s"(F.cov_step), "+s"(F.tables), "+s"(F.halton), "+s"(F.obs_bound), "+s"(F.box_obs),
+                 "+s"(F.sigma2), "+s"(F.sph_local), "+s"(F.sph_body), "+s"(F.body_bound), "+s"(F.self_items));
+    return F;
+}
 
 // LDS copy of the goal (R row-major, p) and the cost weights, by index.
 constexpr int kParArot = 12, kParApos = 15, kParW = 18, kParKm = 25, kParCount = 26;
@@ -206,7 +231,7 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
     //   velocities, accelerations [14]  A1 - C (task-space form only)
     // then the capsules of the spheres [S][4 rows][8] (C - D2), the records of
     // the obstacles (A0 - D2) and the lists of phase D1 (D1 - D2).
-    const int S = R.n_spheres;
+    const int S = first.n_spheres;
     float *s_fr = smem;                        // [8 frames][12][64]: R row-major, p
     float *s_penv = s_fr;                      // [W][64] (over the frames, after phase C)
     float *s_pself = s_penv + W * kLanes;      // [W][64]
@@ -218,18 +243,18 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
     float *s_v = s_cen + rollout_cen_rows(S) * kLanes;  // [7][64] (task-space form only)
     float *s_acc = s_v + kDof * kLanes;                  // [7][64]
     float4 *s_cap = reinterpret_cast<float4 *>(s_v + (kTask ? 2 * kDof * kLanes : 0));  // [S][4][2]
-    const uint32_t mask = P.cost_mask;
-    const int nobs = (mask & STORM_COST_ENV) && S > 0 ? P.n_sph_obs + P.n_box_obs : 0;
-    const int n_items = (mask & STORM_COST_SELF) ? R.n_self_items : 0;
+    const uint32_t mask = first.cost_mask;
+    const int nobs = (mask & STORM_COST_ENV) && S > 0 ? first.n_sph_obs + first.n_box_obs : 0;
+    const int n_items = (mask & STORM_COST_SELF) ? first.n_self_items : 0;
     float4 *s_bound = s_cap + 8 * S;             // [obstacles] centre, radius (of a cuboid: to its corners)
     float4 *s_box = s_bound + nobs;              // [cuboids][4] their records
-    int2 *s_self = reinterpret_cast<int2 *>(s_box + (nobs > 0 ? 4 * P.n_box_obs : 0));  // [items] those that stay: runs
+    int2 *s_self = reinterpret_cast<int2 *>(s_box + (nobs > 0 ? 4 * first.n_box_obs : 0));  // [items] those that stay: runs
                                                                       // and anchors, and the runs' joint reach
     uint8_t *s_near = reinterpret_cast<uint8_t *>(s_self + n_items);  // [8][obstacles] obstacles near each body
 
     const int lane = threadIdx.x & (kLanes - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int N = first.N, H = first.H, ppt = P.ppt;
+    const int N = first.N, H = first.H, ppt = first.ppt;
     // the particle and step of this lane (lane / H by a reciprocal: exact, as
     // the quotients of lane + 1/2 stay 1/128 away from the integers)
     const int pl = (int)(((float)lane + 0.5f) * __builtin_amdgcn_rcpf((float)H));
@@ -244,7 +269,7 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
     const int pos = pl < ppt ? h * ppt + pl : lane;
     const int src = min(lane, n_pts - 1);
     const bool live = valid && i < N - first.n_null;  // sampled (non-null) particle
-    const global_ptr<const float> tab = as_global(P.tables);
+    const global_ptr<const float> tab = as_global(first.tables);
 
     // Per-joint inputs of phase A1, loaded up front so that their latency
     // overlaps the noise generation (vector loads throughout, so that the
@@ -253,30 +278,44 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
     float mu_j = 0.0f, sig2_j = 0.0f, dt_h = 0.0f, vs_h = 0.0f, q0_j = 0.0f, v0_j = 0.0f;
     if (wave < kDof) {
         if (live) mu_j = as_global(first.mean)[h * kDof + wave];
-        sig2_j = P.cov_step ? as_global(P.sigma2)[h * kDof + wave] : vector_load_f32(P.sigma2 + wave);
+        sig2_j = first.cov_step ? as_global(first.sigma2)[h * kDof + wave] : vector_load_f32(first.sigma2 + wave);
         dt_h = tab[kTabDt + h];
         vs_h = tab[kTabVstop + h];
         q0_j = vector_load_f32(x0 + wave);
         v0_j = vector_load_f32(x0 + kDof + wave);
     }
-    // the obstacles' records, by the waves that draw no noise
-    if (wave >= 4 && nobs > 0) {
-        const int n_rec = nobs + 4 * P.n_box_obs;
-        for (int k = (int)threadIdx.x - 4 * kLanes; k < n_rec; k += (W - 4) * kLanes)
-            s_bound[k] = load_float4(k < nobs ? as_global(P.obs_bound) + k
-                                              : as_global(reinterpret_cast<const float4 *>(P.box_obs)) + (k - nobs));
+    // The records that the waves that draw no noise stage in LDS, the first of
+    // each thread: obstacles (their balls, then the cuboids), body spheres with
+    // their frames.  Loads from here on are unconditional, at an index that
+    // exists, and all in flight before the first is waited for.
+    const int n_obs_rec = nobs > 0 ? nobs + 4 * first.n_box_obs : 0;
+    const int n_rec = n_obs_rec + ((mask & (STORM_COST_SELF | STORM_COST_ENV)) ? S : 0);
+    const global_ptr<const float4> g_bound = as_global(first.obs_bound), g_sph = as_global(first.sph_local),
+                                   g_box = as_global(reinterpret_cast<const float4 *>(first.box_obs));
+    auto record = [=](int k) __attribute__((always_inline)) {
+        global_ptr<const float4> r = g_sph + max(min(k - n_obs_rec, S - 1), 0);
+        if (k < n_obs_rec) r = g_box + (k - nobs);
+        if (k < nobs) r = g_bound + k;
+        return r;
+    };
+    const int k_first = (int)threadIdx.x - 4 * kLanes;
+    float4 rec = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    int rec_frame = 0;
+    if (wave >= 4) {
+        rec = load_float4(record(k_first));
+        rec_frame = as_global(first.sph_body)[max(min(k_first - n_obs_rec, S - 1), 0)];
     }
-    // phase D1's bound of the body that this lane tests (as well early)
+    // phase D1's bound of the body that this lane tests, and its first
+    // self-collision item (last wave first)
     const int body8 = lane & (kFrames - 1);
-    float anchor = 0.0f, widen = 0.0f;
-    if (2 * wave < nobs) {
-        anchor = as_global(R.body_bound)[2 * body8];
-        widen = as_global(R.body_bound)[2 * body8 + 1];
-    }
-    // the goal and the cost weights that phases C and E read, staged in
-    // LDS by the last wave while the noise is drawn (read where they are
-    // used, as scalar loads, they would add a memory round trip to those
-    // serial phases)
+    const float anchor = as_global(first.body_bound)[2 * body8], widen = as_global(first.body_bound)[2 * body8 + 1];
+    const int g_first = 16 * (W - 1 - wave) + (lane & 15);
+    const float4 item_bits = load_float4(as_global(reinterpret_cast<const float4 *>(first.self_items)) +
+                                         max(min(g_first, n_items - 1), 0));
+    int item[4] = {__float_as_int(item_bits.x), __float_as_int(item_bits.y), __float_as_int(item_bits.z),
+                   __float_as_int(item_bits.w)};
+    // the goal and the cost weights that phases C and E read, staged by the
+    // last wave
     __shared__ float s_par2[2][kParCount];  // (by parity: the costs of a tile are summed during the next one's noise)
     float *s_par = s_par2[queue.parity];
     __shared__ int s_self_n, s_self_next;  // self-collision items that stay (phase D1), and the queue's head (D2)
@@ -284,16 +323,6 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
     __shared__ uint8_t s_body[STORM_MAX_SPHERES];  // frame
     __shared__ int s_near_n[kFrames];  // obstacles near each body (phase D1)
     if (wave == W - 1 && lane == kParCount) s_self_n = s_self_next = 0;
-    if (wave == W - 3 && lane < S && (mask & (STORM_COST_SELF | STORM_COST_ENV))) {
-        s_sph[lane] = load_float4(as_global(R.sph_local) + lane);
-        s_body[lane] = (uint8_t)as_global(R.sph_body)[lane];
-    }
-    // phase D1's first self-collision item of this lane (last wave first)
-    const int g_first = 16 * (W - 1 - wave) + (lane & 15);
-    int item[4] = {0, 0, 0, 0};
-    if (g_first < n_items)
-#pragma unroll
-        for (int k = 0; k < 4; ++k) item[k] = as_global(R.self_items)[4 * g_first + k];
     if (wave == W - 2 && lane < kFrames) s_near_n[lane] = 0;
     // ---- A0: standard noise ------------------------------------------------
     // waves 0-3, one per SIMD: wave w makes the normal pair w / 2 of Philox
@@ -305,13 +334,30 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
         const int j0 = 4 * k + 2 * half;
         float e[2] = {0.0f, 0.0f};
         const uint32_t counter = *as_global(first.step);
-        if (live) standard_noise2(first, P.seed_lo, P.seed_hi, noise, k, half, i, h, counter, e);
+        if (live) standard_noise2(first, first.seed_lo, first.seed_hi, noise, k, half, i, h, counter, e);
         s_eps[j0 * kLanes + lane] = e[0];
         s_eps[(j0 + 1) * kLanes + lane] = e[1];
-        if (tile == 0 && threadIdx.x == 0) *as_global(P.last_step) = counter;
-    } else if (wave == W - 1 && lane < kParCount) {
-        const float g = goal[lane < 12 ? lane : 0], w = tab[kTabPar + (lane < 12 ? 0 : lane - 12)];
-        s_par[lane] = lane < 12 ? g : w;
+        // (the counter block: step, status, last step)
+        if (tile == 0 && threadIdx.x == 0) as_global(first.step)[2] = counter;
+    } else {
+        float g = 0.0f, w = 0.0f;
+        if (wave == W - 1) {
+            g = goal[lane < 12 ? lane : 0];
+            w = tab[kTabPar + (lane < 12 ? 0 : min(lane - 12, kParCount - 13))];
+        }
+        for (int k = k_first; k < n_rec; k += (W - 4) * kLanes) {
+            if (k != k_first) {
+                rec = load_float4(record(k));
+                rec_frame = as_global(first.sph_body)[max(min(k - n_obs_rec, S - 1), 0)];
+            }
+            if (k < n_obs_rec) {
+                s_bound[k] = rec;
+            } else {
+                s_sph[k - n_obs_rec] = rec;
+                s_body[k - n_obs_rec] = (uint8_t)rec_frame;
+            }
+        }
+        if (wave == W - 1 && lane < kParCount) s_par[lane] = lane < 12 ? g : w;
     }
     __syncthreads();
 
@@ -320,7 +366,7 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
         const int j = wave;
         float e = s_eps[j * kLanes + lane];
         // the comb filter on the sampled Gaussian particles' noise (Sec. 3.3)
-        const bool comb = P.comb && noise == nullptr && live && i >= first.n_halton;
+        const bool comb = first.comb && noise == nullptr && live && i >= first.n_halton;
         if (__builtin_amdgcn_ballot_w64(comb) != 0) {
             const float f = comb_noise(s_eps + j * kLanes, lane, h, H, tab);
             if (comb) e = f;
@@ -559,7 +605,7 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
     // the capsules of the runs' anchor spheres, widened to hold the runs: a
     // lane tests one row of one item.
     if (mask & STORM_COST_SELF) {
-        const global_ptr<const int32_t> items = as_global(R.self_items);
+        const global_ptr<const int32_t> items = as_global(first.self_items);
         const int row = lane >> 4;
         // (16 items a wave, from the last wave down: the obstacles of the
         // loop above start at the first)
@@ -589,7 +635,7 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
     // (items from a queue).
     float env = 0.0f, selfpen = 0.0f;
     if (nobs > 0) {
-        const int nso = P.n_sph_obs;
+        const int nso = first.n_sph_obs;
         // lane k holds the body of this wave's k-th sphere and how many
         // obstacles are near it
         const int s_mine = wave + lane * W;
@@ -672,8 +718,12 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
         // chain of LDS round trips.
         const int n_near_items = __builtin_amdgcn_readfirstlane(s_self_n);
         auto draw = [&]() __attribute__((always_inline)) {
+            // (an address the compiler takes for divergent: it would sum a
+            // uniform one's additions over the wave first, and wait there)
+            __attribute__((address_space(3))) int *head = (__attribute__((address_space(3))) int *)&s_self_next;
+            asm volatile("" : "+v"(head));
             int g = 0;
-            if (lane == 0) g = atomicAdd(&s_self_next, 1);
+            if (lane == 0) g = __hip_atomic_fetch_add(head, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
             return g;
         };
         int drawn = draw();
@@ -794,7 +844,7 @@ __global__ __launch_bounds__(W * kLanes) void rollout_kernel(const PlainDev *dev
     if (kDebug) o = out;
     o.C = C_out;
     const STORM_CONST_AS PlainDev &D = *uniform_ptr(dev);
-    const TileFirst first{step, mean, D.P.halton, N, H, D.P.n_halton, D.P.n_null};
+    const TileFirst first = fetch_first(D.P, D.R, step, mean, N, H);
     NoQueue none;
     rollout_tile<W, kTask>(none, D.P, D.R, first, blockIdx.x, x0, goal, kDebug ? noise : nullptr, o, smem);
 }
@@ -826,7 +876,7 @@ __global__ __launch_bounds__(W * kLanes) __attribute__((amdgpu_waves_per_eu(4)))
         const STORM_CONST_AS RobotDev *R = uniform_ptr(robot);
         asm volatile("" : "+s"(R));  // fields read in each tile, not kept over the loop
         ProblemRef P = uniform_ptr(probs)[p];
-        const TileFirst first{P.step, P.mean, P.halton, P.N, P.H, P.n_halton, P.n_null};
+        const TileFirst first = fetch_first(P, *R, P.step, P.mean, P.N, P.H);
         rollout_tile<W, false>(queue, P, *R, first, tile, x0s + (size_t)p * 3 * kDof, goals + (size_t)p * 12, nullptr,
                                StepOut{}, smem);
         queue.parity ^= 1;
