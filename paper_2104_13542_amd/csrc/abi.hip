@@ -363,6 +363,7 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
     P.n_box_obs = n_box_obs;
     P.ppt = storm::kLanes / H;
     P.n_tiles = (N + P.ppt - 1) / P.ppt;
+    P.n_chunks = storm::adjoint_chunks(P.n_tiles);
     P.cost_mask = params->cost_mask;
     P.grad_mask = params->grad_mask != 0 ? params->grad_mask : params->cost_mask;
     // the learned model replaces the sphere pairs: the rollout leaves the
@@ -417,10 +418,7 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
     STORM_TRY(dalloc(c, &u, (size_t)STORM_DOF * N * H));
     STORM_TRY(dalloc(c, &C, (size_t)N));
     STORM_TRY(dalloc(c, &counters, (size_t)4));
-    {
-        const int chunks = P.n_tiles < storm::kAdjChunks ? P.n_tiles : storm::kAdjChunks;
-        STORM_TRY(dalloc(c, &grad_part, storm::kAdjChunks + (size_t)chunks * STORM_DOF * storm::kMaxH));
-    }
+    STORM_TRY(dalloc(c, &grad_part, storm::kAdjChunks + (size_t)P.n_chunks * STORM_DOF * storm::kMaxH));
     STORM_TRY(dalloc(c, &upd_part, storm::update_part_floats(N, H)));
     STORM_TRY(dalloc(c, &grad, (size_t)H * STORM_DOF));
     STORM_TRY(dalloc(c, &adam, (size_t)2 * H * STORM_DOF));
@@ -773,8 +771,7 @@ int32_t storm_rollout_grad_noalloc(storm_ctx ctx, const float *d_x0, const float
     if (ctx->error != STORM_OK) return ctx->error;
     if (ctx->P.grad_mask & ~kDiffMask) return STORM_E_UNSUPPORTED;
     const ProblemDev &P = ctx->P;
-    const size_t chunks = (size_t)(P.n_tiles < kAdjChunks ? P.n_tiles : kAdjChunks);
-    if (chunks * STORM_DOF * kMaxH > kNoallocGradFloats || P.H > kMaxH) return STORM_E_RANGE;
+    if ((size_t)P.n_chunks * STORM_DOF * kMaxH > kNoallocGradFloats || P.H > kMaxH) return STORM_E_RANGE;
     // the partials go to this device's static scratch instead of the
     // context's own buffers; everything else is the context's
     if (storm::launch_grad(P, ctx->dev, ctx->scratch, d_x0, d_goal, d_mean, d_noise, d_grad, d_J, 0, 0.0f, nullptr, 0,

@@ -5,33 +5,395 @@
 // velocity limits (Eq. 11 form) and stop (Eq. 10); hinge and norm kinks take
 // subgradient 0.  States are recomputed from mu and the noise, never stored.
 //
-// Per 64-lane tile (ppt particles x H steps), eight wavefronts:
-//   A   noise, controls, the forward integrator and sin/cos of q (as kernel R)
-//   B   waves 0-2: forward kinematics to LDS, one frame row each; wave 3:
-//       limit costs and their gradients with respect to q and v
-//   C   wave 0: pose cost and dC/dq through the Jacobian columns,
-//       dp/dq_k = z_k x (p - o_k) and dR/dq_k = [z_k]x R; horizon cost
-//   D   waves 0-6: the integrator backwards, two segmented suffix sums:
-//       dC/dv_k = gv_k + dt_k sum_{h>=k} gq_h,  dC/du_m = dt_m sum_{k>=m} dC/dv_k
-//   E   per (joint, step) sum over the tile's particles -> partial gradient
-// A second kernel adds the tile partials per (joint, step) in a fixed order
-// and, when refining, takes an Adam step (Kingma and Ba, 2015) on mu.
+// One wavefront per 64-lane tile (ppt particles x H steps; a lane is one point
+// and holds all seven joints): the noise, the controls and the integrator (as
+// kernel R); limit costs and their gradients; forward kinematics, keeping each
+// joint's axis z_k and origin o_k; pose cost and dC/dq through the Jacobian
+// columns, dp/dq_k = z_k x (p - o_k) and dR/dq_k = [z_k]x R; then the
+// integrator backwards, two segmented suffix sums:
+//   dC/dv_k = gv_k + dt_k sum_{h>=k} gq_h,  dC/du_m = dt_m sum_{k>=m} dC/dv_k.
+// Nothing is exchanged between wavefronts until the tiles are done, so there is
+// no barrier in the loop and the only idle issue slots are latencies that the
+// other wavefronts of the SIMD cover (four: 128 VGPRs); bound by VALU issue.
+// The same work split over eight wavefronts by joint and row, with six
+// barriers a tile, takes 1.65 ms for 64 problems of 4096 x 64 against 0.82, but
+// is the shorter path where a launch has few tiles: it is kept for those
+// (kSplitTiles), with the same bits.
+// A second kernel adds the partials per (joint, step) in a fixed order and,
+// when refining, takes an Adam step (Kingma and Ba, 2015) on mu.
 #include "kinematics.h"
 #include "sampling.h"
+
+// The same point costs the same bits in either form below: no product is
+// fused into a sum but where fmaf says so.
+#pragma clang fp contract(off)
 
 namespace storm {
 namespace {
 
-constexpr int kAdjWaves = 8;
+constexpr int kSplitWaves = 8;
 constexpr int kRedThreads = 1024;
 
-// Phases A-D for one tile, then the tile's share of the chunk partials:
-// acc (thread t < 7H: joint t / H, step t % H) gains the sum over the tile's
-// particles of dC/du, cacc (thread 0) the tile's horizon-cost sum.
-__device__ __forceinline__ void adjoint_tile(ProblemRef P, RobotRef R, const int N, const int H, const int tile,
-                                             const float *__restrict__ x0, const float *__restrict__ goal,
-                                             const float *__restrict__ mean, const float *__restrict__ noise,
-                                             float &acc, float &cacc)
+// What a chunk's start reads of the problem, fetched in one go.
+struct AdjFirst {
+    int32_t n_halton, n_null, ppt, n_tiles, n_chunks;
+    uint32_t seed_lo, seed_hi, grad_mask, comb, cov_step;
+    const float *tables, *halton;
+    float *sigma2;
+    uint32_t *step;
+    int32_t N, H;
+};
+__device__ __forceinline__ AdjFirst fetch_first(ProblemRef P, int32_t N, int32_t H)
+{
+    AdjFirst F{P.n_halton, P.n_null, P.ppt,      P.n_tiles, P.n_chunks, P.seed_lo, P.seed_hi, P.grad_mask, P.comb,
+               P.cov_step, P.tables, P.halton,   P.sigma2,  P.step,     N,         H};
+    asm volatile("" : "+s"(F.n_halton), "+s"(F.n_null), "+s"(F.ppt), "+s"(F.n_tiles), "+s"(F.n_chunks),
+                 "+s"(F.seed_lo), "+s"(F.seed_hi), "+s"(F.grad_mask), "+s"(F.comb), "+s"(F.cov_step), "+s"(F.tables),
+                 "+s"(F.halton), "+s"(F.sigma2), "+s"(F.step));
+    return F;
+}
+
+// This lane's number, counted anew at each use (threadIdx, or a count that the
+// compiler may keep, would take up a register throughout).
+__device__ __forceinline__ int lane_id()
+{
+    int lane;
+    asm volatile("v_mbcnt_lo_u32_b32 %0, -1, 0\n\tv_mbcnt_hi_u32_b32 %0, -1, %0" : "=v"(lane));
+    return lane;
+}
+
+// n consecutive scalars in one go (n <= 28): a load wherever one is used would
+// put one round trip after another.
+template <int n>
+__device__ __forceinline__ void fetch_scalars(const STORM_CONST_AS float *p, float (&x)[n])
+{
+    static_assert(n % 4 == 0, "four per statement");
+#pragma unroll
+    for (int k = 0; k < n; ++k) x[k] = p[k];
+#pragma unroll
+    for (int k = 0; k < n; k += 4) asm volatile("" : "+s"(x[k]), "+s"(x[k + 1]), "+s"(x[k + 2]), "+s"(x[k + 3]));
+}
+
+// The weights and scales of the differentiated terms.
+struct AdjWeights {
+    float a_joint, a_vel, a_stop, w_pos, w_rot, alpha_pos[3], alpha_rot[3];
+};
+__device__ __forceinline__ AdjWeights fetch_weights(ProblemRef P)
+{
+    AdjWeights w{P.a_joint, P.a_vel, P.a_stop, P.w_pos, P.w_rot, {P.alpha_pos[0], P.alpha_pos[1], P.alpha_pos[2]},
+                 {P.alpha_rot[0], P.alpha_rot[1], P.alpha_rot[2]}};
+    asm volatile("" : "+s"(w.a_joint), "+s"(w.a_vel), "+s"(w.a_stop), "+s"(w.w_pos), "+s"(w.w_rot),
+                 "+s"(w.alpha_pos[0]), "+s"(w.alpha_pos[1]), "+s"(w.alpha_pos[2]), "+s"(w.alpha_rot[0]),
+                 "+s"(w.alpha_rot[1]), "+s"(w.alpha_rot[2]));
+    return w;
+}
+
+// Limit and stop costs of a point from the squared norms of its violations:
+// the cost, and what the violations are scaled by in its gradients.
+struct AdjLimits {
+    float cost, kj, kv, ks;
+};
+__device__ __forceinline__ AdjLimits limit_terms(const AdjWeights &w, uint32_t mask, float nj, float nv, float ns)
+{
+    nj = (mask & STORM_COST_JOINT) ? fast_sqrt(nj) : 0.0f;
+    nv = (mask & STORM_COST_VEL) ? fast_sqrt(nv) : 0.0f;
+    ns = (mask & STORM_COST_STOP) ? fast_sqrt(ns) : 0.0f;
+    return AdjLimits{fmaf(w.a_joint, nj, fmaf(w.a_vel, nv, w.a_stop * ns)), nj > 0.0f ? w.a_joint / nj : 0.0f,
+                     nv > 0.0f ? w.a_vel / nv : 0.0f, ns > 0.0f ? w.a_stop / ns : 0.0f};
+}
+
+// Pose cost of a point with flange (Re, pe), added to `cost`; its gradient
+// with respect to the joints of axes z and origins o, added to gq.
+template <class Goal>
+__device__ __forceinline__ void pose_terms(const AdjWeights &w, const Goal &goal, const float Re[9], const float pe[3],
+                                           const float z[kDof][3], const float o[kDof][3], float gq[kDof], float &cost)
+{
+    // position: e = diag(a2) R_g^T (p - p_g), gradient g_p = w_pos R_g diag(a2) e / |e|
+    float ep[3], pos2 = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+        ep[r] = w.alpha_pos[r] * fmaf(goal[0 * 3 + r], pe[0] - goal[9],
+                                      fmaf(goal[1 * 3 + r], pe[1] - goal[10], goal[2 * 3 + r] * (pe[2] - goal[11])));
+        pos2 = fmaf(ep[r], ep[r], pos2);
+    }
+    const float pos = fast_sqrt(pos2);
+    const float kp = pos > 0.0f ? w.w_pos / pos : 0.0f;
+    float gp[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+        gp[a] = kp * fmaf(goal[a * 3 + 0], w.alpha_pos[0] * ep[0],
+                          fmaf(goal[a * 3 + 1], w.alpha_pos[1] * ep[1], goal[a * 3 + 2] * w.alpha_pos[2] * ep[2]));
+    // rotation: M = diag(a1)(I - R_g^T R), gradient G = -w_rot R_g diag(a1) M / |M|_F
+    float M[9], rot2 = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 3; ++r)
+#pragma unroll
+        for (int c = 0; c < 3; ++c) {
+            const float m = fmaf(goal[0 * 3 + r], Re[0 * 3 + c],
+                                 fmaf(goal[1 * 3 + r], Re[1 * 3 + c], goal[2 * 3 + r] * Re[2 * 3 + c]));
+            M[r * 3 + c] = w.alpha_rot[r] * ((r == c ? 1.0f : 0.0f) - m);
+            rot2 = fmaf(M[r * 3 + c], M[r * 3 + c], rot2);
+        }
+    const float rot = fast_sqrt(rot2);
+    const float kr = rot > 0.0f ? -w.w_rot / rot : 0.0f;
+    float G[9];
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            G[a * 3 + c] = kr * fmaf(goal[a * 3 + 0], w.alpha_rot[0] * M[0 * 3 + c],
+                                     fmaf(goal[a * 3 + 1], w.alpha_rot[1] * M[1 * 3 + c],
+                                          goal[a * 3 + 2] * w.alpha_rot[2] * M[2 * 3 + c]));
+    // <G, [z]x R> = z . w with A = R G^T, w = (A12 - A21, A20 - A02, A01 - A10)
+    auto A = [&](int a, int b) __attribute__((always_inline)) {
+        return fmaf(Re[a * 3 + 0], G[b * 3 + 0], fmaf(Re[a * 3 + 1], G[b * 3 + 1], Re[a * 3 + 2] * G[b * 3 + 2]));
+    };
+    const float w0 = A(1, 2) - A(2, 1);
+    const float w1 = A(2, 0) - A(0, 2);
+    const float w2 = A(0, 1) - A(1, 0);
+#pragma unroll
+    for (int k = 0; k < kDof; ++k) {
+        const float r0 = pe[0] - o[k][0];
+        const float r1 = pe[1] - o[k][1];
+        const float r2 = pe[2] - o[k][2];
+        // (p - o_k) x g_p
+        const float c0 = fmaf(r1, gp[2], -(r2 * gp[1]));
+        const float c1 = fmaf(r2, gp[0], -(r0 * gp[2]));
+        const float c2 = fmaf(r0, gp[1], -(r1 * gp[0]));
+        gq[k] += fmaf(z[k][0], c0 + w0, fmaf(z[k][1], c1 + w1, z[k][2] * (c2 + w2)));
+    }
+    cost = fmaf(w.w_pos, pos, fmaf(w.w_rot, rot, cost));
+}
+
+// One tile on one wavefront: acc gains dC/du of this lane's point, cacc its
+// weighted cost.  row: [8][64] floats of LDS of this wavefront's own.
+__device__ __forceinline__ void adjoint_tile(ProblemRef P, RobotRef R, AdjFirst F, const int tile,
+                                             const uint32_t counter, const STORM_CONST_AS float *x0,
+                                             const STORM_CONST_AS float *goal_in, const float *mean,
+                                             const float *__restrict__ noise, float *row, float acc[kDof],
+                                             float &cacc)
+{
+    // What follows from the lane and the seed is formed, and the step's inputs
+    // are read, in each tile: kept over the loop they would spill.
+    const int lane = lane_id();
+    asm volatile("" : "+s"(F.seed_lo), "+s"(F.seed_hi), "+s"(F.H), "+s"(F.grad_mask));
+    const int N = F.N, H = F.H;
+    const int pl = (int)(((float)lane + 0.5f) * __builtin_amdgcn_rcpf((float)H));  // lane / H (exact, as in kernel R)
+    const int h = lane - pl * H;
+    const int i = tile * F.ppt + pl;
+    const bool valid = pl < F.ppt && i < N;
+    const bool live = valid && i < N - F.n_null;
+    const uint32_t mask = F.grad_mask;
+    const STORM_CONST_AS float *tab = uniform_ptr(F.tables);
+    const float dt = as_global(F.tables)[kTabDt + h], hw = as_global(F.tables)[kTabHw + h],
+                vs = as_global(F.tables)[kTabVstop + h];
+    float mu[kDof], sigma2[kDof];
+    {
+        const global_ptr<const float> m = as_global(mean) + h * kDof,
+                                      s = as_global(F.sigma2) + (F.cov_step ? h * kDof : 0);
+#pragma unroll
+        for (int j = 0; j < kDof; ++j) {
+            mu[j] = m[j];
+            sigma2[j] = s[j];
+        }
+    }
+
+    // noise
+    float e[8];
+#pragma unroll
+    for (int m = 0; m < 8; ++m) e[m] = 0.0f;
+    if (live) {
+        standard_noise4(F, F.seed_lo, F.seed_hi, noise, 0, i, h, counter, e);
+        standard_noise4(F, F.seed_lo, F.seed_hi, noise, 1, i, h, counter, e + 4);
+    }
+    if (F.comb && noise == nullptr) {
+        // the comb filter on the sampled Gaussian particles' noise, as in kernel R
+        const bool comb = live && i >= F.n_halton;
+#pragma unroll
+        for (int j = 0; j < kDof; ++j) row[j * kLanes + lane] = e[j];
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int j = 0; j < kDof; ++j) {
+            const float f = comb_noise(row + j * kLanes, lane, h, H, as_global(F.tables));
+            if (comb) e[j] = f;
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+
+    // controls and the integrator; limit costs and their gradients (signed
+    // violations: negative below the band, positive above)
+    float gq[kDof], gv[kDof], sq[kDof], cq[kDof], cost = 0.0f;
+    AdjWeights w;
+    {
+        // (all scans of a kind together: a joint's alone is a serial chain)
+        float vj[kDof], qj[kDof], es[kDof], x[16], lim[4 * 8];
+        fetch_scalars<12>(x0, reinterpret_cast<float (&)[12]>(x));
+        x[12] = x0[12];
+        x[13] = x0[13];
+        asm volatile("" : "+s"(x[12]), "+s"(x[13]));
+        fetch_scalars(tab + kTabJlo, lim);
+        float nj = 0.0f, nv = 0.0f, ns = 0.0f;
+#pragma unroll
+        for (int j = 0; j < kDof; ++j)
+            vj[j] = dt * (live ? fmaf(sqrtf(sigma2[j]), e[j], mu[j]) : 0.0f);
+        segmented_scans(vj, lane, h);
+#pragma unroll
+        for (int j = 0; j < kDof; ++j) {
+            vj[j] += x[kDof + j];
+            qj[j] = dt * vj[j];
+        }
+        segmented_scans(qj, lane, h);
+#pragma unroll
+        for (int j = 0; j < kDof; ++j) {
+            const float v = vj[j], q = x[j] + qj[j];
+            sincosf(q, &sq[j], &cq[j]);
+            gq[j] = fminf(q - lim[j], 0.0f) + fmaxf(q - lim[8 + j], 0.0f);
+            gv[j] = fminf(v - lim[16 + j], 0.0f) + fmaxf(v - lim[24 + j], 0.0f);
+            const float a = fmaxf(fabsf(v) - vs, 0.0f);
+            nj = fmaf(gq[j], gq[j], nj);
+            nv = fmaf(gv[j], gv[j], nv);
+            ns = fmaf(a, a, ns);
+            es[j] = v > 0.0f ? a : -a;
+        }
+        w = fetch_weights(P);
+        const AdjLimits lt = limit_terms(w, mask, nj, nv, ns);
+#pragma unroll
+        for (int j = 0; j < kDof; ++j) {
+            gq[j] = lt.kj * gq[j];
+            gv[j] = fmaf(lt.kv, gv[j], lt.ks * es[j]);
+        }
+        cost = lt.cost;
+    }
+
+    // pose cost and its gradient
+    if (mask & STORM_COST_POSE) {
+        float Re[9] = {1.0f, 0.0f, 0.0f, 0.0f, 1.0f, 0.0f, 0.0f, 0.0f, 1.0f}, pe[3] = {0.0f, 0.0f, 0.0f};
+        float z[kDof][3], o[kDof][3], dh[4 * kFrames];
+        fetch_scalars(R.ca, dh);
+#pragma unroll
+        for (int f = 0; f < kFrames; ++f) {
+            dh_step(Re, pe, dh[f], dh[kFrames + f], dh[2 * kFrames + f], dh[3 * kFrames + f], f < kDof ? cq[f < kDof ? f : 0] : 1.0f,
+                    f < kDof ? sq[f < kDof ? f : 0] : 0.0f);
+            if (f < kDof)
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    z[f][c] = Re[3 * c + 2];
+                    o[f][c] = pe[c];
+                }
+        }
+        float goal[12];
+        fetch_scalars(goal_in, goal);
+        pose_terms(w, goal, Re, pe, z, o, gq, cost);
+    }
+    cacc += valid ? hw * cost : 0.0f;
+
+    // the integrator backwards
+    const int left = H - 1 - h;
+#pragma unroll
+    for (int j = 0; j < kDof; ++j) gq[j] *= hw;
+    segmented_suffix_scans(gq, lane, left);
+#pragma unroll
+    for (int j = 0; j < kDof; ++j) gq[j] = fmaf(dt, gq[j], hw * gv[j]);
+    segmented_suffix_scans(gq, lane, left);
+#pragma unroll
+    for (int j = 0; j < kDof; ++j) acc[j] += live ? dt * gq[j] : 0.0f;
+}
+
+__device__ __forceinline__ float wave_sum(float x)
+{
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, kLanes);
+    return x;
+}
+
+// The partials of chunk c from its runs' sums in LDS (rows of seven joints,
+// then the cost, by lane), over particles, then runs.  t of `threads` threads.
+template <int runs>
+__device__ __forceinline__ void write_partial(float *__restrict__ part, const int c, const float *rows, const int ppt,
+                                              const int H, const int t, const int threads)
+{
+    for (int k = t; k < kDof * H; k += threads) {
+        const int j = k / H, hh = k - j * H;
+        float s = 0.0f;
+        for (int p = 0; p < ppt; ++p) {
+            float v[runs];
+#pragma unroll
+            for (int w = 0; w < runs; ++w) v[w] = rows[(w * 8 + j) * kLanes + p * H + hh];
+#pragma unroll
+            for (int w = 0; w < runs; ++w) s += v[w];
+        }
+        as_global(part)[kAdjChunks + ((size_t)c * kDof + j) * kMaxH + hh] = s;
+    }
+    if (t < kLanes) {
+        float s = 0.0f;
+#pragma unroll
+        for (int w = 0; w < runs; ++w) s += rows[(w * 8 + kDof) * kLanes + t];
+        s = wave_sum(s);
+        if (t == 0) as_global(part)[c] = s;
+    }
+}
+
+// A workgroup of W wavefronts, a tile per wavefront at a time.  The order of
+// every sum is the problem's alone, not W's nor the batch's: up to kSplitTiles
+// tiles a partial is one tile's (here wavefront w of workgroup c takes tile
+// c W + w); past that, chunk c of a problem covers T / n tiles, the first T % n
+// chunks one more, in runs of every kRuns-th tile (adjoint_runs), a wavefront
+// taking one run after another.
+template <int W>
+__device__ __forceinline__ void adjoint_chunk(ProblemRef P, RobotRef R, const int N, const int H, const int c,
+                                              const float *__restrict__ x0, const float *__restrict__ goal,
+                                              const float *__restrict__ mean, const float *__restrict__ noise,
+                                              float *__restrict__ part)
+{
+    __shared__ float s_buf[kAdjRuns][8 * kLanes];  // the wavefronts' rows, then the runs' sums
+    const AdjFirst F = fetch_first(P, N, H);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t counter = *uniform_ptr(F.step + 2);
+    const bool single = F.n_tiles <= kSplitTiles;
+    const int runs = single ? W : adjoint_runs(F.n_tiles);
+    const int base = F.n_tiles / F.n_chunks, more = F.n_tiles - base * F.n_chunks;
+    const int t0 = single ? c * W : c * base + min(c, more);
+    const int t1 = single ? min(t0 + W, F.n_tiles) : t0 + base + (c < more ? 1 : 0);
+    for (int run = wave; run < runs; run += W) {
+        float acc[kDof] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f}, cacc = 0.0f;
+        for (int tile = t0 + run; tile < t1; tile += runs) {
+            // (scalars read in each tile, not kept over the loop)
+            const STORM_CONST_AS ProblemDev *p = &P;
+            const STORM_CONST_AS RobotDev *r = &R;
+            const STORM_CONST_AS float *x = uniform_ptr(x0), *g = uniform_ptr(goal);
+            asm volatile("" : "+s"(p), "+s"(r), "+s"(x), "+s"(g));
+            adjoint_tile(*p, *r, F, tile, counter, x, g, mean, noise, s_buf[run], acc, cacc);
+        }
+        const int lane = lane_id();
+#pragma unroll
+        for (int j = 0; j < kDof; ++j) s_buf[run][j * kLanes + lane] = acc[j];
+        s_buf[run][kDof * kLanes + lane] = cacc;
+    }
+    __syncthreads();
+    const int lane = lane_id();
+    if (single) {
+        if (t0 + wave >= t1) return;
+        write_partial<1>(part, t0 + wave, s_buf[wave], F.ppt, H, lane, kLanes);
+        return;
+    }
+    if (runs == kAdjRuns)
+        write_partial<kAdjRuns>(part, c, s_buf[0], F.ppt, H, wave * kLanes + lane, W * kLanes);
+    else
+        write_partial<kAdjWaves>(part, c, s_buf[0], F.ppt, H, wave * kLanes + lane, W * kLanes);
+}
+
+// One tile split over a workgroup of eight wavefronts, into the partials of
+// chunk `tile`:
+//   A   noise, controls, the forward integrator and sin/cos of q (as kernel R)
+//   B   waves 0-2: forward kinematics to LDS, one frame row each; wave 3:
+//       limit costs and their gradients with respect to q and v
+//   C   wave 0: pose cost and dC/dq through the Jacobian columns; horizon cost
+//   D   waves 0-6: the integrator backwards
+//   E   per (joint, step) sum over the tile's particles
+__device__ __forceinline__ void adjoint_split(ProblemRef P, RobotRef R, const int N, const int H, const int tile,
+                                              const float *__restrict__ x0, const float *__restrict__ goal,
+                                              const float *__restrict__ mean, const float *__restrict__ noise,
+                                              float *__restrict__ part)
 {
     __shared__ float s_eps[8][kLanes];
     __shared__ float s_q[kDof][kLanes];
@@ -60,7 +422,7 @@ __device__ __forceinline__ void adjoint_tile(ProblemRef P, RobotRef R, const int
     // ---- A: noise, controls, integrator ---------------------------------------
     if (wave < 2) {
         float e[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (live) standard_noise4(P, noise, wave, i, h, *as_global(P.last_step), e);
+        if (live) standard_noise4(P, P.seed_lo, P.seed_hi, noise, wave, i, h, *as_global(P.last_step), e);
 #pragma unroll
         for (int m = 0; m < 4; ++m) s_eps[4 * wave + m][lane] = e[m];
     }
@@ -119,19 +481,14 @@ __device__ __forceinline__ void adjoint_tile(ProblemRef P, RobotRef R, const int
             nv = fmaf(ev[j], ev[j], nv);
             ns = fmaf(es[j], es[j], ns);
         }
-        nj = (mask & STORM_COST_JOINT) ? fast_sqrt(nj) : 0.0f;
-        nv = (mask & STORM_COST_VEL) ? fast_sqrt(nv) : 0.0f;
-        ns = (mask & STORM_COST_STOP) ? fast_sqrt(ns) : 0.0f;
-        const float kj = nj > 0.0f ? P.a_joint / nj : 0.0f;
-        const float kv = nv > 0.0f ? P.a_vel / nv : 0.0f;
-        const float ks = ns > 0.0f ? P.a_stop / ns : 0.0f;
+        const AdjLimits lt = limit_terms(fetch_weights(P), mask, nj, nv, ns);
 #pragma unroll
         for (int j = 0; j < kDof; ++j) {
             const float v = s_v[j][lane];
-            s_gl[j][lane] = kj * ej[j];
-            s_gv[j][lane] = fmaf(kv, ev[j], ks * es[j] * (v > 0.0f ? 1.0f : -1.0f));
+            s_gl[j][lane] = lt.kj * ej[j];
+            s_gv[j][lane] = fmaf(lt.kv, ev[j], lt.ks * (v > 0.0f ? es[j] : -es[j]));
         }
-        s_cl[lane] = fmaf(P.a_joint, nj, fmaf(P.a_vel, nv, P.a_stop * ns));
+        s_cl[lane] = lt.cost;
     }
     __syncthreads();
 
@@ -142,70 +499,19 @@ __device__ __forceinline__ void adjoint_tile(ProblemRef P, RobotRef R, const int
         for (int k = 0; k < kDof; ++k) gq[k] = s_gl[k][lane];
         float cost = s_cl[lane];
         if (mask & STORM_COST_POSE) {
-            float Re[9], pe[3];
+            float Re[9], pe[3], z[kDof][3], o[kDof][3];
 #pragma unroll
             for (int c = 0; c < 9; ++c) Re[c] = s_fr[7 * 12 + c][lane];
 #pragma unroll
             for (int c = 0; c < 3; ++c) pe[c] = s_fr[7 * 12 + 9 + c][lane];
-            // position: e = diag(a2) R_g^T (p - p_g), gradient g_p = w_pos R_g diag(a2) e / |e|
-            float e[3], pos2 = 0.0f;
 #pragma unroll
-            for (int r = 0; r < 3; ++r) {
-                e[r] = P.alpha_pos[r] * fmaf(goal[0 * 3 + r], pe[0] - goal[9],
-                                             fmaf(goal[1 * 3 + r], pe[1] - goal[10], goal[2 * 3 + r] * (pe[2] - goal[11])));
-                pos2 = fmaf(e[r], e[r], pos2);
-            }
-            const float pos = fast_sqrt(pos2);
-            const float kp = pos > 0.0f ? P.w_pos / pos : 0.0f;
-            float gp[3];
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-                gp[a] = kp * fmaf(goal[a * 3 + 0], P.alpha_pos[0] * e[0],
-                                  fmaf(goal[a * 3 + 1], P.alpha_pos[1] * e[1], goal[a * 3 + 2] * P.alpha_pos[2] * e[2]));
-            // rotation: M = diag(a1)(I - R_g^T R), gradient G = -w_rot R_g diag(a1) M / |M|_F
-            float M[9], rot2 = 0.0f;
-#pragma unroll
-            for (int r = 0; r < 3; ++r)
+            for (int k = 0; k < kDof; ++k)
 #pragma unroll
                 for (int c = 0; c < 3; ++c) {
-                    const float m = fmaf(goal[0 * 3 + r], Re[0 * 3 + c],
-                                         fmaf(goal[1 * 3 + r], Re[1 * 3 + c], goal[2 * 3 + r] * Re[2 * 3 + c]));
-                    M[r * 3 + c] = P.alpha_rot[r] * ((r == c ? 1.0f : 0.0f) - m);
-                    rot2 = fmaf(M[r * 3 + c], M[r * 3 + c], rot2);
+                    z[k][c] = s_fr[k * 12 + 3 * c + 2][lane];
+                    o[k][c] = s_fr[k * 12 + 9 + c][lane];
                 }
-            const float rot = fast_sqrt(rot2);
-            const float kr = rot > 0.0f ? -P.w_rot / rot : 0.0f;
-            float G[9];
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-#pragma unroll
-                for (int c = 0; c < 3; ++c)
-                    G[a * 3 + c] = kr * fmaf(goal[a * 3 + 0], P.alpha_rot[0] * M[0 * 3 + c],
-                                             fmaf(goal[a * 3 + 1], P.alpha_rot[1] * M[1 * 3 + c],
-                                                  goal[a * 3 + 2] * P.alpha_rot[2] * M[2 * 3 + c]));
-            // <G, [z]x R> = z . w with A = R G^T, w = (A12 - A21, A20 - A02, A01 - A10)
-            float A[9];
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-#pragma unroll
-                for (int b = 0; b < 3; ++b)
-                    A[a * 3 + b] = fmaf(Re[a * 3 + 0], G[b * 3 + 0], fmaf(Re[a * 3 + 1], G[b * 3 + 1], Re[a * 3 + 2] * G[b * 3 + 2]));
-            const float w0 = A[1 * 3 + 2] - A[2 * 3 + 1];
-            const float w1 = A[2 * 3 + 0] - A[0 * 3 + 2];
-            const float w2 = A[0 * 3 + 1] - A[1 * 3 + 0];
-#pragma unroll
-            for (int k = 0; k < kDof; ++k) {
-                const float z0 = s_fr[k * 12 + 2][lane], z1 = s_fr[k * 12 + 5][lane], z2 = s_fr[k * 12 + 8][lane];
-                const float r0 = pe[0] - s_fr[k * 12 + 9][lane];
-                const float r1 = pe[1] - s_fr[k * 12 + 10][lane];
-                const float r2 = pe[2] - s_fr[k * 12 + 11][lane];
-                // (p - o_k) x g_p
-                const float c0 = r1 * gp[2] - r2 * gp[1];
-                const float c1 = r2 * gp[0] - r0 * gp[2];
-                const float c2 = r0 * gp[1] - r1 * gp[0];
-                gq[k] += fmaf(z0, c0 + w0, fmaf(z1, c1 + w1, z2 * (c2 + w2)));
-            }
-            cost = fmaf(P.w_pos, pos, fmaf(P.w_rot, rot, cost));
+            pose_terms(fetch_weights(P), goal, Re, pe, z, o, gq, cost);
         }
 #pragma unroll
         for (int k = 0; k < kDof; ++k) s_gq[k][lane] = hw_h * gq[k];
@@ -213,79 +519,73 @@ __device__ __forceinline__ void adjoint_tile(ProblemRef P, RobotRef R, const int
         if (h == H - 1) s_Cp[pl] = valid ? Ci : 0.0f;
     }
     __syncthreads();
-    if (threadIdx.x == 0)
+    if (threadIdx.x == 0) {
+        float cacc = 0.0f;
         for (int p = 0; p < P.ppt; ++p) cacc += s_Cp[p];
+        as_global(part)[tile] = cacc;
+    }
 
     // ---- D: the integrator backwards -----------------------------------------
     if (wave < kDof) {
         const int j = wave;
-        const float Gv = fmaf(dt_h, segmented_suffix_scan(s_gq[j][lane], h, H), hw_h * s_gv[j][lane]);
-        const float gu = dt_h * segmented_suffix_scan(Gv, h, H);
-        s_gu[j][lane] = live ? gu : 0.0f;
+        const int left = H - 1 - h;
+        float g[1] = {s_gq[j][lane]};
+        segmented_suffix_scans(g, lane, left);
+        g[0] = fmaf(dt_h, g[0], hw_h * s_gv[j][lane]);
+        segmented_suffix_scans(g, lane, left);
+        s_gu[j][lane] = live ? dt_h * g[0] : 0.0f;
     }
     __syncthreads();
 
     // ---- E: the tile's partial of dJ/dmu (sum over the tile's particles) -----
     if ((int)threadIdx.x < kDof * H) {
         const int j = threadIdx.x / H, hh = threadIdx.x - j * H;
+        float acc = 0.0f;
         for (int p = 0; p < P.ppt; ++p) acc += s_gu[j][p * H + hh];
+        as_global(part)[kAdjChunks + ((size_t)tile * kDof + j) * kMaxH + hh] = acc;
     }
-    __syncthreads();  // LDS is reused by the next tile of the chunk
-}
-
-// Chunks of tiles of one problem: min(n_tiles, kAdjChunks), chunk c covering
-// tiles [c T / n, (c + 1) T / n); one workgroup per chunk, tiles in order.
-__device__ __forceinline__ void adjoint_chunk(ProblemRef P, RobotRef R, const int N, const int H, const int c,
-                                              const float *__restrict__ x0, const float *__restrict__ goal,
-                                              const float *__restrict__ mean, const float *__restrict__ noise,
-                                              float *__restrict__ part)
-{
-    const int T = P.n_tiles, n = min(T, kAdjChunks);
-    const int t0 = (int)((long long)c * T / n), t1 = (int)((long long)(c + 1) * T / n);
-    float acc = 0.0f, cacc = 0.0f;
-    for (int tile = t0; tile < t1; ++tile) adjoint_tile(P, R, N, H, tile, x0, goal, mean, noise, acc, cacc);
-    if ((int)threadIdx.x < kDof * H) {
-        const int j = threadIdx.x / H, hh = threadIdx.x - j * H;
-        as_global(part)[kAdjChunks + ((size_t)c * kDof + j) * kMaxH + hh] = acc;
-    }
-    if (threadIdx.x == 0) as_global(part)[c] = cacc;
 }
 
 // All arguments fit the 14 dwords that are preloaded into SGPRs; the rest of
 // the problem comes from its descriptor in device memory.
-__global__ __launch_bounds__(kAdjWaves *kLanes) void adjoint_kernel(const PlainDev *dev,
-                                                                    const float *__restrict__ mean,
-                                                                    const float *__restrict__ x0,
-                                                                    const float *__restrict__ goal,
-                                                                    const float *__restrict__ noise,
-                                                                    float *__restrict__ part, int32_t N, int32_t H)
+template <int W>
+__global__ __launch_bounds__(W *kLanes) __attribute__((amdgpu_waves_per_eu(4))) void adjoint_kernel(
+    const PlainDev *dev, const float *__restrict__ mean, const float *__restrict__ x0, const float *__restrict__ goal,
+    const float *__restrict__ noise, float *__restrict__ part, int32_t N, int32_t H)
 {
     const STORM_CONST_AS PlainDev &D = *uniform_ptr(dev);
-    adjoint_chunk(D.P, D.R, N, H, blockIdx.x, x0, goal, mean, noise, part);
+    adjoint_chunk<W>(D.P, D.R, N, H, blockIdx.x, x0, goal, mean, noise, part);
 }
 
-// Batched form: workgroup k takes chunk items[k] = (problem, chunk).  At
-// most 80 VGPRs (six waves per SIMD), so that three workgroups share a CU
-// (3 x 41.5 KB of LDS): the third one's serial phases fill the others'
-// stalls (large workload: 2.2 -> 1.65 ms per launch; 88 VGPRs unbounded).
-__global__ __launch_bounds__(kAdjWaves *kLanes) __attribute__((amdgpu_waves_per_eu(6))) void adjoint_batch_kernel(const ProblemDev *__restrict__ probs,
-                                                                          const int2 *__restrict__ items,
-                                                                          const RobotDev *robot,
-                                                                          const float *__restrict__ x0s,
-                                                                          const float *__restrict__ goals)
+__global__ __launch_bounds__(kSplitWaves *kLanes) void adjoint_split_kernel(
+    const PlainDev *dev, const float *__restrict__ mean, const float *__restrict__ x0, const float *__restrict__ goal,
+    const float *__restrict__ noise, float *__restrict__ part, int32_t N, int32_t H)
+{
+    const STORM_CONST_AS PlainDev &D = *uniform_ptr(dev);
+    adjoint_split(D.P, D.R, N, H, blockIdx.x, x0, goal, mean, noise, part);
+}
+
+// Batched forms: workgroup k takes chunk items[k] = (problem, chunk).
+__global__ __launch_bounds__(kAdjWaves *kLanes) __attribute__((amdgpu_waves_per_eu(4))) void adjoint_batch_kernel(
+    const ProblemDev *__restrict__ probs, const int2 *__restrict__ items, const RobotDev *robot,
+    const float *__restrict__ x0s, const float *__restrict__ goals)
 {
     const STORM_CONST_AS int32_t *it = uniform_ptr(reinterpret_cast<const int32_t *>(items));
     const int p = it[2 * blockIdx.x], c = it[2 * blockIdx.x + 1];
     ProblemRef P = uniform_ptr(probs)[p];
-    adjoint_chunk(P, *uniform_ptr(robot), P.N, P.H, c, x0s + (size_t)p * 3 * kDof, goals + (size_t)p * 12, P.mean,
-                  nullptr, P.grad_part);
+    adjoint_chunk<kAdjWaves>(P, *uniform_ptr(robot), P.N, P.H, c, x0s + (size_t)p * 3 * kDof, goals + (size_t)p * 12,
+                             P.mean, nullptr, P.grad_part);
 }
 
-__device__ __forceinline__ float wave_sum(float x)
+__global__ __launch_bounds__(kSplitWaves *kLanes) void adjoint_split_batch_kernel(
+    const ProblemDev *__restrict__ probs, const int2 *__restrict__ items, const RobotDev *robot,
+    const float *__restrict__ x0s, const float *__restrict__ goals)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, kLanes);
-    return x;
+    const STORM_CONST_AS int32_t *it = uniform_ptr(reinterpret_cast<const int32_t *>(items));
+    const int p = it[2 * blockIdx.x], c = it[2 * blockIdx.x + 1];
+    ProblemRef P = uniform_ptr(probs)[p];
+    adjoint_split(P, *uniform_ptr(robot), P.N, P.H, c, x0s + (size_t)p * 3 * kDof, goals + (size_t)p * 12, P.mean,
+                  nullptr, P.grad_part);
 }
 
 // grad[h][j] = (1/N) sum over chunks of the partials, J = (1/N) sum of the
@@ -345,7 +645,7 @@ __device__ __forceinline__ void grad_step(ProblemRef P, int j, const float *__re
     __shared__ float s_wave[kRedThreads / kLanes];
     const int t = threadIdx.x;
     const int lane = t & (kLanes - 1), wave = t / kLanes;
-    const int H = P.H, T = min(P.n_tiles, kAdjChunks);
+    const int H = P.H, T = P.n_chunks;
     const int rows = kRedThreads / H;
     const int r = t / H, h = t - r * H;
     float acc = 0.0f;
@@ -443,9 +743,13 @@ hipError_t launch_grad(const ProblemDev &P, const PlainDev *dev, float *part, co
                        const float *mean, const float *noise, float *grad_out, float *J_out, int it, float lr,
                        float *cmd, int shift, hipStream_t stream)
 {
-    const int chunks = P.n_tiles < kAdjChunks ? P.n_tiles : kAdjChunks;
-    hipLaunchKernelGGL(adjoint_kernel, dim3((unsigned)chunks), dim3(kAdjWaves * kLanes), 0, stream, dev, mean, x0, goal,
-                       noise, part, P.N, P.H);
+    const bool wide = adjoint_runs(P.n_tiles) > kAdjWaves;
+    auto kernel = P.n_tiles <= kSplitTiles ? adjoint_split_kernel
+                  : wide                   ? adjoint_kernel<2 * kAdjWaves>
+                                           : adjoint_kernel<kAdjWaves>;
+    const int waves = P.n_tiles <= kSplitTiles ? kSplitWaves : wide ? 2 * kAdjWaves : kAdjWaves;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)P.n_chunks), dim3((unsigned)(waves * kLanes)), 0, stream, dev, mean, x0,
+                       goal, noise, part, P.N, P.H);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(grad_step_kernel, dim3(kDof), dim3(kRedThreads), 0, stream, dev, part, grad_out, J_out, cmd,
@@ -459,14 +763,15 @@ hipError_t launch_command(const PlainDev *dev, float *cmd, int shift, hipStream_
     return hipGetLastError();
 }
 
-hipError_t launch_refine_batch(const ProblemDev *probs, int n_problems, const int2 *items, int n_items,
+hipError_t launch_refine_batch(const ProblemDev *probs, int n_problems, const int2 *items, int n_items, bool split,
                                const RobotDev *robot, const float *x0s, const float *goals, int iterations,
                                float lr, float *cmd, int shift, hipStream_t stream)
 {
     hipError_t e = hipSuccess;
     for (int it = 1; e == hipSuccess && it <= iterations; ++it) {
-        hipLaunchKernelGGL(adjoint_batch_kernel, dim3((unsigned)n_items), dim3(kAdjWaves * kLanes), 0, stream,
-                           probs, items, robot, x0s, goals);
+        hipLaunchKernelGGL(split ? adjoint_split_batch_kernel : adjoint_batch_kernel, dim3((unsigned)n_items),
+                           dim3((unsigned)((split ? kSplitWaves : kAdjWaves) * kLanes)), 0, stream, probs, items, robot,
+                           x0s, goals);
         e = hipGetLastError();
         if (e != hipSuccess) break;
         hipLaunchKernelGGL(grad_step_batch_kernel, dim3((unsigned)(n_problems * kDof)), dim3(kRedThreads), 0, stream,

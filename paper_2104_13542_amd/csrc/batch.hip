@@ -29,6 +29,7 @@ struct storm_batch_s {
     uint32_t *d_next = nullptr;    // queue head (0 between launches)
     int2 *d_adj_items = nullptr;   // (problem, tile chunk) items of the batched adjoint
     int n_adj_items = 0;
+    bool adj_split = false;        // its items are tiles, each split over a workgroup
     bool differentiable = true;    // every problem's gradient terms are differentiable
     storm_launch_config cfg{8, 0, 1};
     std::vector<void *> allocs;
@@ -111,7 +112,7 @@ int32_t batch_graph(storm_batch b, const float *d_x0, const float *d_goal, float
         if (e == hipSuccess) e = launch_update_batch(b->d_probs, b->n_problems, d_cmd, last_shift, s);
     }
     if (e == hipSuccess && refine_iters > 0)
-        e = launch_refine_batch(b->d_probs, b->n_problems, b->d_adj_items, b->n_adj_items, b->d_robot, d_x0, d_goal,
+        e = launch_refine_batch(b->d_probs, b->n_problems, b->d_adj_items, b->n_adj_items, b->adj_split, b->d_robot, d_x0, d_goal,
                                 refine_iters, lr, d_cmd, shift != 0, s);
     hipGraph_t graph = nullptr;
     const hipError_t e2 = hipStreamEndCapture(s, &graph);
@@ -196,10 +197,14 @@ int32_t storm_batch_init(storm_batch *out, int32_t n_problems, const storm_param
         }
     }
     b->n_items = (int)plain.size();
+    // the adjoint: a tile of all per workgroup where they are few, a chunk
+    // (of small problems, a tile per wavefront) otherwise
+    b->adj_split = b->n_items <= kSplitTiles;
     std::vector<int2> adj;
     for (int p = 0; p < n_problems; ++p) {
-        const int chunks = probs[p].n_tiles < kAdjChunks ? probs[p].n_tiles : kAdjChunks;
-        for (int c = 0; c < chunks; ++c) adj.push_back(make_int2(p, c));
+        const int T = probs[p].n_tiles;
+        const int groups = !b->adj_split && T <= kSplitTiles ? (T + kAdjWaves - 1) / kAdjWaves : probs[p].n_chunks;
+        for (int c = 0; c < groups; ++c) adj.push_back(make_int2(p, c));
         if (probs[p].grad_mask & ~(STORM_COST_POSE | STORM_COST_JOINT | STORM_COST_VEL | STORM_COST_STOP))
             b->differentiable = false;
     }
@@ -283,7 +288,7 @@ int32_t storm_batch_refine(storm_batch b, const float *d_x0, const float *d_goal
     if (!(lr >= 0.0f) || !isfinite(lr)) return STORM_E_PARAM;
     if (b->error != STORM_OK) return b->error;
     if (!b->differentiable) return STORM_E_UNSUPPORTED;
-    if (launch_refine_batch(b->d_probs, b->n_problems, b->d_adj_items, b->n_adj_items, b->d_robot, d_x0, d_goal,
+    if (launch_refine_batch(b->d_probs, b->n_problems, b->d_adj_items, b->n_adj_items, b->adj_split, b->d_robot, d_x0, d_goal,
                             iterations, lr, d_cmd, shift != 0, static_cast<hipStream_t>(stream)) != hipSuccess) {
         b->error = STORM_E_DEVICE;
         return STORM_E_DEVICE;

@@ -8,6 +8,15 @@
 namespace storm {
 namespace {
 
+// a b as one instruction (written as two halves, or as a 64-bit product of two
+// words, it compiles to two: v_mul_lo_u32 and v_mul_hi_u32).
+__device__ __forceinline__ uint64_t wide_mul(uint32_t a, uint32_t b)
+{
+    uint64_t r;
+    asm("v_mad_u64_u32 %0, vcc, %1, %2, 0" : "=v"(r) : "s"(a), "v"(b) : "vcc");
+    return r;
+}
+
 // Philox4x32-10 (Salmon et al., SC'11): ten rounds of two 32x32->64-bit
 // products with the Weyl key schedule.
 __device__ __forceinline__ void philox4x32_10(uint32_t &c0, uint32_t &c1, uint32_t &c2, uint32_t &c3, uint32_t k0,
@@ -15,8 +24,10 @@ __device__ __forceinline__ void philox4x32_10(uint32_t &c0, uint32_t &c1, uint32
 {
 #pragma unroll
     for (int round = 0; round < 10; ++round) {
-        const uint32_t lo0 = 0xD2511F53u * c0, hi0 = __umulhi(0xD2511F53u, c0);
-        const uint32_t lo1 = 0xCD9E8D57u * c2, hi1 = __umulhi(0xCD9E8D57u, c2);
+        // (one 64-bit product each)
+        const uint64_t p0 = wide_mul(0xD2511F53u, c0), p1 = wide_mul(0xCD9E8D57u, c2);
+        const uint32_t lo0 = (uint32_t)p0, hi0 = (uint32_t)(p0 >> 32);
+        const uint32_t lo1 = (uint32_t)p1, hi1 = (uint32_t)(p1 >> 32);
         const uint32_t n0 = hi1 ^ c1 ^ k0;
         const uint32_t n2 = hi0 ^ c3 ^ k1;
         c0 = n0;
@@ -57,26 +68,34 @@ __device__ __forceinline__ float dpp_or_zero(float x)
 // into rows 2-3, each taken only by lanes whose particle began before the
 // source lane.  Segments of the padding lanes past the last particle are
 // scanned the same way.
+// (Several scans step by step together: one alone is a serial chain.)
+template <int kCtrl, int kRowMask, int n>
+__device__ __forceinline__ void scan_step(float (&x)[n], bool take)
+{
+    float y[n];
+#pragma unroll
+    for (int k = 0; k < n; ++k) y[k] = dpp_or_zero<kCtrl, kRowMask>(x[k]);
+#pragma unroll
+    for (int k = 0; k < n; ++k) x[k] += take ? y[k] : 0.0f;
+}
+template <int n>
+__device__ __forceinline__ void segmented_scans(float (&x)[n], int lane, int h)
+{
+    const int in_row = lane & 15;
+    const int reach = h < in_row ? h : in_row;  // lanes back to the row or segment start
+    scan_step<0x111, 0xf>(x, reach >= 1);  // row_shr:1
+    scan_step<0x112, 0xf>(x, reach >= 2);  // row_shr:2
+    scan_step<0x114, 0xf>(x, reach >= 4);  // row_shr:4
+    scan_step<0x118, 0xf>(x, reach >= 8);  // row_shr:8
+    scan_step<0x142, 0xa>(x, h > in_row);  // row_bcast:15 -> rows 1, 3
+    scan_step<0x143, 0xc>(x, lane >= 32 && h > lane - 32);  // row_bcast:31 -> rows 2, 3
+}
 __device__ __forceinline__ float segmented_scan(float x, int h, int H)
 {
     (void)H;
-    const int lane = threadIdx.x & (kLanes - 1);
-    const int in_row = lane & 15;
-    const int reach = h < in_row ? h : in_row;  // lanes back to the row or segment start
-    float y;
-    y = dpp_or_zero<0x111, 0xf>(x);  // row_shr:1
-    x += reach >= 1 ? y : 0.0f;
-    y = dpp_or_zero<0x112, 0xf>(x);  // row_shr:2
-    x += reach >= 2 ? y : 0.0f;
-    y = dpp_or_zero<0x114, 0xf>(x);  // row_shr:4
-    x += reach >= 4 ? y : 0.0f;
-    y = dpp_or_zero<0x118, 0xf>(x);  // row_shr:8
-    x += reach >= 8 ? y : 0.0f;
-    y = dpp_or_zero<0x142, 0xa>(x);  // row_bcast:15 -> rows 1, 3
-    x += h > in_row ? y : 0.0f;
-    y = dpp_or_zero<0x143, 0xc>(x);  // row_bcast:31 -> rows 2, 3
-    x += (lane >= 32 && h > lane - 32) ? y : 0.0f;
-    return x;
+    float a[1] = {x};
+    segmented_scans(a, (int)(threadIdx.x & (kLanes - 1)), h);
+    return a[0];
 }
 
 __device__ __forceinline__ float hinge_box(float x, float lo, float hi)
@@ -85,14 +104,27 @@ __device__ __forceinline__ float hinge_box(float x, float lo, float hi)
 }
 
 // Inclusive suffix sum over the lanes of one particle (the transpose of
-// segmented_scan, used by the reverse pass).
-__device__ __forceinline__ float segmented_suffix_scan(float x, int h, int H)
+// segmented_scan, used by the reverse pass; `left` = H - 1 - h, the steps after
+// this lane's): the same scan towards lower lanes, the rows' sums carried by
+// scalar reads of the rows' first lanes, the last row's first.
+template <int n>
+__device__ __forceinline__ void segmented_suffix_scans(float (&x)[n], int lane, int left)
 {
-    for (int off = 1; off < H; off <<= 1) {
-        const float y = __shfl_down(x, (unsigned)off, kLanes);
-        if (h + off < H) x += y;
+    const int in_row = 15 - (lane & 15);
+    const int reach = left < in_row ? left : in_row;  // lanes on to the row or segment end
+    scan_step<0x101, 0xf>(x, reach >= 1);  // row_shl:1
+    scan_step<0x102, 0xf>(x, reach >= 2);  // row_shl:2
+    scan_step<0x104, 0xf>(x, reach >= 4);  // row_shl:4
+    scan_step<0x108, 0xf>(x, reach >= 8);  // row_shl:8
+#pragma unroll
+    for (int row = 2; row >= 0; --row) {
+        const bool take = (lane >> 4) == row && left > in_row;
+#pragma unroll
+        for (int k = 0; k < n; ++k) {
+            const float y = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x[k]), 16 * (row + 1)));
+            x[k] += take ? y : 0.0f;
+        }
     }
-    return x;
 }
 
 // Comb-filtered noise of one joint at step h (Sec. 3.3), from that joint's
@@ -110,10 +142,10 @@ __device__ __forceinline__ float comb_noise(const float *row, int lane, int h, i
 #pragma unroll
         for (int m = 0; m < 8; ++m) {
             g[m] = tab[kTabComb + k0 + m];
-            e[m] = k0 + m <= h ? row[lane - k0 - m] : 0.0f;
+            e[m] = row[max(lane - k0 - m, 0)];
         }
 #pragma unroll
-        for (int m = 0; m < 8; ++m) acc = fmaf(g[m], e[m], acc);
+        for (int m = 0; m < 8; ++m) acc = fmaf(g[m], k0 + m <= h ? e[m] : 0.0f, acc);
     }
     return acc;
 }
@@ -148,7 +180,7 @@ __device__ __forceinline__ void standard_noise2(Prob &P, uint32_t seed_lo, uint3
 // Standard noise of joints 4k..4k+3 (k = 0 or 1): the same values as
 // standard_noise2's of both halves.
 template <class Prob>
-__device__ __forceinline__ void standard_noise4(Prob &P, const float *__restrict__ noise, int k, int i, int h,
+__device__ __forceinline__ void standard_noise4(Prob &P, uint32_t seed_lo, uint32_t seed_hi, const float *__restrict__ noise, int k, int i, int h,
                                                 uint32_t counter, float e[4])
 {
     const int j0 = 4 * k;
@@ -161,7 +193,7 @@ __device__ __forceinline__ void standard_noise4(Prob &P, const float *__restrict
             e[m] = j0 + m < kDof ? as_global(P.halton)[((size_t)(j0 + m) * P.n_halton + i) * P.H + h] : 0.0f;
     } else {
         uint32_t c0 = (uint32_t)i, c1 = (uint32_t)h, c2 = (uint32_t)k, c3 = counter;
-        philox4x32_10(c0, c1, c2, c3, P.seed_lo, P.seed_hi);
+        philox4x32_10(c0, c1, c2, c3, seed_lo, seed_hi);
         box_muller(c0, c1, e[0], e[1]);
         box_muller(c2, c3, e[2], e[3]);
     }

@@ -22,6 +22,28 @@ constexpr int kPoseWaves = 2;
 constexpr int kMaxH = STORM_MAX_HORIZON;
 constexpr int kMaxSelfItems = 276;  // pairs of at most 24 groups of one body's spheres each
 constexpr int kAdjChunks = 512;  // adjoint workgroups (tile chunks) per problem, at most
+constexpr int kAdjWaves = 4;     // wavefronts of an adjoint workgroup, one tile each at a time
+
+// Up to this many tiles (two per CU) the adjoint splits each tile over a
+// workgroup: the latency of a tile is then all there is.  A call of a step and
+// three refinements, split and a tile per wavefront: 500 x 30 43.8 and 51.1 us,
+// 1024 x 30 (512 tiles) 49.6 and 55.0; past it the split form takes a second
+// round: 2048 x 30 80 and 67 us, 65536 x 30 1290 and 742.
+constexpr int kSplitTiles = 512;
+
+// The adjoint's partials: per tile up to kSplitTiles; then per chunk, a tile per
+// wavefront while there are chunks; and past that in twice the runs, so that a
+// plain launch of twice the wavefronts fills the chip (four per SIMD).
+constexpr int adjoint_chunks(int n_tiles)
+{
+    const int n = n_tiles <= kSplitTiles ? n_tiles : (n_tiles + kAdjWaves - 1) / kAdjWaves;
+    return n < kAdjChunks ? n : kAdjChunks;
+}
+constexpr int kAdjRuns = 2 * kAdjWaves;
+__host__ __device__ constexpr int adjoint_runs(int n_tiles)
+{
+    return n_tiles > kAdjWaves * kAdjChunks ? kAdjRuns : kAdjWaves;
+}
 
 // Offsets (in floats) inside the per-problem table block built at init.
 constexpr int kTabDt = 0;           // dt[H]
@@ -63,7 +85,7 @@ struct alignas(64) ProblemDev {
     uint32_t comb;      // the Gaussian particles' noise is comb-filtered (response in the tables)
     uint32_t cov_step;  // sigma2 is [H][7] (Eq. 5 per step) instead of [7]
     uint32_t selfnet;   // the self-collision term comes from the learned network (its own kernel)
-    uint32_t pad0;
+    int32_t n_chunks;   // the adjoint's workgroups, each a run of tiles (adjoint_chunks)
 
     const float *tables;    // [kTabSize]
     const float *halton;    // [7][n_halton][H] smoothed Halton standard noise
@@ -213,7 +235,7 @@ hipError_t launch_command(const PlainDev *dev, float *cmd, int shift, hipStream_
 // problem (adjoint over the (problem, chunk) items, then reduce + Adam per
 // (problem, joint)), the last also writing the commands cmd [P][7] and the
 // shift.
-hipError_t launch_refine_batch(const ProblemDev *probs, int n_problems, const int2 *items, int n_items,
+hipError_t launch_refine_batch(const ProblemDev *probs, int n_problems, const int2 *items, int n_items, bool split,
                                const RobotDev *robot, const float *x0s, const float *goals, int iterations,
                                float lr, float *cmd, int shift, hipStream_t stream);
 hipError_t launch_fk(const RobotDev &R, const float *q, int n, float *pose, float *manip, hipStream_t stream);
