@@ -29,6 +29,8 @@ struct storm_batch_s {
     uint32_t *d_next = nullptr;    // queue head (0 between launches)
     int2 *d_adj_items = nullptr;   // (problem, tile chunk) items of the batched adjoint
     int n_adj_items = 0;
+    int2 *d_part_items = nullptr;  // (problem, chunk of particles) items of the larger problems' updates
+    int n_part_items = 0;
     bool adj_split = false;        // its items are tiles, each split over a workgroup
     bool differentiable = true;    // every problem's gradient terms are differentiable
     storm_launch_config cfg{8, 0, 1};
@@ -109,7 +111,7 @@ int32_t batch_graph(storm_batch b, const float *d_x0, const float *d_goal, float
     for (int k = 0; e == hipSuccess && k < iterations; ++k) {
         if (launch_batch_step(b, d_x0, d_goal, s) != STORM_OK) e = hipErrorLaunchFailure;
         const bool last_shift = (k == iterations - 1) && shift != 0 && refine_iters == 0;
-        if (e == hipSuccess) e = launch_update_batch(b->d_probs, b->n_problems, d_cmd, last_shift, s);
+        if (e == hipSuccess) e = launch_update_batch(b->d_probs, b->n_problems, b->d_part_items, b->n_part_items, d_cmd, last_shift, s);
     }
     if (e == hipSuccess && refine_iters > 0)
         e = launch_refine_batch(b->d_probs, b->n_problems, b->d_adj_items, b->n_adj_items, b->adj_split, b->d_robot, d_x0, d_goal,
@@ -209,6 +211,10 @@ int32_t storm_batch_init(storm_batch *out, int32_t n_problems, const storm_param
             b->differentiable = false;
     }
     b->n_adj_items = (int)adj.size();
+    std::vector<int2> parts;
+    for (int p = 0; p < n_problems; ++p)
+        for (int c = 0; c < update_parts(probs[p].N, probs[p].H); ++c) parts.push_back(make_int2(p, c));
+    b->n_part_items = (int)parts.size();
     std::vector<int> order(plain.size());
     for (size_t k = 0; k < order.size(); ++k) order[k] = (int)k;
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) { return cost[x] > cost[y]; });
@@ -220,6 +226,9 @@ int32_t storm_batch_init(storm_batch *out, int32_t n_problems, const storm_param
     if (e == hipSuccess) e = balloc(b, &b->d_items_cost, plain.size());
     if (e == hipSuccess) e = balloc(b, &b->d_items_plain, plain.size());
     if (e == hipSuccess) e = balloc(b, &b->d_next, (size_t)1);
+    if (e == hipSuccess && !parts.empty()) e = balloc(b, &b->d_part_items, parts.size());
+    if (e == hipSuccess && !parts.empty())
+        e = hipMemcpy(b->d_part_items, parts.data(), sizeof(int2) * parts.size(), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = balloc(b, &b->d_adj_items, adj.size());
     if (e == hipSuccess)
         e = hipMemcpy(b->d_adj_items, adj.data(), sizeof(int2) * adj.size(), hipMemcpyHostToDevice);
@@ -258,7 +267,7 @@ int32_t storm_batch_update(storm_batch b, float *d_cmd, int32_t shift, void *str
     if (!b || !d_cmd) return STORM_E_NULL;
     if (b->error != STORM_OK) return b->error;
     if (!b->pending) return STORM_E_STATE;
-    if (launch_update_batch(b->d_probs, b->n_problems, d_cmd, shift != 0, static_cast<hipStream_t>(stream)) !=
+    if (launch_update_batch(b->d_probs, b->n_problems, b->d_part_items, b->n_part_items, d_cmd, shift != 0, static_cast<hipStream_t>(stream)) !=
         hipSuccess) {
         b->error = STORM_E_DEVICE;
         return STORM_E_DEVICE;

@@ -206,8 +206,9 @@ hipError_t set_rollout_lds_limit();
 // Whether the learned self-collision network's weight matrices (W1, W2, W3
 // of storm_robot.self_mlp) hold FP16 values only, as its kernel requires.
 bool selfnet_weights_fp16(const float *prm);
-// Floats of the plain update's partial sums (ProblemDev::upd_part); 0 where it
-// needs none.
+// Chunks of particles of a problem's update, and the floats of their partial
+// sums (ProblemDev::upd_part); 0 where one workgroup per joint takes it.
+int update_parts(int N, int H);
 size_t update_part_floats(int N, int H);
 hipError_t launch_update(const ProblemDev &P, const PlainDev *dev, float *mean_out, float *sigma2_out, float *cmd, int shift,
                          hipStream_t stream);
@@ -221,7 +222,8 @@ void pack_selfnet(const float *prm, std::vector<_Float16> &frag, std::vector<flo
 hipError_t launch_rollout_batch(const ProblemDev *probs, const int2 *items, int n_items, uint32_t *next,
                                 const RobotDev &R, const RobotDev *robot, int max_obs, int max_box,
                                 const float *x0s, const float *goals, int waves, int grid, hipStream_t stream);
-hipError_t launch_update_batch(const ProblemDev *probs, int n_problems, float *cmd, int shift, hipStream_t stream);
+hipError_t launch_update_batch(const ProblemDev *probs, int n_problems, const int2 *part_items, int n_part_items,
+                               float *cmd, int shift, hipStream_t stream);
 // Differentiable form: adjoint + fixed-order reduction (grad, J) per joint;
 // with it > 0 the same launch takes Adam step `it` on the stored mean, and
 // with cmd it also writes the command and the shift of the refined mean.

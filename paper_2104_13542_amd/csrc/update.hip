@@ -6,24 +6,16 @@
 //   sigma2' = (1 - alpha_sigma) sigma2
 //             + alpha_sigma mean_h sum_i w_i (u_ih - mu'_h)^2   (per joint)
 //
-// Two forms.  Within the register path's sizes, and in batches, one
-// 1024-thread workgroup per (problem, joint): a joint's new mean and
-// variance depend only on the weights and on that joint's controls, so the
-// seven joints need no synchronisation with each other; every workgroup
-// recomputes min C and the weights of all particles (N exponentials).  The
-// joint's H columns are read by rows of threads, row r taking particles r,
-// r + R, ...  Three ways to gather them:
-//   registers  (N <= 32 R and 2048): every thread loads its up to 32 controls at the
-//              start, together with the costs, so the only global-memory
-//              latency on the path is the first one;
-//   list       (batches; at most 4096 weights not exactly zero, beta small against the
-//              spread of C): only those particles, from a list compacted in
-//              ascending order;
-//   dense      (batches) otherwise: all particles, weights staged in LDS by chunks,
-//              eight loads in flight per thread.
-// Bound by latency: two exchanges, a division and the tail's chain behind the
-// first loads (4.2 us at 500 x 30).  A single problem past those sizes takes
-// update_part_kernel and update_join_kernel (below).
+// Two forms.  Up to 32 R particles (R = 1024 / H rows) and 2048, one
+// 1024-thread workgroup per (problem, joint): a joint's new mean and variance
+// depend only on the weights and on that joint's controls, so the seven joints
+// need no synchronisation with each other; every workgroup recomputes min C and
+// the weights of all particles (N exponentials).  The joint's H columns are
+// read by rows of threads, row r taking particles r, r + R, ...; every thread
+// loads its up to 32 controls at the start, together with the costs, so the
+// only global-memory latency on the path is the first one.  Bound by latency:
+// two exchanges, a division and the tail's chain behind the first loads
+// (4.2 us at 500 x 30).  Past those sizes, update_part and update_join (below).
 //
 // The variance about the new mean comes from the moments about the old one,
 // sum w (d - delta)^2 = S2/S0 - 2 delta S1/S0 + delta^2, in one pass.  Wave
@@ -37,10 +29,8 @@ namespace {
 
 constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / kLanes;
-constexpr int kList = 4096;   // capacity of the nonzero-weight list
-constexpr int kChunk = 8192;  // weights staged in LDS per chunk (dense path)
-constexpr int kUnroll = 8;    // independent loads in flight per thread
-constexpr int kRegU = 32;     // most controls per thread held in registers (register path)
+constexpr int kRows = 8192;   // most rows times controls per thread (weights staged in LDS)
+constexpr int kRegU = 32;     // most controls per thread held in registers
 
 // Full-wave reductions through DPP lane moves (quad permutes, half-row and
 // row mirrors, then the row broadcasts that carry each row's result into the
@@ -110,9 +100,11 @@ __device__ __forceinline__ float block_min(float v, float *s_wave, int lane, int
     return m;
 }
 
+constexpr int kPartMax = 512;      // chunks of the larger form
+
 // Workgroup LDS of the update, declared once per kernel.
 struct UpdateLds {
-    float buf[kChunk];  // register path: weights; list: indices, then weights; dense: a chunk
+    float buf[kRows];  // weights; of the larger form, the chunks' factors
     float red[2 * kThreads];
     float wave[kWaves];
     float wsum[kWaves];
@@ -120,14 +112,14 @@ struct UpdateLds {
     float mold[kMaxH];
 };
 
-// Controls per thread of the register path for N particles over `rows`
-// rows: the smallest of 8, 16 and 32 that holds them (0: other paths).
+// Controls per thread for N particles over `rows` rows: the smallest of 8, 16
+// and 32 that holds them (0: the larger form).
 __host__ __device__ inline int update_slots(int N, int H)
 {
     const int rows = kThreads / H;
     if (N > 2 * kThreads) return 0;
     for (int k = 8; k <= kRegU; k *= 2)
-        if (N <= k * rows && k * rows <= kChunk) return k;
+        if (N <= k * rows && k * rows <= kRows) return k;
     return 0;
 }
 
@@ -246,9 +238,8 @@ __device__ __forceinline__ void update_tail(const TailArgs &T, const int j, cons
 }
 
 // `cov` is P.cov_step, passed apart so that the plain kernel can fix it at
-// compile time; kSlots the register path's controls per thread
-// (update_slots), 32 when that path is not taken; kRegs: it is taken.
-template <int kSlots, bool kRegs = false>
+// compile time; kSlots the controls per thread (update_slots).
+template <int kSlots>
 __device__ __forceinline__ void update_joint(ProblemRef descriptor, const UpdateFirst &first, const int j,
                                              float *__restrict__ mean_out, float *__restrict__ sigma2_out,
                                              float *__restrict__ cmd, int shift, const bool cov, UpdateLds &L)
@@ -269,21 +260,16 @@ __device__ __forceinline__ void update_joint(ProblemRef descriptor, const Update
     float *s_mold = L.mold;
 
     const int lane = t & (kLanes - 1), wave = __builtin_amdgcn_readfirstlane(t / kLanes);
-    int *s_idx = reinterpret_cast<int *>(s_buf);
-    float *s_wl = s_buf + kList;
 
     // thread (r, h): step h of particles r, r + rows, ...
     const int rows = kThreads / H;
     const int r = t / H, h = t - r * H;
     const bool in_rows = r < rows;
-    const global_ptr<const float> U = as_global(first.u) + (size_t)j * N * H + h;
-    const bool regs = kRegs || (N <= kSlots * rows && N <= 2 * kThreads && kSlots * rows <= kChunk);
-
-    // register path: every control load, in flight at once.  The controls come through a buffer resource bounded by the
-    // joint's N H values: slots past the last particle read 0 and cost no
+    // Every control load, in flight at once, through a buffer resource bounded
+    // by the joint's N H values: slots past the last particle read 0 and cost no
     // address arithmetic (the load returns the raw 32 bits).
     float uu[kSlots];
-    if (regs) {
+    {
         const __amdgpu_buffer_rsrc_t ub = __builtin_amdgcn_make_buffer_rsrc(
             const_cast<float *>(first.u + (size_t)j * N * H), (short)0, N * H * (int)sizeof(float), 0x00020000);
         const int stride = rows * H * (int)sizeof(float);
@@ -299,154 +285,48 @@ __device__ __forceinline__ void update_joint(ProblemRef descriptor, const Update
     float S0 = 0.0f, x1 = 0.0f, x2 = 0.0f;
     int any_nonfinite = 0;
     bool ok = false;
-    if (regs) {
-        // min C and the non-finite flag in one exchange, then the weights
-        // and their sum in a second (separate LDS slots: no third barrier)
-        if (t >= N) c0 = INFINITY;
-        if (t + kThreads >= N) c1 = INFINITY;
-        const bool bad = (t < N && !isfinite(c0)) || (t + kThreads < N && !isfinite(c1));
-        const uint64_t bad_lanes = __builtin_amdgcn_ballot_w64(bad);
-        const float wmin = wave_min(fminf(c0, c1));
-        if (lane == 0) {
-            s_wave[wave] = wmin;
-            s_count[wave] = bad_lanes != 0;
-        }
-        __syncthreads();
-        float cmin = s_wave[0];
-        any_nonfinite = s_count[0];
-        for (int k = 1; k < kWaves; ++k) {
-            cmin = fminf(cmin, s_wave[k]);
-            any_nonfinite |= s_count[k];
-        }
-        const float w0 = t < N ? expf((c0 - cmin) * nib) : 0.0f;
-        const float w1 = t + kThreads < N ? expf((c1 - cmin) * nib) : 0.0f;
-        s_buf[t] = w0;
-        s_buf[t + kThreads] = w1;
-        for (int i = 2 * kThreads + t; i < kSlots * rows; i += kThreads) s_buf[i] = 0.0f;  // slots past N
-        const float sw = wave_sum(w0 + w1);
-        if (lane == 0) s_wsum[wave] = sw;
-        __syncthreads();
-        for (int k = 0; k < kWaves; ++k) S0 += s_wsum[k];
-        ok = !any_nonfinite && S0 > 0.0f && isfinite(S0);
-        // straight-line over the 32 slots (weight 0 and control 0 past the
-        // last particle) so that every LDS read is in flight before the first use
-        float a1[4] = {0.0f, 0.0f, 0.0f, 0.0f}, a2[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (in_rows && ok) {
+    // min C and the non-finite flag in one exchange, then the weights
+    // and their sum in a second (separate LDS slots: no third barrier)
+    if (t >= N) c0 = INFINITY;
+    if (t + kThreads >= N) c1 = INFINITY;
+    const bool bad = (t < N && !isfinite(c0)) || (t + kThreads < N && !isfinite(c1));
+    const uint64_t bad_lanes = __builtin_amdgcn_ballot_w64(bad);
+    const float wmin = wave_min(fminf(c0, c1));
+    if (lane == 0) {
+        s_wave[wave] = wmin;
+        s_count[wave] = bad_lanes != 0;
+    }
+    __syncthreads();
+    float cmin = s_wave[0];
+    any_nonfinite = s_count[0];
+    for (int k = 1; k < kWaves; ++k) {
+        cmin = fminf(cmin, s_wave[k]);
+        any_nonfinite |= s_count[k];
+    }
+    const float w0 = t < N ? expf((c0 - cmin) * nib) : 0.0f;
+    const float w1 = t + kThreads < N ? expf((c1 - cmin) * nib) : 0.0f;
+    s_buf[t] = w0;
+    s_buf[t + kThreads] = w1;
+    for (int i = 2 * kThreads + t; i < kSlots * rows; i += kThreads) s_buf[i] = 0.0f;  // slots past N
+    const float sw = wave_sum(w0 + w1);
+    if (lane == 0) s_wsum[wave] = sw;
+    __syncthreads();
+    for (int k = 0; k < kWaves; ++k) S0 += s_wsum[k];
+    ok = !any_nonfinite && S0 > 0.0f && isfinite(S0);
+    // straight-line over the 32 slots (weight 0 and control 0 past the
+    // last particle) so that every LDS read is in flight before the first use
+    float a1[4] = {0.0f, 0.0f, 0.0f, 0.0f}, a2[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (in_rows && ok) {
 #pragma unroll
-            for (int k = 0; k < kSlots; ++k) {
-                const float d = uu[k] - mu;
-                const float wd = s_buf[r + k * rows] * d;
-                a1[k & 3] += wd;
-                a2[k & 3] = fmaf(wd, d, a2[k & 3]);
-            }
-        }
-        x1 = (a1[0] + a1[1]) + (a1[2] + a1[3]);
-        x2 = (a2[0] + a2[1]) + (a2[2] + a2[3]);
-    } else {
-        // min C over all particles, and whether any C is not finite
-        float cmin = INFINITY;
-        int nonfinite = 0;
-        for (int i = t; i < N; i += kThreads) {
-            const float c = C[i];
-            nonfinite |= !isfinite(c);
-            cmin = fminf(cmin, c);
-        }
-        any_nonfinite = __syncthreads_or(nonfinite);
-        cmin = block_min(cmin, s_wave, lane, wave);
-
-        // weight sum (per thread in stride order, per wave, waves in order)
-        // and the list of nonzero weights in ascending particle order
-        float sw = 0.0f;
-        int base = 0;
-        for (int c0 = 0; c0 < N; c0 += kThreads) {
-            const int i = c0 + t;
-            const float w = i < N ? expf((C[i] - cmin) * nib) : 0.0f;
-            sw += w;
-            const bool nz = w > 0.0f;
-            const uint64_t bal = __builtin_amdgcn_ballot_w64(nz);
-            const int before = __builtin_popcountll(bal & ((1ull << lane) - 1ull));
-            if (lane == 0) s_count[wave] = __builtin_popcountll(bal);
-            __syncthreads();
-            int off = 0, total = 0;
-            for (int k = 0; k < kWaves; ++k) {
-                const int c = s_count[k];
-                off += k < wave ? c : 0;
-                total += c;
-            }
-            const int pos = base + off + before;
-            if (nz && pos < kList) {
-                s_idx[pos] = i;
-                s_wl[pos] = w;
-            }
-            base += total;
-            __syncthreads();
-        }
-        sw = wave_sum(sw);
-        if (lane == 0) s_wave[wave] = sw;
-        __syncthreads();
-        for (int k = 0; k < kWaves; ++k) S0 += s_wave[k];
-        ok = !any_nonfinite && S0 > 0.0f && isfinite(S0);
-        const int M = base;
-
-        // moments of d = u - mu over the particles, per step h of joint j
-        const bool act = in_rows && ok;
-        float a1[kUnroll], a2[kUnroll];
-#pragma unroll
-        for (int m = 0; m < kUnroll; ++m) a1[m] = a2[m] = 0.0f;
-        if (M <= kList) {
-            if (act) {
-                int k = r;
-                for (; k + (kUnroll - 1) * rows < M; k += kUnroll * rows) {
-                    float d[kUnroll];
-#pragma unroll
-                    for (int m = 0; m < kUnroll; ++m) d[m] = U[(size_t)s_idx[k + m * rows] * H] - mu;
-#pragma unroll
-                    for (int m = 0; m < kUnroll; ++m) {
-                        const float wd = s_wl[k + m * rows] * d[m];
-                        a1[m] += wd;
-                        a2[m] = fmaf(wd, d[m], a2[m]);
-                    }
-                }
-                for (; k < M; k += rows) {
-                    const float d = U[(size_t)s_idx[k] * H] - mu;
-                    const float wd = s_wl[k] * d;
-                    a1[0] += wd;
-                    a2[0] = fmaf(wd, d, a2[0]);
-                }
-            }
-        } else {
-            for (int c0 = 0; c0 < N; c0 += kChunk) {
-                const int nc = min(kChunk, N - c0);
-                __syncthreads();
-                for (int k = t; k < nc; k += kThreads) s_buf[k] = expf((C[c0 + k] - cmin) * nib);
-                __syncthreads();
-                if (!act) continue;
-                int k = r;
-                for (; k + (kUnroll - 1) * rows < nc; k += kUnroll * rows) {
-                    float d[kUnroll];
-#pragma unroll
-                    for (int m = 0; m < kUnroll; ++m) d[m] = U[(size_t)(c0 + k + m * rows) * H] - mu;
-#pragma unroll
-                    for (int m = 0; m < kUnroll; ++m) {
-                        const float wd = s_buf[k + m * rows] * d[m];
-                        a1[m] += wd;
-                        a2[m] = fmaf(wd, d[m], a2[m]);
-                    }
-                }
-                for (; k < nc; k += rows) {
-                    const float d = U[(size_t)(c0 + k) * H] - mu;
-                    const float wd = s_buf[k] * d;
-                    a1[0] += wd;
-                    a2[0] = fmaf(wd, d, a2[0]);
-                }
-            }
-        }
-#pragma unroll
-        for (int m = 0; m < kUnroll; ++m) {
-            x1 += a1[m];
-            x2 += a2[m];
+        for (int k = 0; k < kSlots; ++k) {
+            const float d = uu[k] - mu;
+            const float wd = s_buf[r + k * rows] * d;
+            a1[k & 3] += wd;
+            a2[k & 3] = fmaf(wd, d, a2[k & 3]);
         }
     }
+    x1 = (a1[0] + a1[1]) + (a1[2] + a1[3]);
+    x2 = (a2[0] + a2[1]) + (a2[2] + a2[3]);
 
     // Wave 0 finishes alone: lane h adds the rows of step h in order (S1, S2)
     // and update_tail does the rest; no further workgroup barrier.
@@ -479,28 +359,10 @@ __global__ __launch_bounds__(kThreads) void update_kernel(const PlainDev *dev, c
     __shared__ UpdateLds L;
     ProblemRef P = uniform_ptr(dev)->P;
     const UpdateFirst first{C, u, N, H};
-    update_joint<kSlots, true>(P, first, blockIdx.x, mean_out, sigma2_out, cmd, shift, kCov, L);
+    update_joint<kSlots>(P, first, blockIdx.x, mean_out, sigma2_out, cmd, shift, kCov, L);
 }
 
-// Workgroup (p, j) of a batch; commands go to cmd[p][7].
-__global__ __launch_bounds__(kThreads) void update_batch_kernel(const ProblemDev *__restrict__ probs,
-                                                                float *__restrict__ cmd, int shift)
-{
-    __shared__ UpdateLds L;
-    const int p = blockIdx.x / kDof, j = blockIdx.x - p * kDof;
-    ProblemRef P = uniform_ptr(probs)[p];
-    const UpdateFirst first{P.C, P.u, P.N, P.H};
-    const int slots = update_slots(P.N, P.H);
-    float *c = cmd + (size_t)p * kDof;
-    if (slots == 8)
-        update_joint<8>(P, first, j, nullptr, nullptr, c, shift, P.cov_step != 0u, L);
-    else if (slots == 16)
-        update_joint<16>(P, first, j, nullptr, nullptr, c, shift, P.cov_step != 0u, L);
-    else
-        update_joint<32>(P, first, j, nullptr, nullptr, c, shift, P.cov_step != 0u, L);
-}
-
-// The same update for particle counts past the register path, over many
+// The larger form: the same update for more particles, over many
 // workgroups.  One workgroup per joint would pull all N H controls of a joint
 // through one CU (N = 65536, H = 30: 90-180 us); instead the particles go to
 // chunks, one workgroup each, which sums the weights and all seven joints'
@@ -509,11 +371,10 @@ __global__ __launch_bounds__(kThreads) void update_batch_kernel(const ProblemDev
 // weight of its least cost.  Particles whose weight (against their chunk's
 // best) is exactly zero are left out; every order is fixed.  64 particles a
 // chunk at least, so that a row of threads still has a few; 512 chunks at
-// most, two workgroups per CU and a join of one pass.  The line is where the
-// one-workgroup form leaves its registers: its list and dense paths lose on
-// both ends of what lies past it.  Control call and graph step, before and
-// after: 4096 x 64 167.7 -> 155.7 us, 65536 x 30 1152 -> 957 us.
-constexpr int kPartMax = 512;      // chunks
+// most, two workgroups per CU and a join of one pass.  The line is where one
+// workgroup can no longer hold a joint's controls in its registers.  Control call
+// and graph step with one workgroup per joint reading twice, and so: 4096 x 64
+// 167.7 -> 155.7 us, 65536 x 30 1152 -> 957 us.
 constexpr int kPartMin = 64;       // particles per chunk, at least
 constexpr int kPartSub = kThreads; // particles weighted at a time
 // floats of one chunk's record: S0, least cost, whether a cost is not finite,
@@ -525,19 +386,21 @@ __host__ __device__ inline int part_chunk(int N)
     const int per = (N + kPartMax - 1) / kPartMax;
     return per < kPartMin ? kPartMin : per;
 }
+__host__ __device__ inline int part_count(int N) { return (N + part_chunk(N) - 1) / part_chunk(N); }
 
-__global__ __launch_bounds__(kThreads) void update_part_kernel(const float *__restrict__ C,
-                                                               const float *__restrict__ u,
-                                                               const float *__restrict__ mean, float *__restrict__ part,
-                                                               int32_t N, int32_t H, float nib, int32_t chunk)
+// Chunk c of a problem.
+__device__ __forceinline__ void update_part(const float *__restrict__ C_in, const float *__restrict__ u_in,
+                                            const float *__restrict__ mean_in, float *__restrict__ part, int32_t N,
+                                            int32_t H, float nib, int32_t chunk, int c)
 {
+    const global_ptr<const float> C = as_global(C_in), u = as_global(u_in), mean = as_global(mean_in);
     __shared__ float s_red[2 * kDof][kThreads];
     __shared__ float s_w[kPartSub];
     __shared__ int s_idx[kPartSub];
     __shared__ float s_wave[kWaves];
     __shared__ int s_count[kWaves];
     const int t = threadIdx.x, lane = t & (kLanes - 1), wave = __builtin_amdgcn_readfirstlane(t / kLanes);
-    const int p0 = blockIdx.x * chunk, p1 = min(N, p0 + chunk);
+    const int p0 = c * chunk, p1 = min(N, p0 + chunk);
     const int rows = kThreads / H, r = t / H, h = t - r * H;
     float mu[kDof];
 #pragma unroll
@@ -546,9 +409,9 @@ __global__ __launch_bounds__(kThreads) void update_part_kernel(const float *__re
     float least = INFINITY;
     int bad = 0;
     for (int i = p0 + t; i < p1; i += kThreads) {
-        const float c = C[i];
-        bad |= !isfinite(c);
-        least = fminf(least, c);
+        const float Ci = C[i];
+        bad |= !isfinite(Ci);
+        least = fminf(least, Ci);
     }
     bad = __syncthreads_or(bad);
     least = block_min(least, s_wave, lane, wave);
@@ -577,7 +440,7 @@ __global__ __launch_bounds__(kThreads) void update_part_kernel(const float *__re
         __syncthreads();
         if (r < rows)
             for (int k = r; k < M; k += rows) {
-                const float *__restrict__ U = u + (size_t)s_idx[k] * H + h;
+                const global_ptr<const float> U = u + (size_t)s_idx[k] * H + h;
                 float d[kDof];
 #pragma unroll
                 for (int j = 0; j < kDof; ++j) d[j] = U[(size_t)j * N * H];
@@ -600,7 +463,7 @@ __global__ __launch_bounds__(kThreads) void update_part_kernel(const float *__re
     sw = wave_sum(sw);
     if (lane == 0) s_wave[wave] = sw;
     __syncthreads();
-    float *out = part + (size_t)blockIdx.x * part_floats(H);
+    const global_ptr<float> out = as_global(part) + (size_t)c * part_floats(H);
     if (t == 0) {
         float S0 = 0.0f;
         for (int k = 0; k < kWaves; ++k) S0 += s_wave[k];
@@ -616,32 +479,50 @@ __global__ __launch_bounds__(kThreads) void update_part_kernel(const float *__re
     }
 }
 
-template <bool kCov>
-__global__ __launch_bounds__(kThreads) void update_join_kernel(const PlainDev *dev, const float *__restrict__ part,
-                                                               float *__restrict__ mean_out,
-                                                               float *__restrict__ sigma2_out,
-                                                               float *__restrict__ cmd, int32_t n_part, int16_t H16,
-                                                               int16_t shift)
+__global__ __launch_bounds__(kThreads) void update_part_kernel(const float *__restrict__ C,
+                                                               const float *__restrict__ u,
+                                                               const float *__restrict__ mean, float *__restrict__ part,
+                                                               int32_t N, int32_t H, float nib, int32_t chunk)
 {
-    __shared__ float s_f[kPartMax];
-    __shared__ float s_red[2 * kThreads];
-    __shared__ float s_wave[kWaves];
-    UpdateProblem P = fetch_problem(uniform_ptr(dev)->P);
+    update_part(C, u, mean, part, N, H, nib, chunk, blockIdx.x);
+}
+
+// Workgroup k of a batch takes chunk items[k] = (problem, chunk).
+__global__ __launch_bounds__(kThreads) void update_part_batch_kernel(const ProblemDev *__restrict__ probs,
+                                                                     const int2 *__restrict__ items)
+{
+    const STORM_CONST_AS int32_t *it = uniform_ptr(reinterpret_cast<const int32_t *>(items));
+    const int p = it[2 * blockIdx.x], c = it[2 * blockIdx.x + 1];
+    ProblemRef P = uniform_ptr(probs)[p];
+    update_part(P.C, P.u, P.mean, P.upd_part, P.N, P.H, -1.0f / P.beta, part_chunk(P.N), c);
+}
+
+// Joint j's update from the problem's chunks.
+__device__ __forceinline__ void update_join(ProblemRef descriptor, const float *__restrict__ part_in, const int j,
+                                            float *__restrict__ mean_out, float *__restrict__ sigma2_out,
+                                            float *__restrict__ cmd, const int n_part, const int H, const int shift,
+                                            const bool cov, UpdateLds &L)
+{
+    float *s_f = L.buf;
+    float *s_red = L.red;
+    float *s_wave = L.wave;
+    const global_ptr<const float> part = as_global(part_in);
+    UpdateProblem P = fetch_problem(descriptor);
     wait_problem(P);
     const int t = threadIdx.x, lane = t & (kLanes - 1), wave = __builtin_amdgcn_readfirstlane(t / kLanes);
-    const int H = H16, j = blockIdx.x, stride = part_floats(H);
+    const int stride = part_floats(H);
     const int rows = kThreads / H, r = t / H, h = t - r * H;
     // every load at once: this chunk's weight sum and least cost, then the
     // moments of chunks r, r + rows, ... at step h
     float S0_c = 0.0f, least_c = INFINITY, bad_c = 0.0f;
     if (t < n_part) {
-        const float *rec = part + (size_t)t * stride;
+        const global_ptr<const float> rec = part + (size_t)t * stride;
         S0_c = rec[0];
         least_c = rec[1];
         bad_c = rec[2];
     }
     const float muo_l = t < H ? as_global(P.mean)[t * kDof + j] : 0.0f;
-    const TailArgs T = fetch_tail(P, mean_out, sigma2_out, cmd, shift, kCov, j, t, H);
+    const TailArgs T = fetch_tail(P, mean_out, sigma2_out, cmd, shift, cov, j, t, H);
     const int bad = __syncthreads_or(bad_c != 0.0f);
     const float least = block_min(least_c, s_wave, lane, wave);
     const float f = t < n_part && !bad ? expf((least_c - least) * (-1.0f / P.beta)) : 0.0f;
@@ -656,7 +537,7 @@ __global__ __launch_bounds__(kThreads) void update_join_kernel(const PlainDev *d
     const bool ok = !bad && S0 > 0.0f && isfinite(S0);
     float x1 = 0.0f, x2 = 0.0f;
     if (r < rows && ok) {
-        const float *__restrict__ src = part + 4 + (size_t)j * H + h;
+        const global_ptr<const float> src = part + 4 + (size_t)j * H + h;
 #pragma unroll 4
         for (int c = r; c < n_part; c += rows) {
             // (a chunk of no weight is left out, as its particles are)
@@ -675,14 +556,53 @@ __global__ __launch_bounds__(kThreads) void update_join_kernel(const PlainDev *d
                 s1 += s_red[k * H + lane];
                 s2 += s_red[kThreads + k * H + lane];
             }
-        update_tail(T, j, H, lane, s1, s2, S0, muo_l, ok, bad, kCov);
+        update_tail(T, j, H, lane, s1, s2, S0, muo_l, ok, bad, cov);
     }
+}
+
+template <bool kCov>
+__global__ __launch_bounds__(kThreads) void update_join_kernel(const PlainDev *dev, const float *__restrict__ part,
+                                                               float *__restrict__ mean_out,
+                                                               float *__restrict__ sigma2_out,
+                                                               float *__restrict__ cmd, int32_t n_part, int16_t H,
+                                                               int16_t shift)
+{
+    __shared__ UpdateLds L;
+    update_join(uniform_ptr(dev)->P, part, blockIdx.x, mean_out, sigma2_out, cmd, n_part, H, shift, kCov, L);
+}
+
+// Workgroup (p, j) of a batch; commands go to cmd[p][7].  (The larger problems'
+// chunks are there.)
+__global__ __launch_bounds__(kThreads) void update_batch_kernel(const ProblemDev *__restrict__ probs,
+                                                                float *__restrict__ cmd, int shift)
+{
+    __shared__ UpdateLds L;
+    const int p = blockIdx.x / kDof, j = blockIdx.x - p * kDof;
+    ProblemRef P = uniform_ptr(probs)[p];
+    const UpdateFirst first{P.C, P.u, P.N, P.H};
+    const int slots = update_slots(P.N, P.H);
+    float *c = cmd + (size_t)p * kDof;
+    if (slots == 8)
+        update_joint<8>(P, first, j, nullptr, nullptr, c, shift, P.cov_step != 0u, L);
+    else if (slots == 16)
+        update_joint<16>(P, first, j, nullptr, nullptr, c, shift, P.cov_step != 0u, L);
+    else if (slots == 32)
+        update_joint<32>(P, first, j, nullptr, nullptr, c, shift, P.cov_step != 0u, L);
+    else
+        update_join(P, P.upd_part, j, nullptr, nullptr, c, part_count(P.N), P.H, shift, P.cov_step != 0u, L);
 }
 
 }  // namespace
 
-hipError_t launch_update_batch(const ProblemDev *probs, int n_problems, float *cmd, int shift, hipStream_t stream)
+hipError_t launch_update_batch(const ProblemDev *probs, int n_problems, const int2 *part_items, int n_part_items,
+                               float *cmd, int shift, hipStream_t stream)
 {
+    if (n_part_items > 0) {
+        hipLaunchKernelGGL(update_part_batch_kernel, dim3((unsigned)n_part_items), dim3(kThreads), 0, stream, probs,
+                           part_items);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     hipLaunchKernelGGL(update_batch_kernel, dim3((unsigned)(n_problems * kDof)), dim3(kThreads), 0, stream, probs,
                        cmd, shift);
     return hipGetLastError();
@@ -693,7 +613,7 @@ hipError_t launch_update(const ProblemDev &P, const PlainDev *dev, float *mean_o
 {
     const int slots = update_slots(P.N, P.H);
     if (slots == 0) {
-        const int chunk = part_chunk(P.N), n_part = (P.N + chunk - 1) / chunk;
+        const int chunk = part_chunk(P.N), n_part = part_count(P.N);
         hipLaunchKernelGGL(update_part_kernel, dim3((unsigned)n_part), dim3(kThreads), 0, stream, P.C, P.u, P.mean,
                            P.upd_part, P.N, P.H, -1.0f / P.beta, chunk);
         const hipError_t e = hipGetLastError();
@@ -714,11 +634,8 @@ hipError_t launch_update(const ProblemDev &P, const PlainDev *dev, float *mean_o
     return hipGetLastError();
 }
 
-size_t update_part_floats(int N, int H)
-{
-    if (update_slots(N, H) != 0) return 0;
-    const int chunk = part_chunk(N);
-    return (size_t)((N + chunk - 1) / chunk) * part_floats(H);
-}
+int update_parts(int N, int H) { return update_slots(N, H) != 0 ? 0 : part_count(N); }
+
+size_t update_part_floats(int N, int H) { return (size_t)update_parts(N, H) * part_floats(H); }
 
 }  // namespace storm

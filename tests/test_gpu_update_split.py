@@ -89,3 +89,36 @@ def test_split_update_keeps_the_policy_on_a_nonfinite_cost(where):
         assert after[2] == 1
     finally:
         r.close()
+
+
+def test_batched_split_update_is_each_problems_own():
+    """A batch that mixes both forms of the update: the same bits as plain."""
+    from paper_2104_13542_amd import storm
+
+    probs = []
+    for k, (n, h) in enumerate([(64, 16), (4100, 8), (513, 64), (1000, 30), (1100, 30), (2049, 1)]):
+        pr = inputs.config3_problem(40 + k)
+        p = pr.params
+        p.n_particles, p.horizon, p.dt, p.n_halton, p.n_null = n, h, np.full(h, 0.02), n // 2, k % 3
+        p.beta, p.cov_per_step = [1.0, 50.0, 1e6][k % 3], k % 2
+        probs.append(pr)
+    goals = torch.tensor([[1, 0, 0, 0, -1, 0, 0, 0, -1, 0.4 + 0.02 * k, 0.1 - 0.03 * k, 0.45]
+                          for k in range(len(probs))], dtype=torch.float32, device="cuda")
+    b = storm.Batch(probs)
+    b.set_config(16, 64, 1)
+    plains = [storm.Rollout(pr) for pr in probs]
+    try:
+        for _ in range(2):
+            b.step(goals)
+            cmd = b.update(shift=True).clone()
+            for k, r in enumerate(plains):
+                r.step(goals[k])
+                c = r.update(shift=True)[0]
+                torch.cuda.synchronize()
+                assert torch.equal(cmd[k], c), k
+                for x, y in zip(b.get_state(k)[:2], r.get_state()[:2]):
+                    np.testing.assert_array_equal(x, y)
+    finally:
+        b.close()
+        for r in plains:
+            r.close()
