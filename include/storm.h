@@ -430,6 +430,10 @@ int32_t storm_plant_step(float *d_x, const float *d_cmd, int32_t n, float dt, vo
 int32_t storm_fk(const storm_robot *robot, const float *d_q, int32_t n, float *d_pose, float *d_manip,
                  void *stream);
 
+/* The same with the configurations as rows, d_q [n][7]. */
+int32_t storm_fk_rows(const storm_robot *robot, const float *d_q, int32_t n, float *d_pose, float *d_manip,
+                      void *stream);
+
 /* Human-readable name of a status code (static storage). */
 const char *storm_status_str(int32_t status);
 

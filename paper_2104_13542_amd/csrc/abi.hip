@@ -818,7 +818,9 @@ int32_t storm_rollout_graph_destroy(storm_graph graph)
     return STORM_OK;
 }
 
-int32_t storm_fk(const storm_robot *robot, const float *d_q, int32_t n, float *d_pose, float *d_manip, void *stream)
+namespace {
+int32_t enqueue_fk(const storm_robot *robot, const float *d_q, bool rows, int32_t n, float *d_pose, float *d_manip,
+                   void *stream)
 {
     if (!robot) return STORM_E_NULL;
     if (n < 0) return STORM_E_RANGE;
@@ -829,8 +831,20 @@ int32_t storm_fk(const storm_robot *robot, const float *d_q, int32_t n, float *d
     RobotDev R{};
     fill_robot_consts(robot, R);
     R.n_spheres = 0;
-    const hipError_t e = storm::launch_fk(R, d_q, n, d_pose, d_manip, static_cast<hipStream_t>(stream));
+    const hipError_t e = storm::launch_fk(R, d_q, rows, n, d_pose, d_manip, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? STORM_OK : STORM_E_DEVICE;
+}
+}  // namespace
+
+int32_t storm_fk(const storm_robot *robot, const float *d_q, int32_t n, float *d_pose, float *d_manip, void *stream)
+{
+    return enqueue_fk(robot, d_q, false, n, d_pose, d_manip, stream);
+}
+
+int32_t storm_fk_rows(const storm_robot *robot, const float *d_q, int32_t n, float *d_pose, float *d_manip,
+                      void *stream)
+{
+    return enqueue_fk(robot, d_q, true, n, d_pose, d_manip, stream);
 }
 
 }  // extern "C"

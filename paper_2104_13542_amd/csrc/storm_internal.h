@@ -240,7 +240,7 @@ hipError_t launch_command(const PlainDev *dev, float *cmd, int shift, hipStream_
 hipError_t launch_refine_batch(const ProblemDev *probs, int n_problems, const int2 *items, int n_items, bool split,
                                const RobotDev *robot, const float *x0s, const float *goals, int iterations,
                                float lr, float *cmd, int shift, hipStream_t stream);
-hipError_t launch_fk(const RobotDev &R, const float *q, int n, float *pose, float *manip, hipStream_t stream);
+hipError_t launch_fk(const RobotDev &R, const float *q, bool rows, int n, float *pose, float *manip, hipStream_t stream);
 
 // Self-collision work items of the robot: pairs of groups (runs of up to four
 // spheres of one body) on bodies at least two apart, four integers each;

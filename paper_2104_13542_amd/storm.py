@@ -89,6 +89,7 @@ EXPORTS = (
     "storm_batch_set_state", "storm_batch_costs", "storm_batch_destroy", "storm_plant_step",
     "storm_rollout_grad", "storm_rollout_grad_noalloc", "storm_rollout_refine", "storm_rollout_graph_create_refine",
     "storm_batch_refine", "storm_batch_graph_create_refine", "storm_rollout_set_ball", "storm_rollout_control",
+    "storm_fk_rows",
 )
 
 
@@ -118,6 +119,7 @@ def lib():
         L.storm_rollout_get_state.argtypes = [vp, vp, vp, vp, vp]
         L.storm_rollout_set_state.argtypes = [vp, vp, vp, vp, vp]
         L.storm_fk.argtypes = [ctypes.POINTER(storm_robot), vp, i32, vp, vp, vp]
+        L.storm_fk_rows.argtypes = L.storm_fk.argtypes
         L.storm_rollout_graph_create.argtypes = [vp, vp, vp, vp, i32, i32, vp, ctypes.POINTER(vp)]
         L.storm_rollout_graph_launch.argtypes = [vp, vp]
         L.storm_rollout_graph_destroy.argtypes = [vp]
@@ -159,12 +161,15 @@ def _check(code, where):
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    # an int: the functions' argument types make the pointer of it
+    return t.data_ptr() if t is not None else None
 
 
 def _stream():
     # the raw handle of the current stream, without building a Stream object
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    # or asking for the device through torch.cuda's checks (every caller holds
+    # a context or a tensor of the device)
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def make_params(p: "inputs.Params"):
@@ -201,16 +206,13 @@ def make_params(p: "inputs.Params"):
 def make_robot(spheres=None, dh=None, q_min=None, q_max=None, qd_max=None, self_mlp=None):
     """storm_robot for the Panda (or the given DH and limits); self_mlp: the
     learned self-collision network's parameters [STORM_SELF_MLP_SIZE]."""
-    r = storm_robot()
-    dh = inputs.PANDA_DH if dh is None else dh
-    for k in range(8):
-        for c in range(3):
-            r.dh[k][c] = float(dh[k][c])
-    qlo = inputs.PANDA_Q_MIN if q_min is None else q_min
-    qhi = inputs.PANDA_Q_MAX if q_max is None else q_max
-    qd = inputs.PANDA_QD_MAX if qd_max is None else qd_max
-    for j in range(DOF):
-        r.q_min[j], r.q_max[j], r.qd_max[j] = float(qlo[j]), float(qhi[j]), float(qd[j])
+    # (the struct begins with its floats: dh, q_min, q_max, qd_max)
+    flat = np.zeros(ctypes.sizeof(storm_robot) // 4, dtype=np.float32)
+    flat[:24].reshape(8, 3)[:] = np.asarray(inputs.PANDA_DH if dh is None else dh)[:8, :3]
+    for k, (given, default) in enumerate(((q_min, inputs.PANDA_Q_MIN), (q_max, inputs.PANDA_Q_MAX),
+                                          (qd_max, inputs.PANDA_QD_MAX))):
+        flat[24 + DOF * k:24 + DOF * (k + 1)] = (default if given is None else given)[:DOF]
+    r = storm_robot.from_buffer_copy(flat)
     sph = np.ascontiguousarray(np.zeros((0, 5)) if spheres is None else spheres, dtype=np.float32)
     r.n_spheres = sph.shape[0]
     r.spheres = sph.ctypes.data_as(ctypes.POINTER(ctypes.c_float)) if sph.size else None
@@ -242,6 +244,7 @@ class Rollout:
         sc, self._obs = make_scene(problem.obstacles)
         self._robot = rb
         handle = ctypes.c_void_p()
+        torch.cuda.init()
         with torch.cuda.device(self.device):
             _check(lib().storm_rollout_init(ctypes.byref(handle), ctypes.byref(sp), ctypes.byref(rb),
                                             ctypes.byref(sc), _stream()), "storm_rollout_init")
@@ -249,6 +252,10 @@ class Rollout:
         self.x0 = torch.tensor(np.concatenate([problem.q0, problem.v0, problem.a0]), dtype=torch.float32,
                                device=self.device)
         self.cmd = torch.zeros(DOF, dtype=torch.float32, device=self.device)
+        # what new outputs are shaped like (an allocation like another tensor
+        # costs less host time than one from a shape)
+        self._mean_like = torch.empty((self.H, DOF), dtype=torch.float32, device=self.device)
+        self._sigma2_like = torch.empty(self._sig_shape(), dtype=torch.float32, device=self.device)
 
     # -- lifecycle ---------------------------------------------------------
     def close(self):
@@ -278,14 +285,13 @@ class Rollout:
                 out[k] = torch.empty((DOF, N, H), **kw)
             out["c"] = torch.empty((N, H), **kw)
             out["terms"] = torch.empty((NTERMS, N, H), **kw)
-            ptrs = [ctypes.c_void_p(out[k].data_ptr()) for k in ("u", "q", "v", "a", "c", "terms")]
-            dbg = storm_debug(*ptrs)
+            dbg = storm_debug(*[out[k].data_ptr() for k in ("u", "q", "v", "a", "c", "terms")])
         if task_space:
             if dbg is None:
                 dbg = storm_debug()
             for k in ("xd", "xdd"):
                 out[k] = torch.empty((6, N, H), dtype=torch.float32, device=self.device)
-                setattr(dbg, k, ctypes.c_void_p(out[k].data_ptr()))
+                setattr(dbg, k, out[k].data_ptr())
         if C is None:
             C = torch.empty(N, dtype=torch.float32, device=self.device)
         out["C"] = C
@@ -307,9 +313,8 @@ class Rollout:
     def update(self, shift=True, want_mean=True, cmd=None):
         """Policy update; returns (cmd [7], mean' [H][7] or None, sigma2' [7]
         ([H][7] with cov_per_step) or None)."""
-        kw = dict(dtype=torch.float32, device=self.device)
-        mean = torch.empty((self.H, DOF), **kw) if want_mean else None
-        sigma2 = torch.empty(self._sig_shape(), **kw) if want_mean else None
+        mean = torch.empty_like(self._mean_like) if want_mean else None
+        sigma2 = torch.empty_like(self._sigma2_like) if want_mean else None
         cmd = self.cmd if cmd is None else cmd
         _check(lib().storm_rollout_update(self._h, _ptr(mean), _ptr(sigma2), _ptr(cmd), int(bool(shift)),
                                           _stream()), "storm_rollout_update")
@@ -357,7 +362,7 @@ class Rollout:
         """(dJ/dmu [H][7], J) of the expected horizon cost at `mean` with the
         last step's noise (or `noise` [7][N][H])."""
         x0 = self.x0 if x0 is None else x0
-        g = torch.empty((self.H, DOF), dtype=torch.float32, device=self.device)
+        g = torch.empty_like(self._mean_like)
         J = torch.empty(1, dtype=torch.float32, device=self.device)
         _check(lib().storm_rollout_grad(self._h, _ptr(x0), _ptr(goal), _ptr(mean.contiguous()), _ptr(noise),
                                         _ptr(g), _ptr(J), _stream()), "storm_rollout_grad")
@@ -395,8 +400,7 @@ class StepGraph:
         self._launch = lib().storm_rollout_graph_launch
 
     def launch(self, stream=None):
-        s = ctypes.c_void_p(torch.cuda.current_stream().cuda_stream if stream is None else stream)
-        code = self._launch(self._h, s)
+        code = self._launch(self._h, _stream() if stream is None else stream)
         if code != STORM_OK:
             raise StormError(code, "storm_rollout_graph_launch")
 
@@ -432,6 +436,7 @@ class Batch:
         rb, sph = make_robot(self.problems[0].spheres)
         self._keep += [rb, sph]
         h = ctypes.c_void_p()
+        torch.cuda.init()
         with torch.cuda.device(self.device):
             _check(lib().storm_batch_init(ctypes.byref(h), P, params, ctypes.byref(rb), scenes, _stream()),
                    "storm_batch_init")
@@ -544,11 +549,14 @@ def plant_step(x, cmd, dt):
 
 def fk(q, spheres=None):
     """Batched flange pose [n][12] and manipulability [n] of joint
-    configurations q [n][7] (device tensor) through storm_fk."""
+    configurations q [n][7] (device tensor) through storm_fk, or, where q is
+    as a program holds it (contiguous float32 rows of seven), storm_fk_rows."""
     n = q.shape[0]
-    qs = q.t().contiguous()
+    rows = q.dtype == torch.float32 and q.dim() == 2 and q.shape[1] == DOF and q.is_contiguous()
+    qs = q if rows else q.t().contiguous()
+    call = lib().storm_fk_rows if rows else lib().storm_fk
     pose = torch.empty((12, n), dtype=torch.float32, device=q.device)
     manip = torch.empty(n, dtype=torch.float32, device=q.device)
     rb, _keep = make_robot(spheres)
-    _check(lib().storm_fk(ctypes.byref(rb), _ptr(qs), int(n), _ptr(pose), _ptr(manip), _stream()), "storm_fk")
+    _check(call(ctypes.byref(rb), _ptr(qs), int(n), _ptr(pose), _ptr(manip), _stream()), "storm_fk")
     return pose.t(), manip
