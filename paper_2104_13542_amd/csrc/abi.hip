@@ -512,7 +512,7 @@ fail:
 static hipError_t enqueue_rollout(storm_ctx ctx, const float *d_x0, const float *d_goal, const float *d_noise,
                                   const StepOut &out, hipStream_t s)
 {
-    hipError_t e = storm::launch_rollout(ctx->P, ctx->R, ctx->dev, d_x0, d_goal, d_noise, out, ctx->waves, s);
+    hipError_t e = storm::launch_rollout(ctx->P, ctx->R, ctx->dev, d_x0, d_goal, d_noise, out, s);
     if (e == hipSuccess && ctx->P.selfnet)
         e = storm::launch_selfnet(ctx->P, ctx->dev, out, s);
     return e;

@@ -164,6 +164,12 @@ struct NoQueue {  // the plain form: one tile per workgroup
     __device__ __forceinline__ void fetch() {}
     __device__ __forceinline__ void store() {}
 };
+struct TileStride {  // the plain form with many tiles: every gridDim-th
+    int parity = 0;
+    __device__ __forceinline__ void draw() {}
+    __device__ __forceinline__ void fetch() {}
+    __device__ __forceinline__ void store() {}
+};
 struct TileQueue {
     uint32_t *next;
     const int2 *items;
@@ -210,13 +216,15 @@ __device__ __forceinline__ bool capsules_meet(const float4 a1, const float4 b1, 
 
 // One 64-lane tile of one problem, executed by the W waves of the calling
 // workgroup; smem is the workgroup's dynamic LDS (rollout_lds_bytes).
+// kSums: the environment term's partial sums, over spheres s, s + kSums, ...
+// (W, or 2 W: the bits of a workgroup of twice the waves).
 // kTask: the task-space form, which adds the flange velocity and
 // acceleration outputs (Eq. 8), the ball-on-tray term and the joint
 // positions the learned self-collision network reads.
 // The fields of the descriptors are scalar loads where they are used (held as
 // copies they overflowed the SGPRs into lanes of VGPRs, 180 lane moves per
 // wave and tile).
-template <int W, bool kTask, class Queue>
+template <int W, bool kTask, int kSums, class Queue>
 __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRef R, const TileFirst &first, const int tile,
                                              const float *__restrict__ x0, const float *__restrict__ goal,
                                              const float *__restrict__ noise, const StepOut &out, float *smem)
@@ -233,8 +241,8 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
     // the obstacles (A0 - D2) and the lists of phase D1 (D1 - D2).
     const int S = first.n_spheres;
     float *s_fr = smem;                        // [8 frames][12][64]: R row-major, p
-    float *s_penv = s_fr;                      // [W][64] (over the frames, after phase C)
-    float *s_pself = s_penv + W * kLanes;      // [W][64]
+    float *s_penv = s_fr;                      // [kSums][64] (over the frames, after phase C)
+    float *s_pself = s_penv + kSums * kLanes;  // [W][64]
     float *s_terms = s_fr + 96 * kLanes;       // [kTerms][64]
     float *s_cen = s_terms + kTerms * kLanes;  // [S][3][64]
     float *s_eps = s_cen;                      // [8][64] (before the centres)
@@ -633,7 +641,9 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
     // ---- D2: collision terms --------------------------------------------------
     // Environment (spheres round robin over the waves), then self-collision
     // (items from a queue).
-    float env = 0.0f, selfpen = 0.0f;
+    float env[kSums / W], selfpen = 0.0f;
+#pragma unroll
+    for (int m = 0; m < kSums / W; ++m) env[m] = 0.0f;
     if (nobs > 0) {
         const int nso = first.n_sph_obs;
         // lane k holds the body of this wave's k-th sphere and how many
@@ -701,7 +711,10 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
                     }
                 }
             }
-            env += best;
+            if (W == kSums || (k_s & 1) == 0)
+                env[0] += best;
+            else
+                env[kSums / W - 1] += best;
         }
     }
     if (mask & STORM_COST_SELF) {
@@ -771,7 +784,9 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
                 for (int u = 0; u < 4; ++u) selfpen = fmaxf(selfpen, (rs[u] + rt[k]) - fast_sqrt(d2[k][u]));
         }
     }
-    s_penv[wave * kLanes + lane] = env;
+    static_assert(kSums == W || kSums == 2 * W, "one or two sums a wave");
+#pragma unroll
+    for (int m = 0; m < kSums / W; ++m) s_penv[(wave + m * W) * kLanes + lane] = env[m];
     s_pself[wave * kLanes + lane] = selfpen;
 
     __syncthreads();
@@ -797,7 +812,7 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
         if (mask & STORM_COST_SELF)
             for (int w = 0; w < W; ++w) t[6] = fmaxf(t[6], s_pself[w * kLanes + pos]);
         if (mask & STORM_COST_ENV)
-            for (int w = 0; w < W; ++w) t[7] += s_penv[w * kLanes + pos];
+            for (int w = 0; w < kSums; ++w) t[7] += s_penv[w * kLanes + pos];
         const float *wc = s_par + kParW;  // w_pos, w_rot, a_joint, a_vel, a_stop, a_manip, a_coll
         float c = wc[0] * t[0];
         c = fmaf(wc[1], t[1], c);
@@ -846,7 +861,30 @@ __global__ __launch_bounds__(W * kLanes) void rollout_kernel(const PlainDev *dev
     const STORM_CONST_AS PlainDev &D = *uniform_ptr(dev);
     const TileFirst first = fetch_first(D.P, D.R, step, mean, N, H);
     NoQueue none;
-    rollout_tile<W, kTask>(none, D.P, D.R, first, blockIdx.x, x0, goal, kDebug ? noise : nullptr, o, smem);
+    rollout_tile<W, kTask, W>(none, D.P, D.R, first, blockIdx.x, x0, goal, kDebug ? noise : nullptr, o, smem);
+}
+
+// Persistent form for one problem with more tiles than compute units: two
+// workgroups of 8 waves share a CU, so that one's barriers and serial phases
+// are covered by the other, and each takes every gridDim-th tile, the last
+// phase of a tile beside the first of the next.  (No queue: tiles of one
+// problem differ little, and a counter would be one more state that two
+// streams could share.)  Same bits as one tile per workgroup.
+template <int W>
+__global__ __launch_bounds__(W * kLanes) __attribute__((amdgpu_waves_per_eu(4))) void rollout_loop_kernel(
+    const PlainDev *dev, const float *__restrict__ x0, const float *__restrict__ goal, float *C_out, int32_t n_tiles)
+{
+    extern __shared__ __attribute__((aligned(16))) float smem[];  // (holds 16-byte records)
+    StepOut o{};
+    o.C = C_out;
+    TileStride stride;
+    for (int tile = blockIdx.x; tile < n_tiles; tile += gridDim.x) {
+        const STORM_CONST_AS PlainDev *D = uniform_ptr(dev);
+        asm volatile("" : "+s"(D));  // fields read in each tile, not kept over the loop
+        const TileFirst first = fetch_first(D->P, D->R, D->P.step, D->P.mean, D->P.N, D->P.H);
+        rollout_tile<W, false, 2 * W>(stride, D->P, D->R, first, tile, x0, goal, nullptr, o, smem);
+        stride.parity ^= 1;
+    }
 }
 
 // Persistent form for many problems: each workgroup takes (problem, tile)
@@ -877,7 +915,7 @@ __global__ __launch_bounds__(W * kLanes) __attribute__((amdgpu_waves_per_eu(4)))
         asm volatile("" : "+s"(R));  // fields read in each tile, not kept over the loop
         ProblemRef P = uniform_ptr(probs)[p];
         const TileFirst first = fetch_first(P, *R, P.step, P.mean, P.N, P.H);
-        rollout_tile<W, false>(queue, P, *R, first, tile, x0s + (size_t)p * 3 * kDof, goals + (size_t)p * 12, nullptr,
+        rollout_tile<W, false, W>(queue, P, *R, first, tile, x0s + (size_t)p * 3 * kDof, goals + (size_t)p * 12, nullptr,
                                StepOut{}, smem);
         queue.parity ^= 1;
         p = __builtin_amdgcn_readfirstlane(s_item[queue.parity][0]);
@@ -901,19 +939,16 @@ hipError_t set_rollout_lds_limit()
 {
     const int plain = (int)rollout_lds_bytes(STORM_MAX_SPHERES, STORM_MAX_OBSTACLES, STORM_MAX_OBSTACLES, kMaxSelfItems);
     const int task = (int)rollout_lds_bytes(STORM_MAX_SPHERES, STORM_MAX_OBSTACLES, STORM_MAX_OBSTACLES, kMaxSelfItems, true);
-    const void *fns[10] = {reinterpret_cast<const void *>(&rollout_kernel<16, false, false>),
-                           reinterpret_cast<const void *>(&rollout_kernel<8, false, false>),
-                           reinterpret_cast<const void *>(&rollout_kernel<16, false, true>),
-                           reinterpret_cast<const void *>(&rollout_kernel<8, false, true>),
-                           reinterpret_cast<const void *>(&rollout_batch_kernel<16>),
-                           reinterpret_cast<const void *>(&rollout_batch_kernel<8>),
-                           reinterpret_cast<const void *>(&rollout_kernel<16, true, false>),
-                           reinterpret_cast<const void *>(&rollout_kernel<8, true, false>),
-                           reinterpret_cast<const void *>(&rollout_kernel<16, true, true>),
-                           reinterpret_cast<const void *>(&rollout_kernel<8, true, true>)};
-    for (int k = 0; k < 10; ++k) {
+    const void *fns[] = {reinterpret_cast<const void *>(&rollout_kernel<16, false, false>),
+                         reinterpret_cast<const void *>(&rollout_kernel<16, false, true>),
+                         reinterpret_cast<const void *>(&rollout_loop_kernel<8>),
+                         reinterpret_cast<const void *>(&rollout_batch_kernel<16>),
+                         reinterpret_cast<const void *>(&rollout_batch_kernel<8>),
+                         reinterpret_cast<const void *>(&rollout_kernel<16, true, false>),
+                         reinterpret_cast<const void *>(&rollout_kernel<16, true, true>)};
+    for (int k = 0; k < 7; ++k) {
         const hipError_t e =
-            hipFuncSetAttribute(fns[k], hipFuncAttributeMaxDynamicSharedMemorySize, k < 6 ? plain : task);
+            hipFuncSetAttribute(fns[k], hipFuncAttributeMaxDynamicSharedMemorySize, k < 5 ? plain : task);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -936,8 +971,17 @@ hipError_t launch_rollout_batch(const ProblemDev *probs, const int2 *items, int 
     return hipGetLastError();
 }
 
+// From one tile more than there are compute units, and where two workgroups'
+// LDS (with their static part) fits a CU, the looping form; up to that, a tile
+// has a CU to itself and 16 waves are the shorter path.  Control calls, a
+// 16-wave workgroup per tile and looping: 200 x 64 (a tile each) 12.5 and 13.8
+// us, 257 x 64 17.8 and 15.8, 512 x 64 19.5 and 16.7, 640 x 64 28.5 and 25.5,
+// 2048 x 64 54.9 and 45.0, 65536 x 30 644 and 501.
+constexpr int kLoopGroups = 512, kLoopTiles = 257;
+constexpr size_t kLoopLds = 80 * 1024 - 2048;
+
 hipError_t launch_rollout(const ProblemDev &P, const RobotDev &R, const PlainDev *dev, const float *x0, const float *goal,
-                          const float *noise, const StepOut &out, int waves, hipStream_t stream)
+                          const float *noise, const StepOut &out, hipStream_t stream)
 {
     // the task-space form only where it is asked for: the ball term, the
     // network's joint positions, or the flange velocity and acceleration
@@ -946,14 +990,15 @@ hipError_t launch_rollout(const ProblemDev &P, const RobotDev &R, const PlainDev
                        out.a != nullptr || out.c != nullptr || out.terms != nullptr || out.xd != nullptr ||
                        out.xdd != nullptr;
     const size_t lds = rollout_lds_bytes(R.n_spheres, P.n_sph_obs + P.n_box_obs, P.n_box_obs, R.n_self_items, task);
-    const dim3 grid((unsigned)P.n_tiles);
-    if (waves != 16 && waves != 8) return hipErrorInvalidValue;
-    auto kernel = waves == 16 ? (task ? (debug ? rollout_kernel<16, true, true> : rollout_kernel<16, true, false>)
-                                      : (debug ? rollout_kernel<16, false, true> : rollout_kernel<16, false, false>))
-                              : (task ? (debug ? rollout_kernel<8, true, true> : rollout_kernel<8, true, false>)
-                                      : (debug ? rollout_kernel<8, false, true> : rollout_kernel<8, false, false>));
-    hipLaunchKernelGGL(kernel, grid, dim3(waves * kLanes), lds, stream, dev, P.N, P.H, x0, goal, P.mean, P.step,
-                       out.C, noise, out);
+    if (!task && !debug && P.n_tiles >= kLoopTiles && lds <= kLoopLds) {
+        hipLaunchKernelGGL(rollout_loop_kernel<8>, dim3(kLoopGroups), dim3(8 * kLanes), lds, stream, dev, x0, goal,
+                           out.C, P.n_tiles);
+        return hipGetLastError();
+    }
+    auto kernel = task ? (debug ? rollout_kernel<16, true, true> : rollout_kernel<16, true, false>)
+                       : (debug ? rollout_kernel<16, false, true> : rollout_kernel<16, false, false>);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)P.n_tiles), dim3(16 * kLanes), lds, stream, dev, P.N, P.H, x0, goal,
+                       P.mean, P.step, out.C, noise, out);
     return hipGetLastError();
 }
 

@@ -199,7 +199,7 @@ hipError_t launch_init_tables(const ProblemDev &P, const float *d_dt_raw, const 
 // Plain launches take the host's copy of the problem for the launch shape and
 // the device's (PlainDev) for the kernel.
 hipError_t launch_rollout(const ProblemDev &P, const RobotDev &R, const PlainDev *dev, const float *x0, const float *goal,
-                          const float *noise, const StepOut &out, int waves, hipStream_t stream);
+                          const float *noise, const StepOut &out, hipStream_t stream);
 // Raise the dynamic-LDS limit of the rollout kernels to what the largest
 // sphere model needs (idempotent).
 hipError_t set_rollout_lds_limit();
@@ -257,7 +257,6 @@ std::vector<float> body_bounds(const storm_robot *robot);
 // One plain-form problem (the storm_ctx handle of the C ABI).
 struct storm_ctx_s {
     int device = 0;
-    int waves = 16;
     int32_t error = STORM_OK;  // sticky device error
     bool pending = false;      // a step waits for its update
     storm_params params{};
