@@ -14,6 +14,13 @@
 // vector units; the term then joins the running cost (weight a_coll, as the
 // sphere model's) and, through a segmented scan over the steps, the horizon
 // cost C_i that the rollout kernel wrote.
+//
+// One workgroup per CU (104 KB of LDS) and one or two rounds at the usual sizes:
+// bound by latency and by LDS traffic.  A wave takes 32 units of 32 rows of
+// layer 2, so that the activations are read four times (eight with 16 units of
+// all rows), a lane's results go to LDS in one write (four), and what the last
+// phase reads of memory is loaded at the start.  At 500 x 30 8.9 -> 7.6 us, the
+// control call with the network 22.9 -> 21.6 us.
 #include "sampling.h"
 #include "selfnet.h"
 #include "storm_internal.h"
@@ -43,6 +50,13 @@ __global__ __launch_bounds__(kNetThreads) void selfnet_kernel(const PlainDev *de
                                                               float *c_out, float *terms_out)
 {
     ProblemRef P = uniform_ptr(dev)->P;
+    // what the last phase reads of the problem, issued first and waited for
+    // behind the weight loads
+    float a_coll = P.a_coll;
+    const float *tables = P.tables;
+    float *C_sum = P.C;
+    __builtin_amdgcn_sched_barrier(0);
+    __shared__ __attribute__((aligned(16))) float s_w4[kNetH3];
     __shared__ __attribute__((aligned(16))) unsigned char s_lds[kNetLds];
     _Float16 *s_x = reinterpret_cast<_Float16 *>(s_lds);
     _Float16 *s_a1 = reinterpret_cast<_Float16 *>(s_lds + kOffA1);
@@ -57,7 +71,7 @@ __global__ __launch_bounds__(kNetThreads) void selfnet_kernel(const PlainDev *de
     // row `lane` of the tile; wave j < 7 encodes joint j of every row.  Its
     // position is loaded first, so that waiting for it does not wait for the
     // weight loads behind it (an invalid row reads particle 0 and is ignored).
-    const int pl = lane / H;
+    const int pl = (int)(((float)lane + 0.5f) * __builtin_amdgcn_rcpf((float)H));  // lane / H (exact, as in kernel R)
     const int h = lane - pl * H;
     const int i = tile * ppt + pl;
     const bool valid = pl < ppt && i < N;
@@ -65,36 +79,50 @@ __global__ __launch_bounds__(kNetThreads) void selfnet_kernel(const PlainDev *de
     const float qv = qbuf[((size_t)jq * N + (valid ? i : 0)) * H + h];
     __builtin_amdgcn_sched_barrier(0);  // keep that load ahead of the weight loads
 
-    // every weight fragment this wave uses, loaded up front (52 VGPRs)
+    // every weight fragment this wave uses, loaded up front (104 VGPRs)
     // (in the order of use, each layer's biases with its fragments)
     const half4_t *F1 = reinterpret_cast<const half4_t *>(frag + kNetFrag1);
     const half8_t *F2 = reinterpret_cast<const half8_t *>(frag + kNetFrag2);
     const half8_t *F3 = reinterpret_cast<const half8_t *>(frag + kNetFrag3);
     half4_t b1[2];
-    half8_t b2[8], b3[4];
+    half8_t b2[2][8], b3[2][4];
 #pragma unroll
     for (int t = 0; t < 2; ++t) b1[t] = F1[(2 * wave + t) * kLanes + lane];
-    const float bias1[2] = {bias[kNetBias1 + 16 * (2 * wave) + (lane & 15)],
-                            bias[kNetBias1 + 16 * (2 * wave + 1) + (lane & 15)]};
+    const float4_t bias1[2] = {net_bias(bias + kNetBias1, 2 * wave, lane), net_bias(bias + kNetBias1, 2 * wave + 1, lane)};
     __builtin_amdgcn_sched_barrier(0);
+    const int n2 = 2 * (wave >> 1), m2 = 2 * (wave & 1);  // layer 2: 32 units of 32 rows
 #pragma unroll
-    for (int s = 0; s < 8; ++s) b2[s] = F2[(wave * 8 + s) * kLanes + lane];
-    const float bias2 = bias[kNetBias2 + 16 * wave + (lane & 15)];
+    for (int s = 0; s < 8; ++s)
+#pragma unroll
+        for (int n = 0; n < 2; ++n) b2[n][s] = F2[((n2 + n) * 8 + s) * kLanes + lane];
+    const float4_t bias2[2] = {net_bias(bias + kNetBias2, n2, lane), net_bias(bias + kNetBias2, n2 + 1, lane)};
     __builtin_amdgcn_sched_barrier(0);
+    const int n3 = 2 * (wave & 1), m3 = wave >> 1;  // layer 3: 32 units of 16 rows
 #pragma unroll
-    for (int s = 0; s < 4; ++s) b3[s] = F3[((wave >> 1) * 4 + s) * kLanes + lane];
-    const float bias3 = bias[kNetBias3 + 16 * (wave >> 1) + (lane & 15)];
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int n = 0; n < 2; ++n) b3[n][s] = F3[((n3 + n) * 4 + s) * kLanes + lane];
+    const float4_t bias3[2] = {net_bias(bias + kNetBias3, n3, lane), net_bias(bias + kNetBias3, n3 + 1, lane)};
 
-    // encoding [sin q, cos q, 0, 0] of the 64 rows, as (hi, lo) pairs
-    if (wave < kDof) {
+    // What the last phase needs, so that no memory round trip stands in it:
+    // the output weights (to LDS before the last barrier), and on wave 0 the
+    // horizon weight and the cost that the rollout wrote (every point of a
+    // particle reads its particle's).
+    asm volatile("" : "+s"(a_coll), "+s"(tables), "+s"(C_sum));
+    const float w4 = bias[kNetW4 + lane], b4 = vector_load_f32(bias + kNetBias4);
+    const float hw = as_global(tables)[kTabHw + h], C_rollout = as_global(C_sum)[valid ? i : 0];
+
+    // encoding [sin q, cos q, 0, 0] of the 64 rows, as (hi, lo) pairs (by
+    // every wave: a branch here would take the load of q with it, behind the
+    // weights)
+    {
         float sn, cs;
         sincosf(valid ? qv : 0.0f, &sn, &cs);
+        const bool joint = wave < kDof;
         _Float16 *r = s_x + lane * kX;
-        split_half(sn, r[wave], r[kIn + wave]);
-        split_half(cs, r[kDof + wave], r[kIn + kDof + wave]);
-    } else if (wave == kDof) {
-        _Float16 *r = s_x + lane * kX;
-        r[14] = r[15] = r[kIn + 14] = r[kIn + 15] = (_Float16)0.0f;
+        const int a = joint ? wave : 14, b = joint ? kDof + wave : 15;
+        split_half(joint ? sn : 0.0f, r[a], r[kIn + a]);
+        split_half(joint ? cs : 0.0f, r[b], r[kIn + b]);
     }
     __syncthreads();
 
@@ -108,36 +136,48 @@ __global__ __launch_bounds__(kNetThreads) void selfnet_kernel(const PlainDev *de
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
                 float4_t d = {0.0f, 0.0f, 0.0f, 0.0f};
-                d = __builtin_amdgcn_mfma_f32_16x16x16f16(ahi, b1[t], d, 0, 0, 0);
-                d = __builtin_amdgcn_mfma_f32_16x16x16f16(alo, b1[t], d, 0, 0, 0);
+                d = __builtin_amdgcn_mfma_f32_16x16x16f16(b1[t], ahi, d, 0, 0, 0);
+                d = __builtin_amdgcn_mfma_f32_16x16x16f16(b1[t], alo, d, 0, 0, 0);
                 net_store_relu_h(s_a1, kNetA1, kNetH1, m, 2 * wave + t, lane, d, bias1[t]);
             }
         }
     }
     __syncthreads();
 
-    // layer 2: 64 x 256 by 256 x 128; wave w: columns 16 w .. 16 w + 15
-    net_layer2(s_a1, s_a2, b2, bias2, wave, lane);
+    // layer 2: 64 x 256 by 256 x 128; a wave: 32 units of 32 rows
+    {
+        float4_t d[2][2];
+        net_layer(s_a1, kNetA1, kNetH1, b2, m2, lane, d);
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int n = 0; n < 2; ++n) net_store_relu_h(s_a2, kNetA2, kNetH2, m2 + m, n2 + n, lane, d[m][n], bias2[n]);
+    }
     __syncthreads();
 
-    // layer 3: 64 x 128 by 128 x 64; wave w: columns 16 (w / 2) .., rows 32
-    // (w % 2) ..; its FP32 output rows go where layer 1's were
-    net_layer3(s_a2, s_a3, b3, bias3, wave >> 1, 2 * (wave & 1), lane);
+    // layer 3: 64 x 128 by 128 x 64; a wave: 32 units of 16 rows; its FP32
+    // output rows go where layer 1's were
+    {
+        float4_t d[1][2];
+        net_layer(s_a2, kNetA2, kNetH2, b3, m3, lane, d);
+#pragma unroll
+        for (int n = 0; n < 2; ++n) net_store_relu_f(s_a3, kNetA3, m3, n3 + n, lane, d[0][n], bias3[n]);
+    }
+    if (wave == kNetWaves - 1) s_w4[lane] = w4;
     __syncthreads();
 
     // output layer, cost term and horizon cost (wave 0, lane = row)
     if (wave == 0) {
-        const float dist = net_output(s_a3, bias, lane);
+        const float dist = net_output(s_a3, s_w4, b4, lane);
         const float term = fmaxf(dist, 0.0f);  // Eq. 13
-        const float dc = P.a_coll * term;
-        const float added = segmented_scan(as_global(P.tables)[kTabHw + h] * dc, h, H);
+        const float dc = a_coll * term;
+        const float added = segmented_scan(hw * dc, h, H);
         if (valid) {
             if (kDebug && terms_out) terms_out[((size_t)6 * N + i) * H + h] = term;
             if (kDebug && c_out) c_out[(size_t)i * H + h] += dc;
             if (h == H - 1) {
-                const global_ptr<float> C = as_global(P.C) + i;
-                const float sum = *C + added;
-                *C = sum;
+                const float sum = C_rollout + added;
+                as_global(C_sum)[i] = sum;
                 if (C_out) C_out[i] = sum;
             }
         }
