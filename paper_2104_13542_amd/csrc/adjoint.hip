@@ -43,14 +43,17 @@ struct AdjFirst {
     uint32_t *step;
     int32_t N, H;
 };
-__device__ __forceinline__ AdjFirst fetch_first(ProblemRef P, int32_t N, int32_t H)
+// (issued; wait_for: here they have to be there)
+__device__ __forceinline__ AdjFirst load_first(ProblemRef P, int32_t N, int32_t H)
 {
-    AdjFirst F{P.n_halton, P.n_null, P.ppt,      P.n_tiles, P.n_chunks, P.seed_lo, P.seed_hi, P.grad_mask, P.comb,
-               P.cov_step, P.tables, P.halton,   P.sigma2,  P.step,     N,         H};
+    return AdjFirst{P.n_halton, P.n_null, P.ppt,    P.n_tiles, P.n_chunks, P.seed_lo, P.seed_hi, P.grad_mask,
+                    P.comb,     P.cov_step, P.tables, P.halton, P.sigma2,  P.step,    N,         H};
+}
+__device__ __forceinline__ void wait_for(AdjFirst &F)
+{
     asm volatile("" : "+s"(F.n_halton), "+s"(F.n_null), "+s"(F.ppt), "+s"(F.n_tiles), "+s"(F.n_chunks),
                  "+s"(F.seed_lo), "+s"(F.seed_hi), "+s"(F.grad_mask), "+s"(F.comb), "+s"(F.cov_step), "+s"(F.tables),
                  "+s"(F.halton), "+s"(F.sigma2), "+s"(F.step));
-    return F;
 }
 
 // This lane's number, counted anew at each use (threadIdx, or a count that the
@@ -62,30 +65,42 @@ __device__ __forceinline__ int lane_id()
     return lane;
 }
 
-// n consecutive scalars in one go (n <= 28): a load wherever one is used would
-// put one round trip after another.
+// n consecutive scalars in one go: a load wherever one is used would put one
+// round trip after another.
 template <int n>
-__device__ __forceinline__ void fetch_scalars(const STORM_CONST_AS float *p, float (&x)[n])
+__device__ __forceinline__ void load_scalars(const STORM_CONST_AS float *p, float (&x)[n])
+{
+#pragma unroll
+    for (int k = 0; k < n; ++k) x[k] = p[k];
+}
+template <int n>
+__device__ __forceinline__ void wait_for(float (&x)[n])
 {
     static_assert(n % 4 == 0, "four per statement");
 #pragma unroll
-    for (int k = 0; k < n; ++k) x[k] = p[k];
-#pragma unroll
     for (int k = 0; k < n; k += 4) asm volatile("" : "+s"(x[k]), "+s"(x[k + 1]), "+s"(x[k + 2]), "+s"(x[k + 3]));
+}
+template <int n>
+__device__ __forceinline__ void fetch_scalars(const STORM_CONST_AS float *p, float (&x)[n])
+{
+    load_scalars(p, x);
+    wait_for(x);
 }
 
 // The weights and scales of the differentiated terms.
 struct AdjWeights {
     float a_joint, a_vel, a_stop, w_pos, w_rot, alpha_pos[3], alpha_rot[3];
 };
-__device__ __forceinline__ AdjWeights fetch_weights(ProblemRef P)
+__device__ __forceinline__ AdjWeights load_weights(ProblemRef P)
 {
-    AdjWeights w{P.a_joint, P.a_vel, P.a_stop, P.w_pos, P.w_rot, {P.alpha_pos[0], P.alpha_pos[1], P.alpha_pos[2]},
-                 {P.alpha_rot[0], P.alpha_rot[1], P.alpha_rot[2]}};
+    return AdjWeights{P.a_joint, P.a_vel, P.a_stop, P.w_pos, P.w_rot, {P.alpha_pos[0], P.alpha_pos[1], P.alpha_pos[2]},
+                      {P.alpha_rot[0], P.alpha_rot[1], P.alpha_rot[2]}};
+}
+__device__ __forceinline__ void wait_for(AdjWeights &w)
+{
     asm volatile("" : "+s"(w.a_joint), "+s"(w.a_vel), "+s"(w.a_stop), "+s"(w.w_pos), "+s"(w.w_rot),
                  "+s"(w.alpha_pos[0]), "+s"(w.alpha_pos[1]), "+s"(w.alpha_pos[2]), "+s"(w.alpha_rot[0]),
                  "+s"(w.alpha_rot[1]), "+s"(w.alpha_rot[2]));
-    return w;
 }
 
 // Limit and stop costs of a point from the squared norms of its violations:
@@ -102,11 +117,10 @@ __device__ __forceinline__ AdjLimits limit_terms(const AdjWeights &w, uint32_t m
                      nv > 0.0f ? w.a_vel / nv : 0.0f, ns > 0.0f ? w.a_stop / ns : 0.0f};
 }
 
-// Pose cost of a point with flange (Re, pe), added to `cost`; its gradient
-// with respect to the joints of axes z and origins o, added to gq.
-template <class Goal>
-__device__ __forceinline__ void pose_terms(const AdjWeights &w, const Goal &goal, const float Re[9], const float pe[3],
-                                           const float z[kDof][3], const float o[kDof][3], float gq[kDof], float &cost)
+// Pose cost of a point with flange (Re, pe), added to `cost`, and its gradient
+// with respect to the flange's motion: gp to its position, gr to its rotation.
+__device__ __forceinline__ void pose_gradient(const AdjWeights &w, const float (&goal)[12], const float Re[9],
+                                              const float pe[3], float gp[3], float gr[3], float &cost)
 {
     // position: e = diag(a2) R_g^T (p - p_g), gradient g_p = w_pos R_g diag(a2) e / |e|
     float ep[3], pos2 = 0.0f;
@@ -118,7 +132,6 @@ __device__ __forceinline__ void pose_terms(const AdjWeights &w, const Goal &goal
     }
     const float pos = fast_sqrt(pos2);
     const float kp = pos > 0.0f ? w.w_pos / pos : 0.0f;
-    float gp[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a)
         gp[a] = kp * fmaf(goal[a * 3 + 0], w.alpha_pos[0] * ep[0],
@@ -148,21 +161,22 @@ __device__ __forceinline__ void pose_terms(const AdjWeights &w, const Goal &goal
     auto A = [&](int a, int b) __attribute__((always_inline)) {
         return fmaf(Re[a * 3 + 0], G[b * 3 + 0], fmaf(Re[a * 3 + 1], G[b * 3 + 1], Re[a * 3 + 2] * G[b * 3 + 2]));
     };
-    const float w0 = A(1, 2) - A(2, 1);
-    const float w1 = A(2, 0) - A(0, 2);
-    const float w2 = A(0, 1) - A(1, 0);
-#pragma unroll
-    for (int k = 0; k < kDof; ++k) {
-        const float r0 = pe[0] - o[k][0];
-        const float r1 = pe[1] - o[k][1];
-        const float r2 = pe[2] - o[k][2];
-        // (p - o_k) x g_p
-        const float c0 = fmaf(r1, gp[2], -(r2 * gp[1]));
-        const float c1 = fmaf(r2, gp[0], -(r0 * gp[2]));
-        const float c2 = fmaf(r0, gp[1], -(r1 * gp[0]));
-        gq[k] += fmaf(z[k][0], c0 + w0, fmaf(z[k][1], c1 + w1, z[k][2] * (c2 + w2)));
-    }
+    gr[0] = A(1, 2) - A(2, 1);
+    gr[1] = A(2, 0) - A(0, 2);
+    gr[2] = A(0, 1) - A(1, 0);
     cost = fmaf(w.w_pos, pos, fmaf(w.w_rot, rot, cost));
+}
+
+// The same gradient with respect to the joint of axis z and origin o.
+__device__ __forceinline__ float pose_joint(const float pe[3], const float z[3], const float o[3], const float gp[3],
+                                            const float gr[3])
+{
+    const float r0 = pe[0] - o[0], r1 = pe[1] - o[1], r2 = pe[2] - o[2];
+    // (p - o) x g_p
+    const float c0 = fmaf(r1, gp[2], -(r2 * gp[1]));
+    const float c1 = fmaf(r2, gp[0], -(r0 * gp[2]));
+    const float c2 = fmaf(r0, gp[1], -(r1 * gp[0]));
+    return fmaf(z[0], c0 + gr[0], fmaf(z[1], c1 + gr[1], z[2] * (c2 + gr[2])));
 }
 
 // One tile on one wavefront: acc gains dC/du of this lane's point, cacc its
@@ -255,7 +269,8 @@ __device__ __forceinline__ void adjoint_tile(ProblemRef P, RobotRef R, AdjFirst 
             ns = fmaf(a, a, ns);
             es[j] = v > 0.0f ? a : -a;
         }
-        w = fetch_weights(P);
+        w = load_weights(P);
+        wait_for(w);
         const AdjLimits lt = limit_terms(w, mask, nj, nv, ns);
 #pragma unroll
         for (int j = 0; j < kDof; ++j) {
@@ -283,7 +298,10 @@ __device__ __forceinline__ void adjoint_tile(ProblemRef P, RobotRef R, AdjFirst 
         }
         float goal[12];
         fetch_scalars(goal_in, goal);
-        pose_terms(w, goal, Re, pe, z, o, gq, cost);
+        float gp[3], gr[3];
+        pose_gradient(w, goal, Re, pe, gp, gr, cost);
+#pragma unroll
+        for (int k = 0; k < kDof; ++k) gq[k] += pose_joint(pe, z[k], o[k], gp, gr);
     }
     cacc += valid ? hw * cost : 0.0f;
 
@@ -346,7 +364,8 @@ __device__ __forceinline__ void adjoint_chunk(ProblemRef P, RobotRef R, const in
                                               float *__restrict__ part)
 {
     __shared__ float s_buf[kAdjRuns][8 * kLanes];  // the wavefronts' rows, then the runs' sums
-    const AdjFirst F = fetch_first(P, N, H);
+    AdjFirst F = load_first(P, N, H);
+    wait_for(F);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t counter = *uniform_ptr(F.step + 2);
     const bool single = F.n_tiles <= kSplitTiles;
@@ -383,65 +402,84 @@ __device__ __forceinline__ void adjoint_chunk(ProblemRef P, RobotRef R, const in
 }
 
 // One tile split over a workgroup of eight wavefronts, into the partials of
-// chunk `tile`:
-//   A   noise, controls, the forward integrator and sin/cos of q (as kernel R)
-//   B   waves 0-2: forward kinematics to LDS, one frame row each; wave 3:
-//       limit costs and their gradients with respect to q and v
-//   C   wave 0: pose cost and dC/dq through the Jacobian columns; horizon cost
-//   D   waves 0-6: the integrator backwards
+// chunk `tile`; bound by latency:
+//   A   waves 0-3: noise; waves 0-6, one joint each: controls, the integrator,
+//       sin/cos of q, violations of the limits
+//   B   waves 0-2: forward kinematics to LDS, one frame row each; wave 3: limit
+//       costs and what the violations are scaled by
+//   C   wave 0: pose cost, its gradient by the flange's motion; horizon cost
+//   D   waves 0-6: dC/dq of the joint, the integrator backwards
 //   E   per (joint, step) sum over the tile's particles
+// Every load is issued at the start, and a joint's share of the gradient is
+// formed by its own wave (a step and three refinements of 64 x 16 43.5 -> 38.4 us,
+// of 1024 x 30 48.2 -> 44.7, with the partials' sum below).
 __device__ __forceinline__ void adjoint_split(ProblemRef P, RobotRef R, const int N, const int H, const int tile,
-                                              const float *__restrict__ x0, const float *__restrict__ goal,
+                                              const float *__restrict__ x0, const float *__restrict__ goal_in,
                                               const float *__restrict__ mean, const float *__restrict__ noise,
                                               float *__restrict__ part)
 {
     __shared__ float s_eps[8][kLanes];
-    __shared__ float s_q[kDof][kLanes];
-    __shared__ float s_v[kDof][kLanes];
-    __shared__ float s_fr[kFrames * 12][kLanes];
     __shared__ float s_sc[2 * kDof][kLanes];  // sin q_j, cos q_j
-    __shared__ float s_gl[kDof][kLanes];  // limit-cost gradient d c / d q
-    __shared__ float s_gv[kDof][kLanes];  // limit and stop gradient d c / d v
-    __shared__ float s_gq[kDof][kLanes];  // horizon-weighted d C / d q
+    __shared__ float s_ej[kDof][kLanes], s_ev[kDof][kLanes], s_es[kDof][kLanes];  // signed violations
+    __shared__ float s_fr[kFrames * 12][kLanes];
+    __shared__ float s_k[4][kLanes];   // the violations' scales, the weighted limit costs
+    __shared__ float s_g[6][kLanes];   // the pose cost's gradient by the flange's motion
     __shared__ float s_gu[kDof][kLanes];  // d C / d u
-    __shared__ float s_cl[kLanes];        // weighted limit and stop costs
     __shared__ float s_Cp[kLanes];        // horizon cost per particle of the tile
 
     const int lane = threadIdx.x & (kLanes - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int pl = lane / H;
+    AdjFirst F = load_first(P, N, H);
+    AdjWeights w = load_weights(P);
+    float dh[4 * kFrames], goal[12];
+    load_scalars(R.ca, dh);
+    load_scalars(uniform_ptr(goal_in), goal);
+    __builtin_amdgcn_sched_barrier(0);  // (all of them before the first is waited for)
+    wait_for(F);
+    const int pl = (int)(((float)lane + 0.5f) * __builtin_amdgcn_rcpf((float)H));  // lane / H (exact, as in kernel R)
     const int h = lane - pl * H;
-    const int i = tile * P.ppt + pl;
-    const bool valid = pl < P.ppt && i < N;
-    const bool live = valid && i < N - P.n_null;
-    const uint32_t mask = P.grad_mask;
-    const global_ptr<const float> tab = as_global(P.tables);
-    const float dt_h = tab[kTabDt + h];
-    const float hw_h = tab[kTabHw + h];
+    const int i = tile * F.ppt + pl;
+    const bool valid = pl < F.ppt && i < N;
+    const bool live = valid && i < N - F.n_null;
+    const uint32_t mask = F.grad_mask;
+    const global_ptr<const float> tab = as_global(F.tables);
+    const int j = min(wave, kDof - 1);  // (this wave's joint)
+    const float dt = tab[kTabDt + h], hw = tab[kTabHw + h], vs = tab[kTabVstop + h];
+    const float mu = as_global(mean)[h * kDof + j],
+                sigma2 = as_global(F.sigma2)[F.cov_step ? h * kDof + j : j];
+    const float q0 = vector_load_f32(x0 + j), v0 = vector_load_f32(x0 + kDof + j);
+    const float jlo = tab[kTabJlo + j], jhi = tab[kTabJhi + j], vlo = tab[kTabVlo + j], vhi = tab[kTabVhi + j];
+
+    wait_for(w);
+    wait_for(dh);
+    wait_for(goal);
 
     // ---- A: noise, controls, integrator ---------------------------------------
-    if (wave < 2) {
-        float e[4] = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (live) standard_noise4(P, P.seed_lo, P.seed_hi, noise, wave, i, h, *as_global(P.last_step), e);
-#pragma unroll
-        for (int m = 0; m < 4; ++m) s_eps[4 * wave + m][lane] = e[m];
+    if (wave < 4) {
+        const int k = wave & 1, half = wave >> 1;
+        float e[2] = {0.0f, 0.0f};
+        const uint32_t counter = *uniform_ptr(F.step + 2);
+        if (live) standard_noise2(F, F.seed_lo, F.seed_hi, noise, k, half, i, h, counter, e);
+        s_eps[4 * k + 2 * half][lane] = e[0];
+        s_eps[4 * k + 2 * half + 1][lane] = e[1];
     }
     __syncthreads();
     if (wave < kDof) {
-        const int j = wave;
         float e = s_eps[j][lane];
         // the comb filter on the sampled Gaussian particles' noise, as in kernel R
-        const bool comb = P.comb && noise == nullptr && live && i >= P.n_halton;
+        const bool comb = F.comb && noise == nullptr && live && i >= F.n_halton;
         if (__builtin_amdgcn_ballot_w64(comb) != 0) {
             const float f = comb_noise(&s_eps[j][0], lane, h, H, tab);
             if (comb) e = f;
         }
-        float u = 0.0f;
-        if (live) u = fmaf(sqrtf(as_global(P.sigma2)[P.cov_step ? h * kDof + j : j]), e, mean[h * kDof + j]);
-        const float v = x0[kDof + j] + segmented_scan(dt_h * u, h, H);
-        const float q = x0[j] + segmented_scan(dt_h * v, h, H);
-        s_q[j][lane] = q;
-        s_v[j][lane] = v;
+        const float u = live ? fmaf(sqrtf(sigma2), e, mu) : 0.0f;
+        const float v = v0 + segmented_scan(dt * u, h, H);
+        const float q = q0 + segmented_scan(dt * v, h, H);
+        // signed violations: negative below the band, positive above
+        s_ej[j][lane] = fminf(q - jlo, 0.0f) + fmaxf(q - jhi, 0.0f);
+        s_ev[j][lane] = fminf(v - vlo, 0.0f) + fmaxf(v - vhi, 0.0f);
+        const float a = fmaxf(fabsf(v) - vs, 0.0f);
+        s_es[j][lane] = v > 0.0f ? a : -a;
         float sq, cq;
         sincosf(q, &sq, &cq);
         s_sc[2 * j][lane] = sq;
@@ -449,7 +487,7 @@ __device__ __forceinline__ void adjoint_split(ProblemRef P, RobotRef R, const in
     }
     __syncthreads();
 
-    // ---- B: kinematics, one frame row per wave | limit costs and gradients ---
+    // ---- B: kinematics, one frame row per wave | limit costs ------------------
     if (wave < 3) {
         const int row = wave;
         float r[3] = {row == 0 ? 1.0f : 0.0f, row == 1 ? 1.0f : 0.0f, row == 2 ? 1.0f : 0.0f};
@@ -461,88 +499,85 @@ __device__ __forceinline__ void adjoint_split(ProblemRef P, RobotRef R, const in
                 st = s_sc[2 * f][lane];
                 ct = s_sc[2 * f + 1][lane];
             }
-            dh_step_row(r, p, R.ca[f], R.sa[f], R.a[f], R.d[f], ct, st);
+            dh_step_row(r, p, dh[f], dh[kFrames + f], dh[2 * kFrames + f], dh[3 * kFrames + f], ct, st);
 #pragma unroll
             for (int c = 0; c < 3; ++c) s_fr[f * 12 + row * 3 + c][lane] = r[c];
             s_fr[f * 12 + 9 + row][lane] = p;
         }
     } else if (wave == 3) {
-        float ej[kDof], ev[kDof], es[kDof];
         float nj = 0.0f, nv = 0.0f, ns = 0.0f;
-        const float vs = tab[kTabVstop + h];
 #pragma unroll
-        for (int j = 0; j < kDof; ++j) {
-            const float q = s_q[j][lane], v = s_v[j][lane];
-            // signed violations: negative below the band, positive above
-            ej[j] = fminf(q - tab[kTabJlo + j], 0.0f) + fmaxf(q - tab[kTabJhi + j], 0.0f);
-            ev[j] = fminf(v - tab[kTabVlo + j], 0.0f) + fmaxf(v - tab[kTabVhi + j], 0.0f);
-            es[j] = fmaxf(fabsf(v) - vs, 0.0f);
-            nj = fmaf(ej[j], ej[j], nj);
-            nv = fmaf(ev[j], ev[j], nv);
-            ns = fmaf(es[j], es[j], ns);
+        for (int k = 0; k < kDof; ++k) {
+            const float ej = s_ej[k][lane], ev = s_ev[k][lane], es = s_es[k][lane];
+            nj = fmaf(ej, ej, nj);
+            nv = fmaf(ev, ev, nv);
+            ns = fmaf(es, es, ns);
         }
-        const AdjLimits lt = limit_terms(fetch_weights(P), mask, nj, nv, ns);
-#pragma unroll
-        for (int j = 0; j < kDof; ++j) {
-            const float v = s_v[j][lane];
-            s_gl[j][lane] = lt.kj * ej[j];
-            s_gv[j][lane] = fmaf(lt.kv, ev[j], lt.ks * (v > 0.0f ? es[j] : -es[j]));
-        }
-        s_cl[lane] = lt.cost;
+        const AdjLimits lt = limit_terms(w, mask, nj, nv, ns);
+        s_k[0][lane] = lt.kj;
+        s_k[1][lane] = lt.kv;
+        s_k[2][lane] = lt.ks;
+        s_k[3][lane] = lt.cost;
     }
     __syncthreads();
 
     // ---- C: pose cost and its gradient; horizon cost ------------------------
     if (wave == 0) {
-        float gq[kDof];
-#pragma unroll
-        for (int k = 0; k < kDof; ++k) gq[k] = s_gl[k][lane];
-        float cost = s_cl[lane];
+        float cost = s_k[3][lane];
         if (mask & STORM_COST_POSE) {
-            float Re[9], pe[3], z[kDof][3], o[kDof][3];
+            float Re[9], pe[3], gp[3], gr[3];
 #pragma unroll
             for (int c = 0; c < 9; ++c) Re[c] = s_fr[7 * 12 + c][lane];
 #pragma unroll
             for (int c = 0; c < 3; ++c) pe[c] = s_fr[7 * 12 + 9 + c][lane];
+            pose_gradient(w, goal, Re, pe, gp, gr, cost);
 #pragma unroll
-            for (int k = 0; k < kDof; ++k)
-#pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    z[k][c] = s_fr[k * 12 + 3 * c + 2][lane];
-                    o[k][c] = s_fr[k * 12 + 9 + c][lane];
-                }
-            pose_terms(fetch_weights(P), goal, Re, pe, z, o, gq, cost);
+            for (int c = 0; c < 3; ++c) {
+                s_g[c][lane] = gp[c];
+                s_g[3 + c][lane] = gr[c];
+            }
         }
-#pragma unroll
-        for (int k = 0; k < kDof; ++k) s_gq[k][lane] = hw_h * gq[k];
-        const float Ci = segmented_scan(hw_h * cost, h, H);
+        const float Ci = segmented_scan(hw * cost, h, H);
         if (h == H - 1) s_Cp[pl] = valid ? Ci : 0.0f;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
+    if (threadIdx.x == 7 * kLanes) {
         float cacc = 0.0f;
-        for (int p = 0; p < P.ppt; ++p) cacc += s_Cp[p];
+        for (int p = 0; p < F.ppt; ++p) cacc += s_Cp[p];
         as_global(part)[tile] = cacc;
     }
 
-    // ---- D: the integrator backwards -----------------------------------------
+    // ---- D: dC/dq, then the integrator backwards --------------------------------
     if (wave < kDof) {
-        const int j = wave;
+        float g[1] = {s_k[0][lane] * s_ej[j][lane]};
+        if (mask & STORM_COST_POSE) {
+            float pe[3], z[3], o[3], gp[3], gr[3];
+#pragma unroll
+            for (int c = 0; c < 3; ++c) {
+                pe[c] = s_fr[7 * 12 + 9 + c][lane];
+                z[c] = s_fr[j * 12 + 3 * c + 2][lane];
+                o[c] = s_fr[j * 12 + 9 + c][lane];
+                gp[c] = s_g[c][lane];
+                gr[c] = s_g[3 + c][lane];
+            }
+            g[0] += pose_joint(pe, z, o, gp, gr);
+        }
+        g[0] *= hw;
+        const float gv = fmaf(s_k[1][lane], s_ev[j][lane], s_k[2][lane] * s_es[j][lane]);
         const int left = H - 1 - h;
-        float g[1] = {s_gq[j][lane]};
         segmented_suffix_scans(g, lane, left);
-        g[0] = fmaf(dt_h, g[0], hw_h * s_gv[j][lane]);
+        g[0] = fmaf(dt, g[0], hw * gv);
         segmented_suffix_scans(g, lane, left);
-        s_gu[j][lane] = live ? dt_h * g[0] : 0.0f;
+        s_gu[j][lane] = live ? dt * g[0] : 0.0f;
     }
     __syncthreads();
 
     // ---- E: the tile's partial of dJ/dmu (sum over the tile's particles) -----
     if ((int)threadIdx.x < kDof * H) {
-        const int j = threadIdx.x / H, hh = threadIdx.x - j * H;
+        const int jj = threadIdx.x / H, hh = threadIdx.x - jj * H;
         float acc = 0.0f;
-        for (int p = 0; p < P.ppt; ++p) acc += s_gu[j][p * H + hh];
-        as_global(part)[kAdjChunks + ((size_t)tile * kDof + j) * kMaxH + hh] = acc;
+        for (int p = 0; p < F.ppt; ++p) acc += s_gu[jj][p * H + hh];
+        as_global(part)[kAdjChunks + ((size_t)tile * kDof + jj) * kMaxH + hh] = acc;
     }
 }
 
@@ -588,23 +623,18 @@ __global__ __launch_bounds__(kSplitWaves *kLanes) void adjoint_split_batch_kerne
                   nullptr, P.grad_part);
 }
 
-// grad[h][j] = (1/N) sum over chunks of the partials, J = (1/N) sum of the
-// chunk cost sums; rows of threads take chunks r, r + R, ..., then the rows
-// are added in order.
-// One Adam step with gradient g on the stored mean, element t (moments
-// restart at it == 1).
-__device__ __forceinline__ void adam_step(ProblemRef P, int t, float g, int it, float lr, float b1, float b2,
-                                          float eps)
+// One Adam step with gradient g on the stored mean mu, element t, with the
+// moments m0 and v0 before it; returns the new mean.  b1_it, b2_it: b1^it, b2^it.
+__device__ __forceinline__ float adam_step(float *adam_m, float *adam_v, int t, float g, float m0, float v0, float mu,
+                                           float lr, float b1, float b2, float b1_it, float b2_it, float eps)
 {
-    const float m0 = it == 1 ? 0.0f : as_global(P.adam_m)[t];
-    const float v0 = it == 1 ? 0.0f : as_global(P.adam_v)[t];
     const float m = fmaf(b1, m0, (1.0f - b1) * g);
     const float v = fmaf(b2, v0, (1.0f - b2) * g * g);
-    as_global(P.adam_m)[t] = m;
-    as_global(P.adam_v)[t] = v;
-    const float mh = m / (1.0f - powf(b1, (float)it));
-    const float vh = v / (1.0f - powf(b2, (float)it));
-    as_global(P.mean)[t] -= lr * mh / (sqrtf(vh) + eps);
+    as_global(adam_m)[t] = m;
+    as_global(adam_v)[t] = v;
+    const float mh = m / (1.0f - b1_it);
+    const float vh = v / (1.0f - b2_it);
+    return mu - lr * mh / (sqrtf(vh) + eps);
 }
 
 // cmd = mu_0, then the warm-start shift of the stored mean (and of a
@@ -635,47 +665,84 @@ __device__ __forceinline__ void command(ProblemRef P, float *__restrict__ cmd, i
 // mu[h][j]; with cmd, it writes the command mu[0][j] and the warm-start
 // shift of the joint (the next step's value through a DPP wave shift), with
 // a per-step variance shifted alike.
+// (Bound by latency: everything it reads is loaded at the start.)
+struct GradFields {
+    int32_t N, H, n_chunks;
+    uint32_t cov_step;
+    const float *tables;
+    float *mean, *sigma2, *grad, *adam_m, *adam_v;
+};
+// The sum over chunks r, r + rows, ... of a thread's partial, the first `kAt`
+// of them in flight at once; past the last chunk the resource reads 0.
+template <int kAt>
+__device__ __forceinline__ float sum_chunks(__amdgpu_buffer_rsrc_t src, int first, int stride)
+{
+    float v[kAt], acc = 0.0f;
+#pragma unroll
+    for (int i = 0; i < kAt; ++i)
+        v[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(src, first + i * stride, 0, 0));
+#pragma unroll
+    for (int i = 0; i < kAt; ++i) acc += v[i];
+    return acc;
+}
 __device__ __forceinline__ void grad_step(ProblemRef P, int j, const float *__restrict__ part,
                                           float *__restrict__ grad_out,
                                           float *__restrict__ J_out, int it, float lr, float *__restrict__ cmd,
                                           int shift)
 {
     constexpr int kMaxPerThread = (kAdjChunks * kMaxH + kRedThreads - 1) / kRedThreads;
+    static_assert(kMaxPerThread <= 32, "chunks of a thread at the longest horizon");
     __shared__ float s_red[kRedThreads];
     __shared__ float s_wave[kRedThreads / kLanes];
     const int t = threadIdx.x;
-    const int lane = t & (kLanes - 1), wave = t / kLanes;
-    const int H = P.H, T = P.n_chunks;
+    const int lane = t & (kLanes - 1), wave = __builtin_amdgcn_readfirstlane(t / kLanes);
+    GradFields F{P.N, P.H, P.n_chunks, P.cov_step, P.tables, P.mean, P.sigma2, P.grad, P.adam_m, P.adam_v};
+    asm volatile("" : "+s"(F.N), "+s"(F.H), "+s"(F.n_chunks), "+s"(F.cov_step), "+s"(F.tables), "+s"(F.mean),
+                 "+s"(F.sigma2), "+s"(F.grad), "+s"(F.adam_m), "+s"(F.adam_v));
+    const int H = F.H, T = F.n_chunks;
     const int rows = kRedThreads / H;
     const int r = t / H, h = t - r * H;
-    float acc = 0.0f;
-    if (r < rows) {
-        const global_ptr<const float> src = as_global(part) + kAdjChunks + (size_t)j * kMaxH + h;
-        float v[kMaxPerThread];
-#pragma unroll
-        for (int i = 0; i < kMaxPerThread; ++i) {
-            const int k = r + i * rows;
-            v[i] = k < T ? src[(size_t)k * kDof * kMaxH] : 0.0f;
+    // what the end of wave 0 reads (element e = (step `lane`, joint j))
+    const int e = min(lane, H - 1) * kDof + j;
+    float m0 = 0.0f, v0 = 0.0f, mu = 0.0f, s2 = 0.0f, sig0 = 0.0f, b1_it = 0.0f, b2_it = 0.0f;
+    const bool shift_cov = cmd != nullptr && shift && F.cov_step;
+    if (wave == 0) {
+        if (it > 1) {  // (the moments restart with the first step)
+            m0 = as_global(F.adam_m)[e];
+            v0 = as_global(F.adam_v)[e];
         }
-#pragma unroll
-        for (int i = 0; i < kMaxPerThread; ++i) acc += v[i];
+        if (it > 0 || cmd) mu = as_global(F.mean)[e];
+        if (shift_cov) {
+            s2 = as_global(F.sigma2)[e];
+            sig0 = as_global(F.tables)[kTabSig0 + j];
+        }
     }
-    s_red[t] = acc;
-    if (j == 0) {
+    const __amdgpu_buffer_rsrc_t src = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float *>(part + kAdjChunks), (short)0, T * kDof * kMaxH * (int)sizeof(float), 0x00020000);
+    const int first = ((r * kDof + j) * kMaxH + h) * (int)sizeof(float), stride = rows * kDof * kMaxH * (int)sizeof(float);
+    const int need = (T + rows - 1) / rows;
+    const float acc = need <= 8    ? sum_chunks<8>(src, first, stride)
+                      : need <= 16 ? sum_chunks<16>(src, first, stride)
+                                   : sum_chunks<32>(src, first, stride);
+    s_red[t] = r < rows ? acc : 0.0f;
+    if (j == 0 && J_out) {
         float cs = 0.0f;
         for (int k = t; k < T; k += kRedThreads) cs += as_global(part)[k];
         cs = wave_sum(cs);
         if (lane == 0) s_wave[wave] = cs;
     }
+    if (wave == 0 && it > 0) {
+        b1_it = powf(0.9f, (float)it);
+        b2_it = powf(0.999f, (float)it);
+    }
     __syncthreads();
     if (wave != 0) return;
-    const float invN = 1.0f / (float)P.N;
+    const float invN = 1.0f / (float)F.N;
     if (j == 0 && lane == 0 && J_out) {
         float J = 0.0f;
         for (int k = 0; k < kRedThreads / kLanes; ++k) J += s_wave[k];
         *J_out = J * invN;
     }
-    float mu = 0.0f;
     if (lane < H) {
         float p4[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         int k = 0;
@@ -686,25 +753,25 @@ __device__ __forceinline__ void grad_step(ProblemRef P, int j, const float *__re
         for (int m = 0; m < 3; ++m)
             if (k + m < rows) p4[m] += s_red[(k + m) * H + lane];
         const float g = ((p4[0] + p4[1]) + (p4[2] + p4[3])) * invN;
-        const int e = lane * kDof + j;
-        as_global(P.grad)[e] = g;
+        as_global(F.grad)[e] = g;
         if (grad_out) grad_out[e] = g;
-        if (it > 0) adam_step(P, e, g, it, lr, 0.9f, 0.999f, 1e-8f);
-        if (cmd) mu = as_global(P.mean)[e];
+        if (it > 0) mu = adam_step(F.adam_m, F.adam_v, e, g, m0, v0, mu, lr, 0.9f, 0.999f, b1_it, b2_it, 1e-8f);
+    } else {
+        mu = 0.0f;
     }
     if (cmd) {
         const float mu_next = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(mu), 0x130, 0xf, 0xf,
                                                                          true));  // wave_shl:1
         if (lane == 0) cmd[j] = mu;
-        if (shift && lane < H) as_global(P.mean)[lane * kDof + j] = lane + 1 < H ? mu_next : 0.0f;
-        if (shift && P.cov_step) {
+        if (shift) mu = lane + 1 < H ? mu_next : 0.0f;
+        if (shift_cov) {
             // a per-step variance moves forward too, sigma_init^2 appended
-            const float s2 = lane < H ? as_global(P.sigma2)[lane * kDof + j] : 0.0f;
             const float s2_next = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(s2), 0x130, 0xf, 0xf,
                                                                              true));  // wave_shl:1
-            if (lane < H) as_global(P.sigma2)[lane * kDof + j] = lane + 1 < H ? s2_next : as_global(P.tables)[kTabSig0 + j];
+            if (lane < H) as_global(F.sigma2)[e] = lane + 1 < H ? s2_next : sig0;
         }
     }
+    if ((it > 0 || cmd) && lane < H) as_global(F.mean)[e] = mu;
 }
 
 // All arguments fit the 14 dwords that are preloaded into SGPRs.

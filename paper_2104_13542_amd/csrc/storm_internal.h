@@ -27,7 +27,8 @@ constexpr int kAdjWaves = 4;     // wavefronts of an adjoint workgroup, one tile
 // Up to this many tiles (two per CU) the adjoint splits each tile over a
 // workgroup: the latency of a tile is then all there is.  A call of a step and
 // three refinements, split and a tile per wavefront: 500 x 30 43.8 and 51.1 us,
-// 1024 x 30 (512 tiles) 49.6 and 55.0; past it the split form takes a second
+// 1024 x 30 (512 tiles) 49.6 and 55.0 (before the split form's last step: 39.2
+// and 44.7 now); past it the split form takes a second
 // round: 2048 x 30 80 and 67 us, 65536 x 30 1290 and 742.
 constexpr int kSplitTiles = 512;
 
