@@ -396,7 +396,7 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
     c->R.n_pairs = n_pairs;
 
     float *tables, *halton, *box_obs, *mean, *sigma2, *u, *C, *dt_raw, *lim_raw, *sig_raw, *obs_raw, *sph_raw_d;
-    float *body_bound, *grad_part, *upd_part, *grad, *adam, *ball, *qbuf = nullptr;
+    float *body_bound, *grad_part, *upd_part = nullptr, *grad, *adam, *ball, *qbuf = nullptr;
     float4 *obs_bound, *sph_local;
     int32_t *sph_body, *self_seg;
     uint32_t *counters;
@@ -417,13 +417,19 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
     STORM_TRY(dalloc(c, &sigma2, (size_t)H * STORM_DOF));  // [7] or [H][7] (cov_per_step)
     STORM_TRY(dalloc(c, &u, (size_t)STORM_DOF * N * H));
     STORM_TRY(dalloc(c, &C, (size_t)N));
-    STORM_TRY(dalloc(c, &counters, (size_t)4));
     STORM_TRY(dalloc(c, &grad_part, storm::kAdjChunks + (size_t)P.n_chunks * STORM_DOF * storm::kMaxH));
-    STORM_TRY(dalloc(c, &upd_part, storm::update_part_floats(N, H)));
+    if (storm::update_part_floats(N, H) > 0) STORM_TRY(dalloc(c, &upd_part, storm::update_part_floats(N, H)));
     STORM_TRY(dalloc(c, &grad, (size_t)H * STORM_DOF));
     STORM_TRY(dalloc(c, &adam, (size_t)2 * H * STORM_DOF));
-    STORM_TRY(dalloc(c, &ball, (size_t)8));
-    STORM_TRY(dalloc(c, &c->dev, (size_t)1));
+    {
+        // one allocation: the descriptors, then a line each for the counters
+        // and the ball
+        char *block = nullptr;
+        STORM_TRY(dalloc(c, &block, sizeof(PlainDev) + 2 * 64));
+        c->dev = reinterpret_cast<PlainDev *>(block);
+        counters = reinterpret_cast<uint32_t *>(block + sizeof(PlainDev));
+        ball = reinterpret_cast<float *>(block + sizeof(PlainDev) + 64);
+    }
     if (P.selfnet) {
         STORM_TRY(dalloc(c, &qbuf, (size_t)STORM_DOF * N * H));
         STORM_TRY(dalloc(c, &c->net_frag, net_frag.size()));

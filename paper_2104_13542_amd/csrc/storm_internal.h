@@ -119,7 +119,8 @@ static_assert(offsetof(ProblemDev, tables) == 64 && offsetof(ProblemDev, step) =
                   offsetof(ProblemDev, k_m) == 192,
               "groups of 64 bytes");
 
-// Robot constants, passed by value (kernel-argument segment, wave-uniform).
+// Robot constants (wave-uniform; in device memory for the rollouts and the adjoint,
+// by value for the FK kernel).
 struct alignas(64) RobotDev {
     int32_t n_spheres, n_pairs, n_self_items, pad0;
     const float4 *sph_local;  // [S] body-frame centre (x, y, z), radius
