@@ -493,6 +493,14 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
         c->R.body_bound = body_bound;
         c->R.self_items = self_seg;
         c->R.n_self_items = n_seg;
+        c->R.cap_mask = 0;
+        for (int b = 0; b < STORM_NFRAMES; ++b) {
+            int a;
+            memcpy(&a, &bounds[2 * b], sizeof(a));
+            if (bounds[2 * b + 1] > -1.0e30f) c->R.cap_mask |= 1ull << a;
+        }
+        for (int k = 0; k < n_seg; ++k)
+            c->R.cap_mask |= 1ull << (seg[4 * k + 1] & 63) | 1ull << (seg[4 * k + 1] >> 6 & 63);
         dev.P = P;
         dev.R = c->R;
         STORM_TRY(hipMemcpyAsync(c->dev, &dev, sizeof(dev), hipMemcpyHostToDevice, s));

@@ -16,8 +16,8 @@
 //   B   waves 0-2  forward kinematics (Eq. 8), one row of the eight frames
 //                  per wave, to LDS
 //       wave W-1   the hinge norms over the joints (Eq. 10-11)
-//   C   waves 0..W-3  world centres of the body spheres and the capsules
-//                  that hold them, to LDS
+//   C   waves 0..W-3  world centres of the body spheres, and the capsules
+//                  that hold the anchor spheres, to LDS
 //       wave W-2   manipulability (Eq. 12)
 //       wave W-1   pose (Eq. 9)
 //   D1  all waves  obstacles near each body and near pairs of sphere runs,
@@ -37,8 +37,8 @@
 // Three forms: a 16-wave workgroup per tile up to one tile per CU (bound by the
 // latency of its phases), 8-wave workgroups that loop over the tiles of one
 // larger problem, and the same over the tiles of a batch (both bound by VALU
-// issue).  500 x 30 control call 17.7 -> 14.1 us, 4096 x 64 228 -> 128 us, 65536
-// x 30 1420 -> 756 us, a batch of 256 problems 2530 -> 1937 us.
+// issue).  500 x 30 control call 17.7 -> 14.1 us, 4096 x 64 228 -> 123 us, 65536
+// x 30 1420 -> 717 us, a batch of 256 problems 2530 -> 1840 us.
 #include <algorithm>
 
 #include "kinematics.h"
@@ -77,6 +77,29 @@ __device__ __forceinline__ float row_max_nonneg(float x)
 // exact test would report is ever culled.
 constexpr float kCullMargin = 1.0e-4f;
 
+// The capsule that holds a sphere's centres cc over the caller's row of 16
+// points, in every lane: the chord from the row's first centre a (a.xyz) to its
+// last (a + b.xyz), and as radius (a.w) the largest distance of a centre to the
+// chord's point at its own time (tau in [0, 1]; any point of the chord serves)
+// plus r_s and a margin; b.w is 1 / |b|^2.  Where a row holds a centre that is
+// not finite, a ball that meets everything.
+__device__ __forceinline__ void row_capsule(const float cc[3], float tau, float rs, float4 &a, float4 &b)
+{
+    const float ax = row_lane<0>(cc[0]), ay = row_lane<0>(cc[1]), az = row_lane<0>(cc[2]);
+    const float dx = cc[0] - ax, dy = cc[1] - ay, dz = cc[2] - az;
+    const float bx = row_lane<15>(dx), by = row_lane<15>(dy), bz = row_lane<15>(dz);
+    const float ex = fmaf(-tau, bx, dx), ey = fmaf(-tau, by, dy), ez = fmaf(-tau, bz, dz);
+    const float rad = fast_sqrt(row_max_nonneg(fminf(fmaf(ex, ex, fmaf(ey, ey, ez * ez)), 1.0e30f)));
+    a = make_float4(ax, ay, az, rad + (rs + kCullMargin));
+    b = make_float4(bx, by, bz, __builtin_amdgcn_rcpf(fmaxf(fmaf(bx, bx, fmaf(by, by, bz * bz)), 1.0e-20f)));
+    if (__builtin_amdgcn_ballot_w64(!(rad < 1.0e6f)) != 0) {
+        const bool bad = !(rad < 1.0e6f);
+        const float zero = fminf(fabsf(rad), 0.0f);  // (formed here, rarely)
+        a = make_float4(bad ? zero : a.x, bad ? zero : a.y, bad ? zero : a.z, bad ? 1.0e15f : a.w);
+        b = make_float4(bad ? zero : b.x, bad ? zero : b.y, bad ? zero : b.z, bad ? zero : b.w);
+    }
+}
+
 // Whether the capsule (segment a.xyz + t b.xyz, t in [0, 1], radius `reach`
 // already holding the obstacle's; b.w = 1 / |b.xyz|^2) meets the point o.
 __device__ __forceinline__ bool capsule_hits(const float4 a, const float4 b, float reach, float ox, float oy, float oz)
@@ -103,6 +126,7 @@ struct TileFirst {
     const int32_t *sph_body;
     const float *body_bound;
     const int32_t *self_items;
+    uint64_t cap_mask;
 };
 // (step, mean, N and H: known to the plain kernel from its arguments)
 __device__ __forceinline__ TileFirst fetch_first(ProblemRef P, RobotRef R, uint32_t *step, const float *mean,
@@ -111,11 +135,11 @@ __device__ __forceinline__ TileFirst fetch_first(ProblemRef P, RobotRef R, uint3
     TileFirst F{step,         mean,          N,           H,           P.n_halton,  P.n_null,     P.n_sph_obs,
                 P.n_box_obs,  P.ppt,         R.n_spheres, R.n_self_items, P.cost_mask, P.seed_lo, P.seed_hi,
                 P.comb,       P.cov_step,    P.tables,    P.halton,    P.obs_bound, P.box_obs,    P.sigma2,
-                R.sph_local,  R.sph_body,    R.body_bound, R.self_items};
+                R.sph_local,  R.sph_body,    R.body_bound, R.self_items, R.cap_mask};
     asm volatile("" : "+s"(F.n_halton), "+s"(F.n_null), "+s"(F.n_sph_obs), "+s"(F.n_box_obs), "+s"(F.ppt),
                  "+s"(F.n_spheres), "+s"(F.n_self_items), "+s"(F.cost_mask), "+s"(F.seed_lo), "+s"(F.seed_hi),
                  "+s"(F.comb), "+s"(F.cov_step), "+s"(F.tables), "+s"(F.halton), "+s"(F.obs_bound), "+s"(F.box_obs),
-                 "+s"(F.sigma2), "+s"(F.sph_local), "+s"(F.sph_body), "+s"(F.body_bound), "+s"(F.self_items));
+                 "+s"(F.sigma2), "+s"(F.sph_local), "+s"(F.sph_body), "+s"(F.body_bound), "+s"(F.self_items), "+s"(F.cap_mask));
     return F;
 }
 
@@ -454,16 +478,16 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
     // (Eq. 12) terms from the frames while the others place the spheres, so
     // that the collision phase is spread evenly over all waves.
     constexpr int WC = W - kPoseWaves;
+    // where in its row's span of steps this lane lies, in [0, 1]
+    const float step_l = floorf(((float)src + 0.5f) * __builtin_amdgcn_rcpf((float)ppt));
+    const float step0 = row_lane<0>(step_l);
+    const float tau =
+        fminf((step_l - step0) * __builtin_amdgcn_rcpf(fmaxf(row_lane<15>(step_l) - step0, 1.0f)), 1.0f);
     if (wave < WC) {
         const int s0 = wave * S / WC, s1 = (wave + 1) * S / WC;
         if ((mask & (STORM_COST_SELF | STORM_COST_ENV)) && s0 < s1) {
             // a contiguous run of spheres per wave (sorted by body): the
             // frame of a body is read from LDS once per run
-            // where in its row's span of steps this lane lies, in [0, 1]
-            const float step = floorf(((float)src + 0.5f) * __builtin_amdgcn_rcpf((float)ppt));
-            const float step0 = row_lane<0>(step);
-            const float tau =
-                fminf((step - step0) * __builtin_amdgcn_rcpf(fmaxf(row_lane<15>(step) - step0, 1.0f)), 1.0f);
             // (the next sphere's record is read one ahead)
             float F[12];
             int fb = __builtin_amdgcn_readfirstlane((int)s_body[s0]);
@@ -480,27 +504,18 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
                     cc[c] = fmaf(F[c * 3 + 0], loc.x, fmaf(F[c * 3 + 1], loc.y, fmaf(F[c * 3 + 2], loc.z, F[9 + c])));
                     s_cen[(s * 3 + c) * kLanes + lane] = cc[c];
                 }
-                // The capsule of each row of 16 points, which phase D tests
-                // against the obstacles and other spheres: the chord from the row's first
-                // centre a to its last, and as radius the largest distance
-                // of a centre to the chord's point at its own time (any
-                // point of the chord serves), plus r_s and a margin.  A row with a
-                // centre that is not finite gets a ball that meets
-                // everything.
-                const float dx = cc[0] - row_lane<0>(cc[0]), dy = cc[1] - row_lane<0>(cc[1]),
-                            dz = cc[2] - row_lane<0>(cc[2]);
-                const float bx = row_lane<15>(dx), by = row_lane<15>(dy), bz = row_lane<15>(dz);
-                const float ex = fmaf(-tau, bx, dx), ey = fmaf(-tau, by, dy), ez = fmaf(-tau, bz, dz);
-                const float rad = fast_sqrt(row_max_nonneg(fminf(fmaf(ex, ex, fmaf(ey, ey, ez * ez)), 1.0e30f)));
-                const float inv = __builtin_amdgcn_rcpf(fmaxf(fmaf(bx, bx, fmaf(by, by, bz * bz)), 1.0e-20f));
-                float4 *cap = s_cap + (s * 4 + (lane >> 4)) * 2;
-                if ((lane & 15) == 0) {
-                    cap[0] = make_float4(cc[0], cc[1], cc[2], rad + (loc.w + kCullMargin));
-                    cap[1] = make_float4(bx, by, bz, inv);
-                    if (!(rad < 1.0e6f)) {
-                        const float zero = fminf(rad, 0.0f);  // (formed here, rarely)
-                        cap[0] = make_float4(zero, zero, zero, 1.0e15f);
-                        cap[1] = make_float4(zero, zero, zero, zero);
+                // The capsules of the anchors, which phase D1 tests.  The
+                // others (about 30 of 52) are formed in D2, only where an
+                // obstacle is near their body: this phase is bound by issue
+                // (batch of 256 1937 -> 1840 us, 65536 x 30 748 -> 717 us,
+                // 4096 x 64 127 -> 123 us, 64 x 4096 x 64 12.84 -> 12.55 ms).
+                if (first.cap_mask >> s & 1) {
+                    float4 a, b;
+                    row_capsule(cc, tau, loc.w, a, b);
+                    float4 *cap = s_cap + (s * 4 + (lane >> 4)) * 2;
+                    if ((lane & 15) == 0) {
+                        cap[0] = a;
+                        cap[1] = b;
                     }
                 }
                 const int b = __builtin_amdgcn_readfirstlane(b_next);
@@ -666,8 +681,15 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
             const float y = s_cen[(s * 3 + 1) * kLanes + lane];
             const float z = s_cen[(s * 3 + 2) * kLanes + lane];
             const float rs = s_sph[s].w;
-            const float4 *cap = s_cap + (s * 4 + (lane >> 4)) * 2;
-            const float4 ca = cap[0], cb = cap[1];
+            float4 ca, cb;
+            if (first.cap_mask >> s & 1) {
+                const float4 *cap = s_cap + (s * 4 + (lane >> 4)) * 2;
+                ca = cap[0];
+                cb = cap[1];
+            } else {
+                const float cc[3] = {x, y, z};
+                row_capsule(cc, tau, rs, ca, cb);
+            }
             float best = 0.0f;
             for (int k0 = 0; k0 < n_near; k0 += 16) {
                 // the sphere's four capsules against 16 of its body's

@@ -127,7 +127,8 @@ struct alignas(64) RobotDev {
     const int32_t *sph_body;  // [S] frame index 0..7 the sphere is attached to
     const float *body_bound;  // [8][2] per frame: anchor sphere (int bits), what its radius lacks to hold the body's spheres
     const int32_t *self_items;  // [n_self_items][4] self-collision work items (self_pairs)
-    int32_t pad1[4];
+    uint64_t cap_mask;  // spheres that anchor a body or a run of self_items (their capsules are kept in LDS)
+    int32_t pad1[2];
     float ca[kFrames], sa[kFrames], a[kFrames], d[kFrames];  // DH: cos/sin alpha_{k-1}, a_{k-1}, d_k
 };
 
