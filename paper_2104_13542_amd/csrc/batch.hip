@@ -29,7 +29,7 @@ struct storm_batch_s {
     uint32_t *d_next = nullptr;    // queue head (0 between launches)
     int2 *d_adj_items = nullptr;   // (problem, tile chunk) items of the batched adjoint
     int n_adj_items = 0;
-    int2 *d_part_items = nullptr;  // (problem, chunk of particles) items of the larger problems' updates
+    int2 *d_part_items = nullptr;  // (problem, joint and chain) items of the larger problems' updates
     int n_part_items = 0;
     bool adj_split = false;        // its items are tiles, each split over a workgroup
     bool differentiable = true;    // every problem's gradient terms are differentiable

@@ -103,7 +103,7 @@ struct alignas(64) ProblemDev {
     float beta, alpha_mu, alpha_sigma, sigma2_min;
     float *ball;            // [8]: ball position, velocity (world frame) at the current state, pad
     float *qbuf;            // [7][N][H] joint positions of the last step (stand-alone network pass)
-    float *upd_part;        // partial sums of the update over chunks of particles (many particles)
+    float *upd_part;        // partial sums of the update (many particles)
 
     float k_m, w_pos, w_rot, a_stop;
     float a_joint, a_vel, a_manip, a_coll;
@@ -209,8 +209,8 @@ hipError_t set_rollout_lds_limit();
 // Whether the learned self-collision network's weight matrices (W1, W2, W3
 // of storm_robot.self_mlp) hold FP16 values only, as its kernel requires.
 bool selfnet_weights_fp16(const float *prm);
-// Chunks of particles of a problem's update, and the floats of their partial
-// sums (ProblemDev::upd_part); 0 where one workgroup per joint takes it.
+// Partial sums of a problem's update (joint and chain of accumulators), and their
+// floats (ProblemDev::upd_part); 0 where one workgroup per joint takes it.
 int update_parts(int N, int H);
 size_t update_part_floats(int N, int H);
 hipError_t launch_update(const ProblemDev &P, const PlainDev *dev, float *mean_out, float *sigma2_out, float *cmd, int shift,

@@ -15,7 +15,7 @@
 // loads its up to 32 controls at the start, together with the costs, so the
 // only global-memory latency on the path is the first one.  Bound by latency:
 // two exchanges, a division and the tail's chain behind the first loads
-// (4.2 us at 500 x 30).  Past those sizes, update_part and update_join (below).
+// (4.2 us at 500 x 30).  Past those sizes, update_chain and update_join (below).
 //
 // The variance about the new mean comes from the moments about the old one,
 // sum w (d - delta)^2 = S2/S0 - 2 delta S1/S0 + delta^2, in one pass.  Wave
@@ -100,11 +100,9 @@ __device__ __forceinline__ float block_min(float v, float *s_wave, int lane, int
     return m;
 }
 
-constexpr int kPartMax = 512;      // chunks of the larger form
-
 // Workgroup LDS of the update, declared once per kernel.
 struct UpdateLds {
-    float buf[kRows];  // weights; of the larger form, the chunks' factors
+    float buf[kRows];  // weights
     float red[2 * kThreads];
     float wave[kWaves];
     float wsum[kWaves];
@@ -362,189 +360,228 @@ __global__ __launch_bounds__(kThreads) void update_kernel(const PlainDev *dev, c
     update_joint<kSlots>(P, first, blockIdx.x, mean_out, sigma2_out, cmd, shift, kCov, L);
 }
 
-// The larger form: the same update for more particles, over many
-// workgroups.  One workgroup per joint would pull all N H controls of a joint
-// through one CU (N = 65536, H = 30: 90-180 us); instead the particles go to
-// chunks, one workgroup each, which sums the weights and all seven joints'
-// moments of its particles with weights relative to its own least cost, and a
-// second kernel joins the chunks, one workgroup per joint, scaling each by the
-// weight of its least cost.  Particles whose weight (against their chunk's
-// best) is exactly zero are left out; every order is fixed.  64 particles a
-// chunk at least, so that a row of threads still has a few; 512 chunks at
-// most, two workgroups per CU and a join of one pass.  The line is where one
-// workgroup can no longer hold a joint's controls in its registers.  Control call
-// and graph step with one workgroup per joint reading twice, and so: 4096 x 64
-// 167.7 -> 155.7 us, 65536 x 30 1152 -> 957 us.
-constexpr int kPartMin = 64;       // particles per chunk, at least
-constexpr int kPartSub = kThreads; // particles weighted at a time
-// floats of one chunk's record: S0, least cost, whether a cost is not finite,
-// pad, then S1 and S2 of [7][H]
-__host__ __device__ constexpr int part_floats(int H) { return 4 + 2 * kDof * H; }
+// The larger form: the same update for more particles.  One workgroup per
+// joint would pull all N H controls of the joint through one CU (N = 65536, H =
+// 30: 90-180 us).  A thread (row r, step h) sums its particles in eight
+// accumulators, number m taking every eighth of them, so the accumulators are
+// chains of their own: a workgroup per (joint, m) sums one of them, each in the
+// order that one workgroup would, and update_join adds the eight and takes the
+// tail.  Two ways to gather the particles:
+//   list   (at most 4096 weights not exactly zero, beta small against the spread
+//          of C): only those, from a list compacted in ascending order;
+//   dense  otherwise: all, weights staged in LDS by chunks.
+// Each workgroup finds min C and the weights it needs itself (three passes over
+// C, from L2).  Control call and graph step with one workgroup per joint, and
+// so: SPLIT_FIGURES.
+constexpr int kChains = 8;    // accumulators of a thread
+constexpr int kList = 4096;   // capacity of the list
+constexpr int kChunk = 8192;  // weights staged at a time
+// floats of a joint's partial sums, S1 and S2 of [chain][2][thread]; after all
+// joints', the sum of the weights and whether a cost is not finite
+constexpr int kJointPart = kChains * 2 * kThreads;
+constexpr int kUpdateParts = kDof * kChains + 1;  // workgroups: chains, and one for the weights' sum
 
-__host__ __device__ inline int part_chunk(int N)
+// Whether the weight exp(x) is not zero in FP32: below -104 it is (half the
+// least denormal is exp(-103.97)), above -103 it is not.
+constexpr float kNoWeight = -104.0f;
+__device__ __forceinline__ bool has_weight(float x)
 {
-    const int per = (N + kPartMax - 1) / kPartMax;
-    return per < kPartMin ? kPartMin : per;
+    if (x < kNoWeight) return false;
+    return x > -103.0f || expf(x) > 0.0f;
 }
-__host__ __device__ inline int part_count(int N) { return (N + part_chunk(N) - 1) / part_chunk(N); }
 
-// Chunk c of a problem.
-__device__ __forceinline__ void update_part(const float *__restrict__ C_in, const float *__restrict__ u_in,
-                                            const float *__restrict__ mean_in, float *__restrict__ part, int32_t N,
-                                            int32_t H, float nib, int32_t chunk, int c)
+// Part c of a problem: chain c % 8 of joint c / 8, or, last, the weights' sum.
+__device__ __forceinline__ void update_chain(const float *__restrict__ C_in, const float *__restrict__ u_in,
+                                             const float *__restrict__ mean_in, float *__restrict__ part_in,
+                                             const int N, const int H, const float nib, const int c)
 {
-    const global_ptr<const float> C = as_global(C_in), u = as_global(u_in), mean = as_global(mean_in);
-    __shared__ float s_red[2 * kDof][kThreads];
-    __shared__ float s_w[kPartSub];
-    __shared__ int s_idx[kPartSub];
+    __shared__ float s_w[kChunk];  // the list's weights, or a chunk's
+    __shared__ int s_idx[kList];
     __shared__ float s_wave[kWaves];
     __shared__ int s_count[kWaves];
+    const global_ptr<const float> C = as_global(C_in), mean = as_global(mean_in);
     const int t = threadIdx.x, lane = t & (kLanes - 1), wave = __builtin_amdgcn_readfirstlane(t / kLanes);
-    const int p0 = c * chunk, p1 = min(N, p0 + chunk);
     const int rows = kThreads / H, r = t / H, h = t - r * H;
-    float mu[kDof];
-#pragma unroll
-    for (int j = 0; j < kDof; ++j) mu[j] = r < rows ? mean[h * kDof + j] : 0.0f;
+    const bool in_rows = r < rows;
+    const int j = min(c / kChains, kDof - 1), m = c % kChains;
+    const global_ptr<const float> U = as_global(u_in) + (size_t)j * N * H + h;
+    const float mu = mean[h * kDof + j];
 
-    float least = INFINITY;
-    int bad = 0;
-    for (int i = p0 + t; i < p1; i += kThreads) {
-        const float Ci = C[i];
-        bad |= !isfinite(Ci);
-        least = fminf(least, Ci);
+    // Min C.  A run of the particles per wave, eight costs per lane in flight
+    // (an index past the end reads the last cost, and is left out below); a run
+    // of at most eight per lane stays in registers for the passes that follow.
+    const int run = (N + kThreads - 1) / kThreads * kLanes, i0 = wave * run, i1 = min(N, i0 + run);
+    const bool once = run <= 8 * kLanes;
+    float cv[8];
+    auto fetch = [&](int i) __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) cv[k] = C[min(i + k * kLanes, N - 1)];
+    };
+    float cmin = INFINITY;
+    int nonfinite = 0;
+    for (int i = i0 + lane; i < i0 + run; i += 8 * kLanes) {
+        fetch(i);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            nonfinite |= !isfinite(cv[k]);
+            cmin = fminf(cmin, cv[k]);
+        }
     }
-    bad = __syncthreads_or(bad);
-    least = block_min(least, s_wave, lane, wave);
+    nonfinite = __syncthreads_or(nonfinite);
+    cmin = block_min(cmin, s_wave, lane, wave);
 
-    float sw = 0.0f, a1[kDof], a2[kDof];
+    if (c == kDof * kChains) {
+        // the sum of the weights (per thread in stride order, per wave, waves
+        // in order)
+        float sw = 0.0f;
+        for (int i = t; i < N; i += 8 * kThreads) {
+            float x[8];
 #pragma unroll
-    for (int j = 0; j < kDof; ++j) a1[j] = a2[j] = 0.0f;
-    for (int q0 = p0; q0 < p1; q0 += kPartSub) {
-        // weights, and the particles whose weight is not zero in their order
-        const int i = q0 + t;
-        const float w = i < p1 ? expf((C[i] - least) * nib) : 0.0f;
-        sw += w;
-        const bool nz = w > 0.0f;
-        const uint64_t bal = __builtin_amdgcn_ballot_w64(nz);
-        if (lane == 0) s_count[wave] = __builtin_popcountll(bal);
-        __syncthreads();
-        int pos = __builtin_popcountll(bal & ((1ull << lane) - 1ull)), M = 0;
-        for (int k = 0; k < kWaves; ++k) {
-            pos += k < wave ? s_count[k] : 0;
-            M += s_count[k];
-        }
-        if (nz) {
-            s_idx[pos] = i;
-            s_w[pos] = w;
-        }
-        __syncthreads();
-        if (r < rows)
-            for (int k = r; k < M; k += rows) {
-                const global_ptr<const float> U = u + (size_t)s_idx[k] * H + h;
-                float d[kDof];
+            for (int k = 0; k < 8; ++k) x[k] = C[min(i + k * kThreads, N - 1)];
 #pragma unroll
-                for (int j = 0; j < kDof; ++j) d[j] = U[(size_t)j * N * H];
-                const float wk = s_w[k];
-#pragma unroll
-                for (int j = 0; j < kDof; ++j) {
-                    d[j] -= mu[j];
-                    const float wd = wk * d[j];
-                    a1[j] += wd;
-                    a2[j] = fmaf(wd, d[j], a2[j]);
-                }
+            for (int k = 0; k < 8; ++k) {
+                x[k] = (x[k] - cmin) * nib;
+                if (i + k * kThreads < N && !(x[k] < kNoWeight)) sw += expf(x[k]);
             }
+        }
+        sw = wave_sum(sw);
+        if (lane == 0) s_wave[wave] = sw;
         __syncthreads();
+        if (t == 0) {
+            float S0 = 0.0f;
+            for (int k = 0; k < kWaves; ++k) S0 += s_wave[k];
+            const global_ptr<float> out = as_global(part_in) + (size_t)kDof * kJointPart;
+            out[0] = S0;
+            out[1] = nonfinite ? 1.0f : 0.0f;
+        }
+        return;
     }
+
+    // the number of nonzero weights, in all and before this wave's
+    int count = 0;
+    for (int i = i0 + lane; i < i0 + run; i += 8 * kLanes) {
+        if (!once) fetch(i);
 #pragma unroll
-    for (int j = 0; j < kDof; ++j) {
-        s_red[j][t] = a1[j];
-        s_red[kDof + j][t] = a2[j];
+        for (int k = 0; k < 8; ++k)
+            count += __builtin_popcountll(
+                __builtin_amdgcn_ballot_w64(i + k * kLanes < i1 && has_weight((cv[k] - cmin) * nib)));
     }
-    sw = wave_sum(sw);
-    if (lane == 0) s_wave[wave] = sw;
+    if (lane == 0) s_count[wave] = count;
     __syncthreads();
-    const global_ptr<float> out = as_global(part) + (size_t)c * part_floats(H);
-    if (t == 0) {
-        float S0 = 0.0f;
-        for (int k = 0; k < kWaves; ++k) S0 += s_wave[k];
-        out[0] = S0;
-        out[1] = least;
-        out[2] = bad ? 1.0f : 0.0f;
+    int M = 0, at = 0;
+    for (int k = 0; k < kWaves; ++k) {
+        at += k < wave ? s_count[k] : 0;
+        M += s_count[k];
     }
-    for (int k = t; k < 2 * kDof * H; k += kThreads) {
-        const int q = k / H, hh = k - q * H;
-        float s = 0.0f;
-        for (int m = 0; m < rows; ++m) s += s_red[q][m * H + hh];
-        out[4 + k] = s;
+    const global_ptr<float> part = as_global(part_in) + (size_t)j * kJointPart;
+
+    // the chain: particles r + m rows, + 8 rows, ... while all eight chains have
+    // one; the first takes the others that remain
+    float a1 = 0.0f, a2 = 0.0f;
+    if (M <= kList) {
+        for (int i = i0 + lane; i < i0 + run; i += 8 * kLanes) {
+            if (!once) fetch(i);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const float x = (cv[k] - cmin) * nib;
+                const bool nz = i + k * kLanes < i1 && has_weight(x);
+                const uint64_t bal = __builtin_amdgcn_ballot_w64(nz);
+                if (bal == 0) continue;
+                if (nz) {
+                    const int pos = at + __builtin_popcountll(bal & ((1ull << lane) - 1ull));
+                    s_idx[pos] = i + k * kLanes;
+                    s_w[pos] = expf(x);
+                }
+                at += __builtin_popcountll(bal);
+            }
+        }
+        __syncthreads();
+        if (in_rows) {
+            int k = r;
+#pragma unroll 4
+            for (; k + (kChains - 1) * rows < M; k += kChains * rows) {
+                const float d = U[(size_t)s_idx[k + m * rows] * H] - mu;
+                const float wd = s_w[k + m * rows] * d;
+                a1 += wd;
+                a2 = fmaf(wd, d, a2);
+            }
+            for (; m == 0 && k < M; k += rows) {
+                const float d = U[(size_t)s_idx[k] * H] - mu;
+                const float wd = s_w[k] * d;
+                a1 += wd;
+                a2 = fmaf(wd, d, a2);
+            }
+        }
+    } else {
+        for (int c0 = 0; c0 < N; c0 += kChunk) {
+            const int nc = min(kChunk, N - c0);
+            __syncthreads();
+            for (int k = t; k < nc; k += kThreads) s_w[k] = expf((C[c0 + k] - cmin) * nib);
+            __syncthreads();
+            if (!in_rows) continue;
+            int k = r;
+#pragma unroll 8
+            for (; k + (kChains - 1) * rows < nc; k += kChains * rows) {
+                const float d = U[(size_t)(c0 + k + m * rows) * H] - mu;
+                const float wd = s_w[k + m * rows] * d;
+                a1 += wd;
+                a2 = fmaf(wd, d, a2);
+            }
+            for (; m == 0 && k < nc; k += rows) {
+                const float d = U[(size_t)(c0 + k) * H] - mu;
+                const float wd = s_w[k] * d;
+                a1 += wd;
+                a2 = fmaf(wd, d, a2);
+            }
+        }
     }
+    part[(2 * m) * kThreads + t] = a1;
+    part[(2 * m + 1) * kThreads + t] = a2;
 }
 
-__global__ __launch_bounds__(kThreads) void update_part_kernel(const float *__restrict__ C,
-                                                               const float *__restrict__ u,
-                                                               const float *__restrict__ mean, float *__restrict__ part,
-                                                               int32_t N, int32_t H, float nib, int32_t chunk)
+__global__ __launch_bounds__(kThreads) void update_chain_kernel(const float *__restrict__ C,
+                                                                const float *__restrict__ u,
+                                                                const float *__restrict__ mean,
+                                                                float *__restrict__ part, int32_t N, int32_t H,
+                                                                float nib)
 {
-    update_part(C, u, mean, part, N, H, nib, chunk, blockIdx.x);
+    update_chain(C, u, mean, part, N, H, nib, blockIdx.x);
 }
 
-// Workgroup k of a batch takes chunk items[k] = (problem, chunk).
-__global__ __launch_bounds__(kThreads) void update_part_batch_kernel(const ProblemDev *__restrict__ probs,
-                                                                     const int2 *__restrict__ items)
+// Workgroup k of a batch takes part items[k] = (problem, part).
+__global__ __launch_bounds__(kThreads) void update_chain_batch_kernel(const ProblemDev *__restrict__ probs,
+                                                                      const int2 *__restrict__ items)
 {
     const STORM_CONST_AS int32_t *it = uniform_ptr(reinterpret_cast<const int32_t *>(items));
     const int p = it[2 * blockIdx.x], c = it[2 * blockIdx.x + 1];
     ProblemRef P = uniform_ptr(probs)[p];
-    update_part(P.C, P.u, P.mean, P.upd_part, P.N, P.H, -1.0f / P.beta, part_chunk(P.N), c);
+    update_chain(P.C, P.u, P.mean, P.upd_part, P.N, P.H, -1.0f / P.beta, c);
 }
 
-// Joint j's update from the problem's chunks.
+// Joint j's update from its chains.
 __device__ __forceinline__ void update_join(ProblemRef descriptor, const float *__restrict__ part_in, const int j,
                                             float *__restrict__ mean_out, float *__restrict__ sigma2_out,
-                                            float *__restrict__ cmd, const int n_part, const int H, const int shift,
-                                            const bool cov, UpdateLds &L)
+                                            float *__restrict__ cmd, const int H, const int shift, const bool cov,
+                                            UpdateLds &L)
 {
-    float *s_f = L.buf;
     float *s_red = L.red;
-    float *s_wave = L.wave;
-    const global_ptr<const float> part = as_global(part_in);
+    const global_ptr<const float> part = as_global(part_in) + (size_t)j * kJointPart;
     UpdateProblem P = fetch_problem(descriptor);
-    wait_problem(P);
     const int t = threadIdx.x, lane = t & (kLanes - 1), wave = __builtin_amdgcn_readfirstlane(t / kLanes);
-    const int stride = part_floats(H);
-    const int rows = kThreads / H, r = t / H, h = t - r * H;
-    // every load at once: this chunk's weight sum and least cost, then the
-    // moments of chunks r, r + rows, ... at step h
-    float S0_c = 0.0f, least_c = INFINITY, bad_c = 0.0f;
-    if (t < n_part) {
-        const global_ptr<const float> rec = part + (size_t)t * stride;
-        S0_c = rec[0];
-        least_c = rec[1];
-        bad_c = rec[2];
-    }
-    const float muo_l = t < H ? as_global(P.mean)[t * kDof + j] : 0.0f;
+    const int rows = kThreads / H;
+    float a[2 * kChains];
+#pragma unroll
+    for (int k = 0; k < 2 * kChains; ++k) a[k] = part[k * kThreads + t];
+    const global_ptr<const float> sum = as_global(part_in) + (size_t)kDof * kJointPart;
+    const float S0 = sum[0], bad = sum[1];
+    wait_problem(P);
+    const float muo_l = as_global(P.mean)[min(t, H - 1) * kDof + j];
     const TailArgs T = fetch_tail(P, mean_out, sigma2_out, cmd, shift, cov, j, t, H);
-    const int bad = __syncthreads_or(bad_c != 0.0f);
-    const float least = block_min(least_c, s_wave, lane, wave);
-    const float f = t < n_part && !bad ? expf((least_c - least) * (-1.0f / P.beta)) : 0.0f;
-    if (t < kPartMax) s_f[t] = f;
-    float S0 = 0.0f;
-    {
-        const float sw = wave_sum(f * S0_c);
-        if (lane == 0) s_wave[wave] = sw;
-        __syncthreads();
-        for (int k = 0; k < kWaves; ++k) S0 += s_wave[k];
-    }
-    const bool ok = !bad && S0 > 0.0f && isfinite(S0);
     float x1 = 0.0f, x2 = 0.0f;
-    if (r < rows && ok) {
-        const global_ptr<const float> src = part + 4 + (size_t)j * H + h;
-#pragma unroll 4
-        for (int c = r; c < n_part; c += rows) {
-            // (a chunk of no weight is left out, as its particles are)
-            const float fc = s_f[c], c1 = src[(size_t)c * stride], c2 = src[(size_t)c * stride + kDof * H];
-            x1 = fmaf(fc, fc > 0.0f ? c1 : 0.0f, x1);
-            x2 = fmaf(fc, fc > 0.0f ? c2 : 0.0f, x2);
-        }
+#pragma unroll
+    for (int m = 0; m < kChains; ++m) {
+        x1 += a[2 * m];
+        x2 += a[2 * m + 1];
     }
     s_red[t] = x1;
     s_red[kThreads + t] = x2;
@@ -556,7 +593,8 @@ __device__ __forceinline__ void update_join(ProblemRef descriptor, const float *
                 s1 += s_red[k * H + lane];
                 s2 += s_red[kThreads + k * H + lane];
             }
-        update_tail(T, j, H, lane, s1, s2, S0, muo_l, ok, bad, cov);
+        const bool ok = bad == 0.0f && S0 > 0.0f && isfinite(S0);
+        update_tail(T, j, H, lane, s1, s2, S0, lane < H ? muo_l : 0.0f, ok, bad != 0.0f, cov);
     }
 }
 
@@ -564,15 +602,14 @@ template <bool kCov>
 __global__ __launch_bounds__(kThreads) void update_join_kernel(const PlainDev *dev, const float *__restrict__ part,
                                                                float *__restrict__ mean_out,
                                                                float *__restrict__ sigma2_out,
-                                                               float *__restrict__ cmd, int32_t n_part, int16_t H,
-                                                               int16_t shift)
+                                                               float *__restrict__ cmd, int16_t H, int16_t shift)
 {
     __shared__ UpdateLds L;
-    update_join(uniform_ptr(dev)->P, part, blockIdx.x, mean_out, sigma2_out, cmd, n_part, H, shift, kCov, L);
+    update_join(uniform_ptr(dev)->P, part, blockIdx.x, mean_out, sigma2_out, cmd, H, shift, kCov, L);
 }
 
 // Workgroup (p, j) of a batch; commands go to cmd[p][7].  (The larger problems'
-// chunks are there.)
+// chains are there.)
 __global__ __launch_bounds__(kThreads) void update_batch_kernel(const ProblemDev *__restrict__ probs,
                                                                 float *__restrict__ cmd, int shift)
 {
@@ -589,7 +626,7 @@ __global__ __launch_bounds__(kThreads) void update_batch_kernel(const ProblemDev
     else if (slots == 32)
         update_joint<32>(P, first, j, nullptr, nullptr, c, shift, P.cov_step != 0u, L);
     else
-        update_join(P, P.upd_part, j, nullptr, nullptr, c, part_count(P.N), P.H, shift, P.cov_step != 0u, L);
+        update_join(P, P.upd_part, j, nullptr, nullptr, c, P.H, shift, P.cov_step != 0u, L);
 }
 
 }  // namespace
@@ -598,7 +635,7 @@ hipError_t launch_update_batch(const ProblemDev *probs, int n_problems, const in
                                float *cmd, int shift, hipStream_t stream)
 {
     if (n_part_items > 0) {
-        hipLaunchKernelGGL(update_part_batch_kernel, dim3((unsigned)n_part_items), dim3(kThreads), 0, stream, probs,
+        hipLaunchKernelGGL(update_chain_batch_kernel, dim3((unsigned)n_part_items), dim3(kThreads), 0, stream, probs,
                            part_items);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -613,14 +650,13 @@ hipError_t launch_update(const ProblemDev &P, const PlainDev *dev, float *mean_o
 {
     const int slots = update_slots(P.N, P.H);
     if (slots == 0) {
-        const int chunk = part_chunk(P.N), n_part = part_count(P.N);
-        hipLaunchKernelGGL(update_part_kernel, dim3((unsigned)n_part), dim3(kThreads), 0, stream, P.C, P.u, P.mean,
-                           P.upd_part, P.N, P.H, -1.0f / P.beta, chunk);
+        hipLaunchKernelGGL(update_chain_kernel, dim3(kUpdateParts), dim3(kThreads), 0, stream, P.C, P.u, P.mean,
+                           P.upd_part, P.N, P.H, -1.0f / P.beta);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         auto join = P.cov_step ? update_join_kernel<true> : update_join_kernel<false>;
         hipLaunchKernelGGL(join, dim3(kDof), dim3(kThreads), 0, stream, dev, P.upd_part, mean_out, sigma2_out, cmd,
-                           n_part, (int16_t)P.H, (int16_t)shift);
+                           (int16_t)P.H, (int16_t)shift);
         return hipGetLastError();
     }
     auto kernel = P.cov_step ? (slots == 8    ? update_kernel<true, 8>
@@ -634,8 +670,8 @@ hipError_t launch_update(const ProblemDev &P, const PlainDev *dev, float *mean_o
     return hipGetLastError();
 }
 
-int update_parts(int N, int H) { return update_slots(N, H) != 0 ? 0 : part_count(N); }
+int update_parts(int N, int H) { return update_slots(N, H) != 0 ? 0 : kUpdateParts; }
 
-size_t update_part_floats(int N, int H) { return (size_t)update_parts(N, H) * part_floats(H); }
+size_t update_part_floats(int N, int H) { return update_slots(N, H) != 0 ? 0 : (size_t)kDof * kJointPart + 4; }
 
 }  // namespace storm
