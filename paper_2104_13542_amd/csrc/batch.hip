@@ -213,7 +213,7 @@ int32_t storm_batch_init(storm_batch *out, int32_t n_problems, const storm_param
     b->n_adj_items = (int)adj.size();
     std::vector<int2> parts;
     for (int p = 0; p < n_problems; ++p)
-        for (int c = 0; c < update_parts(probs[p].N, probs[p].H); ++c) parts.push_back(make_int2(p, c));
+        for (int c = 0; c < update_batch_parts(probs[p].N, probs[p].H); ++c) parts.push_back(make_int2(p, c));
     b->n_part_items = (int)parts.size();
     std::vector<int> order(plain.size());
     for (size_t k = 0; k < order.size(); ++k) order[k] = (int)k;

@@ -37,8 +37,8 @@
 // Three forms: a 16-wave workgroup per tile up to one tile per CU (bound by the
 // latency of its phases), 8-wave workgroups that loop over the tiles of one
 // larger problem, and the same over the tiles of a batch (both bound by VALU
-// issue).  500 x 30 control call 17.7 -> 14.1 us, 4096 x 64 228 -> 123 us, 65536
-// x 30 1420 -> 717 us, a batch of 256 problems 2530 -> 1840 us.
+// issue).  500 x 30 control call 17.7 -> 14.1 us, 4096 x 64 228 -> 131 us, 65536
+// x 30 1420 -> 764 us, a batch of 256 problems 2530 -> 1840 us.
 #include <algorithm>
 
 #include "kinematics.h"

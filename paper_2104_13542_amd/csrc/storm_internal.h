@@ -209,9 +209,10 @@ hipError_t set_rollout_lds_limit();
 // Whether the learned self-collision network's weight matrices (W1, W2, W3
 // of storm_robot.self_mlp) hold FP16 values only, as its kernel requires.
 bool selfnet_weights_fp16(const float *prm);
-// Partial sums of a problem's update (joint and chain of accumulators), and their
-// floats (ProblemDev::upd_part); 0 where one workgroup per joint takes it.
-int update_parts(int N, int H);
+// Workgroups of a problem's update in a batch before the join (0: none), and the
+// floats of its partial sums (ProblemDev::upd_part; 0 where one workgroup per
+// joint takes a single problem).
+int update_batch_parts(int N, int H);
 size_t update_part_floats(int N, int H);
 hipError_t launch_update(const ProblemDev &P, const PlainDev *dev, float *mean_out, float *sigma2_out, float *cmd, int shift,
                          hipStream_t stream);

@@ -372,13 +372,17 @@ __global__ __launch_bounds__(kThreads) void update_kernel(const PlainDev *dev, c
 //   dense  otherwise: all, weights staged in LDS by chunks.
 // Each workgroup finds min C and the weights it needs itself (three passes over
 // C, from L2).  Control call and graph step with one workgroup per joint, and
-// so: SPLIT_FIGURES.
+// so: 65536 x 30 update alone 89 -> 59 us; 4096 x 64 about the same (9 and 13 us
+// of 131).  A batch, which has workgroups enough, takes problems of up to 8192
+// particles with one workgroup per joint (update_all: 64 problems of 4096 x 64 27
+// us, by chains 81), to the same bits.
 constexpr int kChains = 8;    // accumulators of a thread
 constexpr int kList = 4096;   // capacity of the list
 constexpr int kChunk = 8192;  // weights staged at a time
 // floats of a joint's partial sums, S1 and S2 of [chain][2][thread]; after all
 // joints', the sum of the weights and whether a cost is not finite
 constexpr int kJointPart = kChains * 2 * kThreads;
+constexpr int kOnce = 8 * kThreads;  // costs that a workgroup holds in registers
 constexpr int kUpdateParts = kDof * kChains + 1;  // workgroups: chains, and one for the weights' sum
 
 // Whether the weight exp(x) is not zero in FP32: below -104 it is (half the
@@ -391,10 +395,15 @@ __device__ __forceinline__ bool has_weight(float x)
 }
 
 // Part c of a problem: chain c % 8 of joint c / 8, or, last, the weights' sum.
+// kAll: all chains of joint c and the sum, in x1, x2, S0 and bad, and nothing in
+// part_in.
+template <bool kAll>
 __device__ __forceinline__ void update_chain(const float *__restrict__ C_in, const float *__restrict__ u_in,
                                              const float *__restrict__ mean_in, float *__restrict__ part_in,
-                                             const int N, const int H, const float nib, const int c)
+                                             const int N, const int H, const float nib, const int c, float &x1,
+                                             float &x2, float &S0, int &bad)
 {
+    constexpr int kN = kAll ? kChains : 1;  // chains summed here
     __shared__ float s_w[kChunk];  // the list's weights, or a chunk's
     __shared__ int s_idx[kList];
     __shared__ float s_wave[kWaves];
@@ -403,7 +412,7 @@ __device__ __forceinline__ void update_chain(const float *__restrict__ C_in, con
     const int t = threadIdx.x, lane = t & (kLanes - 1), wave = __builtin_amdgcn_readfirstlane(t / kLanes);
     const int rows = kThreads / H, r = t / H, h = t - r * H;
     const bool in_rows = r < rows;
-    const int j = min(c / kChains, kDof - 1), m = c % kChains;
+    const int j = kAll ? c : min(c / kChains, kDof - 1), m = kAll ? 0 : c % kChains;
     const global_ptr<const float> U = as_global(u_in) + (size_t)j * N * H + h;
     const float mu = mean[h * kDof + j];
 
@@ -430,7 +439,7 @@ __device__ __forceinline__ void update_chain(const float *__restrict__ C_in, con
     nonfinite = __syncthreads_or(nonfinite);
     cmin = block_min(cmin, s_wave, lane, wave);
 
-    if (c == kDof * kChains) {
+    if (kAll || c == kDof * kChains) {
         // the sum of the weights (per thread in stride order, per wave, waves
         // in order)
         float sw = 0.0f;
@@ -447,14 +456,17 @@ __device__ __forceinline__ void update_chain(const float *__restrict__ C_in, con
         sw = wave_sum(sw);
         if (lane == 0) s_wave[wave] = sw;
         __syncthreads();
-        if (t == 0) {
-            float S0 = 0.0f;
-            for (int k = 0; k < kWaves; ++k) S0 += s_wave[k];
+        S0 = 0.0f;
+        for (int k = 0; k < kWaves; ++k) S0 += s_wave[k];
+        bad = nonfinite;
+        if (!kAll) {
             const global_ptr<float> out = as_global(part_in) + (size_t)kDof * kJointPart;
-            out[0] = S0;
-            out[1] = nonfinite ? 1.0f : 0.0f;
+            if (t == 0) {
+                out[0] = S0;
+                out[1] = nonfinite ? 1.0f : 0.0f;
+            }
+            return;
         }
-        return;
     }
 
     // the number of nonzero weights, in all and before this wave's
@@ -473,11 +485,12 @@ __device__ __forceinline__ void update_chain(const float *__restrict__ C_in, con
         at += k < wave ? s_count[k] : 0;
         M += s_count[k];
     }
-    const global_ptr<float> part = as_global(part_in) + (size_t)j * kJointPart;
 
     // the chain: particles r + m rows, + 8 rows, ... while all eight chains have
     // one; the first takes the others that remain
-    float a1 = 0.0f, a2 = 0.0f;
+    float a1[kN], a2[kN];
+#pragma unroll
+    for (int q = 0; q < kN; ++q) a1[q] = a2[q] = 0.0f;
     if (M <= kList) {
         for (int i = i0 + lane; i < i0 + run; i += 8 * kLanes) {
             if (!once) fetch(i);
@@ -498,18 +511,23 @@ __device__ __forceinline__ void update_chain(const float *__restrict__ C_in, con
         __syncthreads();
         if (in_rows) {
             int k = r;
-#pragma unroll 4
+#pragma unroll kAll ? 1 : 4
             for (; k + (kChains - 1) * rows < M; k += kChains * rows) {
-                const float d = U[(size_t)s_idx[k + m * rows] * H] - mu;
-                const float wd = s_w[k + m * rows] * d;
-                a1 += wd;
-                a2 = fmaf(wd, d, a2);
+                float d[kN];
+#pragma unroll
+                for (int q = 0; q < kN; ++q) d[q] = U[(size_t)s_idx[k + (m + q) * rows] * H] - mu;
+#pragma unroll
+                for (int q = 0; q < kN; ++q) {
+                    const float wd = s_w[k + (m + q) * rows] * d[q];
+                    a1[q] += wd;
+                    a2[q] = fmaf(wd, d[q], a2[q]);
+                }
             }
             for (; m == 0 && k < M; k += rows) {
                 const float d = U[(size_t)s_idx[k] * H] - mu;
                 const float wd = s_w[k] * d;
-                a1 += wd;
-                a2 = fmaf(wd, d, a2);
+                a1[0] += wd;
+                a2[0] = fmaf(wd, d, a2[0]);
             }
         }
     } else {
@@ -520,23 +538,38 @@ __device__ __forceinline__ void update_chain(const float *__restrict__ C_in, con
             __syncthreads();
             if (!in_rows) continue;
             int k = r;
-#pragma unroll 8
+#pragma unroll kAll ? 1 : 8
             for (; k + (kChains - 1) * rows < nc; k += kChains * rows) {
-                const float d = U[(size_t)(c0 + k + m * rows) * H] - mu;
-                const float wd = s_w[k + m * rows] * d;
-                a1 += wd;
-                a2 = fmaf(wd, d, a2);
+                float d[kN];
+#pragma unroll
+                for (int q = 0; q < kN; ++q) d[q] = U[(size_t)(c0 + k + (m + q) * rows) * H] - mu;
+#pragma unroll
+                for (int q = 0; q < kN; ++q) {
+                    const float wd = s_w[k + (m + q) * rows] * d[q];
+                    a1[q] += wd;
+                    a2[q] = fmaf(wd, d[q], a2[q]);
+                }
             }
             for (; m == 0 && k < nc; k += rows) {
                 const float d = U[(size_t)(c0 + k) * H] - mu;
                 const float wd = s_w[k] * d;
-                a1 += wd;
-                a2 = fmaf(wd, d, a2);
+                a1[0] += wd;
+                a2[0] = fmaf(wd, d, a2[0]);
             }
         }
     }
-    part[(2 * m) * kThreads + t] = a1;
-    part[(2 * m + 1) * kThreads + t] = a2;
+    if (kAll) {
+        x1 = x2 = 0.0f;
+#pragma unroll
+        for (int q = 0; q < kN; ++q) {
+            x1 += a1[q];
+            x2 += a2[q];
+        }
+    } else {
+        const global_ptr<float> part = as_global(part_in) + (size_t)j * kJointPart;
+        part[(2 * m) * kThreads + t] = a1[0];
+        part[(2 * m + 1) * kThreads + t] = a2[0];
+    }
 }
 
 __global__ __launch_bounds__(kThreads) void update_chain_kernel(const float *__restrict__ C,
@@ -545,7 +578,9 @@ __global__ __launch_bounds__(kThreads) void update_chain_kernel(const float *__r
                                                                 float *__restrict__ part, int32_t N, int32_t H,
                                                                 float nib)
 {
-    update_chain(C, u, mean, part, N, H, nib, blockIdx.x);
+    float x1, x2, S0;
+    int bad;
+    update_chain<false>(C, u, mean, part, N, H, nib, blockIdx.x, x1, x2, S0, bad);
 }
 
 // Workgroup k of a batch takes part items[k] = (problem, part).
@@ -555,7 +590,28 @@ __global__ __launch_bounds__(kThreads) void update_chain_batch_kernel(const Prob
     const STORM_CONST_AS int32_t *it = uniform_ptr(reinterpret_cast<const int32_t *>(items));
     const int p = it[2 * blockIdx.x], c = it[2 * blockIdx.x + 1];
     ProblemRef P = uniform_ptr(probs)[p];
-    update_chain(P.C, P.u, P.mean, P.upd_part, P.N, P.H, -1.0f / P.beta, c);
+    float x1, x2, S0;
+    int bad;
+    update_chain<false>(P.C, P.u, P.mean, P.upd_part, P.N, P.H, -1.0f / P.beta, c, x1, x2, S0, bad);
+}
+
+// The rows' sums, then the tail, on wave 0.
+__device__ __forceinline__ void sum_rows(const TailArgs &T, const int j, const int H, float x1, float x2, float S0,
+                                         float muo, const bool bad, const bool cov, float *s_red)
+{
+    const int t = threadIdx.x, lane = t & (kLanes - 1), rows = kThreads / H;
+    s_red[t] = x1;
+    s_red[kThreads + t] = x2;
+    __syncthreads();
+    if (t >= kLanes) return;
+    float s1 = 0.0f, s2 = 0.0f;
+    if (lane < H)
+        for (int k = 0; k < rows; ++k) {
+            s1 += s_red[k * H + lane];
+            s2 += s_red[kThreads + k * H + lane];
+        }
+    const bool ok = !bad && S0 > 0.0f && isfinite(S0);
+    update_tail(T, j, H, lane, s1, s2, S0, lane < H ? muo : 0.0f, ok, bad, cov);
 }
 
 // Joint j's update from its chains.
@@ -567,8 +623,7 @@ __device__ __forceinline__ void update_join(ProblemRef descriptor, const float *
     float *s_red = L.red;
     const global_ptr<const float> part = as_global(part_in) + (size_t)j * kJointPart;
     UpdateProblem P = fetch_problem(descriptor);
-    const int t = threadIdx.x, lane = t & (kLanes - 1), wave = __builtin_amdgcn_readfirstlane(t / kLanes);
-    const int rows = kThreads / H;
+    const int t = threadIdx.x;
     float a[2 * kChains];
 #pragma unroll
     for (int k = 0; k < 2 * kChains; ++k) a[k] = part[k * kThreads + t];
@@ -583,19 +638,23 @@ __device__ __forceinline__ void update_join(ProblemRef descriptor, const float *
         x1 += a[2 * m];
         x2 += a[2 * m + 1];
     }
-    s_red[t] = x1;
-    s_red[kThreads + t] = x2;
-    __syncthreads();
-    if (wave == 0) {
-        float s1 = 0.0f, s2 = 0.0f;
-        if (lane < H)
-            for (int k = 0; k < rows; ++k) {
-                s1 += s_red[k * H + lane];
-                s2 += s_red[kThreads + k * H + lane];
-            }
-        const bool ok = bad == 0.0f && S0 > 0.0f && isfinite(S0);
-        update_tail(T, j, H, lane, s1, s2, S0, lane < H ? muo_l : 0.0f, ok, bad != 0.0f, cov);
-    }
+    sum_rows(T, j, H, x1, x2, S0, muo_l, bad != 0.0f, cov, s_red);
+}
+
+// Joint j's update by one workgroup, from its own chains.
+__device__ __forceinline__ void update_all(ProblemRef descriptor, const float *__restrict__ C,
+                                           const float *__restrict__ u, const int N, const int H, const int j,
+                                           float *__restrict__ mean_out, float *__restrict__ sigma2_out,
+                                           float *__restrict__ cmd, const int shift, const bool cov, UpdateLds &L)
+{
+    UpdateProblem P = fetch_problem(descriptor);
+    wait_problem(P);
+    const float muo_l = as_global(P.mean)[min((int)threadIdx.x, H - 1) * kDof + j];
+    const TailArgs T = fetch_tail(P, mean_out, sigma2_out, cmd, shift, cov, j, threadIdx.x, H);
+    float x1, x2, S0;
+    int bad;
+    update_chain<true>(C, u, P.mean, nullptr, N, H, -1.0f / P.beta, j, x1, x2, S0, bad);
+    sum_rows(T, j, H, x1, x2, S0, muo_l, bad != 0, cov, L.red);
 }
 
 template <bool kCov>
@@ -625,6 +684,8 @@ __global__ __launch_bounds__(kThreads) void update_batch_kernel(const ProblemDev
         update_joint<16>(P, first, j, nullptr, nullptr, c, shift, P.cov_step != 0u, L);
     else if (slots == 32)
         update_joint<32>(P, first, j, nullptr, nullptr, c, shift, P.cov_step != 0u, L);
+    else if (P.N <= kOnce)
+        update_all(P, P.C, P.u, P.N, P.H, j, nullptr, nullptr, c, shift, P.cov_step != 0u, L);
     else
         update_join(P, P.upd_part, j, nullptr, nullptr, c, P.H, shift, P.cov_step != 0u, L);
 }
@@ -670,7 +731,7 @@ hipError_t launch_update(const ProblemDev &P, const PlainDev *dev, float *mean_o
     return hipGetLastError();
 }
 
-int update_parts(int N, int H) { return update_slots(N, H) != 0 ? 0 : kUpdateParts; }
+int update_batch_parts(int N, int H) { return update_slots(N, H) != 0 || N <= kOnce ? 0 : kUpdateParts; }
 
 size_t update_part_floats(int N, int H) { return update_slots(N, H) != 0 ? 0 : (size_t)kDof * kJointPart + 4; }
 

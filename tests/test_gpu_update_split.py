@@ -1,7 +1,8 @@
-"""The policy update over chunks of particles (particle counts past the
-register path) against the oracle's update fed with the kernel's own costs and
-controls, at the edges of its chunks and rows, for weights from one-hot to
-uniform, and with a cost that is not finite (marked gpu)."""
+"""The policy update of more particles than one workgroup per joint holds in
+registers, in one workgroup per joint (up to 8192) and in parallel chains, against
+the oracle's update fed with the kernel's own costs and controls, at the edges of
+its forms and rows, for weights from one-hot to uniform, and with a cost that is
+not finite (marked gpu)."""
 import numpy as np
 import pytest
 
@@ -30,11 +31,12 @@ def _problem(n, h, beta, cov):
     return prob
 
 
-# the register path holds 32 * (1024 // h) particles, and 2048 at most; chunks
-# hold 64 particles up to 512 * 64
+# the register path holds 32 * (1024 // h) particles, and 2048 at most; the list
+# 4096 weights; chains begin at 8193 particles
 @pytest.mark.parametrize("n,h,beta,cov", [(2049, 1, 1.0, 0), (2049, 16, 1e-4, 1), (513, 64, 50.0, 0),
                                           (1089, 30, 1e6, 1), (545, 63, 1.0, 0), (32768, 3, 20.0, 0),
-                                          (32769, 2, 1e6, 1), (70001, 5, 5.0, 0)])
+                                          (32769, 2, 1e6, 1), (70001, 5, 5.0, 0), (4097, 8, 1e6, 0),
+                                          (8192, 8, 1e6, 1), (8193, 8, 1e6, 0)])
 def test_split_update_against_oracle(oracle_lib, n, h, beta, cov):
     from paper_2104_13542_amd import storm
 
@@ -96,7 +98,7 @@ def test_batched_split_update_is_each_problems_own():
     from paper_2104_13542_amd import storm
 
     probs = []
-    for k, (n, h) in enumerate([(64, 16), (4100, 8), (513, 64), (1000, 30), (1100, 30), (2049, 1)]):
+    for k, (n, h) in enumerate([(64, 16), (4100, 8), (513, 64), (1000, 30), (9000, 8), (2049, 1)]):
         pr = inputs.config3_problem(40 + k)
         p = pr.params
         p.n_particles, p.horizon, p.dt, p.n_halton, p.n_null = n, h, np.full(h, 0.02), n // 2, k % 3
