@@ -206,13 +206,21 @@ def make_params(p: "inputs.Params"):
 def make_robot(spheres=None, dh=None, q_min=None, q_max=None, qd_max=None, self_mlp=None):
     """storm_robot for the Panda (or the given DH and limits); self_mlp: the
     learned self-collision network's parameters [STORM_SELF_MLP_SIZE]."""
-    # (the struct begins with its floats: dh, q_min, q_max, qd_max)
+    # the Panda in one go (the struct begins with its floats: dh, q_min, q_max,
+    # qd_max), then what is given, element by element
     flat = np.zeros(ctypes.sizeof(storm_robot) // 4, dtype=np.float32)
-    flat[:24].reshape(8, 3)[:] = np.asarray(inputs.PANDA_DH if dh is None else dh)[:8, :3]
-    for k, (given, default) in enumerate(((q_min, inputs.PANDA_Q_MIN), (q_max, inputs.PANDA_Q_MAX),
-                                          (qd_max, inputs.PANDA_QD_MAX))):
-        flat[24 + DOF * k:24 + DOF * (k + 1)] = (default if given is None else given)[:DOF]
+    flat[:24].reshape(8, 3)[:] = inputs.PANDA_DH
+    for k, limits in enumerate((inputs.PANDA_Q_MIN, inputs.PANDA_Q_MAX, inputs.PANDA_QD_MAX)):
+        flat[24 + DOF * k:24 + DOF * (k + 1)] = limits
     r = storm_robot.from_buffer_copy(flat)
+    if dh is not None:
+        for k in range(8):
+            for c in range(3):
+                r.dh[k][c] = float(dh[k][c])
+    for field, given in ((r.q_min, q_min), (r.q_max, q_max), (r.qd_max, qd_max)):
+        if given is not None:
+            for j in range(DOF):
+                field[j] = float(given[j])
     sph = np.ascontiguousarray(np.zeros((0, 5)) if spheres is None else spheres, dtype=np.float32)
     r.n_spheres = sph.shape[0]
     r.spheres = sph.ctypes.data_as(ctypes.POINTER(ctypes.c_float)) if sph.size else None
