@@ -408,7 +408,7 @@ class StepGraph:
         self._launch = lib().storm_rollout_graph_launch
 
     def launch(self, stream=None):
-        code = self._launch(self._h, _stream() if stream is None else stream)
+        code = self._launch(self._h, _stream() if stream is None else ctypes.c_void_p(stream))
         if code != STORM_OK:
             raise StormError(code, "storm_rollout_graph_launch")
 
