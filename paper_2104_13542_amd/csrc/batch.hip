@@ -25,7 +25,7 @@ struct storm_batch_s {
     int2 *d_items_cost = nullptr;  // work queue, most expensive tiles first
     int2 *d_items_plain = nullptr; // work queue in problem order
     int n_items = 0;
-    int max_obs = 0, max_box = 0;  // most obstacles and most cuboids of any problem
+    RolloutLds lds8{}, lds16{};    // what any problem's tiles need, by wavefronts per workgroup
     uint32_t *d_next = nullptr;    // queue head (0 between launches)
     int2 *d_adj_items = nullptr;   // (problem, tile chunk) items of the batched adjoint
     int n_adj_items = 0;
@@ -77,8 +77,8 @@ int32_t launch_batch_step(storm_batch b, const float *d_x0, const float *d_goal,
 {
     const int2 *items = b->cfg.cost_order ? b->d_items_cost : b->d_items_plain;
     const hipError_t e =
-        launch_rollout_batch(b->d_probs, items, b->n_items, b->d_next, b->R, b->d_robot, b->max_obs,
-                             b->max_box, d_x0, d_goal, b->cfg.waves, b->cfg.grid, s);
+        launch_rollout_batch(b->d_probs, items, b->n_items, b->d_next, b->d_robot,
+                             b->cfg.waves == 16 ? b->lds16 : b->lds8, d_x0, d_goal, b->cfg.waves, b->cfg.grid, s);
     return e == hipSuccess ? STORM_OK : STORM_E_DEVICE;
 }
 
@@ -190,8 +190,12 @@ int32_t storm_batch_init(storm_batch *out, int32_t n_problems, const storm_param
     std::vector<double> cost;
     for (int p = 0; p < n_problems; ++p) {
         probs[p] = b->ctxs[p]->P;
-        b->max_obs = std::max(b->max_obs, probs[p].n_sph_obs + probs[p].n_box_obs);
-        b->max_box = std::max(b->max_box, probs[p].n_box_obs);
+        for (int w : {8, 16}) {
+            RolloutLds &most = w == 8 ? b->lds8 : b->lds16;
+            const RolloutLds lds = rollout_batch_lds(probs[p], b->R, w);
+            most.bytes = std::max(most.bytes, lds.bytes);
+            most.late = most.late || lds.late;
+        }
         const double tc = tile_cost(probs[p], robot->n_spheres, b->ctxs[p]->R.n_pairs);
         for (int t = 0; t < probs[p].n_tiles; ++t) {
             plain.push_back(make_int2(p, t));
