@@ -6,7 +6,7 @@
 //   sigma2' = (1 - alpha_sigma) sigma2
 //             + alpha_sigma mean_h sum_i w_i (u_ih - mu'_h)^2   (per joint)
 //
-// Two forms.  Up to 32 R particles (R = 1024 / H rows) and 2048, one
+// Three forms.  Up to 32 R particles (R = 1024 / H rows) and 2048, one
 // 1024-thread workgroup per (problem, joint): a joint's new mean and variance
 // depend only on the weights and on that joint's controls, so the seven joints
 // need no synchronisation with each other; every workgroup recomputes min C and
@@ -15,7 +15,9 @@
 // loads its up to 32 controls at the start, together with the costs, so the
 // only global-memory latency on the path is the first one.  Bound by latency:
 // two exchanges, a division and the tail's chain behind the first loads
-// (4.2 us at 500 x 30).  Past those sizes, update_chain and update_join (below).
+// (4.2 us at 500 x 30).  Past those sizes, the controls of the particles that
+// have a weight, gathered by one workgroup per joint (update_all) or, of more
+// points, by one per chain of sums (update_chain and update_join), both below.
 //
 // The variance about the new mean comes from the moments about the old one,
 // sum w (d - delta)^2 = S2/S0 - 2 delta S1/S0 + delta^2, in one pass.  Wave
@@ -360,22 +362,23 @@ __global__ __launch_bounds__(kThreads) void update_kernel(const PlainDev *dev, c
     update_joint<kSlots>(P, first, blockIdx.x, mean_out, sigma2_out, cmd, shift, kCov, L);
 }
 
-// The larger form: the same update for more particles.  One workgroup per
-// joint would pull all N H controls of the joint through one CU (N = 65536, H =
-// 30: 90-180 us).  A thread (row r, step h) sums its particles in eight
-// accumulators, number m taking every eighth of them, so the accumulators are
-// chains of their own: a workgroup per (joint, m) sums one of them, each in the
-// order that one workgroup would, and update_join adds the eight and takes the
-// tail.  Two ways to gather the particles:
+// The larger forms: the same update for more particles.  A thread (row r, step
+// h) sums its particles in eight accumulators, number m taking every eighth of
+// them: eight chains.  Two ways to gather the particles:
 //   list   (at most 4096 weights not exactly zero, beta small against the spread
 //          of C): only those, from a list compacted in ascending order;
 //   dense  otherwise: all, weights staged in LDS by chunks.
-// Each workgroup finds min C and the weights it needs itself (three passes over
-// C, from L2).  Control call and graph step with one workgroup per joint, and
-// so: 65536 x 30 update alone 89 -> 59 us; 4096 x 64 about the same (9 and 13 us
-// of 131).  A batch, which has workgroups enough, takes problems of up to 8192
-// particles with one workgroup per joint (update_all: 64 problems of 4096 x 64 27
-// us, by chains 81), to the same bits.
+// update_all: one workgroup per joint sums all eight.  It pulls the N H controls
+// of the joint through one CU, eight loads in flight per thread, and that time is
+// its bound.  update_chain: a workgroup per (joint, m) sums one chain, each in the
+// order that one workgroup would, and update_join adds the eight and takes the
+// tail, to the same bits; each workgroup finds min C and the weights it needs
+// itself (three passes over C, from L2).  The update alone, one kernel and two,
+// us: 600 x 64 8.0 and 10.5, 1500 x 30 8.9 and 11.2, 2500 x 30 10.5 and 11.4, 4096
+// x 30 13.4 and 12.2, 2048 x 64 12.7 and 10.8, 8000 x 6 15.2 and 16.4, 65536 x 30
+// (by one workgroup per joint 90-180) 67: the line lies at 90000 points.  A batch
+// has workgroups enough and takes update_all as far as its registers hold the
+// costs (64 problems of 2048 x 64 42 us, of 4096 x 64 102).
 constexpr int kChains = 8;    // accumulators of a thread
 constexpr int kList = 4096;   // capacity of the list
 constexpr int kChunk = 8192;  // weights staged at a time
@@ -384,6 +387,9 @@ constexpr int kChunk = 8192;  // weights staged at a time
 constexpr int kJointPart = kChains * 2 * kThreads;
 constexpr int kOnce = 8 * kThreads;  // costs that a workgroup holds in registers
 constexpr int kUpdateParts = kDof * kChains + 1;  // workgroups: chains, and one for the weights' sum
+
+// Whether one workgroup per joint takes a single problem past the register form.
+inline bool update_once(int N, int H) { return N <= kOnce && N * H <= 90000; }
 
 // Whether the weight exp(x) is not zero in FP32: below -104 it is (half the
 // least denormal is exp(-103.97)), above -103 it is not.
@@ -395,15 +401,10 @@ __device__ __forceinline__ bool has_weight(float x)
 }
 
 // Part c of a problem: chain c % 8 of joint c / 8, or, last, the weights' sum.
-// kAll: all chains of joint c and the sum, in x1, x2, S0 and bad, and nothing in
-// part_in.
-template <bool kAll>
 __device__ __forceinline__ void update_chain(const float *__restrict__ C_in, const float *__restrict__ u_in,
                                              const float *__restrict__ mean_in, float *__restrict__ part_in,
-                                             const int N, const int H, const float nib, const int c, float &x1,
-                                             float &x2, float &S0, int &bad)
+                                             const int N, const int H, const float nib, const int c)
 {
-    constexpr int kN = kAll ? kChains : 1;  // chains summed here
     __shared__ float s_w[kChunk];  // the list's weights, or a chunk's
     __shared__ int s_idx[kList];
     __shared__ float s_wave[kWaves];
@@ -412,7 +413,7 @@ __device__ __forceinline__ void update_chain(const float *__restrict__ C_in, con
     const int t = threadIdx.x, lane = t & (kLanes - 1), wave = __builtin_amdgcn_readfirstlane(t / kLanes);
     const int rows = kThreads / H, r = t / H, h = t - r * H;
     const bool in_rows = r < rows;
-    const int j = kAll ? c : min(c / kChains, kDof - 1), m = kAll ? 0 : c % kChains;
+    const int j = min(c / kChains, kDof - 1), m = c % kChains;
     const global_ptr<const float> U = as_global(u_in) + (size_t)j * N * H + h;
     const float mu = mean[h * kDof + j];
 
@@ -439,7 +440,7 @@ __device__ __forceinline__ void update_chain(const float *__restrict__ C_in, con
     nonfinite = __syncthreads_or(nonfinite);
     cmin = block_min(cmin, s_wave, lane, wave);
 
-    if (kAll || c == kDof * kChains) {
+    if (c == kDof * kChains) {
         // the sum of the weights (per thread in stride order, per wave, waves
         // in order)
         float sw = 0.0f;
@@ -456,17 +457,14 @@ __device__ __forceinline__ void update_chain(const float *__restrict__ C_in, con
         sw = wave_sum(sw);
         if (lane == 0) s_wave[wave] = sw;
         __syncthreads();
-        S0 = 0.0f;
+        float S0 = 0.0f;
         for (int k = 0; k < kWaves; ++k) S0 += s_wave[k];
-        bad = nonfinite;
-        if (!kAll) {
-            const global_ptr<float> out = as_global(part_in) + (size_t)kDof * kJointPart;
-            if (t == 0) {
-                out[0] = S0;
-                out[1] = nonfinite ? 1.0f : 0.0f;
-            }
-            return;
+        const global_ptr<float> out = as_global(part_in) + (size_t)kDof * kJointPart;
+        if (t == 0) {
+            out[0] = S0;
+            out[1] = nonfinite ? 1.0f : 0.0f;
         }
+        return;
     }
 
     // the number of nonzero weights, in all and before this wave's
@@ -488,9 +486,7 @@ __device__ __forceinline__ void update_chain(const float *__restrict__ C_in, con
 
     // the chain: particles r + m rows, + 8 rows, ... while all eight chains have
     // one; the first takes the others that remain
-    float a1[kN], a2[kN];
-#pragma unroll
-    for (int q = 0; q < kN; ++q) a1[q] = a2[q] = 0.0f;
+    float a1 = 0.0f, a2 = 0.0f;
     if (M <= kList) {
         for (int i = i0 + lane; i < i0 + run; i += 8 * kLanes) {
             if (!once) fetch(i);
@@ -511,23 +507,18 @@ __device__ __forceinline__ void update_chain(const float *__restrict__ C_in, con
         __syncthreads();
         if (in_rows) {
             int k = r;
-#pragma unroll kAll ? 1 : 4
+#pragma unroll 4
             for (; k + (kChains - 1) * rows < M; k += kChains * rows) {
-                float d[kN];
-#pragma unroll
-                for (int q = 0; q < kN; ++q) d[q] = U[(size_t)s_idx[k + (m + q) * rows] * H] - mu;
-#pragma unroll
-                for (int q = 0; q < kN; ++q) {
-                    const float wd = s_w[k + (m + q) * rows] * d[q];
-                    a1[q] += wd;
-                    a2[q] = fmaf(wd, d[q], a2[q]);
-                }
+                const float d = U[(size_t)s_idx[k + m * rows] * H] - mu;
+                const float wd = s_w[k + m * rows] * d;
+                a1 += wd;
+                a2 = fmaf(wd, d, a2);
             }
             for (; m == 0 && k < M; k += rows) {
                 const float d = U[(size_t)s_idx[k] * H] - mu;
                 const float wd = s_w[k] * d;
-                a1[0] += wd;
-                a2[0] = fmaf(wd, d, a2[0]);
+                a1 += wd;
+                a2 = fmaf(wd, d, a2);
             }
         }
     } else {
@@ -538,38 +529,24 @@ __device__ __forceinline__ void update_chain(const float *__restrict__ C_in, con
             __syncthreads();
             if (!in_rows) continue;
             int k = r;
-#pragma unroll kAll ? 1 : 8
+#pragma unroll 8
             for (; k + (kChains - 1) * rows < nc; k += kChains * rows) {
-                float d[kN];
-#pragma unroll
-                for (int q = 0; q < kN; ++q) d[q] = U[(size_t)(c0 + k + (m + q) * rows) * H] - mu;
-#pragma unroll
-                for (int q = 0; q < kN; ++q) {
-                    const float wd = s_w[k + (m + q) * rows] * d[q];
-                    a1[q] += wd;
-                    a2[q] = fmaf(wd, d[q], a2[q]);
-                }
+                const float d = U[(size_t)(c0 + k + m * rows) * H] - mu;
+                const float wd = s_w[k + m * rows] * d;
+                a1 += wd;
+                a2 = fmaf(wd, d, a2);
             }
             for (; m == 0 && k < nc; k += rows) {
                 const float d = U[(size_t)(c0 + k) * H] - mu;
                 const float wd = s_w[k] * d;
-                a1[0] += wd;
-                a2[0] = fmaf(wd, d, a2[0]);
+                a1 += wd;
+                a2 = fmaf(wd, d, a2);
             }
         }
     }
-    if (kAll) {
-        x1 = x2 = 0.0f;
-#pragma unroll
-        for (int q = 0; q < kN; ++q) {
-            x1 += a1[q];
-            x2 += a2[q];
-        }
-    } else {
-        const global_ptr<float> part = as_global(part_in) + (size_t)j * kJointPart;
-        part[(2 * m) * kThreads + t] = a1[0];
-        part[(2 * m + 1) * kThreads + t] = a2[0];
-    }
+    const global_ptr<float> part = as_global(part_in) + (size_t)j * kJointPart;
+    part[(2 * m) * kThreads + t] = a1;
+    part[(2 * m + 1) * kThreads + t] = a2;
 }
 
 __global__ __launch_bounds__(kThreads) void update_chain_kernel(const float *__restrict__ C,
@@ -578,9 +555,7 @@ __global__ __launch_bounds__(kThreads) void update_chain_kernel(const float *__r
                                                                 float *__restrict__ part, int32_t N, int32_t H,
                                                                 float nib)
 {
-    float x1, x2, S0;
-    int bad;
-    update_chain<false>(C, u, mean, part, N, H, nib, blockIdx.x, x1, x2, S0, bad);
+    update_chain(C, u, mean, part, N, H, nib, blockIdx.x);
 }
 
 // Workgroup k of a batch takes part items[k] = (problem, part).
@@ -590,14 +565,12 @@ __global__ __launch_bounds__(kThreads) void update_chain_batch_kernel(const Prob
     const STORM_CONST_AS int32_t *it = uniform_ptr(reinterpret_cast<const int32_t *>(items));
     const int p = it[2 * blockIdx.x], c = it[2 * blockIdx.x + 1];
     ProblemRef P = uniform_ptr(probs)[p];
-    float x1, x2, S0;
-    int bad;
-    update_chain<false>(P.C, P.u, P.mean, P.upd_part, P.N, P.H, -1.0f / P.beta, c, x1, x2, S0, bad);
+    update_chain(P.C, P.u, P.mean, P.upd_part, P.N, P.H, -1.0f / P.beta, c);
 }
 
 // The rows' sums, then the tail, on wave 0.
 __device__ __forceinline__ void sum_rows(const TailArgs &T, const int j, const int H, float x1, float x2, float S0,
-                                         float muo, const bool bad, const bool cov, float *s_red)
+                                         const float *s_mold, const bool bad, const bool cov, float *s_red)
 {
     const int t = threadIdx.x, lane = t & (kLanes - 1), rows = kThreads / H;
     s_red[t] = x1;
@@ -611,7 +584,7 @@ __device__ __forceinline__ void sum_rows(const TailArgs &T, const int j, const i
             s2 += s_red[kThreads + k * H + lane];
         }
     const bool ok = !bad && S0 > 0.0f && isfinite(S0);
-    update_tail(T, j, H, lane, s1, s2, S0, lane < H ? muo : 0.0f, ok, bad, cov);
+    update_tail(T, j, H, lane, s1, s2, S0, lane < H ? s_mold[lane] : 0.0f, ok, bad, cov);
 }
 
 // Joint j's update from its chains.
@@ -630,7 +603,7 @@ __device__ __forceinline__ void update_join(ProblemRef descriptor, const float *
     const global_ptr<const float> sum = as_global(part_in) + (size_t)kDof * kJointPart;
     const float S0 = sum[0], bad = sum[1];
     wait_problem(P);
-    const float muo_l = as_global(P.mean)[min(t, H - 1) * kDof + j];
+    const float mu = as_global(P.mean)[min(t, H - 1) * kDof + j];
     const TailArgs T = fetch_tail(P, mean_out, sigma2_out, cmd, shift, cov, j, t, H);
     float x1 = 0.0f, x2 = 0.0f;
 #pragma unroll
@@ -638,23 +611,154 @@ __device__ __forceinline__ void update_join(ProblemRef descriptor, const float *
         x1 += a[2 * m];
         x2 += a[2 * m + 1];
     }
-    sum_rows(T, j, H, x1, x2, S0, muo_l, bad != 0.0f, cov, s_red);
+    if (t < H) L.mold[t] = mu;
+    sum_rows(T, j, H, x1, x2, S0, L.mold, bad != 0.0f, cov, s_red);
 }
 
-// Joint j's update by one workgroup, from its own chains.
-__device__ __forceinline__ void update_all(ProblemRef descriptor, const float *__restrict__ C,
-                                           const float *__restrict__ u, const int N, const int H, const int j,
+// Joint j's update by one workgroup: its eight chains, with every cost read once
+// (thread t holds those of particles t, t + 1024, ...) and the controls at byte
+// offsets from the joint's first (with 64-bit addresses the loads in flight cost
+// twice the registers: 600 x 64 9.0 us, 64 x 2048 x 64 46).
+__device__ __forceinline__ void update_all(ProblemRef descriptor, const float *__restrict__ C_in,
+                                           const float *__restrict__ u_in, const int N, const int H, const int j,
                                            float *__restrict__ mean_out, float *__restrict__ sigma2_out,
                                            float *__restrict__ cmd, const int shift, const bool cov, UpdateLds &L)
 {
+    static_assert(kOnce <= kRows && 2 * kList <= kRows, "the weights, or the list, fit in the weights' space");
+    constexpr int kMost = kOnce / kThreads;  // costs of a thread
+    __shared__ int s_nonzero[kMost][kWaves];
     UpdateProblem P = fetch_problem(descriptor);
+    const global_ptr<const float> C = as_global(C_in);
+    const int t = threadIdx.x, lane = t & (kLanes - 1), wave = __builtin_amdgcn_readfirstlane(t / kLanes);
+    const int rows = kThreads / H, r = t / H, h = t - r * H;
+    const int n_each = (N + kThreads - 1) / kThreads;
+    float w[kMost];
+#pragma unroll
+    for (int k = 0; k < kMost; ++k)
+        if (k < n_each) w[k] = C[min(t + k * kThreads, N - 1)];
     wait_problem(P);
-    const float muo_l = as_global(P.mean)[min((int)threadIdx.x, H - 1) * kDof + j];
-    const TailArgs T = fetch_tail(P, mean_out, sigma2_out, cmd, shift, cov, j, threadIdx.x, H);
-    float x1, x2, S0;
-    int bad;
-    update_chain<true>(C, u, P.mean, nullptr, N, H, -1.0f / P.beta, j, x1, x2, S0, bad);
-    sum_rows(T, j, H, x1, x2, S0, muo_l, bad != 0, cov, L.red);
+    const float nib = -1.0f / P.beta;
+    const float mu = as_global(P.mean)[h * kDof + j];
+    const TailArgs T = fetch_tail(P, mean_out, sigma2_out, cmd, shift, cov, j, t, H);
+
+    // min C and whether a cost is not finite
+    float least = INFINITY;
+    bool bad = false;
+#pragma unroll
+    for (int k = 0; k < kMost; ++k) {
+        if (k >= n_each) break;
+        bad |= !isfinite(w[k]);
+        least = fminf(least, w[k]);
+    }
+    const uint64_t bad_lanes = __builtin_amdgcn_ballot_w64(bad);
+    least = wave_min(least);
+    if (lane == 0) {
+        L.wave[wave] = least;
+        L.count[wave] = bad_lanes != 0;
+    }
+    __syncthreads();
+    float cmin = L.wave[0];
+    int any_nonfinite = L.count[0];
+    for (int k = 1; k < kWaves; ++k) {
+        cmin = fminf(cmin, L.wave[k]);
+        any_nonfinite |= L.count[k];
+    }
+
+    // the weights, their sum (per thread, per wave, waves in order), and how
+    // many are not zero
+    float sw = 0.0f;
+#pragma unroll
+    for (int k = 0; k < kMost; ++k) {
+        if (k >= n_each) break;
+        w[k] = t + k * kThreads < N ? expf((w[k] - cmin) * nib) : 0.0f;
+        sw += w[k];
+        const uint64_t nonzero = __builtin_amdgcn_ballot_w64(w[k] > 0.0f);
+        if (lane == 0) s_nonzero[k][wave] = __builtin_popcountll(nonzero);
+    }
+    sw = wave_sum(sw);
+    if (lane == 0) L.wsum[wave] = sw;
+    __syncthreads();
+    float S0 = 0.0f;
+    for (int k = 0; k < kWaves; ++k) S0 += L.wsum[k];
+    // the particles in ascending order, as the chains take them: the list, or,
+    // where it overflows, all
+    int *s_at = reinterpret_cast<int *>(L.buf + kList);
+    int M = 0;
+#pragma unroll
+    for (int k = 0; k < kMost; ++k) {
+        if (k >= n_each) break;
+        int at = 0;
+        for (int v = 0; v < kWaves; ++v) {
+            if (v == wave) at = M;
+            M += s_nonzero[k][v];
+        }
+        const uint64_t nonzero = __builtin_amdgcn_ballot_w64(w[k] > 0.0f);
+        at += __builtin_popcountll(nonzero & ((1ull << lane) - 1ull));
+        if (w[k] > 0.0f && at < kList) {
+            L.buf[at] = w[k];
+            s_at[at] = 4 * H * (t + k * kThreads);  // (of its controls in bytes)
+        }
+    }
+    const bool list = M <= kList;
+    __syncthreads();
+    if (!list) {
+#pragma unroll
+        for (int k = 0; k < kMost; ++k)
+            if (t + k * kThreads < N) L.buf[t + k * kThreads] = w[k];
+        __syncthreads();
+    }
+    const __amdgpu_buffer_rsrc_t U = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float *>(u_in + (size_t)j * N * H), (short)0, N * H * (int)sizeof(float), 0x00020000);
+    float a1[kChains], a2[kChains];
+#pragma unroll
+    for (int m = 0; m < kChains; ++m) a1[m] = a2[m] = 0.0f;
+    auto gather = [&](int n, auto offset) __attribute__((always_inline)) {
+        int k = r;
+#pragma unroll 1
+        for (; k + (kChains - 1) * rows < n; k += kChains * rows) {
+            float d[kChains];
+#pragma unroll
+            for (int m = 0; m < kChains; ++m)
+                d[m] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(U, offset(k + m * rows), 0, 0)) - mu;
+#pragma unroll
+            for (int m = 0; m < kChains; ++m) {
+                const float wd = L.buf[k + m * rows] * d[m];
+                a1[m] += wd;
+                a2[m] = fmaf(wd, d[m], a2[m]);
+            }
+        }
+        for (; k < n; k += rows) {
+            const float d = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(U, offset(k), 0, 0)) - mu;
+            const float wd = L.buf[k] * d;
+            a1[0] += wd;
+            a2[0] = fmaf(wd, d, a2[0]);
+        }
+    };
+    if (r < rows) {
+        if (list)
+            gather(M, [&](int k) { return s_at[k] + 4 * h; });
+        else
+            gather(N, [&](int k) { return 4 * (k * H + h); });
+    }
+    float x1 = 0.0f, x2 = 0.0f;
+#pragma unroll
+    for (int m = 0; m < kChains; ++m) {
+        x1 += a1[m];
+        x2 += a2[m];
+    }
+    if (r == 0) L.mold[h] = mu;
+    sum_rows(T, j, H, x1, x2, S0, L.mold, any_nonfinite != 0, cov, L.red);
+}
+
+template <bool kCov>
+__global__ __launch_bounds__(kThreads) void update_all_kernel(const PlainDev *dev, const float *__restrict__ C,
+                                                              const float *__restrict__ u,
+                                                              float *__restrict__ mean_out,
+                                                              float *__restrict__ sigma2_out, float *__restrict__ cmd,
+                                                              int32_t N, int16_t H, int16_t shift)
+{
+    __shared__ UpdateLds L;
+    update_all(uniform_ptr(dev)->P, C, u, N, H, blockIdx.x, mean_out, sigma2_out, cmd, shift, kCov, L);
 }
 
 template <bool kCov>
@@ -668,8 +772,10 @@ __global__ __launch_bounds__(kThreads) void update_join_kernel(const PlainDev *d
 }
 
 // Workgroup (p, j) of a batch; commands go to cmd[p][7].  (The larger problems'
-// chains are there.)
-__global__ __launch_bounds__(kThreads) void update_batch_kernel(const ProblemDev *__restrict__ probs,
+// chains are there.)  At most 96 VGPRs, so that the next workgroup of a CU starts
+// beside the last wavefront of the one before (1024 problems of 256 x 30 111 -> 88
+// us).
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(5))) void update_batch_kernel(const ProblemDev *__restrict__ probs,
                                                                 float *__restrict__ cmd, int shift)
 {
     __shared__ UpdateLds L;
@@ -710,6 +816,12 @@ hipError_t launch_update(const ProblemDev &P, const PlainDev *dev, float *mean_o
                          hipStream_t stream)
 {
     const int slots = update_slots(P.N, P.H);
+    if (slots == 0 && update_once(P.N, P.H)) {
+        auto kernel = P.cov_step ? update_all_kernel<true> : update_all_kernel<false>;
+        hipLaunchKernelGGL(kernel, dim3(kDof), dim3(kThreads), 0, stream, dev, P.C, P.u, mean_out, sigma2_out, cmd,
+                           P.N, (int16_t)P.H, (int16_t)shift);
+        return hipGetLastError();
+    }
     if (slots == 0) {
         hipLaunchKernelGGL(update_chain_kernel, dim3(kUpdateParts), dim3(kThreads), 0, stream, P.C, P.u, P.mean,
                            P.upd_part, P.N, P.H, -1.0f / P.beta);
@@ -733,6 +845,9 @@ hipError_t launch_update(const ProblemDev &P, const PlainDev *dev, float *mean_o
 
 int update_batch_parts(int N, int H) { return update_slots(N, H) != 0 || N <= kOnce ? 0 : kUpdateParts; }
 
-size_t update_part_floats(int N, int H) { return update_slots(N, H) != 0 ? 0 : (size_t)kDof * kJointPart + 4; }
+size_t update_part_floats(int N, int H)
+{
+    return update_slots(N, H) != 0 || update_once(N, H) ? 0 : (size_t)kDof * kJointPart + 4;
+}
 
 }  // namespace storm

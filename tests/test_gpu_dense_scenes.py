@@ -1,12 +1,11 @@
 """Scenes of up to 256 obstacles: what the looping and the batched rollout keep of
 a scene in LDS leaves room for two workgroups on a compute unit, and cuboids whose
 records stay in memory give the same costs (marked gpu)."""
-import ctypes
-
 import numpy as np
 import pytest
 
 from paper_2104_13542_amd import inputs
+from tests.gpu_launches import launches, residency
 
 torch = pytest.importorskip("torch")
 
@@ -20,48 +19,6 @@ def _gpu():
     from paper_2104_13542_amd import storm
 
     storm.lib()
-
-
-class KernelParams(ctypes.Structure):
-    """hipKernelNodeParams."""
-    _fields_ = [("block", ctypes.c_uint * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
-                ("grid", ctypes.c_uint * 3), ("args", ctypes.c_void_p), ("lds", ctypes.c_uint)]
-
-
-def _hip():
-    path = next(line.split()[-1] for line in open("/proc/self/maps") if "libamdhip64.so" in line)
-    return ctypes.CDLL(path)
-
-
-def _launches(call):
-    """The kernel launches of `call`, captured and not run."""
-    hip, vp = _hip(), ctypes.c_void_p
-    stream, graph, n = torch.cuda.Stream(), vp(), ctypes.c_size_t()
-    torch.cuda.synchronize()
-    with torch.cuda.stream(stream):
-        assert hip.hipStreamBeginCapture(vp(stream.cuda_stream), 1) == 0  # (thread-local)
-        try:
-            call()
-        finally:
-            assert hip.hipStreamEndCapture(vp(stream.cuda_stream), ctypes.byref(graph)) == 0
-    assert hip.hipGraphGetNodes(graph, None, ctypes.byref(n)) == 0
-    nodes = (vp * n.value)()
-    assert hip.hipGraphGetNodes(graph, nodes, ctypes.byref(n)) == 0
-    out = []
-    for node in nodes:
-        p = KernelParams()
-        assert hip.hipGraphKernelNodeGetParams(vp(node), ctypes.byref(p)) == 0
-        out.append(p)
-    assert hip.hipGraphDestroy(graph) == 0
-    return out
-
-
-def _residency(p):
-    """Workgroups of a launch that a compute unit holds."""
-    n = ctypes.c_int()
-    assert _hip().hipOccupancyMaxActiveBlocksPerMultiprocessor(ctypes.byref(n), ctypes.c_void_p(p.func),
-                                                               int(np.prod(p.block)), ctypes.c_size_t(p.lds)) == 0
-    return n.value
 
 
 def _problem(seed, n, h, n_sph, n_box):
@@ -88,9 +45,9 @@ def test_two_workgroups_share_a_compute_unit(n_sph, n_box):
         goals = goal.repeat(2, 1).contiguous()
         for call in (lambda: r.step(goal, C=costs), lambda: b.step(goals)):
             costs = torch.empty(300, device="cuda")
-            p, = _launches(call)
+            p, = launches(call)
             assert tuple(p.block) == (512, 1, 1)
-            assert _residency(p) >= 2
+            assert residency(p) >= 2
     finally:
         r.close()
         b.close()
