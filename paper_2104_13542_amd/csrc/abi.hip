@@ -203,8 +203,7 @@ std::vector<float> storm::body_bounds(const storm_robot *robot)
 // The spheres of each body in runs of up to four, as even as they come (at
 // most 64 / 4 + 8 runs), and one item per pair of runs whose bodies are at
 // least two apart: first sphere and count - 1 of the later and of the earlier
-// run (6, 2, 6 and 2 bits), the runs' anchor spheres (6 bits each; anchor_mask
-// adds the ranks of their capsules, 6 bits each), the sum of
+// run (6, 2, 6 and 2 bits), the runs' anchor spheres (6 bits each), the sum of
 // the radii about the anchors that hold the runs, and what the anchors' own
 // radii lack of it (each with 0.1 mm for the rounding of the centres, which is
 // micrometres within the robot's reach).
@@ -249,29 +248,6 @@ int storm::self_pairs(const storm_robot *robot, std::vector<int> &items)
             pairs += t.count * s.count;
         }
     return pairs;
-}
-
-uint64_t storm::anchor_mask(std::vector<float> &bounds, std::vector<int> &items)
-{
-    uint64_t mask = 0;
-    auto body_anchor = [&](int b) {
-        int a;
-        memcpy(&a, &bounds[2 * b], sizeof(a));
-        return a;
-    };
-    for (int b = 0; b < STORM_NFRAMES; ++b)
-        if (bounds[2 * b + 1] > -1.0e30f) mask |= 1ull << body_anchor(b);
-    for (size_t k = 0; k < items.size(); k += 4) mask |= 1ull << (items[k + 1] & 63) | 1ull << (items[k + 1] >> 6 & 63);
-    auto rank = [&](int s) { return __builtin_popcountll(mask & ((1ull << s) - 1ull)); };
-    for (int b = 0; b < STORM_NFRAMES; ++b) {
-        const int r = rank(body_anchor(b));
-        memcpy(&bounds[2 * b], &r, sizeof(r));
-    }
-    for (size_t k = 0; k < items.size(); k += 4) {
-        const int anchors = items[k + 1];
-        items[k + 1] = anchors | rank(anchors & 63) << 12 | rank(anchors >> 6 & 63) << 18;
-    }
-    return mask;
 }
 
 namespace {
@@ -373,8 +349,7 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
     std::vector<_Float16> net_frag;
     std::vector<float> net_bias;
     if (params->self_model == 1) storm::pack_selfnet(robot->self_mlp, net_frag, net_bias);
-    std::vector<float> bounds = storm::body_bounds(robot);
-    const uint64_t cap_mask = storm::anchor_mask(bounds, seg);
+    const std::vector<float> bounds = storm::body_bounds(robot);
     const int n_seg = (int)seg.size() / 4;
 
     ProblemDev &P = c->P;
@@ -518,7 +493,14 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
         c->R.body_bound = body_bound;
         c->R.self_items = self_seg;
         c->R.n_self_items = n_seg;
-        c->R.cap_mask = cap_mask;
+        c->R.cap_mask = 0;
+        for (int b = 0; b < STORM_NFRAMES; ++b) {
+            int a;
+            memcpy(&a, &bounds[2 * b], sizeof(a));
+            if (bounds[2 * b + 1] > -1.0e30f) c->R.cap_mask |= 1ull << a;
+        }
+        for (int k = 0; k < n_seg; ++k)
+            c->R.cap_mask |= 1ull << (seg[4 * k + 1] & 63) | 1ull << (seg[4 * k + 1] >> 6 & 63);
         dev.P = P;
         dev.R = c->R;
         STORM_TRY(hipMemcpyAsync(c->dev, &dev, sizeof(dev), hipMemcpyHostToDevice, s));

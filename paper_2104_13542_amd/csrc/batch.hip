@@ -194,7 +194,7 @@ int32_t storm_batch_init(storm_batch *out, int32_t n_problems, const storm_param
             RolloutLds &most = w == 8 ? b->lds8 : b->lds16;
             const RolloutLds lds = rollout_batch_lds(probs[p], b->R, w);
             most.bytes = std::max(most.bytes, lds.bytes);
-            most.late = most.late || lds.late;
+            most.dense = most.dense || lds.dense;
         }
         const double tc = tile_cost(probs[p], robot->n_spheres, b->ctxs[p]->R.n_pairs);
         for (int t = 0; t < probs[p].n_tiles; ++t) {

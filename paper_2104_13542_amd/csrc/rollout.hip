@@ -52,28 +52,30 @@ namespace {
 // and hinge rows of phases A0-B (8 + 14 + 21) before the centres exist.
 __host__ __device__ constexpr int rollout_cen_rows(int S) { return 3 * S > 43 ? 3 * S : 43; }
 
-// LDS of a tile apart from the cuboids' records: the rows, the capsules of n_cap
-// spheres, the balls of n_obs obstacles, and the lists of phase D1 (of n_items
-// self-collision items, and of the obstacles near each body).
+// LDS of a tile apart from the cuboids' records: the rows, n_cap capsules, the
+// balls of n_obs obstacles, and the lists of phase D1 (of n_items self-collision
+// items, and of the obstacles near each body).
 __host__ __device__ constexpr int rollout_base_bytes(int S, int n_cap, int n_obs, int n_items, bool task)
 {
     return (96 + kTerms + rollout_cen_rows(S) + (task ? 2 * kDof : 0)) * kLanes * 4 + 8 * n_cap * 16 +
            n_obs * (16 + kFrames) + n_items * 8;
 }
 
-// Of how many of n_box cuboids the records lie behind that: in workgroups of 8
-// waves as many as leave room for a second one on their CU (160 KB, kStaticLds
-// of each workgroup's static), or all where none fits anyway; those of 16 waves
-// have a CU to themselves.  The others go over the frames once those are dead
-// (kLate: loaded in phase D1).  A form of its own, since the choice for each
-// cuboid's test costs 1% where all lie together, and read from memory instead 4%
-// (65536 x 30 with 50 obstacles 760, 770 and 783 us).
+// The dense form (kDense), for scenes past the LDS of two 8-wave workgroups on a
+// CU (160 KB, kStaticLds of each workgroup's static): capsules by their rank in
+// cap_mask, and the records of the cuboids past the first rollout_boxes loaded in
+// phase D1, over the frames, which are dead by then.  A form of its own, since
+// both cost 1% where all fits, and such records read from memory instead 4%
+// (65536 x 30 with 50 obstacles 760, 770 and 783 us).  64 problems of 512 x 30
+// with 60 spheres and 60 cuboids, one workgroup per CU and two: 747 and 441 us;
+// a control call of 4096 x 64 with them, by a 16-wave workgroup per tile: 139 and
+// 109.
 constexpr int kStaticLds = 1360;
 constexpr int kTwoGroupsLds = 80 * 1024 - kStaticLds;
-__host__ __device__ constexpr int rollout_boxes(int waves, int base_bytes, int n_box)
+__host__ __device__ constexpr int rollout_boxes(int base_bytes, int n_box)
 {
     const int room = (kTwoGroupsLds - base_bytes) / 64;
-    return waves > 8 || base_bytes > kTwoGroupsLds || room > n_box ? n_box : room;
+    return base_bytes > kTwoGroupsLds || room > n_box ? n_box : room;
 }
 constexpr int kLateRow = 32;
 static_assert(kLateRow >= 3 * 8 && kLateRow * kLanes * 4 + STORM_MAX_OBSTACLES * 64 <= 96 * kLanes * 4,
@@ -276,14 +278,14 @@ __device__ __forceinline__ bool capsules_meet(const float4 a1, const float4 b1, 
 // workgroup; smem is the workgroup's dynamic LDS (rollout_lds).
 // kSums: the environment term's partial sums, over spheres s, s + kSums, ...
 // (W, or 2 W: the bits of a workgroup of twice the waves).
-// kLate: with cuboids whose records do not fit (rollout_boxes).
+// kDense: with the scene packed (rollout_boxes).
 // kTask: the task-space form, which adds the flange velocity and
 // acceleration outputs (Eq. 8), the ball-on-tray term and the joint
 // positions the learned self-collision network reads.
 // The fields of the descriptors are scalar loads where they are used (held as
 // copies they overflowed the SGPRs into lanes of VGPRs, 180 lane moves per
 // wave and tile).
-template <int W, bool kTask, int kSums, bool kLate, class Queue>
+template <int W, bool kTask, int kSums, bool kDense, class Queue>
 __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRef R, const TileFirst &first, const int tile,
                                              const float *__restrict__ x0, const float *__restrict__ goal,
                                              const float *__restrict__ noise, const StepOut &out, float *smem)
@@ -296,10 +298,10 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
     //   centres [3S]             C - D2;  before them noise [8] A0 - A1,
     //                            sin/cos [14] and hinges [21] A1 - B
     //   velocities, accelerations [14]  A1 - C (task-space form only)
-    // then the capsules of the anchor spheres [rank in cap_mask][4 rows][8] (C -
-    // D2), the records of the obstacles (A0 - D2) and the lists of phase D1 (D1 -
-    // D2).  Cuboids' records that leave no room for a second workgroup lie over
-    // the frames from row kLateRow on (kLate; D1 - D2).
+    // then the capsules of the spheres [S][4 rows][8] (C - D2; kDense: of the
+    // anchors, by rank), the records of the obstacles (A0 - D2) and the lists of
+    // phase D1 (D1 - D2).  kDense: the other cuboids' records lie over the frames
+    // from row kLateRow on (D1 - D2).
     const int S = first.n_spheres;
     float *s_fr = smem;                        // [8 frames][12][64]: R row-major, p
     float *s_penv = s_fr;                      // [kSums][64] (over the frames, after phase C)
@@ -311,15 +313,18 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
     float *s_lim = s_sc + 14 * kLanes;         // [3][7][64]: squared joint, velocity, stop hinges per joint
     float *s_v = s_cen + rollout_cen_rows(S) * kLanes;  // [7][64] (task-space form only)
     float *s_acc = s_v + kDof * kLanes;                  // [7][64]
-    float4 *s_cap = reinterpret_cast<float4 *>(s_v + (kTask ? 2 * kDof * kLanes : 0));  // [anchors][4][2]
-    const int n_cap = __builtin_popcountll(first.cap_mask);
+    float4 *s_cap = reinterpret_cast<float4 *>(s_v + (kTask ? 2 * kDof * kLanes : 0));  // [S, or anchors][4][2]
+    const int n_cap = kDense ? __builtin_popcountll(first.cap_mask) : S;
+    auto cap_index = [&](int s) __attribute__((always_inline)) {  // of an anchor
+        return kDense ? __builtin_popcountll(first.cap_mask & ((1ull << s) - 1ull)) : s;
+    };
     const uint32_t mask = first.cost_mask;
     const int nobs = (mask & STORM_COST_ENV) && S > 0 ? first.n_sph_obs + first.n_box_obs : 0;
     const int n_items = (mask & STORM_COST_SELF) ? first.n_self_items : 0;
     float4 *s_bound = s_cap + 8 * n_cap;         // [obstacles] centre, radius (of a cuboid: to its corners)
     float4 *s_box = s_bound + nobs;              // [n_box][4] records of the first cuboids
     const int n_box = nobs == 0 ? 0
-                      : kLate   ? rollout_boxes(W, rollout_base_bytes(S, n_cap, nobs, n_items, kTask), first.n_box_obs)
+                      : kDense  ? rollout_boxes(rollout_base_bytes(S, n_cap, nobs, n_items, kTask), first.n_box_obs)
                                 : first.n_box_obs;
     int2 *s_self = reinterpret_cast<int2 *>(s_box + 4 * n_box);  // [items] those that stay: runs and anchors, and the
                                                                  // runs' joint reach
@@ -526,7 +531,7 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
             // (the next sphere's record is read one ahead)
             float F[12];
             int fb = __builtin_amdgcn_readfirstlane((int)s_body[s0]);
-            float4 *cap = s_cap + (__builtin_popcountll(first.cap_mask & ((1ull << s0) - 1ull)) * 4 + (lane >> 4)) * 2;
+            int rank = kDense ? cap_index(s0) : 0;
             float4 next = s_sph[s0];
 #pragma unroll
             for (int c = 0; c < 12; ++c) F[c] = s_fr[(fb * 12 + c) * kLanes + lane];
@@ -548,11 +553,11 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
                 if (first.cap_mask >> s & 1) {
                     float4 a, b;
                     row_capsule(cc, tau, loc.w, a, b);
+                    float4 *cap = s_cap + ((kDense ? rank++ : s) * 4 + (lane >> 4)) * 2;
                     if ((lane & 15) == 0) {
                         cap[0] = a;
                         cap[1] = b;
                     }
-                    cap += 8;
                 }
                 const int b = __builtin_amdgcn_readfirstlane(b_next);
                 if (b != fb) {
@@ -633,7 +638,7 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
     if (wave == W - 1 && lane == 0) queue.store();
 
     // the cuboids' records that had no room before (D2 reads them)
-    if (kLate && nobs > 0) {
+    if (kDense && nobs > 0) {
         float4 *late = reinterpret_cast<float4 *>(s_fr + kLateRow * kLanes);
         for (int k = threadIdx.x; k < 4 * (first.n_box_obs - n_box); k += W * kLanes)
             late[k] = load_float4(g_box + 4 * n_box + k);
@@ -658,7 +663,7 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
     // obstacle; the waves share the obstacles.
     if (2 * wave < nobs) {
         const int body = body8, row = (lane >> 3) & 3, half = lane >> 5;
-        const float4 *cap = s_cap + (__float_as_int(anchor) * 4 + row) * 2;
+        const float4 *cap = s_cap + (cap_index(__float_as_int(anchor)) * 4 + row) * 2;
         const float4 a = cap[0], b = cap[1];
         const float reach = a.w + widen;
         for (int o0 = 2 * wave; o0 < nobs; o0 += 2 * W) {
@@ -688,7 +693,8 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
 #pragma unroll
                 for (int k = 0; k < 4; ++k) item[k] = items[4 * g + k];
             const int anchors = item[1];
-            const float4 *ct = s_cap + ((anchors >> 12 & 63) * 4 + row) * 2, *cs = s_cap + ((anchors >> 18) * 4 + row) * 2;
+            const float4 *ct = s_cap + (cap_index(anchors & 63) * 4 + row) * 2,
+                         *cs = s_cap + (cap_index(anchors >> 6) * 4 + row) * 2;
             uint64_t meet = __builtin_amdgcn_ballot_w64(
                 g < n_items &&
                 capsules_meet(ct[0], ct[1], cs[0], cs[1], (ct[0].w + cs[0].w) + __int_as_float(item[3])));
@@ -697,7 +703,7 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
             meet |= meet >> 16;
             if (row == 0 && ((meet >> lane) & 1ull)) {
                 const int k = atomicAdd(&s_self_n, 1);
-                s_self[k] = make_int2(item[0] | (anchors & 0xfff) << 16, item[2]);
+                s_self[k] = make_int2(item[0] | anchors << 16, item[2]);
             }
         }
     }
@@ -726,8 +732,7 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
             const float rs = s_sph[s].w;
             float4 ca, cb;
             if (first.cap_mask >> s & 1) {
-                const float4 *cap =
-                    s_cap + (__builtin_popcountll(first.cap_mask & ((1ull << s) - 1ull)) * 4 + (lane >> 4)) * 2;
+                const float4 *cap = s_cap + (cap_index(s) * 4 + (lane >> 4)) * 2;
                 ca = cap[0];
                 cb = cap[1];
             } else {
@@ -761,7 +766,7 @@ __device__ __forceinline__ void rollout_tile(Queue &queue, ProblemRef P, RobotRe
                         const float rc = rs + so.w;
                         if (__builtin_amdgcn_ballot_w64(d2 < rc * rc) != 0) best = fmaxf(best, rc - fast_sqrt(d2));
                     } else {
-                        const float4 *bb = (!kLate || o - nso < n_box ? s_box : s_late) + (o - nso) * 4;
+                        const float4 *bb = (!kDense || o - nso < n_box ? s_box : s_late) + (o - nso) * 4;
                         const float4 b0 = bb[0], b1 = bb[1], b2 = bb[2], b3 = bb[3];
                         const float lx = fmaf(b0.x, x, fmaf(b0.y, y, fmaf(b0.z, z, b2.y)));
                         const float ly = fmaf(b0.w, x, fmaf(b1.x, y, fmaf(b1.y, z, b2.z)));
@@ -943,7 +948,7 @@ __global__ __launch_bounds__(W * kLanes) void rollout_kernel(const PlainDev *dev
 // phase of a tile beside the first of the next.  (No queue: tiles of one
 // problem differ little, and a counter would be one more state that two
 // streams could share.)  Same bits as one tile per workgroup.
-template <int W, bool kLate>
+template <int W, bool kDense>
 __global__ __launch_bounds__(W * kLanes) __attribute__((amdgpu_waves_per_eu(4))) void rollout_loop_kernel(
     const PlainDev *dev, const float *__restrict__ x0, const float *__restrict__ goal, float *C_out, int32_t n_tiles)
 {
@@ -955,7 +960,7 @@ __global__ __launch_bounds__(W * kLanes) __attribute__((amdgpu_waves_per_eu(4)))
         const STORM_CONST_AS PlainDev *D = uniform_ptr(dev);
         asm volatile("" : "+s"(D));  // fields read in each tile, not kept over the loop
         const TileFirst first = fetch_first(D->P, D->R, D->P.step, D->P.mean, D->P.N, D->P.H);
-        rollout_tile<W, false, 2 * W, kLate>(stride, D->P, D->R, first, tile, x0, goal, nullptr, o, smem);
+        rollout_tile<W, false, 2 * W, kDense>(stride, D->P, D->R, first, tile, x0, goal, nullptr, o, smem);
         stride.parity ^= 1;
     }
 }
@@ -970,7 +975,7 @@ __global__ __launch_bounds__(W * kLanes) __attribute__((amdgpu_waves_per_eu(4)))
 // memory round trip of its own stands between two tiles.  256 problems 2.35
 // -> 2.19 ms, 64 x 4096 x 64 with refinement 16.36 -> 16.00 ms.
 // (Four waves per SIMD: two workgroups of 8 waves share a CU.)
-template <int W, bool kLate>
+template <int W, bool kDense>
 __global__ __launch_bounds__(W * kLanes) __attribute__((amdgpu_waves_per_eu(4))) void rollout_batch_kernel(const ProblemDev *__restrict__ probs,
                                                                    const int2 *__restrict__ items, int n_items,
                                                                    uint32_t *next, const RobotDev *robot,
@@ -988,7 +993,7 @@ __global__ __launch_bounds__(W * kLanes) __attribute__((amdgpu_waves_per_eu(4)))
         asm volatile("" : "+s"(R));  // fields read in each tile, not kept over the loop
         ProblemRef P = uniform_ptr(probs)[p];
         const TileFirst first = fetch_first(P, *R, P.step, P.mean, P.N, P.H);
-        rollout_tile<W, false, W, kLate>(queue, P, *R, first, tile, x0s + (size_t)p * 3 * kDof, goals + (size_t)p * 12, nullptr,
+        rollout_tile<W, false, W, kDense>(queue, P, *R, first, tile, x0s + (size_t)p * 3 * kDof, goals + (size_t)p * 12, nullptr,
                                StepOut{}, smem);
         queue.parity ^= 1;
         p = __builtin_amdgcn_readfirstlane(s_item[queue.parity][0]);
@@ -1000,11 +1005,12 @@ __global__ __launch_bounds__(W * kLanes) __attribute__((amdgpu_waves_per_eu(4)))
 RolloutLds rollout_lds(const ProblemDev &P, const RobotDev &R, int waves, bool task)
 {
     const bool env = (P.cost_mask & STORM_COST_ENV) && R.n_spheres > 0;
-    const int base = rollout_base_bytes(R.n_spheres, __builtin_popcountll(R.cap_mask),
-                                        env ? P.n_sph_obs + P.n_box_obs : 0,
-                                        P.cost_mask & STORM_COST_SELF ? R.n_self_items : 0, task);
-    const int n_box = env ? rollout_boxes(waves, base, P.n_box_obs) : 0;
-    return RolloutLds{(size_t)(base + 64 * n_box), env && n_box < P.n_box_obs};
+    const int n_obs = env ? P.n_sph_obs + P.n_box_obs : 0, n_box = env ? P.n_box_obs : 0;
+    const int n_items = P.cost_mask & STORM_COST_SELF ? R.n_self_items : 0;
+    const int all = rollout_base_bytes(R.n_spheres, R.n_spheres, n_obs, n_items, task) + 64 * n_box;
+    const int base = rollout_base_bytes(R.n_spheres, __builtin_popcountll(R.cap_mask), n_obs, n_items, task);
+    if (waves > 8 || all <= kTwoGroupsLds || base > kTwoGroupsLds) return RolloutLds{(size_t)all, false};
+    return RolloutLds{(size_t)(base + 64 * rollout_boxes(base, n_box)), true};
 }
 
 }  // namespace
@@ -1042,7 +1048,7 @@ hipError_t launch_rollout_batch(const ProblemDev *probs, const int2 *items, int 
         hipLaunchKernelGGL((rollout_batch_kernel<16, false>), dim3((unsigned)grid), dim3(16 * kLanes), lds.bytes, stream, probs,
                            items, n_items, next, robot, x0s, goals);
     } else if (waves == 8) {
-        hipLaunchKernelGGL((lds.late ? rollout_batch_kernel<8, true> : rollout_batch_kernel<8, false>),
+        hipLaunchKernelGGL((lds.dense ? rollout_batch_kernel<8, true> : rollout_batch_kernel<8, false>),
                            dim3((unsigned)grid), dim3(8 * kLanes), lds.bytes, stream, probs, items, n_items, next, robot, x0s, goals);
     } else {
         return hipErrorInvalidValue;
@@ -1069,7 +1075,7 @@ hipError_t launch_rollout(const ProblemDev &P, const RobotDev &R, const PlainDev
                        out.xdd != nullptr;
     const RolloutLds loop = rollout_lds(P, R, 8, false);
     if (!task && !debug && P.n_tiles >= kLoopTiles && loop.bytes <= kTwoGroupsLds) {
-        hipLaunchKernelGGL((loop.late ? rollout_loop_kernel<8, true> : rollout_loop_kernel<8, false>), dim3(kLoopGroups),
+        hipLaunchKernelGGL((loop.dense ? rollout_loop_kernel<8, true> : rollout_loop_kernel<8, false>), dim3(kLoopGroups),
                            dim3(8 * kLanes), loop.bytes, stream, dev, x0, goal, out.C, P.n_tiles);
         return hipGetLastError();
     }

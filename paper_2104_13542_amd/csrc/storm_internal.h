@@ -125,9 +125,9 @@ struct alignas(64) RobotDev {
     int32_t n_spheres, n_pairs, n_self_items, pad0;
     const float4 *sph_local;  // [S] body-frame centre (x, y, z), radius
     const int32_t *sph_body;  // [S] frame index 0..7 the sphere is attached to
-    const float *body_bound;  // [8][2] per frame: rank of its anchor sphere (int bits), what that one's radius lacks to hold the body's spheres
+    const float *body_bound;  // [8][2] per frame: anchor sphere (int bits), what its radius lacks to hold the body's spheres
     const int32_t *self_items;  // [n_self_items][4] self-collision work items (self_pairs)
-    uint64_t cap_mask;  // spheres that anchor a body or a run of self_items (their capsules are kept in LDS, by rank)
+    uint64_t cap_mask;  // spheres that anchor a body or a run of self_items (their capsules are kept in LDS)
     int32_t pad1[2];
     float ca[kFrames], sa[kFrames], a[kFrames], d[kFrames];  // DH: cos/sin alpha_{k-1}, a_{k-1}, d_k
 };
@@ -225,7 +225,7 @@ void pack_selfnet(const float *prm, std::vector<_Float16> &frag, std::vector<flo
 // update workgroup per problem (descriptors in device memory).
 struct RolloutLds {
     size_t bytes;  // dynamic LDS
-    bool late;     // some cuboids' records come later, over what is dead by then
+    bool dense;    // in the form that packs a scene to leave room for a second workgroup
 };
 hipError_t launch_rollout_batch(const ProblemDev *probs, const int2 *items, int n_items, uint32_t *next,
                                 const RobotDev *robot, const RolloutLds &lds, const float *x0s, const float *goals,
@@ -261,9 +261,6 @@ int self_pairs(const storm_robot *robot, std::vector<int> &items);
 int anchor_sphere(const float *spheres, int lo, int hi, double &radius);
 // Two floats per frame, the bodies' bounds of RobotDev::body_bound.
 std::vector<float> body_bounds(const storm_robot *robot);
-// The anchor spheres of both (RobotDev::cap_mask), by whose rank in the mask both
-// then refer to them (the items beside their spheres).
-uint64_t anchor_mask(std::vector<float> &bounds, std::vector<int> &items);
 
 }  // namespace storm
 
