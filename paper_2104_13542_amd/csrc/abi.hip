@@ -294,6 +294,14 @@ const char *storm_status_str(int32_t status)
 int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const storm_robot *robot,
                            const storm_scene *scene, void *stream)
 {
+    return storm::init_context(out, params, robot, scene, stream, false);
+}
+
+}  // extern "C"
+
+int32_t storm::init_context(storm_ctx *out, const storm_params *params, const storm_robot *robot,
+                            const storm_scene *scene, void *stream, bool batched)
+{
     if (!out) return STORM_E_NULL;
     *out = nullptr;
     int32_t st = validate_params(params);
@@ -418,7 +426,8 @@ int32_t storm_rollout_init(storm_ctx *out, const storm_params *params, const sto
     STORM_TRY(dalloc(c, &u, (size_t)STORM_DOF * N * H));
     STORM_TRY(dalloc(c, &C, (size_t)N));
     STORM_TRY(dalloc(c, &grad_part, storm::kAdjChunks + (size_t)P.n_chunks * STORM_DOF * storm::kMaxH));
-    if (storm::update_part_floats(N, H) > 0) STORM_TRY(dalloc(c, &upd_part, storm::update_part_floats(N, H)));
+    if (storm::update_part_floats(N, H) > 0 && (!batched || storm::update_batch_parts(N, H) > 0))
+        STORM_TRY(dalloc(c, &upd_part, storm::update_part_floats(N, H)));
     STORM_TRY(dalloc(c, &grad, (size_t)H * STORM_DOF));
     STORM_TRY(dalloc(c, &adam, (size_t)2 * H * STORM_DOF));
     {
@@ -520,6 +529,8 @@ fail:
     delete c;
     return map_error(e);
 }
+
+extern "C" {
 
 // The rollout of one step, and with the learned self-collision model its
 // network pass after it.

@@ -167,7 +167,7 @@ int32_t storm_batch_init(storm_batch *out, int32_t n_problems, const storm_param
     int32_t st = STORM_OK;
     for (int p = 0; p < n_problems && st == STORM_OK; ++p) {
         storm_ctx c = nullptr;
-        st = storm_rollout_init(&c, &params[p], robot, scenes ? &scenes[p] : nullptr, stream);
+        st = init_context(&c, &params[p], robot, scenes ? &scenes[p] : nullptr, stream, true);
         if (st == STORM_OK) b->ctxs.push_back(c);
     }
     if (st != STORM_OK) {

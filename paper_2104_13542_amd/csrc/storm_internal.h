@@ -209,6 +209,10 @@ hipError_t set_rollout_lds_limit();
 // Whether the learned self-collision network's weight matrices (W1, W2, W3
 // of storm_robot.self_mlp) hold FP16 values only, as its kernel requires.
 bool selfnet_weights_fp16(const float *prm);
+// The work of storm_rollout_init; a context of a batch (`batched`) lacks the
+// buffers that only plain launches use.
+int32_t init_context(storm_ctx *out, const storm_params *params, const storm_robot *robot, const storm_scene *scene,
+                     void *stream, bool batched);
 // Workgroups of a problem's update in a batch before the join (0: none), and the
 // floats of its partial sums (ProblemDev::upd_part; 0 where one workgroup per
 // joint takes a single problem).

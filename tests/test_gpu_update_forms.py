@@ -68,3 +68,25 @@ def test_one_workgroup_per_joint_equals_chains(n, h, beta, cov):
     finally:
         b.close()
         r.close()
+
+
+def test_a_batch_holds_no_partial_sums_that_it_does_not_use():
+    """Contexts of 2049 x 64 hold the chains' partial sums (448 KiB); a batch updates
+    such problems with one workgroup per joint."""
+    from paper_2104_13542_amd import storm
+
+    def held(make):
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        owned = make()
+        torch.cuda.synchronize()
+        used = free - torch.cuda.mem_get_info()[0]
+        for o in owned:
+            o.close()
+        return used
+
+    probs = [_problem(2049, 64) for _ in range(64)]
+    storm.Rollout(_problem(8, 8)).close()
+    batch = held(lambda: [storm.Batch(probs)])
+    plain = held(lambda: [storm.Rollout(pr) for pr in probs])
+    assert plain - batch >= 0.9 * 64 * 448 * 1024
