@@ -207,7 +207,7 @@ std::vector<float> storm::body_bounds(const storm_robot *robot)
 // the radii about the anchors that hold the runs, and what the anchors' own
 // radii lack of it (each with 0.1 mm for the rounding of the centres, which is
 // micrometres within the robot's reach).
-int storm::self_pairs(const storm_robot *robot, std::vector<int> &items)
+void storm::self_pairs(const storm_robot *robot, std::vector<int> &items)
 {
     struct Run {
         int first, count, body, anchor;
@@ -233,7 +233,6 @@ int storm::self_pairs(const storm_robot *robot, std::vector<int> &items)
         lo = hi;
     }
     items.clear();
-    int pairs = 0;
     for (const Run &t : runs)
         for (const Run &s : runs) {
             if (s.body > t.body - 2) continue;
@@ -245,9 +244,7 @@ int storm::self_pairs(const storm_robot *robot, std::vector<int> &items)
             items.push_back(t.anchor | s.anchor << 6);
             items.push_back(bits[0]);
             items.push_back(bits[1]);
-            pairs += t.count * s.count;
         }
-    return pairs;
 }
 
 namespace {
@@ -353,7 +350,7 @@ int32_t storm::init_context(storm_ctx *out, const storm_params *params, const st
     const float comb[3] = {params->comb_filter ? params->comb[0] : 1.0f, params->comb_filter ? params->comb[1] : 0.0f,
                            params->comb_filter ? params->comb[2] : 0.0f};
     std::vector<int> seg;
-    const int n_pairs = storm::self_pairs(robot, seg);
+    storm::self_pairs(robot, seg);
     std::vector<_Float16> net_frag;
     std::vector<float> net_bias;
     if (params->self_model == 1) storm::pack_selfnet(robot->self_mlp, net_frag, net_bias);
@@ -401,7 +398,6 @@ int32_t storm::init_context(storm_ctx *out, const storm_params *params, const st
     P.ball_c[0] = params->ball_center[0];
     P.ball_c[1] = params->ball_center[1];
     fill_robot_consts(robot, c->R);
-    c->R.n_pairs = n_pairs;
 
     float *tables, *halton, *box_obs, *mean, *sigma2, *u, *C, *dt_raw, *lim_raw, *sig_raw, *obs_raw, *sph_raw_d;
     float *body_bound, *grad_part, *upd_part = nullptr, *grad, *adam, *ball, *qbuf = nullptr;

@@ -58,19 +58,19 @@ void free_batch(storm_batch b)
     b->allocs.clear();
 }
 
-// Estimated VALU work of one tile of problem p (the scheduler's sort key),
-// in instructions per wave: the per-point kinematics, the environment broad
-// phase (wave ball per sphere, one 64-obstacle chunk per pass) plus the few
-// exact tests that survive it (about 2% of the pairs), and the sphere pairs.
-double tile_cost(const ProblemDev &P, int n_spheres, int n_pairs)
+// Estimated time of one tile of problem p (the scheduler's sort key), in units of
+// a tile's without collision terms.  From steps of 64 problems of 512 x 30 with
+// the robot of 52 spheres (83 pairs of runs): 192 us without collision terms, 229
+// with self-collision, and 1.5 us more for each sphere and 3.7 for each cuboid of
+// a scene.  (Which order the queue has hardly matters where tiles are many:
+// batches of 256 problems of 128 to 1024 particles 1906 us by cost and 1905 by
+// problem.)
+double tile_cost(const ProblemDev &P, const RobotDev &R)
 {
-    double per_wave = 1500.0;
-    if (P.cost_mask & STORM_COST_ENV) {
-        const int chunks = (P.n_sph_obs + P.n_box_obs + 63) / 64;
-        per_wave += n_spheres * (40.0 + 12.0 * chunks + 0.02 * (5.0 * P.n_sph_obs + 19.0 * P.n_box_obs));
-    }
-    if (P.cost_mask & STORM_COST_SELF) per_wave += 7.0 * n_pairs;
-    return per_wave;
+    double cost = 1.0;
+    if (P.cost_mask & STORM_COST_ENV) cost += R.n_spheres * (1.5e-4 * P.n_sph_obs + 3.7e-4 * P.n_box_obs);
+    if (P.cost_mask & STORM_COST_SELF) cost += 2.3e-3 * R.n_self_items;
+    return cost;
 }
 
 int32_t launch_batch_step(storm_batch b, const float *d_x0, const float *d_goal, hipStream_t s)
@@ -196,7 +196,7 @@ int32_t storm_batch_init(storm_batch *out, int32_t n_problems, const storm_param
             most.bytes = std::max(most.bytes, lds.bytes);
             most.dense = most.dense || lds.dense;
         }
-        const double tc = tile_cost(probs[p], robot->n_spheres, b->ctxs[p]->R.n_pairs);
+        const double tc = tile_cost(probs[p], b->R);
         for (int t = 0; t < probs[p].n_tiles; ++t) {
             plain.push_back(make_int2(p, t));
             cost.push_back(tc);

@@ -122,7 +122,7 @@ static_assert(offsetof(ProblemDev, tables) == 64 && offsetof(ProblemDev, step) =
 // Robot constants (wave-uniform; in device memory for the rollouts and the adjoint,
 // by value for the FK kernel).
 struct alignas(64) RobotDev {
-    int32_t n_spheres, n_pairs, n_self_items, pad0;
+    int32_t n_spheres, n_self_items, pad0[2];
     const float4 *sph_local;  // [S] body-frame centre (x, y, z), radius
     const int32_t *sph_body;  // [S] frame index 0..7 the sphere is attached to
     const float *body_bound;  // [8][2] per frame: anchor sphere (int bits), what its radius lacks to hold the body's spheres
@@ -257,9 +257,8 @@ hipError_t launch_refine_batch(const ProblemDev *probs, int n_problems, const in
 hipError_t launch_fk(const RobotDev &R, const float *q, bool rows, int n, float *pose, float *manip, hipStream_t stream);
 
 // Self-collision work items of the robot: pairs of groups (runs of up to four
-// spheres of one body) on bodies at least two apart, four integers each;
-// returns the number of sphere pairs.
-int self_pairs(const storm_robot *robot, std::vector<int> &items);
+// spheres of one body) on bodies at least two apart, four integers each.
+void self_pairs(const storm_robot *robot, std::vector<int> &items);
 // The sphere of [lo, hi) about whose centre (in the body's frame) the ball
 // that holds all of them is smallest, and that ball's radius.
 int anchor_sphere(const float *spheres, int lo, int hi, double &radius);
