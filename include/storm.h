@@ -333,8 +333,8 @@ int32_t storm_rollout_graph_destroy(storm_graph graph);
 /* ------------------------------------------------------------------------
  * Batched form: many independent problems (not in the paper).  One
  * persistent rollout launch covers every (problem, tile) work item of all
- * problems through an integer work queue; one update workgroup per problem
- * follows.  Each problem keeps its own parameters, scene, policy state and
+ * problems through an integer work queue; the update of every problem and
+ * joint follows.  Each problem keeps its own parameters, scene, policy state and
  * sampling counter, and computes exactly what a plain context would.
  * ------------------------------------------------------------------------ */
 typedef struct storm_batch_s *storm_batch;

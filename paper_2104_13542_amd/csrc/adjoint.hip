@@ -15,10 +15,10 @@
 // Nothing is exchanged between wavefronts until the tiles are done, so there is
 // no barrier in the loop and the only idle issue slots are latencies that the
 // other wavefronts of the SIMD cover (four: 128 VGPRs); bound by VALU issue.
-// The same work split over eight wavefronts by joint and row, with six
-// barriers a tile, takes 1.65 ms for 64 problems of 4096 x 64 against 0.82, but
-// is the shorter path where a launch has few tiles: it is kept for those
-// (kSplitTiles), with the same bits.
+// The same work split over eight wavefronts by joint and row (1.65 ms for 64
+// problems of 4096 x 64, with six barriers a tile, against 0.82) is the shorter
+// path where a launch has few tiles: it is kept for those (kSplitTiles), with the
+// same bits.
 // A second kernel adds the partials per (joint, step) in a fixed order and,
 // when refining, takes an Adam step (Kingma and Ba, 2015) on mu.
 #include "kinematics.h"

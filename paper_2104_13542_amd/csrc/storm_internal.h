@@ -24,12 +24,12 @@ constexpr int kMaxSelfItems = 276;  // pairs of at most 24 groups of one body's 
 constexpr int kAdjChunks = 512;  // adjoint workgroups (tile chunks) per problem, at most
 constexpr int kAdjWaves = 4;     // wavefronts of an adjoint workgroup, one tile each at a time
 
-// Up to this many tiles (two per CU) the adjoint splits each tile over a
-// workgroup: the latency of a tile is then all there is.  A call of a step and
-// three refinements, split and a tile per wavefront: 500 x 30 43.8 and 51.1 us,
-// 1024 x 30 (512 tiles) 49.6 and 55.0 (before the split form's last step: 39.2
-// and 44.7 now); past it the split form takes a second
-// round: 2048 x 30 80 and 67 us, 65536 x 30 1290 and 742.
+// Up to this many tiles, the most that have a partial each, the adjoint splits
+// each tile over a workgroup: the latency of a tile is then all there is.  One
+// gradient, split and a tile per wavefront, us: 513 tiles of 30 steps 9.7 and
+// 11.0, 640 11.0 and 11.0, 768 11.1 and 11.0 (of 16 steps 10.3 and 11.3, of 64
+// 11.7 and 11.1), and past three workgroups per CU 900 13.4 and 11.0, 1024 13.5
+// and 11.0 (512, split, 9.2).
 constexpr int kSplitTiles = 512;
 
 // The adjoint's partials: per tile up to kSplitTiles; then per chunk, a tile per
@@ -226,7 +226,8 @@ hipError_t launch_update(const ProblemDev &P, const PlainDev *dev, float *mean_o
 hipError_t launch_selfnet(const ProblemDev &P, const PlainDev *dev, const StepOut &out, hipStream_t stream);
 void pack_selfnet(const float *prm, std::vector<_Float16> &frag, std::vector<float> &bias);
 // Many problems: persistent rollout over a (problem, tile) work queue, and one
-// update workgroup per problem (descriptors in device memory).
+// update workgroup per problem and joint, behind the larger problems' chains
+// (descriptors in device memory).
 struct RolloutLds {
     size_t bytes;  // dynamic LDS
     bool dense;    // in the form that packs a scene to leave room for a second workgroup
