@@ -38,8 +38,10 @@
 // Three forms: a 16-wave workgroup per tile up to one tile per CU (bound by the
 // latency of its phases), 8-wave workgroups that loop over the tiles of one
 // larger problem, and the same over the tiles of a batch (both bound by VALU
-// issue).  500 x 30 control call 17.7 -> 14.1 us, 4096 x 64 228 -> 131 us, 65536
-// x 30 1420 -> 764 us, a batch of 256 problems 2530 -> 1840 us.
+// issue).  Against sphere balls, sixteen waves for every plain tile and a barrier
+// between a batch's, over four scenes: 500 x 30 control call 17.5-19.5 -> 13.9-14.3
+// us, 4096 x 64 236-269 -> 130-151, 65536 x 30 step 1530-1810 -> 755-815, a batch of
+// 256 problems 2520-2630 -> 1820-1900.
 #include <algorithm>
 
 #include "kinematics.h"
