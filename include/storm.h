@@ -349,7 +349,8 @@ typedef struct storm_launch_config {
 /* Create a batch of n_problems problems (params[p], scenes[p]) sharing one
  * robot.  Every per-problem limit and validation rule of storm_rollout_init
  * applies.  Default launch shape: 8 waves, two workgroups per compute unit,
- * cost-ordered queue.  Synchronises `stream`.  Errors: as init, plus E_RANGE
+ * cost-ordered queue (a compute unit holds both at once with up to about 57
+ * body spheres in any scene, with more in smaller scenes).  Synchronises `stream`.  Errors: as init, plus E_RANGE
  * for n_problems < 1 and E_UNSUPPORTED for a problem with the ball term or
  * the learned self-collision model. */
 int32_t storm_batch_init(storm_batch *out, int32_t n_problems, const storm_params *params,
